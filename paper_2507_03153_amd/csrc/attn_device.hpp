@@ -42,6 +42,16 @@ struct KernelArgs {
 
 // ---- pieces shared by all split kernels ---------------------------------------------------
 
+// Tokens per split of a set of n tokens that n_splits workgroups share: the host fixes the number of splits from
+// the CAPACITY (lengths and list counts are device memory), so a set that fills half of its capacity would leave half
+// of its workgroups empty and the others with twice the work.  A whole number of 64-token rounds, at most `chunk`.
+// Measured: managed decode step with 2 007 listed entries per head and room for 4 096 (batch 8, 32 heads, window
+// 4 096) 96.9 -> 71.4 us; sets that fill their capacity are cut as before.
+__device__ __forceinline__ int even_chunk(int chunk, int n, int n_splits)
+{
+    return min(chunk, ((n + n_splits - 1) / n_splits + 63) / 64 * 64);
+}
+
 template <int D, int NH, int BLOCK = kBlock>
 __device__ __forceinline__ void write_empty_partial(const Partials &part, int64_t bh0, int split)
 {
@@ -226,13 +236,14 @@ struct SplitValu {
         const int64_t bh0 = (int64_t)b * Hq + h0;
         const int64_t list = PER_HEAD_LIST ? bh0 : (int64_t)b * Hkv + unit;      // row of idx / cnt
         const int n = GATHER ? (a.kv.cap > 0 ? min(a.cnt[list], a.k_max) : 0) : tier_len(a.kv, b);
-        const int t0 = split * a.chunk;
+        const int chunk = MODE == kScores ? a.chunk : even_chunk(a.chunk, n, a.part.n_splits);
+        const int t0 = split * chunk;
 
         if (t0 >= n) {                               // empty split (uniform over the workgroup)
             if (MODE != kScores) write_empty_partial<D, NH>(a.part, bh0, split);
             return;
         }
-        const int nt = min(a.chunk, n - t0);         // 1 .. chunk tokens in this split
+        const int nt = min(chunk, n - t0);           // 1 .. chunk tokens in this split
         if (MODE == kGatherScored) {                 // the caller already holds the scores of the listed entries
             const float *given = a.sel_scores + bh0 * a.k_max + t0;
             for (int j = tid; j < nt; j += kBlock) s_p[0][j] = given[j];

@@ -41,33 +41,36 @@ __global__ __launch_bounds__(kBlock, HGCA_DG_OCC) void dense_gather_kernel(Kerne
     if (dense_role) {                            // uniform over the workgroup
         const int split = u % dense_splits, kvh = (u / dense_splits) % da.sh.n_kv_heads,
                   b = u / (dense_splits * da.sh.n_kv_heads);
-        int n = tier_len(da.kv, b);
-        const int t0 = split * da.chunk;
+        int n = tier_len(da.kv, b), len = 0, first = 0;
+        bool takes_token = false;
         if (k_new) {                             // uniform over the launch: the window takes one more token first
-            const int len = da.kv.seq_lens[b], first = da.kv.first_block[b];
+            len = da.kv.seq_lens[b];
+            first = da.kv.first_block[b];
             const int grown = pending_window_len(len, first, 1, da.kv.cap, da.kv.block_size, da.kv.max_blocks, nullptr);
             n = min(max(grown, 0), da.kv.cap);
-            if (grown > len && len >= t0 && len < t0 + da.chunk) {
-                // this split owns the token's position: its K and V rows go into the window's block, then the split
-                // reads them back like any other row (no other workgroup of the launch touches that position)
-                constexpr int kPieces = D * 2 / 16, kRow = D * 2;
-                if (threadIdx.x < 2 * kPieces) {
-                    const bool is_v = threadIdx.x >= kPieces;
-                    const int piece = threadIdx.x % kPieces;
-                    const int64_t blk = da.kv.block_table[(int64_t)b * da.kv.max_blocks + first + len / da.kv.block_size];
-                    const int64_t dst = ((blk * da.sh.n_kv_heads + kvh) * da.kv.block_size + len % da.kv.block_size) * kRow;
-                    const int64_t src = ((int64_t)b * da.sh.n_kv_heads + kvh) * kRow;
-                    *reinterpret_cast<uint4 *>(const_cast<char *>(is_v ? da.kv.v : da.kv.k) + dst + 16 * piece) =
-                        *reinterpret_cast<const uint4 *>((is_v ? v_new : k_new) + src + 16 * piece);
-                }
-                __syncthreads();
+            takes_token = grown > len;
+        }
+        const int chunk = even_chunk(da.chunk, n, dense_splits), t0 = split * chunk;
+        if (takes_token && len >= t0 && len < t0 + chunk) {      // uniform over the workgroup
+            // this split owns the token's position: its K and V rows go into the window's block, then the split
+            // reads them back like any other row (no other workgroup of the launch touches that position)
+            constexpr int kPieces = D * 2 / 16, kRow = D * 2;
+            if (threadIdx.x < 2 * kPieces) {
+                const bool is_v = threadIdx.x >= kPieces;
+                const int piece = threadIdx.x % kPieces;
+                const int64_t blk = da.kv.block_table[(int64_t)b * da.kv.max_blocks + first + len / da.kv.block_size];
+                const int64_t dst = ((blk * da.sh.n_kv_heads + kvh) * da.kv.block_size + len % da.kv.block_size) * kRow;
+                const int64_t src = ((int64_t)b * da.sh.n_kv_heads + kvh) * kRow;
+                *reinterpret_cast<uint4 *>(const_cast<char *>(is_v ? da.kv.v : da.kv.k) + dst + 16 * piece) =
+                    *reinterpret_cast<const uint4 *>((is_v ? v_new : k_new) + src + 16 * piece);
             }
+            __syncthreads();
         }
         if (t0 >= n) {
             write_empty_partial<D, G>(da.part, (int64_t)b * da.sh.n_q_heads + (int64_t)kvh * G, split);
             return;
         }
-        DS::run(da, s_lds, split, kvh, b, t0, min(da.chunk, n - t0));
+        DS::run(da, s_lds, split, kvh, b, t0, min(chunk, n - t0));
         return;
     }
     GS::run(ga, s_lds, u % gather_splits, (u / gather_splits) % ga.sh.n_q_heads, u / (gather_splits * ga.sh.n_q_heads));
