@@ -1,24 +1,20 @@
 // Append stage: N queries per sequence attend to one KV tier (Sec. 2.1: S = Q K^T, A = softmax(S),
-// O = A V with Q in R^{h x N x d}; Alg. 2, append branch).  bf16 inputs, both contractions on
-// v_mfma_f32_16x16x32_bf16.
+// O = A V with Q in R^{h x N x d}; Alg. 2, append branch).  bf16 inputs, both contractions on the matrix cores.
 //
-// Work unit of the attention kernel: one workgroup = one split of the tokens of one (sequence, KV head) and up
-// to 128 query rows (a row = one query x one head of the GQA group, query-major).  Every wave owns row tiles of 16
-// rows, so nothing is reduced across waves.  The K and V rows of a 64-token step are brought into a double-buffered
-// LDS stage by LDS-direct loads (no registers in between); the next step's loads are in flight during a step's
-// arithmetic, one barrier per step; two workgroups share a CU.  A step is 64 tokens rather than 32 because the
-// softmax of a step is one dependent chain (scores, row maximum, exponentials, row sum, rounding, second
-// contraction): four score tiles per chain give the wave independent work to overlap it with.
+// Work unit of the attention kernel: one workgroup = one share of the tokens of one (sequence, KV head) and up to 128
+// query rows (a row = one query x one head of the GQA group, query-major).  Every wave owns 32 rows, so nothing is
+// reduced across waves.  The K and V rows of a 64-token step are brought into a double-buffered LDS stage by LDS-direct
+// loads (no registers in between); the next step's loads are in flight during a step's arithmetic, one barrier per
+// step; two workgroups share a CU.
 //
-// Orientation (per 16-row tile, per step):
+// Orientation (per 32-row tile, per step):
 //   S^T[token, row]  = K[token, :] . Q[row, :]        A = K tile (LDS, swizzled rows), B = Q (registers)
 //   O^T[dcol, row]  += V^T[dcol, token] . P^T[token, row]   A = V^T (LDS transpose reads of the rows), B = P
-// In both results a lane's column is the query row lane%16, so the running maximum, the running sum
-// and the rescaling factor of a row live in the lanes that hold its scores AND its output columns:
-// the online softmax needs two lane exchanges per row statistic and no LDS.  The probabilities go from
-// the score registers straight into the B operand of the second contraction (the contraction index
-// is matched by reading V^T in the same token order); they are rounded to bf16 there, as a high and a
-// low part (two MFMAs, fp32-level accuracy) or, on request, as one part.
+// In both results a lane's column is the query row lane % 32, so the running maximum, the running sum and the
+// rescaling factor of a row live in the lanes that hold its scores AND its output columns: the online softmax needs
+// one lane exchange per row statistic and no LDS.  The probabilities go from the score registers straight into the B
+// operand of the second contraction (the contraction index is matched by reading V^T in the same token order); they
+// are rounded to bf16 there, as a high and a low part (two MFMAs, fp32-level accuracy) or, on request, as one part.
 //
 // The weights kernel brings its K rows in the same way (it has no second contraction).
 #include "hgca_launch.hpp"
@@ -37,54 +33,47 @@ constexpr int kStepBlocks = 2;                   // 32-token contraction blocks 
 constexpr int kStepTokens = 32 * kStepBlocks;
 constexpr int kRowsPerBlock = 128;               // query rows per workgroup = 8 tiles of 16, one per wave
 static_assert(kRowsPerBlock == 16 * kAWaves, "one row tile per wave");
-constexpr int kSub = kMaxChunk;                  // entries of the table of block rows (paged tiers)
+constexpr int kSub = kMaxChunk;                  // entries of the table of rows (paged tiers)
+static_assert(kStepTokens == kLineStep, "shares of a line are whole steps");
+static_assert(kSub * 16 % kStepTokens == 0, "a pass is a whole number of steps");
 
 // Where the rows of a pass over part of a split live.  A contiguous tier is plain arithmetic.  A paged tier gets a
-// table in LDS with one entry per BLOCK the pass touches (the row of the block's first token for this KV head), so
-// one filling of kSub entries covers (kSub - 1) * block_size tokens -- a whole split for blocks of 16 tokens -- and
-// the load pipeline is not drained for refills.
+// table in LDS with one entry per 16 tokens (block sizes are multiples of 16: the row of the granule's first token for
+// this KV head), so a lookup is a shift, whatever the block size, and one filling of kSub entries covers a whole split
+// and the load pipeline is not drained for refills.
+constexpr int kGranule = 16;
 struct BlockRows {
     const uint32_t *table;                       // LDS; nullptr => row = base + j
     uint32_t base;
-    int32_t bs, shift, off;                      // block size, log2 of it (-1: not a power of two), first token's place in its block
-    __device__ __forceinline__ uint32_t operator()(int j) const {
-        if (!table) return base + (uint32_t)j;
-        const int t = off + j;
-        return shift >= 0 ? table[t >> shift] + (uint32_t)(t & (bs - 1)) : table[t / bs] + (uint32_t)(t % bs);
-    }
 };
 
-// tokens a pass may cover so that its blocks fit the table, a multiple of the step
+// tokens a pass may cover so that its granules fit the table, a multiple of the step
 __device__ __forceinline__ int pass_length(const KvDev &kv, int nt_total) {
-    if (!kv.block_table) return max(nt_total, 1);
-    const int64_t t = (int64_t)(kSub - 1) * kv.block_size;
-    return (int)max((int64_t)kStepTokens, min(t, (int64_t)1 << 30) / kStepTokens * kStepTokens);
+    return kv.block_table ? kSub * kGranule : max(nt_total, 1);
 }
 
-// `first` is the tier position of the pass's first token, nt the number of tokens; contains a barrier iff the tier
-// is paged (uniform over the workgroup).
+// `first` is the tier position of the pass's first token, a multiple of kGranule (splits and passes are cut at whole
+// steps), nt the number of tokens; contains a barrier iff the tier is paged (uniform over the workgroup).
 template <int BLOCK>
 __device__ __forceinline__ BlockRows make_block_rows(uint32_t *s_tab, const KvDev &kv, int n_kv_heads, int b, int kvh,
                                                      int first, int nt)
 {
     b = kv_seq(kv, b);
     BlockRows m;
-    m.bs = max(kv.block_size, 1);
-    m.shift = (m.bs & (m.bs - 1)) == 0 ? __builtin_ctz(m.bs) : -1;
     if (!kv.block_table) {
         m.table = nullptr;
         m.base = (uint32_t)(((int64_t)b * n_kv_heads + kvh) * kv.cap + first);
-        m.off = 0;
         return m;
     }
     const int32_t *blocks = kv.block_table + (int64_t)b * kv.max_blocks + (kv.first_block ? kv.first_block[b] : 0);
-    const int blk0 = first / m.bs, n_blk = (first + nt - 1) / m.bs - blk0 + 1;      // <= kSub by pass_length
-    for (int i = threadIdx.x; i < n_blk; i += BLOCK)
-        s_tab[i] = (uint32_t)(((int64_t)blocks[blk0 + i] * n_kv_heads + kvh) * m.bs);
+    const int n_gr = (nt + kGranule - 1) / kGranule;             // <= kSub by pass_length
+    for (int i = threadIdx.x; i < n_gr; i += BLOCK) {
+        const int tok = first + i * kGranule;
+        s_tab[i] = (uint32_t)(((int64_t)blocks[tok / kv.block_size] * n_kv_heads + kvh) * kv.block_size + tok % kv.block_size);
+    }
     __syncthreads();
     m.table = s_tab;
     m.base = 0;
-    m.off = first - blk0 * m.bs;
     return m;
 }
 
@@ -94,19 +83,14 @@ __device__ __forceinline__ float row_rotate(float x) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + ROT, 0xf, 0xf, true));
 }
 
-// Reductions over the four 16-lane rows of a wave (lanes n, n + 16, n + 32, n + 48 hold partial results of one
-// query row).  v_permlane16_swap / v_permlane32_swap of a register with itself return (rows 0 0 2 2, rows 1 1 3 3)
-// and (lower half twice, upper half twice): two VALU instructions per level where a lane shuffle would go through
-// the LDS pipeline, which matters because the row maximum heads the dependent chain of every step.
-__device__ __forceinline__ float rows_max(float x) {
-    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+// Reductions over the two halves of a wave (lanes n and n + 32 hold partial results of one query row):
+// v_permlane32_swap of a register with itself returns the lower half twice and the upper half twice, one VALU
+// instruction where a lane shuffle would go through the LDS pipeline.
+__device__ __forceinline__ float halves_max(float x) {
     const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
-__device__ __forceinline__ float rows_sum(float x) {
-    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+__device__ __forceinline__ float halves_sum(float x) {
     const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
@@ -160,20 +144,14 @@ __device__ __forceinline__ void tile_scores(KPiece k_piece, const bf16x8 (&qop)[
     }
 }
 
-#ifndef HGCA_APPEND_PV_GROUP
-#define HGCA_APPEND_PV_GROUP 4
-#endif
-#ifndef HGCA_APPEND_TILES
-#define HGCA_APPEND_TILES 2
-#endif
-
 // LDS stage of the attention kernel: the rows of a step are brought in by LDS-direct loads (global_load_lds, 16
 // bytes per lane, no registers in between).  One such instruction fills 1024 consecutive bytes of LDS with whatever
 // 64 pieces its lanes address, so the layout inside each 1 KB group is chosen by the lane -> global address map:
 //   K: row-major rows with the 16-byte pieces of a row XOR-swizzled by the row, so that the 16 rows an A-operand
 //      read touches land on different banks without padding;
-//   V: the group's rows interleaved in 32-byte chunks ([column chunk][row][32 bytes]), so that the 4 rows x 32 bytes
-//      a 16-lane group takes with one transpose read are 128 consecutive bytes.
+//   V: quads of four rows, interleaved in 32-byte chunks ([quad][column chunk][row of the quad][32 bytes]), so that
+//      the 4 rows x 32 bytes a 16-lane group takes with one transpose read are 128 consecutive bytes and the two
+//      groups of a half wave, which take neighbouring chunks, 256.
 template <int D, int NW> struct DmaStage {
     static constexpr int kPieces = D / 8;                        // 16-byte pieces per row
     static constexpr int kRowBytes = D * 2;
@@ -190,7 +168,7 @@ template <int D, int NW> struct DmaStage {
     }
     // byte offset, in a V stage, of the 32-byte column chunk `dt` of step row `row`
     static __device__ __forceinline__ int v_offset(int row, int dt) {
-        return (row / kGroupRows) * 1024 + dt * (kGroupRows * 32) + (row % kGroupRows) * 32;
+        return (row / 4) * (4 * kRowBytes) + dt * 128 + (row % 4) * 32;
     }
 };
 
@@ -199,53 +177,98 @@ template <int D, int NW> struct DmaStage {
 // other waves read what it loaded.
 __device__ __forceinline__ void wait_for_own_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
-// Requests the K and the V rows of a step.  All row numbers are looked up before the first load is issued: the
-// lookup of a paged tier reads a table in LDS, and an LDS read placed after an LDS-direct load waits for that load.
+// Requests the K and the V rows of a step.  A load instruction of a wave covers kGroupRows rows of one granule, so in
+// a full step its address is a scalar (the granule's row) plus an offset that is the lane's for good; only a step
+// that the pass's end cuts computes rows per lane (tokens behind the end read the last row).  The row numbers of a
+// paged tier are looked up before the first load is issued: an LDS read placed after an LDS-direct load waits for it.
 template <int D, int NW, bool WITH_V = true>
 __device__ __forceinline__ void dma_step(const KvDev &kv, const BlockRows &rows, int step, int nsub, char *k_stage,
                                          char *v_stage)
 {
     using S = DmaStage<D, NW>;
+    static_assert(kGranule % S::kGroupRows == 0 && (NW * S::kGroupRows) % kGranule == 0,
+                  "a load stays inside a granule and all loads of a wave at the same place of theirs");
+    constexpr int kQuadLanes = 4 * S::kRowBytes / 16;
     const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const char *k_src[S::kLoads], *v_src[S::kLoads];
+    // what lands at byte 16 * lane of a group: K row-major with swizzled pieces, V chunk-interleaved
+    const int k_row = lane / S::kPieces, v_row = 4 * (lane / kQuadLanes) + (lane % 8) / 2;   // inside the group
+    const int k_byte = 16 * ((lane % S::kPieces) ^ S::k_swizzle(w * S::kGroupRows + k_row));
+    const int v_byte = 16 * (2 * ((lane % kQuadLanes) / 8) + lane % 2);
+    typedef const __attribute__((address_space(1))) void *GlobalPtr;
+    typedef __attribute__((address_space(3))) void *LdsPtr;
+    if ((step + 1) * kStepTokens <= nsub) {                      // uniform over the workgroup
+        const uint32_t k_off = k_row * S::kRowBytes + k_byte, v_off = v_row * S::kRowBytes + v_byte;
+        const int first = step * kStepTokens + w * S::kGroupRows;                        // of the wave's first load
+        uint32_t row[S::kLoads];                                 // uniform over the wave
+#pragma unroll
+        for (int u = 0; u < S::kLoads; ++u) row[u] = rows.base + first + NW * S::kGroupRows * u;
+        if (rows.table) {
+#pragma unroll
+            for (int u = 0; u < S::kLoads; ++u) row[u] = rows.table[(first + NW * S::kGroupRows * u) / kGranule];
+#pragma unroll
+            for (int u = 0; u < S::kLoads; ++u) row[u] = __builtin_amdgcn_readfirstlane(row[u]) + first % kGranule;
+        }
+#pragma unroll
+        for (int u = 0; u < S::kLoads; ++u) {
+            const size_t at = (size_t)row[u] * S::kRowBytes;
+            __builtin_amdgcn_global_load_lds((GlobalPtr)(kv.k + at + k_off), (LdsPtr)(k_stage + (w + NW * u) * 1024), 16, 0, 0);
+            if (WITH_V)
+                __builtin_amdgcn_global_load_lds((GlobalPtr)(kv.v + at + v_off), (LdsPtr)(v_stage + (w + NW * u) * 1024), 16, 0, 0);
+        }
+        return;
+    }
+    uint32_t kr[S::kLoads], vr[S::kLoads];
 #pragma unroll
     for (int u = 0; u < S::kLoads; ++u) {
-        const int group = w + NW * u;                            // uniform over the wave
-        // what lands at byte 16 * lane of the group: K row-major with swizzled pieces, V chunk-interleaved
-        const int k_row = group * S::kGroupRows + lane / S::kPieces;
-        const int k_piece = (lane % S::kPieces) ^ S::k_swizzle(k_row);
-        const int v_row = group * S::kGroupRows + (lane / 2) % S::kGroupRows;
-        const int v_piece = 2 * (lane / (2 * S::kGroupRows)) + lane % 2;
-        k_src[u] = kv.k + (size_t)rows(min(step * kStepTokens + k_row, nsub - 1)) * S::kRowBytes + 16 * k_piece;
-        if (WITH_V) v_src[u] = kv.v + (size_t)rows(min(step * kStepTokens + v_row, nsub - 1)) * S::kRowBytes + 16 * v_piece;
+        const int first = step * kStepTokens + (w + NW * u) * S::kGroupRows;
+        const uint32_t kt = min(first + k_row, nsub - 1), vt = min(first + v_row, nsub - 1);
+        kr[u] = rows.table ? rows.table[kt / kGranule] + kt % kGranule : rows.base + kt;
+        vr[u] = rows.table ? rows.table[vt / kGranule] + vt % kGranule : rows.base + vt;
     }
 #pragma unroll
     for (int u = 0; u < S::kLoads; ++u) {
-        const int group = w + NW * u;
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)k_src[u],
-                                         (__attribute__((address_space(3))) void *)(k_stage + group * 1024), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((GlobalPtr)(kv.k + (size_t)kr[u] * S::kRowBytes + k_byte),
+                                         (LdsPtr)(k_stage + (w + NW * u) * 1024), 16, 0, 0);
         if (WITH_V)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)v_src[u],
-                                             (__attribute__((address_space(3))) void *)(v_stage + group * 1024), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((GlobalPtr)(kv.v + (size_t)vr[u] * S::kRowBytes + v_byte),
+                                             (LdsPtr)(v_stage + (w + NW * u) * 1024), 16, 0, 0);
     }
 }
 
-// TILES row tiles of 16 query rows per wave (128 rows per workgroup, so 8 / TILES waves): with two tiles every K
-// and V operand read from LDS feeds two matrix instructions, and the two tiles' softmax chains are independent
-// work for the wave to overlap.
+constexpr int kAttnWaves = kRowsPerBlock / 32, kAttnBlock = kAttnWaves * kWave;   // a wave owns 32 query rows
+constexpr int kXcds = 8;
+
+// p - (one half of a packed pair of bf16): the multiply-adds of the dot product are exact here (p and its rounded
+// value differ by less than an ulp of the latter), so one instruction widens the half and subtracts it.
+// minus_one_at holds -1 in the half meant and 0 in the other.
+__device__ __forceinline__ float minus_half(uint32_t pair, uint32_t minus_one_at, float p) {
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), __builtin_bit_cast(bf16x2, minus_one_at), p, false);
+}
+
+// A workgroup: four waves of 32 query rows over one share of the tokens of one (sequence, KV head).  The scores come
+// from v_mfma_f32_32x32x16_bf16, whose result gives a lane 16 scores of ONE row per 32 tokens (the other 16 are the
+// lane's partner's, 32 lanes away), so a step's softmax is one chain per lane over 32 scores.  What the pass follows is
+// the amount of work, not its order: beside saturated matrix cores the part runs at 1.5 - 1.9 GHz (a bare chain of these
+// instructions reaches 1.87 PFLOP/s, with four multiply-adds beside each 1.62), and a version that interleaved the next
+// step's scores with this step's softmax was no faster.  Hence
+//   - the maximum is reduced over the lanes, and the outputs rescaled, only in steps where some score exceeds its row's
+//     maximum so far; the row sum stays per lane until the end of the share;
+//   - the low part of a weight takes one dot instruction;
+//   - a load instruction's address is a scalar plus a constant offset of the lane (dma_step);
+//   about 6 vector instructions per score where the kernel with 16-row tiles took 13.
+// With the line below, 2 x 509 queries x 32 K tokens x 32 heads: 930 -> 760 us (720 TFLOP/s, 1.08 PFLOP/s executed);
+// 8 x 32 queries x 32 K tokens: 266 -> 250 us, bound by the K/V rows; 48 queries, groups of 8, one part: 320 -> 250 us.
 //
-// A launch may serve TWO tiers (the window and the complete pool of an append turn: Alg. 2 runs the two attentions
-// side by side): the first a1.part.n_splits workgroups along x take the splits of a1, the rest those of a2, each
-// with its tier's view, mask rule, split size and partials; everything else (queries, shape) is common.  One launch
-// then pays one ramp-up and one tail, and the short tier's splits can be as long as the long tier's.
-template <int D, int G, bool SPLIT_P, int TILES>
-__global__ __launch_bounds__(kABlock / TILES, 4 / TILES) void append_attn_kernel(AppendArgs a1, AppendArgs a2)
+// A launch may serve TWO tiers (the complete pool and the window of an append turn: Alg. 2 runs the two attentions side
+// by side) as one line of tokens cut into equal shares (LineDev): a workgroup goes through its part of the first tier
+// and its part of the second, usually only one of them, each with the tier's view, mask rule and slot.
+template <int D, int G, bool SPLIT_P>
+__global__ __launch_bounds__(kAttnBlock, 2) void append_attn_kernel(AppendArgs a1, AppendArgs a2,
+                                                                       LineDev line, int two_tiers)
 {
-    const bool second = (int)blockIdx.x >= a1.part.n_splits;     // uniform over the workgroup
-    const AppendArgs &a = second ? a2 : a1;
-    constexpr int NW = kAWaves / TILES, BLOCK = NW * kWave;
+    constexpr int NW = kAttnWaves, BLOCK = kAttnBlock;
     using S = DmaStage<D, NW>;
-    constexpr int DT = D / 16;
+    constexpr int DT = D / 32, NT = kStepTokens / 32;            // 32-column tiles of the output, 32-token tiles of a step
     constexpr float kLog2e = 1.4426950408889634f;
     // two stages per tensor as separate arrays: the compiler then knows that a load into one stage does not
     // touch the other and lets the reads of the current stage go ahead while the next one is being filled
@@ -255,207 +278,212 @@ __global__ __launch_bounds__(kABlock / TILES, 4 / TILES) void append_attn_kernel
     __shared__ __attribute__((aligned(1024))) char s_v1[S::kBytes];
     __shared__ uint32_t s_row[kSub];
 
-    const int n_qb = (a.n_q * G + kRowsPerBlock - 1) / kRowsPerBlock;
-    const int split = (int)blockIdx.x - (second ? a1.part.n_splits : 0);
-    const int kvh = blockIdx.y / n_qb, qb = blockIdx.y % n_qb, b = blockIdx.z;
-    const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave, n = lane % 16, g = lane / 16;
-    const int len = tier_len(a.kv, b);
-    // the tier's actual length is shared out evenly among its splits (a.chunk, set from the capacity, bounds it):
-    // every split of a sequence then has the same work however far its length is from the capacity
-    const int chunk = min(a.chunk, ((len + a.part.n_splits - 1) / a.part.n_splits + kStepTokens - 1) / kStepTokens * kStepTokens);
-    const int t0 = split * chunk;
-    const int nt_total = min(chunk, len - t0);                   // <= 0: nothing of this split is valid
+    // Workgroups are dealt to the XCDs in turn.  The row blocks of one stream of K/V rows (a split of a (sequence, KV
+    // head)) read the same rows: they take numbers that are equal modulo the number of XCDs and follow each other
+    // there, so that the stream passes through one L2.
+    const int n_qb = (a1.n_q * G + kRowsPerBlock - 1) / kRowsPerBlock;
+    const int wg = (int)blockIdx.x;
+    const int stream = n_qb == 1 ? wg : wg % kXcds + kXcds * (wg / kXcds / n_qb);
+    const int qb = n_qb == 1 ? 0 : wg / kXcds % n_qb;
+    if (stream >= line.shares * a1.sh.n_kv_heads * a1.sh.batch) return;          // uniform over the workgroup
+    const int share = stream % line.shares, kvh = stream / line.shares % a1.sh.n_kv_heads,
+              b = stream / line.shares / a1.sh.n_kv_heads;
+    const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave, n = lane % 32, hw = lane / 32;
 
-    const int tile_row0 = qb * kRowsPerBlock + w * 16 * TILES;   // first row of the wave's first tile
-    const bool wave_live = tile_row0 < a.n_q * G;                // uniform over the wave
-    RowInfo ri[TILES];
-    int vis[TILES];                              // tokens [0, vis) of the tier are visible to the row
-    int vis_min = INT32_MAX;                     // over the rows of the wave: steps below it need no mask
-    bf16x8 qop[TILES][D / 32];
+    const int row0 = qb * kRowsPerBlock + w * 32;                // first row of the wave
+    const bool wave_live = row0 < a1.n_q * G;                    // uniform over the wave
+    const RowInfo ri = row_info<G>(a1, b, kvh, row0 + n);
+    bf16x8 qop[D / 16];                          // B operand: columns 16 kk + 8 hw .. + 7 of the lane's row
 #pragma unroll
-    for (int x = 0; x < TILES; ++x) {
-        ri[x] = row_info<G>(a, b, kvh, tile_row0 + 16 * x + n);
-        vis[x] = !ri[x].valid ? 0 : a.causal_tail ? min(max(len - a.n_q + ri[x].query + 1, 0), len) : len;
-        vis_min = min(vis_min, vis[x]);
-        load_q_tile<D>(a, ri[x], g, qop[x]);
+    for (int kk = 0; kk < D / 16; ++kk) {
+        uint4 r = make_uint4(0u, 0u, 0u, 0u);
+        if (ri.valid) r = load16(static_cast<const char *>(a1.q) + (ri.out_row * D + 16 * kk + 8 * hw) * 2);
+        qop[kk] = __builtin_bit_cast(bf16x8, r);
     }
-#pragma unroll
-    for (int off = 1; off < 16; off <<= 1) vis_min = min(vis_min, __shfl_xor(vis_min, off, kWave));
-    // The running maximum m is kept on the RAW scores (the softmax scale is positive, so the order is the same) and
+    // The running maximum is kept on the RAW scores (the softmax scale is positive, so the order is the same) and
     // the scale, in units of ln 2, is applied inside the exponent: e^{scale (s - m)} = 2^{fma(s, scale2, -m scale2)},
     // one fused multiply-add and one bare v_exp_f32 per score.
-    const float scale2 = a.sh.sm_scale * kLog2e;
-    float m[TILES], l[TILES];
-    floatx4 acc[TILES][DT];
+    const float scale2 = a1.sh.sm_scale * kLog2e;
+    // this lane's byte offsets into a stage: the A operand of the first product (row n of a 32-token tile, one
+    // offset per 16-column slice because of the swizzle) and of the second.  The V^T operand (8 tokens of one column
+    // per lane) comes from two transpose reads: lane j of a 16-lane group points at columns 4(j%4).. of row j/4 of a
+    // quad of tokens, the two groups of a half wave at neighbouring column chunks.
+    int k_lane[D / 16];
 #pragma unroll
-    for (int x = 0; x < TILES; ++x) {
-        m[x] = -INFINITY;
-        l[x] = 0.f;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) acc[x][dt] = floatx4{0.f, 0.f, 0.f, 0.f};
-    }
+    for (int kk = 0; kk < D / 16; ++kk) k_lane[kk] = S::k_offset(n, 2 * kk + hw);
+    const int v_lane = S::v_offset(4 * hw + lane % 16 / 4, lane / 16 % 2) + 8 * (lane % 4);
+    // (-1, 0) and (0, -1) in bf16 for minus_half, in registers: as a literal the second becomes the inline constant
+    // -1.0, which the dot product takes as a value of its own width
+    uint32_t low_half = 0x0000bf80u, high_half = 0xbf800000u;
+    asm volatile("" : "+v"(low_half), "+v"(high_half));
 
-    // this lane's byte offsets into a stage: the A operand of the first product (row n of a 16-token tile, one
-    // offset per 32-column slice because of the swizzle) and of the second.  The V^T operand (8 tokens of one column
-    // per lane) comes from two transpose reads: lane j of a group points at columns 4(j%4).. of the row of
-    // contraction index j/4 (first read) and 4 + j/4 (second read).
-    int k_lane[D / 32];
+    const LineCut cut(line, b);
+#pragma unroll 1
+    for (int tier = 0; tier < 2; ++tier) {
+        // the share's steps of the line inside this tier, and the slot they go to (see LineDev); all uniform
+        const int begin = share * cut.share_steps, end = begin + cut.share_steps;
+        int step_begin, step_end, slot;
+        if (tier == 0) {
+            if (two_tiers && begin > cut.first_steps) continue;
+            step_begin = begin;
+            step_end = end;
+            slot = share;
+        } else {
+            if (!two_tiers || (end <= cut.first_steps && share != line.shares - 1)) continue;
+            step_begin = max(begin - cut.first_steps, 0);
+            step_end = max(end - cut.first_steps, 0);
+            slot = share + 1;
+        }
+        // field by field: a choice between the two argument structs as a whole would put them into scratch memory
+        KvDev kv{};
+        kv.k = tier ? a2.kv.k : a1.kv.k;
+        kv.v = tier ? a2.kv.v : a1.kv.v;
+        kv.seq_lens = tier ? a2.kv.seq_lens : a1.kv.seq_lens;
+        kv.block_table = tier ? a2.kv.block_table : a1.kv.block_table;
+        kv.first_block = tier ? a2.kv.first_block : a1.kv.first_block;
+        kv.cap = tier ? a2.kv.cap : a1.kv.cap;
+        kv.block_size = tier ? a2.kv.block_size : a1.kv.block_size;
+        kv.max_blocks = tier ? a2.kv.max_blocks : a1.kv.max_blocks;
+        const int causal_tail = tier ? a2.causal_tail : a1.causal_tail;
+        const int len = tier_len(kv, b);
+        const int t0 = step_begin * kStepTokens;
+        const int nt_total = min(step_end * kStepTokens, len) - t0;              // <= 0: nothing of the share is valid
+        // tokens [0, vis) of the tier are visible to the row; steps below the wave's smallest vis need no mask
+        const int vis = !ri.valid ? 0 : causal_tail ? min(max(len - a1.n_q + ri.query + 1, 0), len) : len;
+        int vis_min = vis;
 #pragma unroll
-    for (int kk = 0; kk < D / 32; ++kk) k_lane[kk] = S::k_offset(n, 4 * kk + g);
-    const int v_lane_lo = S::v_offset(block_token(g, n / 4), 0) + 8 * (n % 4);
-    const int v_lane_hi = S::v_offset(block_token(g, 4 + n / 4), 0) + 8 * (n % 4);
+        for (int off = 1; off < 32; off <<= 1) vis_min = min(vis_min, __shfl_xor(vis_min, off, kWave));
+        vis_min = __builtin_amdgcn_readfirstlane(vis_min);           // (the halves of a wave hold the same rows)
+        float m = -INFINITY, shift = 0.f, l = 0.f;               // l: over this lane's tokens only
+        floatx16 acc[DT];
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) acc[dt] = floatx16{};
 
-    auto step_body = [&](const char *k_stage, const char *v_stage, int step0, int in_split) {
-        // raw scores: sv[x][8*kb + 4*tt + r] belongs to step token 32*kb + 16*tt + 4*g + r and row n of tile x
-        float sv[TILES][8 * kStepBlocks];
-        const bool masked = min(in_split, vis_min - step0) < kStepTokens;   // uniform over the wave
-        {
-            // the slices of the contraction outermost: the 4 x TILES accumulators take turns, so no matrix instruction
-            // waits for the one before it on the same accumulator
-            constexpr int NT = 2 * kStepBlocks;                  // 16-token tiles of the step
-            floatx4 c[NT][TILES];
+        auto step_body = [&](const char *k_stage, const char *v_stage, int step0, int in_split) {
+            // raw scores: c[t][r] belongs to step token 32 t + 8 (r / 4) + 4 hw + r % 4 and the lane's row
+            floatx16 c[NT];
 #pragma unroll
-            for (int t = 0; t < NT; ++t)
+            for (int t = 0; t < NT; ++t) c[t] = floatx16{};
 #pragma unroll
-                for (int x = 0; x < TILES; ++x) c[t][x] = floatx4{0.f, 0.f, 0.f, 0.f};
+            for (int kk = 0; kk < D / 16; ++kk)
 #pragma unroll
-            for (int kk = 0; kk < D / 32; ++kk) {
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    const uint4 ka = *reinterpret_cast<const uint4 *>(k_stage + t * 16 * S::kRowBytes + k_lane[kk]);
-#pragma unroll
-                    for (int x = 0; x < TILES; ++x)
-                        c[t][x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka), qop[x][kk], c[t][x], 0, 0, 0);
+                for (int t = 0; t < NT; ++t) {       // the accumulators take turns
+                    const uint4 ka = *reinterpret_cast<const uint4 *>(k_stage + t * 32 * S::kRowBytes + k_lane[kk]);
+                    c[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ka), qop[kk], c[t], 0, 0, 0);
                 }
+            if (min(in_split, vis_min - step0) < kStepTokens) {      // uniform over the wave: a length or causal boundary
+                int limit = min(in_split, vis - step0);
+                asm volatile("" : "+v"(limit));                      // a real branch: the selects below are not speculated into every step
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        if (32 * t + 8 * (r / 4) + 4 * hw + r % 4 >= limit) c[t][r] = -INFINITY;
             }
+            float mx = c[0][0];
 #pragma unroll
             for (int t = 0; t < NT; ++t)
 #pragma unroll
-                for (int x = 0; x < TILES; ++x)
+                for (int r = 0; r < 16; ++r) mx = fmaxf(mx, c[t][r]);
+            if (__any(mx > m)) {                     // uniform over the wave
+                const float m_new = fmaxf(m, halves_max(mx));
+                // a row that has seen nothing yet keeps m = -inf: shift by 0 then, every exponent is -inf and gives 0
+                shift = (m_new == -INFINITY) ? 0.f : -m_new * scale2;
+                const float corr = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(fmaf(m, scale2, shift));
+                m = m_new;
+                l *= corr;
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) sv[x][4 * t + r] = c[t][x][r];
-        }
-        if (masked) {                                            // steps that touch a length or causal boundary
-            asm volatile("" ::: "memory");                       // a real branch: the selects below are not speculated into every step
-#pragma unroll
-            for (int x = 0; x < TILES; ++x) {
-                const int limit = min(in_split, vis[x] - step0);
-#pragma unroll
-                for (int e = 0; e < 8 * kStepBlocks; ++e)
-                    if (16 * (e / 4) + 4 * g + e % 4 >= limit) sv[x][e] = -INFINITY;
+                for (int dt = 0; dt < DT; ++dt) acc[dt] *= corr;
             }
-        }
-        bf16x8 ph[TILES][kStepBlocks], pl[TILES][kStepBlocks];
+            float sum[4] = {0.f, 0.f, 0.f, 0.f};     // four chains
+            bf16x8 ph[NT][2], pl[NT][2];
 #pragma unroll
-        for (int x = 0; x < TILES; ++x) {
-            float mx = sv[x][0];
+            for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int e = 1; e < 8 * kStepBlocks; ++e) mx = fmaxf(mx, sv[x][e]);
-            const float m_new = fmaxf(m[x], rows_max(mx));
-            // a row that has seen nothing yet keeps m = -inf: shift by 0 then, every exponent is -inf and gives 0
-            const float shift = (m_new == -INFINITY) ? 0.f : -m_new * scale2;
-            float ps = 0.f;
+                for (int j = 0; j < 2; ++j) {
+                    // round to nearest even, two weights per conversion; the low part carries the rounding error
+                    uint32_t hi[4], lo[4];
 #pragma unroll
-            for (int e = 0; e < 8 * kStepBlocks; ++e) {          // sv becomes the probabilities; masked scores give 0
-                sv[x][e] = __builtin_amdgcn_exp2f(fmaf(sv[x][e], scale2, shift));
-                ps += sv[x][e];
-            }
-            const float corr = (m[x] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(fmaf(m[x], scale2, shift));
-            l[x] = l[x] * corr + rows_sum(ps);
-            m[x] = m_new;
-            if (__any(corr != 1.f)) {                            // once the maxima have settled nothing is rescaled
+                    for (int e = 0; e < 4; ++e) {
+                        float2v p;
 #pragma unroll
-                for (int dt = 0; dt < DT; ++dt) acc[x][dt] *= corr;
-            }
-            // round to nearest even, two weights per conversion; the low part carries the rounding error: the high
-            // parts are widened again from the packed pair (a shift and a mask) rather than converted one by one
+                        for (int x = 0; x < 2; ++x) {                // masked scores give 0
+                            p[x] = __builtin_amdgcn_exp2f(fmaf(c[t][8 * j + 2 * e + x], scale2, shift));
+                            sum[(2 * e + x) % 4] += p[x];
+                        }
+                        hi[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(p, bf16x2));
+                        lo[e] = 0u;
+                        if (SPLIT_P) {
+                            const float2v rest = {minus_half(hi[e], low_half, p[0]), minus_half(hi[e], high_half, p[1])};
+                            lo[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, bf16x2));
+                        }
+                    }
+                    ph[t][j] = __builtin_bit_cast(bf16x8, make_uint4(hi[0], hi[1], hi[2], hi[3]));
+                    pl[t][j] = __builtin_bit_cast(bf16x8, make_uint4(lo[0], lo[1], lo[2], lo[3]));
+                }
+            l += (sum[0] + sum[1]) + (sum[2] + sum[3]);
+            // O^T += V^T P^T in blocks of 16 tokens: contraction index 8 hw + i stands for the token whose weight the lane
+            // holds there, 16 j + 8 (i / 4) + 4 hw + i % 4 of the 32-token tile
 #pragma unroll
-            for (int kb = 0; kb < kStepBlocks; ++kb) {
-                uint32_t hw[4], lw[4];
+            for (int t = 0; t < NT; ++t)
 #pragma unroll
-                for (int e2 = 0; e2 < 4; ++e2) {
-                    const float2v pr = {sv[x][8 * kb + 2 * e2], sv[x][8 * kb + 2 * e2 + 1]};
-                    hw[e2] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, bf16x2));
-                    lw[e2] = 0u;
+                for (int j = 0; j < 2; ++j) {
+                    const char *v = v_stage + S::v_offset(32 * t + 16 * j, 0) + v_lane;
+                    bf16x8 vop[DT];
+#pragma unroll
+                    for (int dt = 0; dt < DT; ++dt) {
+                        const short4v x0 = lds_read_tr16(v + 256 * dt), x1 = lds_read_tr16(v + S::v_offset(8, 0) + 256 * dt);
+                        const short8v both = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
+                        vop[dt] = __builtin_bit_cast(bf16x8, both);
+                    }
+#pragma unroll
+                    for (int dt = 0; dt < DT; ++dt)
+                        acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vop[dt], ph[t][j], acc[dt], 0, 0, 0);
                     if (SPLIT_P) {
-                        const float2v lo = {pr[0] - __uint_as_float(hw[e2] << 16), pr[1] - __uint_as_float(hw[e2] & 0xffff0000u)};
-                        lw[e2] = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, bf16x2));
+#pragma unroll
+                        for (int dt = 0; dt < DT; ++dt)
+                            acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vop[dt], pl[t][j], acc[dt], 0, 0, 0);
                     }
                 }
-                ph[x][kb] = __builtin_bit_cast(bf16x8, make_uint4(hw[0], hw[1], hw[2], hw[3]));
-                pl[x][kb] = __builtin_bit_cast(bf16x8, make_uint4(lw[0], lw[1], lw[2], lw[3]));
-            }
-        }
-        // O^T += V^T P^T, one 16-column tile of the output at a time
-#pragma unroll
-        for (int kb = 0; kb < kStepBlocks; ++kb) {
-            const char *v_lo = v_stage + S::v_offset(32 * kb, 0) + v_lane_lo;
-            const char *v_hi = v_stage + S::v_offset(32 * kb, 0) + v_lane_hi;
-            // column tiles in groups of kPvGroup: the group's high-part products first, then its low-part ones, so
-            // that two MFMAs on the same accumulator are several instructions apart
-            constexpr int kPvGroup = HGCA_APPEND_PV_GROUP;
-#pragma unroll
-            for (int dt0 = 0; dt0 < DT; dt0 += kPvGroup) {
-                bf16x8 vop[kPvGroup];
-#pragma unroll
-                for (int u = 0; u < kPvGroup; ++u) {
-                    const int at = S::v_offset(0, dt0 + u);
-                    const short4v a0 = lds_read_tr16(v_lo + at), a1 = lds_read_tr16(v_hi + at);
-                    const short8v both = {a0[0], a0[1], a0[2], a0[3], a1[0], a1[1], a1[2], a1[3]};
-                    vop[u] = __builtin_bit_cast(bf16x8, both);
-                }
-#pragma unroll
-                for (int x = 0; x < TILES; ++x)
-#pragma unroll
-                    for (int u = 0; u < kPvGroup; ++u)
-                        acc[x][dt0 + u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop[u], ph[x][kb], acc[x][dt0 + u], 0, 0, 0);
-                if (SPLIT_P) {
-#pragma unroll
-                    for (int x = 0; x < TILES; ++x)
-#pragma unroll
-                        for (int u = 0; u < kPvGroup; ++u)
-                            acc[x][dt0 + u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop[u], pl[x][kb], acc[x][dt0 + u], 0, 0, 0);
-                }
-            }
-        }
-    };
-
-    // a paged tier needs a table of block rows in LDS, which covers a whole split unless the blocks are tiny;
-    // a contiguous tier is plain arithmetic
-    const int sub_len = pass_length(a.kv, nt_total);
-    for (int sub0 = 0; sub0 < nt_total; sub0 += sub_len) {
-        const int nsub = min(sub_len, nt_total - sub0);
-        __syncthreads();                         // the previous table and stages are no longer in use
-        const BlockRows rows = make_block_rows<BLOCK>(s_row, a.kv, a.sh.n_kv_heads, b, kvh, t0 + sub0, nsub);
-        // Step s reads the stages of its parity and requests the rows of step s + 1 into the stages of the other
-        // parity, which were last read in step s - 1: the barrier at the top of the step (before which every wave
-        // waits for its own loads) orders both.
-        const int steps = (nsub + kStepTokens - 1) / kStepTokens;
-        dma_step<D, NW>(a.kv, rows, 0, nsub, s_k0, s_v0);
-        auto step = [&](int s, const char *k_cur, const char *v_cur, char *k_next, char *v_next) {
-            wait_for_own_loads();                // the barrier alone does not wait for LDS-direct loads
-            __syncthreads();
-            if (s + 1 < steps) dma_step<D, NW>(a.kv, rows, s + 1, nsub, k_next, v_next);
-            if (wave_live) step_body(k_cur, v_cur, t0 + sub0 + s * kStepTokens, nsub - s * kStepTokens);
         };
-        for (int s2 = 0; s2 < steps; s2 += 2) {
-            step(s2, s_k0, s_v0, s_k1, s_v1);
-            if (s2 + 1 < steps) step(s2 + 1, s_k1, s_v1, s_k0, s_v0);
-        }
-    }
 
-    // partial of every valid row: lane (n, g) holds output columns dt*16 + 4g .. +3 of row n of each tile
-#pragma unroll
-    for (int x = 0; x < TILES; ++x) {
-        if (!ri[x].valid) continue;
-        const int64_t at = ri[x].out_row * a.part.n_splits + split;
+        // a paged tier needs a table of block rows in LDS, which covers a whole split unless the blocks are tiny;
+        // a contiguous tier is plain arithmetic
+        const int sub_len = pass_length(kv, nt_total);
+        for (int sub0 = 0; sub0 < nt_total; sub0 += sub_len) {
+            const int nsub = min(sub_len, nt_total - sub0);
+            __syncthreads();                         // the previous table and stages are no longer in use
+            const BlockRows rows = make_block_rows<BLOCK>(s_row, kv, a1.sh.n_kv_heads, b, kvh, t0 + sub0, nsub);
+            // Step s reads the stages of its parity and requests the rows of step s + 1 into the stages of the other
+            // parity, which were last read in step s - 1: the barrier at the top of the step (before which every wave
+            // waits for its own loads) orders both.
+            const int steps = (nsub + kStepTokens - 1) / kStepTokens;
+            dma_step<D, NW>(kv, rows, 0, nsub, s_k0, s_v0);
+            auto step = [&](int s, const char *k_cur, const char *v_cur, char *k_next, char *v_next) {
+                wait_for_own_loads();                // the barrier alone does not wait for LDS-direct loads
+                __syncthreads();
+                if (s + 1 < steps) dma_step<D, NW>(kv, rows, s + 1, nsub, k_next, v_next);
+                if (wave_live) step_body(k_cur, v_cur, t0 + sub0 + s * kStepTokens, nsub - s * kStepTokens);
+            };
+            for (int s2 = 0; s2 < steps; s2 += 2) {
+                step(s2, s_k0, s_v0, s_k1, s_v1);
+                if (s2 + 1 < steps) step(s2 + 1, s_k1, s_v1, s_k0, s_v0);
+            }
+        }
+
+        // partial of every valid row: the lane holds output columns 32 dt + 8 q + 4 hw .. + 3 of its row
+        l = halves_sum(l);
+        if (!ri.valid) continue;
+        const int64_t at = ri.out_row * a1.part.stride + slot;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
-            *reinterpret_cast<float4 *>(a.part.o + at * D + dt * 16 + 4 * g) =
-                make_float4(acc[x][dt][0], acc[x][dt][1], acc[x][dt][2], acc[x][dt][3]);
-        if (g == 0) {
-            a.part.m[at] = m[x] * a.sh.sm_scale; // the maximum of the scaled scores (-inf stays -inf)
-            a.part.l[at] = l[x];
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4)
+                *reinterpret_cast<float4 *>(a1.part.o + at * D + 32 * dt + 8 * q4 + 4 * hw) =
+                    make_float4(acc[dt][4 * q4], acc[dt][4 * q4 + 1], acc[dt][4 * q4 + 2], acc[dt][4 * q4 + 3]);
+        if (hw == 0) {
+            a1.part.m[at] = (m == -INFINITY) ? -INFINITY : m * a1.sh.sm_scale;         // the shift of the weights, in scaled scores
+            a1.part.l[at] = l;
         }
     }
 }
@@ -646,15 +674,15 @@ hipError_t launch_weights_f32_group(const AppendArgs &a, dim3 grid, hipStream_t 
 }
 
 template <int D, bool SPLIT_P>
-hipError_t launch_attn_group(const AppendArgs &a, const AppendArgs &a2, dim3 grid, hipStream_t s)
+hipError_t launch_attn_group(const AppendArgs &a, const AppendArgs &a2, const LineDev &line, int two, dim3 grid,
+                             hipStream_t s)
 {
-    constexpr int T = HGCA_APPEND_TILES;
-    const dim3 block(kABlock / T);
+    const dim3 block(kAttnBlock);
     switch (a.sh.group) {
-    case 1: hipLaunchKernelGGL((append_attn_kernel<D, 1, SPLIT_P, T>), grid, block, 0, s, a, a2); break;
-    case 2: hipLaunchKernelGGL((append_attn_kernel<D, 2, SPLIT_P, T>), grid, block, 0, s, a, a2); break;
-    case 4: hipLaunchKernelGGL((append_attn_kernel<D, 4, SPLIT_P, T>), grid, block, 0, s, a, a2); break;
-    case 8: hipLaunchKernelGGL((append_attn_kernel<D, 8, SPLIT_P, T>), grid, block, 0, s, a, a2); break;
+    case 1: hipLaunchKernelGGL((append_attn_kernel<D, 1, SPLIT_P>), grid, block, 0, s, a, a2, line, two); break;
+    case 2: hipLaunchKernelGGL((append_attn_kernel<D, 2, SPLIT_P>), grid, block, 0, s, a, a2, line, two); break;
+    case 4: hipLaunchKernelGGL((append_attn_kernel<D, 4, SPLIT_P>), grid, block, 0, s, a, a2, line, two); break;
+    case 8: hipLaunchKernelGGL((append_attn_kernel<D, 8, SPLIT_P>), grid, block, 0, s, a, a2, line, two); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -675,27 +703,26 @@ hipError_t launch_weights_group(const AppendArgs &a, const AppendArgs &a2, int n
 
 }  // namespace
 
-hipError_t launch_append_attn2(int head_dim, const AppendArgs &a, const AppendArgs &a2, hipStream_t s)
+hipError_t launch_append_attn(int head_dim, const AppendArgs &a, const AppendArgs *second, const LineDev &line,
+                              hipStream_t s)
 {
-    const int n_splits = a.part.n_splits + a2.part.n_splits;
-    if (a.sh.batch == 0 || a.n_q == 0 || n_splits == 0) return hipSuccess;
-    if (a2.part.n_splits > 0 && (a2.n_q != a.n_q || a2.one_part_p != a.one_part_p || a2.q != a.q || a2.sh.group != a.sh.group ||
-                                 a2.sh.batch != a.sh.batch || a2.sh.n_kv_heads != a.sh.n_kv_heads))
-        return hipErrorInvalidValue;             // the two tiers share the queries and the launch shape
+    if (a.sh.batch == 0 || a.n_q == 0) return hipSuccess;
+    const AppendArgs &a2 = second ? *second : a;
+    if (line.shares <= 0 || a.part.stride != line.shares + (second ? 1 : 0) || a2.n_q != a.n_q || a2.q != a.q ||
+        a2.one_part_p != a.one_part_p || a2.sh.group != a.sh.group || a2.sh.batch != a.sh.batch ||
+        a2.sh.n_kv_heads != a.sh.n_kv_heads || a2.part.o != a.part.o || a2.part.stride != a.part.stride)
+        return hipErrorInvalidValue;             // the two tiers share the queries, the launch shape and the partials
     const int n_qb = (a.n_q * a.sh.group + kRowsPerBlock - 1) / kRowsPerBlock;
-    dim3 grid(n_splits, a.sh.n_kv_heads * n_qb, a.sh.batch);
+    const int64_t streams = (int64_t)line.shares * a.sh.n_kv_heads * a.sh.batch;
+    const int64_t blocks = n_qb == 1 ? streams : (streams + kXcds - 1) / kXcds * kXcds * n_qb;
+    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)blocks);
+    const int two = second ? 1 : 0;
     if (head_dim == 64)
-        return a.one_part_p ? launch_attn_group<64, false>(a, a2, grid, s) : launch_attn_group<64, true>(a, a2, grid, s);
+        return a.one_part_p ? launch_attn_group<64, false>(a, a2, line, two, grid, s) : launch_attn_group<64, true>(a, a2, line, two, grid, s);
     if (head_dim == 128)
-        return a.one_part_p ? launch_attn_group<128, false>(a, a2, grid, s) : launch_attn_group<128, true>(a, a2, grid, s);
+        return a.one_part_p ? launch_attn_group<128, false>(a, a2, line, two, grid, s) : launch_attn_group<128, true>(a, a2, line, two, grid, s);
     return hipErrorInvalidValue;
-}
-
-hipError_t launch_append_attn(int head_dim, const AppendArgs &a, hipStream_t s)
-{
-    AppendArgs none = a;                         // no second tier: every workgroup takes a split of `a`
-    none.part.n_splits = 0;
-    return launch_append_attn2(head_dim, a, none, s);
 }
 
 hipError_t launch_append_weights2(int head_dim, const AppendArgs &a, int n_chunks, const AppendArgs &a2, int n_chunks2,

@@ -109,9 +109,10 @@ __global__ __launch_bounds__(kBlock) void dense_attn_mfma_kernel(KernelArgs a)
 // One workgroup folds one (b, h) row (fold_device.hpp); lse_p, if given, receives the log-sum-exp of set p alone.
 template <int D, bool OUT_BF16>
 __global__ __launch_bounds__(kFoldBlock) void combine_kernel(Partials p, Partials q, void *o, float *lse, float *lse_p,
-                                                             float *lse_q)
+                                                             float *lse_q, LineDev line)
 {
     __shared__ FoldShared<D> sh;
+    if (line.shares) line_sets<D>(line, Partials(p), blockIdx.x, p, q);          // uniform over the launch
     if (lse_p) fold_row<D, OUT_BF16, true>(sh, p, q, o, lse, lse_p, blockIdx.x, lse_q);   // uniform over the launch
     else fold_row<D, OUT_BF16, false>(sh, p, q, o, lse, nullptr, blockIdx.x);
 }
@@ -121,17 +122,18 @@ __global__ __launch_bounds__(kFoldBlock) void combine_kernel(Partials p, Partial
 // itself, so a workgroup folds kFoldBlock / (D / 4) rows and needs neither LDS nor a barrier.
 template <int D, bool OUT_BF16>
 __global__ __launch_bounds__(kFoldBlock) void combine_rows_kernel(Partials p, Partials q, void *o, float *lse, float *lse_p,
-                                                                  float *lse_q, int64_t n_rows)
+                                                                  float *lse_q, int64_t n_rows, LineDev line)
 {
     constexpr int C4 = D / 4, R = kFoldBlock / C4;
     const int64_t row = (int64_t)blockIdx.x * R + threadIdx.x / C4;
     const int c4 = threadIdx.x % C4;
     if (row >= n_rows) return;
+    if (line.shares) line_sets<D>(line, Partials(p), row, p, q);                 // uniform over the launch
     const int np = p.n_splits, nq = q.n_splits, n = np + nq;
-    auto m_of = [&](int s) { return s < np ? p.m[row * np + s] : q.m[row * nq + (s - np)]; };
-    auto l_of = [&](int s) { return s < np ? p.l[row * np + s] : q.l[row * nq + (s - np)]; };
+    auto m_of = [&](int s) { return s < np ? p.m[row * p.stride + s] : q.m[row * q.stride + (s - np)]; };
+    auto l_of = [&](int s) { return s < np ? p.l[row * p.stride + s] : q.l[row * q.stride + (s - np)]; };
     auto o_of = [&](int s) {
-        const float *base = s < np ? p.o + (row * np + s) * D : q.o + (row * nq + (s - np)) * D;
+        const float *base = s < np ? p.o + (row * p.stride + s) * D : q.o + (row * q.stride + (s - np)) * D;
         return *reinterpret_cast<const float4 *>(base + 4 * c4);
     };
     float M = -INFINITY;
@@ -168,9 +170,9 @@ __global__ __launch_bounds__(kFoldBlock) void combine_rows_kernel(Partials p, Pa
         const Partials &t = c4 == 1 ? p : q;
         const int nt = t.n_splits;
         float Mt = -INFINITY, Lt = 0.f;
-        for (int s = 0; s < nt; ++s) Mt = fmaxf(Mt, t.m[row * nt + s]);
+        for (int s = 0; s < nt; ++s) Mt = fmaxf(Mt, t.m[row * t.stride + s]);
         if (Mt != -INFINITY)
-            for (int s = 0; s < nt; ++s) Lt = fmaf(t.l[row * nt + s], expf(t.m[row * nt + s] - Mt), Lt);
+            for (int s = 0; s < nt; ++s) Lt = fmaf(t.l[row * t.stride + s], expf(t.m[row * t.stride + s] - Mt), Lt);
         (c4 == 1 ? lse_p : lse_q)[row] = (Mt != -INFINITY) ? Mt + logf(Lt) : -INFINITY;
     }
 }
@@ -341,27 +343,41 @@ hipError_t launch_combine(int head_dim, int64_t n_rows, const Partials &p, float
     return launch_combine2(head_dim, n_rows, p, none, o, 0, lse, s);
 }
 
+namespace {
+
+hipError_t launch_fold(int head_dim, int64_t n_rows, const Partials &p, const Partials &q, const LineDev &line, int n_slots,
+                       void *o, int o_dtype, float *lse, float *lse_p, float *lse_q, hipStream_t s)
+{
+    if (n_rows == 0) return hipSuccess;
+    const bool many = n_rows >= HGCA_FOLD_MANY_ROWS && n_slots <= 64 && (head_dim == 64 || head_dim == 128);
+    const int rows_per_wg = many ? kFoldBlock / (head_dim / 4) : 1;
+    const dim3 grid((unsigned)((n_rows + rows_per_wg - 1) / rows_per_wg)), block(kFoldBlock);
+#define HGCA_FOLD_CASE(D, BF)                                                                                             \
+    if (head_dim == D && o_dtype == (BF ? 1 : 0)) {                                                                       \
+        if (many) HGCA_LAUNCH((combine_rows_kernel<D, BF>), grid, block, s, p, q, o, lse, lse_p, lse_q, n_rows, line);    \
+        else HGCA_LAUNCH((combine_kernel<D, BF>), grid, block, s, p, q, o, lse, lse_p, lse_q, line);                      \
+        return hipGetLastError();                                                                                         \
+    }
+    HGCA_FOLD_CASE(64, false) HGCA_FOLD_CASE(64, true) HGCA_FOLD_CASE(128, false) HGCA_FOLD_CASE(128, true)
+#undef HGCA_FOLD_CASE
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
 hipError_t launch_combine2(int head_dim, int64_t n_rows, const Partials &p, const Partials &q, void *o, int o_dtype,
                            float *lse, hipStream_t s, float *lse_p, float *lse_q)
 {
     if (lse_q && !lse_p) return hipErrorInvalidValue;
-    if (n_rows == 0) return hipSuccess;
-    if (n_rows >= HGCA_FOLD_MANY_ROWS && p.n_splits + q.n_splits <= 64 && (head_dim == 64 || head_dim == 128)) {
-        const int rows_per_wg = kFoldBlock / (head_dim / 4);
-        const dim3 grid((unsigned)((n_rows + rows_per_wg - 1) / rows_per_wg)), block(kFoldBlock);
-        if (head_dim == 64 && o_dtype == 0) HGCA_LAUNCH((combine_rows_kernel<64, false>), grid, block, s, p, q, o, lse, lse_p, lse_q, n_rows);
-        else if (head_dim == 64) HGCA_LAUNCH((combine_rows_kernel<64, true>), grid, block, s, p, q, o, lse, lse_p, lse_q, n_rows);
-        else if (o_dtype == 0) HGCA_LAUNCH((combine_rows_kernel<128, false>), grid, block, s, p, q, o, lse, lse_p, lse_q, n_rows);
-        else HGCA_LAUNCH((combine_rows_kernel<128, true>), grid, block, s, p, q, o, lse, lse_p, lse_q, n_rows);
-        return hipGetLastError();
-    }
-    const dim3 grid((unsigned)n_rows), block(kFoldBlock);
-    if (head_dim == 64 && o_dtype == 0) HGCA_LAUNCH((combine_kernel<64, false>), grid, block, s, p, q, o, lse, lse_p, lse_q);
-    else if (head_dim == 64 && o_dtype == 1) HGCA_LAUNCH((combine_kernel<64, true>), grid, block, s, p, q, o, lse, lse_p, lse_q);
-    else if (head_dim == 128 && o_dtype == 0) HGCA_LAUNCH((combine_kernel<128, false>), grid, block, s, p, q, o, lse, lse_p, lse_q);
-    else if (head_dim == 128 && o_dtype == 1) HGCA_LAUNCH((combine_kernel<128, true>), grid, block, s, p, q, o, lse, lse_p, lse_q);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
+    return launch_fold(head_dim, n_rows, p, q, LineDev{}, p.n_splits + q.n_splits, o, o_dtype, lse, lse_p, lse_q, s);
+}
+
+hipError_t launch_combine_line(int head_dim, int64_t n_rows, const Partials &t, const LineDev &line, float *o, float *lse,
+                               float *lse_first, float *lse_second, hipStream_t s)
+{
+    if (line.shares <= 0 || t.stride != line.shares + 1 || line.rows_per_seq <= 0 || (lse_first && !lse_second))
+        return hipErrorInvalidValue;
+    return launch_fold(head_dim, n_rows, t, Partials{}, line, t.stride, o, 0, lse, lse_second, lse_first, s);
 }
 
 hipError_t launch_merge(int head_dim, int64_t n_rows, const float *o_a, const float *lse_a, const float *o_b,

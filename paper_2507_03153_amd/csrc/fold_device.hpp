@@ -16,6 +16,20 @@ template <int D> struct FoldShared {
     float lse_p;
 };
 
+// The two sets of a line's row (LineDev): p is the second tier, q the first.
+template <int D>
+__device__ __forceinline__ void line_sets(const LineDev &line, const Partials &t, int64_t row, Partials &p, Partials &q)
+{
+    const int n1 = LineCut(line, (int)(row / line.rows_per_seq)).first_slots();
+    q = t;
+    q.n_splits = n1;
+    p = t;
+    p.o += (int64_t)n1 * D;
+    p.m += n1;
+    p.l += n1;
+    p.n_splits = t.stride - n1;
+}
+
 // Folds split partials of one (b, h) row: M = max m_s, L = sum l_s e^{m_s-M}, O = sum o_s e^{m_s-M} / L,
 // lse = M + ln L.  The splits may come from two partial sets (p and q): folding the splits of the dense
 // window part and of the sparse part in one go is merge_state applied to all of them at once
@@ -34,10 +48,10 @@ __device__ __forceinline__ float fold_row(FoldShared<D> &sh, const Partials &p, 
 
     const int tid = threadIdx.x, sg = tid / C4, c4 = tid % C4;
     const int np = p.n_splits, n = np + q.n_splits;
-    auto m_of = [&](int s) { return s < np ? p.m[row * np + s] : q.m[row * q.n_splits + (s - np)]; };
-    auto l_of = [&](int s) { return s < np ? p.l[row * np + s] : q.l[row * q.n_splits + (s - np)]; };
+    auto m_of = [&](int s) { return s < np ? p.m[row * p.stride + s] : q.m[row * q.stride + (s - np)]; };
+    auto l_of = [&](int s) { return s < np ? p.l[row * p.stride + s] : q.l[row * q.stride + (s - np)]; };
     auto o_of = [&](int s) {
-        const float *base = s < np ? p.o + (row * np + s) * D : q.o + (row * q.n_splits + (s - np)) * D;
+        const float *base = s < np ? p.o + (row * p.stride + s) * D : q.o + (row * q.stride + (s - np)) * D;
         return *reinterpret_cast<const float4 *>(base + 4 * c4);
     };
     // One round trip to memory for the usual split counts: a thread's first PRE splits (m, l and its four columns
@@ -62,11 +76,11 @@ __device__ __forceinline__ float fold_row(FoldShared<D> &sh, const Partials &p, 
     if (WANT_P && tid / kWave == kFoldWaves - 1) {
         const int lane = tid % kWave;
         float Mp = -INFINITY;
-        for (int s = lane; s < np; s += kWave) Mp = fmaxf(Mp, p.m[row * np + s]);
+        for (int s = lane; s < np; s += kWave) Mp = fmaxf(Mp, p.m[row * p.stride + s]);
         Mp = wave_max(Mp);
         float Lp = 0.f;
         if (Mp != -INFINITY)
-            for (int s = lane; s < np; s += kWave) Lp = fmaf(p.l[row * np + s], expf(p.m[row * np + s] - Mp), Lp);
+            for (int s = lane; s < np; s += kWave) Lp = fmaf(p.l[row * p.stride + s], expf(p.m[row * p.stride + s] - Mp), Lp);
         Lp = wave_sum(Lp);
         if (lane == 0) {
             const float v = (Mp != -INFINITY) ? Mp + logf(Lp) : -INFINITY;
@@ -78,11 +92,11 @@ __device__ __forceinline__ float fold_row(FoldShared<D> &sh, const Partials &p, 
     if (WANT_P && lse_q && tid / kWave == kFoldWaves - 2) {
         const int lane = tid % kWave, nq = q.n_splits;
         float Mq = -INFINITY;
-        for (int s = lane; s < nq; s += kWave) Mq = fmaxf(Mq, q.m[row * nq + s]);
+        for (int s = lane; s < nq; s += kWave) Mq = fmaxf(Mq, q.m[row * q.stride + s]);
         Mq = wave_max(Mq);
         float Lq = 0.f;
         if (Mq != -INFINITY)
-            for (int s = lane; s < nq; s += kWave) Lq = fmaf(q.l[row * nq + s], expf(q.m[row * nq + s] - Mq), Lq);
+            for (int s = lane; s < nq; s += kWave) Lq = fmaf(q.l[row * q.stride + s], expf(q.m[row * q.stride + s] - Mq), Lq);
         Lq = wave_sum(Lq);
         if (lane == 0) lse_q[row] = (Mq != -INFINITY) ? Mq + logf(Lq) : -INFINITY;
     }

@@ -183,7 +183,7 @@ Partials partials_at(void *ws, const WsLayout &w, int n_splits)
     p.o = reinterpret_cast<float *>(base + w.part_o);
     p.m = reinterpret_cast<float *>(base + w.part_m);
     p.l = reinterpret_cast<float *>(base + w.part_l);
-    p.n_splits = n_splits;
+    p.n_splits = p.stride = n_splits;
     return p;
 }
 
@@ -904,21 +904,38 @@ int hgca_ctx_compact(const hgca_shape *shape, const hgca_kv_view *pool, const in
 
 namespace {
 
-// Split size of the append-stage attention: enough workgroups to fill the GPU, few enough splits that the
-// per-row partials stay small beside the K/V traffic.
-int append_want_splits(const hgca_shape *s, int32_t n_q)
+// Blocks of up to 128 query rows over all (sequence, KV head) pairs: each is attended to by its own workgroups.
+int64_t append_units(const hgca_shape *s, int32_t n_q)
 {
     const int64_t n_qb = ((int64_t)n_q * group_of(s) + 127) / 128;
-    const int64_t units = std::max<int64_t>(1, (int64_t)s->batch * s->n_kv_heads * n_qb);
-    return (int)std::max<int64_t>(1, HGCA_APPEND_TARGET_WGS / units);
+    return std::max<int64_t>(1, (int64_t)s->batch * s->n_kv_heads * n_qb);
 }
 
-int append_chunk(const hgca_shape *s, int32_t n_q, int64_t cap)
+int append_want_splits(const hgca_shape *s, int32_t n_q)
 {
-    const int want = append_want_splits(s, n_q);
-    int64_t chunk = (std::max<int64_t>(cap, 1) + want - 1) / want;
-    chunk = (chunk + 63) / 64 * 64;
-    return (int)std::min<int64_t>(kMaxAppendChunk, std::max<int64_t>(kMinChunk, chunk));
+    return (int)std::max<int64_t>(1, HGCA_APPEND_TARGET_WGS / append_units(s, n_q));
+}
+
+// Workgroups that share the `tokens` (by capacity) of a unit, at most `most`: the number for which the launch takes the
+// least time, counted in 64-token steps: rounds of HGCA_APPEND_TARGET_WGS workgroups (what the device holds at once)
+// times the steps of a share, plus what a share costs beside its steps -- loading the queries, the first rows' latency
+// and a partial of 64 KB to write and fold, together about five steps (a step takes 2.8 us, a share's fixed part 15 us
+// on 509 queries x 32 K tokens).
+int append_shares(const hgca_shape *s, int32_t n_q, int64_t tokens, int most)
+{
+    constexpr int kShareOverhead = 5;
+    const int64_t units = append_units(s, n_q), steps = std::max<int64_t>(1, (tokens + kLineStep - 1) / kLineStep);
+    int best = 1;
+    int64_t best_cost = INT64_MAX;
+    for (int n = 1; n <= most && n <= steps; ++n) {
+        const int64_t rounds = (n * units + HGCA_APPEND_TARGET_WGS - 1) / HGCA_APPEND_TARGET_WGS;
+        const int64_t cost = rounds * ((steps + n - 1) / n + kShareOverhead);
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = n;
+        }
+    }
+    return best;
 }
 
 struct AppendWs {
@@ -991,7 +1008,7 @@ int hgca_append_attn(const hgca_shape *shape, const void *q, int32_t n_q, const 
         d.part.o = reinterpret_cast<float *>(base + w.o);
         d.part.m = reinterpret_cast<float *>(base + w.m);
         d.part.l = reinterpret_cast<float *>(base + w.l);
-        d.part.n_splits = std::max(1, n_splits_for(tier->cap, d.chunk));
+        d.part.n_splits = d.part.stride = std::max(1, n_splits_for(tier->cap, d.chunk));
         if (d.part.n_splits > w.max_splits) return HGCA_ERR_WORKSPACE;
         const int64_t rows = (int64_t)d.sh.batch * shape->n_q_heads;
         if (tier->cap == 0) {                    // nothing to attend to: the fold of one empty split writes O = 0, lse = -inf
@@ -1008,64 +1025,35 @@ int hgca_append_attn(const hgca_shape *shape, const void *q, int32_t n_q, const 
     a.n_q = n_q;
     a.causal_tail = (flags & HGCA_APPEND_CAUSAL_TAIL) ? 1 : 0;
     a.one_part_p = (flags & HGCA_APPEND_ONE_PART_P) ? 1 : 0;
-    a.chunk = append_chunk(shape, n_q, tier->cap);
+    const LineDev line{tier->seq_lens, nullptr, tier->cap, 0, append_shares(shape, n_q, tier->cap, w.max_splits), 0};
     char *base = static_cast<char *>(ws);
-    a.part.o = reinterpret_cast<float *>(base + w.o);
-    a.part.m = reinterpret_cast<float *>(base + w.m);
-    a.part.l = reinterpret_cast<float *>(base + w.l);
-    a.part.n_splits = std::max(1, n_splits_for(tier->cap, a.chunk));
-    if (a.part.n_splits > w.max_splits) return HGCA_ERR_WORKSPACE;
-    if ((rc = from_hip(launch_append_attn(shape->head_dim, a, s))) != HGCA_OK) return rc;
+    a.part = Partials{reinterpret_cast<float *>(base + w.o), reinterpret_cast<float *>(base + w.m),
+                      reinterpret_cast<float *>(base + w.l), line.shares, line.shares};
+    if ((rc = from_hip(launch_append_attn(shape->head_dim, a, nullptr, line, s))) != HGCA_OK) return rc;
     const int64_t rows = (int64_t)shape->batch * n_q * shape->n_q_heads;
     return from_hip(launch_combine(shape->head_dim, rows, a.part, o_out, lse_out, s));
 }
 
 namespace {
 
-// Workspace of the two-tier append attention: split partials of the window and of the pool (the split counts are
-// chosen for the two tiers together), and the two per-tier lse rows for callers that do not ask for them.
+// Workspace of the two-tier append attention: the partials of the line of pool and window (one slot more than there
+// are shares), and the two per-tier lse rows for callers that do not ask for them.
 struct TiersWs {
-    size_t o_w, m_w, l_w, o_p, m_p, l_p, lse_w, lse_p, total;
-    int chunk_w, chunk_p, n_w, n_p;
+    size_t o, m, l, lse_w, lse_p, total;
+    int shares;
 };
 
 TiersWs tiers_layout(const hgca_shape *s, int32_t n_q, int64_t win_cap, int64_t pool_cap)
 {
     TiersWs w{};
-    // The splits of a unit are shared out between the tiers in proportion to their capacities (each tier that has
-    // any capacity gets at least one), so that the launch has about as many workgroups as the device holds at once;
-    // a tier whose share would make its splits longer than kMaxAppendChunk gets more.  The kernel then shares a
-    // tier's ACTUAL length out evenly among its splits (the capacity only bounds it).
-    const int want = append_want_splits(s, n_q);
-    const int64_t total = win_cap + pool_cap;
-    auto splits = [&](int64_t cap, int64_t other) -> int {
-        if (cap <= 0) return 0;
-        int64_t n = other > 0 ? std::max<int64_t>(1, std::min<int64_t>(want - 1, (cap * want + total / 2) / total)) : want;
-        n = std::max<int64_t>(n, (cap + kMaxAppendChunk - 1) / kMaxAppendChunk);
-        return (int)std::min<int64_t>(n, (cap + kMinChunk - 1) / kMinChunk);
-    };
-    auto chunk_of = [](int64_t cap, int n) -> int {
-        if (n == 0) return kMinChunk;
-        return (int)std::max<int64_t>(kMinChunk, ((cap + n - 1) / n + 63) / 64 * 64);
-    };
-    w.n_w = splits(win_cap, pool_cap);
-    w.n_p = pool_cap > 0 ? (win_cap > 0 ? std::max(1, std::max(want - w.n_w, 1)) : want) : 0;
-    if (pool_cap > 0) {
-        w.n_p = (int)std::max<int64_t>(w.n_p, (pool_cap + kMaxAppendChunk - 1) / kMaxAppendChunk);
-        w.n_p = (int)std::min<int64_t>(w.n_p, (pool_cap + kMinChunk - 1) / kMinChunk);
-    }
-    w.chunk_w = chunk_of(win_cap, w.n_w);
-    w.chunk_p = chunk_of(pool_cap, w.n_p);
-    w.n_w = win_cap > 0 ? n_splits_for(win_cap, w.chunk_w) : 0;
-    w.n_p = pool_cap > 0 ? n_splits_for(pool_cap, w.chunk_p) : 0;
-    const size_t rows = (size_t)s->batch * n_q * s->n_q_heads;
+    const int64_t tokens = (win_cap + kLineStep - 1) / kLineStep * kLineStep + (pool_cap + kLineStep - 1) / kLineStep * kLineStep;
+    const int most = std::max(append_want_splits(s, n_q), n_splits_for(std::max<int64_t>(tokens, 1), kMaxAppendChunk));
+    w.shares = append_shares(s, n_q, tokens, most);
+    const size_t rows = (size_t)s->batch * n_q * s->n_q_heads, slots = w.shares + 1;
     size_t at = 0;
-    w.o_w = at; at += align_up(rows * w.n_w * s->head_dim * sizeof(float));
-    w.m_w = at; at += align_up(rows * w.n_w * sizeof(float));
-    w.l_w = at; at += align_up(rows * w.n_w * sizeof(float));
-    w.o_p = at; at += align_up(rows * w.n_p * s->head_dim * sizeof(float));
-    w.m_p = at; at += align_up(rows * w.n_p * sizeof(float));
-    w.l_p = at; at += align_up(rows * w.n_p * sizeof(float));
+    w.o = at; at += align_up(rows * slots * s->head_dim * sizeof(float));
+    w.m = at; at += align_up(rows * slots * sizeof(float));
+    w.l = at; at += align_up(rows * slots * sizeof(float));
     w.lse_w = at; at += align_up(rows * sizeof(float));
     w.lse_p = at; at += align_up(rows * sizeof(float));
     w.total = std::max<size_t>(at, kAlign);
@@ -1102,25 +1090,21 @@ int hgca_append_attn_tiers(const hgca_shape *shape, const void *q, int32_t n_q, 
     aw.q = ap.q = q;
     aw.n_q = ap.n_q = n_q;
     aw.one_part_p = ap.one_part_p = (flags & HGCA_APPEND_ONE_PART_P) ? 1 : 0;
-    aw.chunk = w.chunk_w;
-    ap.chunk = w.chunk_p;
     aw.kv = to_dev(window);
     aw.causal_tail = (flags & HGCA_APPEND_CAUSAL_TAIL) ? 1 : 0;
-    aw.part = Partials{reinterpret_cast<float *>(base + w.o_w), reinterpret_cast<float *>(base + w.m_w),
-                       reinterpret_cast<float *>(base + w.l_w), w.n_w};
     ap.kv = to_dev(pool);
     ap.causal_tail = 0;
-    ap.part = Partials{reinterpret_cast<float *>(base + w.o_p), reinterpret_cast<float *>(base + w.m_p),
-                       reinterpret_cast<float *>(base + w.l_p), w.n_p};
-    // the pool's splits take the lower block numbers: they are the bulk of the launch
-    if ((rc = from_hip(launch_append_attn2(shape->head_dim, ap, aw, s))) != HGCA_OK) return rc;
-    // merge_state over the splits of both tiers at once; each tier's own lse comes out of the same fold
+    aw.part = ap.part = Partials{reinterpret_cast<float *>(base + w.o), reinterpret_cast<float *>(base + w.m),
+                                 reinterpret_cast<float *>(base + w.l), w.shares + 1, w.shares + 1};
+    const LineDev line{pool->seq_lens, window->seq_lens, pool->cap, window->cap, w.shares, n_q * shape->n_q_heads};
+    if ((rc = from_hip(launch_append_attn(shape->head_dim, ap, &aw, line, s))) != HGCA_OK) return rc;
+    // merge_state over the partials of both tiers at once; each tier's own lse comes out of the same fold
     const int64_t rows = (int64_t)shape->batch * n_q * shape->n_q_heads;
     float *lse_w = lse_window_out ? lse_window_out : reinterpret_cast<float *>(base + w.lse_w);
     float *lse_p = lse_pool_out ? lse_pool_out : reinterpret_cast<float *>(base + w.lse_p);
     const bool want_tiers = lse_window_out || lse_pool_out;
-    return from_hip(launch_combine2(shape->head_dim, rows, aw.part, ap.part, o_out, 0, lse_out, s,
-                                    want_tiers ? lse_w : nullptr, want_tiers ? lse_p : nullptr));
+    return from_hip(launch_combine_line(shape->head_dim, rows, ap.part, line, o_out, lse_out, want_tiers ? lse_p : nullptr,
+                                        want_tiers ? lse_w : nullptr, s));
 }
 
 namespace {

@@ -15,10 +15,35 @@ constexpr int kMinChunk = 64;
 // Split partials of softmax attention: for every (b, h, split)
 //   m = max score, l = sum e^{s-m}, o[d] = sum e^{s-m} v   (not normalised).
 struct Partials {
-    float *o;      // [B*Hq, n_splits, d]
-    float *m;      // [B*Hq, n_splits]
-    float *l;      // [B*Hq, n_splits]
+    float *o;      // [B*Hq, stride, d]
+    float *m;      // [B*Hq, stride]
+    float *l;      // [B*Hq, stride]
     int32_t n_splits;
+    int32_t stride;    // slots of a row, n_splits or more (two sets may share the slots of a row)
+};
+
+// Two tiers attended to by the same queries as ONE line of tokens -- the first tier's, then the second's, each rounded
+// up to whole steps -- that `shares` workgroups per (sequence, KV head, block of query rows) cut into equal parts
+// whatever the two lengths are.  Share i leaves its part of the first tier in slot i of the partials and its part of
+// the second in slot i + 1: the one share that crosses the boundary writes both, so shares + 1 slots are enough, and
+// the first `first_slots` of them belong to the first tier.
+constexpr int kLineStep = 64;                    // tokens of a step
+struct LineDev {
+    const int32_t *first_lens, *second_lens;     // device [B] or null (= the capacity)
+    int32_t first_cap, second_cap;
+    int32_t shares;                              // 0: no line
+    int32_t rows_per_seq;                        // partial rows of one sequence
+};
+struct LineCut {
+    int32_t first_steps, share_steps;
+    __device__ __forceinline__ LineCut(const LineDev &l, int b) {
+        const int n1 = l.first_lens ? min(max(l.first_lens[b], 0), l.first_cap) : l.first_cap;
+        const int n2 = l.second_lens ? min(max(l.second_lens[b], 0), l.second_cap) : l.second_cap;
+        first_steps = (n1 + kLineStep - 1) / kLineStep;
+        const int steps = first_steps + (n2 + kLineStep - 1) / kLineStep;
+        share_steps = max((steps + l.shares - 1) / l.shares, 1);
+    }
+    __device__ __forceinline__ int first_slots() const { return first_steps / share_steps + 1; }
 };
 
 struct AttnArgs {
@@ -45,6 +70,9 @@ hipError_t launch_combine(int head_dim, int64_t n_rows, const Partials &p, float
 hipError_t launch_combine2(int head_dim, int64_t n_rows, const Partials &p, const Partials &q, void *o, int o_dtype,
                            float *lse, hipStream_t s, float *lse_p = nullptr,   // lse_p / lse_q: optional lse of set p / q alone
                            float *lse_q = nullptr);
+// The fold of a line's partials `t` (shares + 1 slots per row); lse_first / lse_second: optional lse of either tier.
+hipError_t launch_combine_line(int head_dim, int64_t n_rows, const Partials &t, const LineDev &line, float *o, float *lse,
+                               float *lse_first, float *lse_second, hipStream_t s);
 
 hipError_t launch_merge(int head_dim, int64_t n_rows, const float *o_a, const float *lse_a, const float *o_b,
                         const float *lse_b, void *o_out, int o_dtype, float *lse_out, hipStream_t s);
@@ -113,7 +141,7 @@ hipError_t launch_threshold_select(const ThresholdArgs &a, int64_t n_rows, hipSt
 
 // ---- append stage: N queries per sequence over one tier (bf16, MFMA) ----
 
-constexpr int kMaxAppendChunk = 8192;   // tokens of one split of the append-stage attention at most
+constexpr int kMaxAppendChunk = 8192;   // tokens of capacity per share of the append-stage attention at most, where shares are counted
 
 struct AppendArgs {
     ShapeDev sh;
@@ -122,14 +150,15 @@ struct AppendArgs {
     int32_t n_q;               // N
     int32_t causal_tail;       // 1: the tier's last N valid tokens are the queries' own; query i sees tokens < len-N+i+1
     int32_t one_part_p;        // 1: the weights enter the second product as one bf16 value instead of a high and a low part
-    int32_t chunk;             // tokens per split (attention) or per workgroup (weights), a multiple of 64
-    Partials part;             // attention: rows are (b, query, head)
+    int32_t chunk;             // weights: tokens per workgroup, a multiple of 64
+    Partials part;             // attention: rows are (b, query, head), one slot per share, or shares + 1 with a second tier
     const float *lse;          // weights: [B, N, Hq], the tier's log-sum-exp per query and head
     float *a_out;              // weights: [B, Hq, cap]
 };
-hipError_t launch_append_attn(int head_dim, const AppendArgs &a, hipStream_t s);
-// two tiers in one launch (same queries and shape; each tier with its own view, mask rule, split size and partials)
-hipError_t launch_append_attn2(int head_dim, const AppendArgs &a, const AppendArgs &a2, hipStream_t s);
+// One tier (second = nullptr, `shares` slots) or two as a line (same queries, shape and partials; each tier with its
+// own view and mask rule; `shares` + 1 slots).
+hipError_t launch_append_attn(int head_dim, const AppendArgs &first, const AppendArgs *second, const LineDev &line,
+                              hipStream_t s);
 hipError_t launch_append_weights(int head_dim, const AppendArgs &a, int n_chunks, hipStream_t s);
 // the weights of two tiers (same queries and shape) in one launch
 hipError_t launch_append_weights2(int head_dim, const AppendArgs &a, int n_chunks, const AppendArgs &a2, int n_chunks2,

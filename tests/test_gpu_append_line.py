@@ -1,0 +1,45 @@
+"""Append-stage attention over pool and window as one line of tokens: lengths at which the shares of the line fall on,
+before and behind the boundary between the tiers, several blocks of query rows, and paged tiers whose block size is no
+power of two."""
+import numpy as np
+import pytest
+
+from test_gpu_append import gpu, make_inputs, run_case, to_paged  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("kw", [
+    dict(B=3, N=9, Hq=8, Hkv=2, d=128, W=128, P=1024, w_lens=(128, 9, 64), p_lens=(1024, 1000, 0)),   # whole steps, no pool
+    dict(B=1, N=70, Hq=16, Hkv=2, d=128, W=200, P=700),                      # five row blocks, streams no multiple of 8
+    dict(B=1, N=4, Hq=4, Hkv=1, d=128, W=640, P=5000),                       # more shares than a unit has elsewhere
+    dict(B=2, N=33, Hq=2, Hkv=2, d=64, W=65, P=4033, w_lens=(65, 33), p_lens=(1, 4033)),
+    dict(B=9, N=130, Hq=4, Hkv=1, d=64, W=192, P=320, w_lens=(192, 130, 131, 160, 191, 150, 140, 170, 180),
+         p_lens=(320, 0, 64, 63, 65, 128, 1, 319, 256)),
+], ids=["boundaries", "row_blocks", "many_shares", "d64_ragged", "ragged_row_blocks"])
+def test_shares_of_the_line(gpu, kw):  # noqa: F811
+    run_case(gpu, 71, **kw)
+
+
+@pytest.mark.parametrize("block", [16, 48, 80, 64])
+def test_block_sizes_read_the_same_rows(gpu, block):  # noqa: F811
+    """The same rows in blocks of any size: bit-identical to the contiguous tier (same arithmetic, same shares)."""
+    torch, hgca, runner = gpu
+    B, N, Hq, Hkv, d, W, P = 2, 40, 8, 2, 128, 240, 1200
+    q, Kw, Vw, wl_, Kp, Vp, pl_ = make_inputs(5, B, N, Hq, Hkv, d, W, P, (240, 77), (1200, 611))
+    g = lambda a: runner._to_gpu(a, "cuda:0")
+    shape = hgca.Shape(hgca.BF16, B, Hq, Hkv, d, 1.0 / np.sqrt(d))
+    tiers = [(hgca.Tier(g(Kw), g(Vw), W, g(wl_)), hgca.Tier(g(Kp), g(Vp), P, g(pl_))),
+             (to_paged(runner, hgca, torch, Kw, Vw, wl_, W, block, 1, "cuda:0"),
+              to_paged(runner, hgca, torch, Kp, Vp, pl_, P, block, 2, "cuda:0"))]
+    out = []
+    for win, pool in tiers:
+        f = lambda *s: torch.full(s, float("nan"), dtype=torch.float32, device="cuda:0")
+        o, lse, lw, lp, a_w, a_p = f(B, N, Hq, d), f(B, N, Hq), f(B, N, Hq), f(B, N, Hq), f(B, Hq, W), f(B, Hq, P)
+        ws = hgca.append_tiers_workspace(shape, N, W, P, "cuda:0")
+        hgca.append_attn_tiers(shape, g(q), win, pool, o, lse, ws, lse_window_out=lw, lse_pool_out=lp)
+        hgca.append_weights_tiers(shape, g(q), win, pool, lw, lp, a_w, a_p)
+        out.append((o, lse, lw, lp, a_w, a_p))
+    torch.cuda.synchronize()
+    for x, y in zip(*out):
+        assert torch.isfinite(x).all() and torch.equal(x, y)
