@@ -77,12 +77,6 @@ __device__ __forceinline__ BlockRows make_block_rows(uint32_t *s_tab, const KvDe
     return m;
 }
 
-// The value of the lane ROT places further on in the same row of 16 lanes (DPP row_ror).
-template <int ROT>
-__device__ __forceinline__ float row_rotate(float x) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + ROT, 0xf, 0xf, true));
-}
-
 // Reductions over the two halves of a wave (lanes n and n + 32 hold partial results of one query row):
 // v_permlane32_swap of a register with itself returns the lower half twice and the upper half twice, one VALU
 // instruction where a lane shuffle would go through the LDS pipeline.
@@ -109,39 +103,6 @@ __device__ __forceinline__ RowInfo row_info(const AppendArgs &a, int b, int kvh,
     ri.query = ri.valid ? r / G : 0;
     ri.out_row = ((int64_t)b * a.n_q + ri.query) * a.sh.n_q_heads + kvh * G + (ri.valid ? r % G : 0);
     return ri;
-}
-
-template <int D>
-__device__ __forceinline__ void load_q_tile(const AppendArgs &a, const RowInfo &ri, int g, bf16x8 (&qop)[D / 32]) {
-#pragma unroll
-    for (int kk = 0; kk < D / 32; ++kk) {
-        uint4 r = make_uint4(0u, 0u, 0u, 0u);
-        if (ri.valid) r = load16(static_cast<const char *>(a.q) + (ri.out_row * D + 32 * kk + 8 * g) * 2);
-        qop[kk] = __builtin_bit_cast(bf16x8, r);
-    }
-}
-
-// Raw scores <q, k> (no softmax scale yet) of one 16-row tile for the step's tokens: sv[8*kb + 4*tt + r] belongs
-// to step token 32*kb + 16*tt + 4*g + r and query row lane % 16.  With MASK, tokens at or beyond `limit` (counted
-// from the step's first token) read -inf.
-// `k_piece(t, kk)` reads this lane's A operand: 8 elements from column 32 kk + 8 (lane / 16) on of the K row of
-// token 16 t + lane % 16 of the step.
-template <int D, bool MASK, typename KPiece>
-__device__ __forceinline__ void tile_scores(KPiece k_piece, const bf16x8 (&qop)[D / 32], int limit,
-                                            float (&sv)[8 * kStepBlocks])
-{
-    const int lane = threadIdx.x % kWave, g = lane / 16;
-#pragma unroll
-    for (int t = 0; t < 2 * kStepBlocks; ++t) {  // 16-token tiles of the step
-        floatx4 c = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kk = 0; kk < D / 32; ++kk) {
-            const uint4 ka = k_piece(t, kk);
-            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka), qop[kk], c, 0, 0, 0);
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) sv[4 * t + r] = (!MASK || 16 * t + 4 * g + r < limit) ? c[r] : -INFINITY;
-    }
 }
 
 // LDS stage of the attention kernel: the rows of a step are brought in by LDS-direct loads (global_load_lds, 16
@@ -488,112 +449,226 @@ __global__ __launch_bounds__(kAttnBlock, 2) void append_attn_kernel(AppendArgs a
     }
 }
 
-// Query-averaged softmax weights of a tier: a_out[b, h, t] = (1/N) sum_i e^{s_it - lse_i} over the queries i
-// that see token t (lse_i is the tier's own log-sum-exp for query i), 0 beyond the length.  One workgroup
-// owns a_out[b, heads of kvh, t0 .. t0 + chunk): every step the waves' sums go through LDS to one thread
-// per entry, which writes (first block of 128 query rows) or adds to (further blocks) the entry.
+// Query-averaged softmax weights of a tier: a_out[b, h, t] = (1/N) sum_i e^{s_it - lse_i} over the queries i that see
+// token t (lse_i is the tier's own log-sum-exp for query i), 0 beyond the length.
+//
+// Here the scores are wanted with a TOKEN per lane, S[row, token] = Q[row, :] . K[token, :] (A = Q, B = K): the rows of
+// a tile are the result's registers, so the sum over the queries is an addition per score into one of min(G, 4)
+// registers and nothing is exchanged between lanes but one last addition of the two halves of a wave.  A wave takes
+// 32-token tiles of its own and meets all rows: the queries (128 rows at a time) stay in LDS for the eight waves of the
+// workgroup, a tile's K rows arrive by LDS-direct loads in a slot that only its wave reads, go to registers as the B
+// operand, and the slot takes the next tile at once -- no barrier and no sums through LDS in the loop.  Window and pool
+// are one line of equal shares, as in the attention kernel, so that the launch is one full round of workgroups however
+// the two lengths compare.  With more than 128 rows a share goes through blocks of 512 tokens, every block once per 128
+// rows (it stays in the caches meanwhile), adding to a_out.
+// 8 x 32 queries on 32 K tokens, 32 / 8 heads: 185 -> 126 us.  The loads alone take 101 us (124 us without the
+// streaming policy; more of them in flight, 12 or 15 waves, change nothing), the arithmetic alone 115 us.  The previous
+// kernel (tokens in registers, rows over the lanes) spent two lane exchanges per score and a barrier per 64 tokens,
+// and its 2048-token workgroups came out at 1.2 rounds.
+template <int D> struct WeightsStage {
+    static constexpr int kPieces = D / 8, kRowBytes = D * 2, kGroupRows = 1024 / kRowBytes;
+    static __device__ __forceinline__ int swizzle(int row) { return (row / (16 / kPieces)) % kPieces; }
+    static __device__ __forceinline__ int offset(int row, int piece) { return row * kRowBytes + 16 * (piece ^ swizzle(row)); }
+};
+constexpr int kWTile = 32, kWWaves = 8, kWBlock = kWWaves * kWave;
+constexpr int kNonTemporal = 2;                  // cache policy of a load: streamed once
+constexpr int kWManyRowTokens = 512;             // tokens of a block that more than one pass over the rows goes through
+
 template <int D, int G>
-__global__ __launch_bounds__(kABlock) void append_weights_kernel(AppendArgs a1, AppendArgs a2, int n1)
+__global__ __launch_bounds__(kWBlock, 2) void append_weights_kernel(AppendArgs a1, AppendArgs a2, LineDev line, int two_tiers)
 {
-    // a launch may serve two tiers: the first n1 workgroups along x take chunks of a1's tier, the rest of a2's
-    const bool second = (int)blockIdx.x >= n1;                   // uniform over the workgroup
-    const AppendArgs &a = second ? a2 : a1;
-    using S = DmaStage<D, kAWaves>;
-    // the K rows of a step arrive by LDS-direct loads, as in the attention kernel: two stages as separate arrays
-    __shared__ __attribute__((aligned(1024))) char s_k0[S::kBytes];
-    __shared__ __attribute__((aligned(1024))) char s_k1[S::kBytes];
-    __shared__ uint32_t s_row[kSub];
-    __shared__ __attribute__((aligned(16))) float s_part[2][kAWaves][G][kStepTokens];   // read after the next step's barrier
-
-    const int chunk_id = (int)blockIdx.x - (second ? n1 : 0), kvh = blockIdx.y, b = blockIdx.z;
-    const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave, n = lane % 16, g = lane / 16;
-    const int len = tier_len(a.kv, b);
-    const int t0 = chunk_id * a.chunk;
-    const int n_here = min(a.chunk, a.kv.cap - t0);              // entries of a_out this workgroup writes
-    const int nt_total = min(a.chunk, len - t0);                 // valid tokens among them (may be <= 0)
-    const float inv_n = 1.f / (float)a.n_q;
+    using S = WeightsStage<D>;
+    constexpr int KK = D / 16, RT = kRowsPerBlock / 32, NS = G < 4 ? G : 4;
     constexpr float kLog2e = 1.4426950408889634f;
-    const float scale2 = a.sh.sm_scale * kLog2e;
-    float *out = a.a_out + ((int64_t)b * a.sh.n_q_heads + kvh * G) * a.kv.cap + t0;
+    typedef const __attribute__((address_space(1))) void *GlobalPtr;
+    typedef __attribute__((address_space(3))) void *LdsPtr;
+    __shared__ __attribute__((aligned(1024))) char s_q[kRowsPerBlock * S::kRowBytes];
+    __shared__ __attribute__((aligned(1024))) char s_k[kWWaves][kWTile * S::kRowBytes];
+    __shared__ __attribute__((aligned(16))) float s_shift[kRowsPerBlock];        // minus the rows' lse in units of ln 2
+    __shared__ uint32_t s_row[kSub];
 
-    int k_lane[D / 32];                          // this lane's A-operand offsets in a stage (swizzled pieces)
-#pragma unroll
-    for (int kk = 0; kk < D / 32; ++kk) k_lane[kk] = S::k_offset(n, 4 * kk + g);
+    const int wg = (int)blockIdx.x;
+    const int share = wg % line.shares, kvh = wg / line.shares % a1.sh.n_kv_heads, b = wg / line.shares / a1.sh.n_kv_heads;
+    const int tid = threadIdx.x, lane = tid % kWave, w = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int n = lane % 32, hw = lane / 32;
+    const int n_rows = a1.n_q * G, n_qb = (n_rows + kRowsPerBlock - 1) / kRowsPerBlock;
+    const float inv_n = 1.f / (float)a1.n_q, scale2 = a1.sh.sm_scale * kLog2e;
+    const int frag0 = S::offset(n, hw);          // operand of row / token n; slice kk is an exclusive-or of 32 kk away
+    char *const slot = s_k[w];
 
-    const int n_qb = (a.n_q * G + kRowsPerBlock - 1) / kRowsPerBlock;
-    const int sub_len = pass_length(a.kv, nt_total);
-    for (int qb = 0; qb < n_qb && nt_total > 0; ++qb) {
-        const RowInfo ri = row_info<G>(a, b, kvh, qb * kRowsPerBlock + w * 16 + n);
-        const int vis = !ri.valid ? 0 : a.causal_tail ? min(max(len - a.n_q + ri.query + 1, 0), len) : len;
-        // minus the row's lse in units of ln 2; a row that sees nothing has lse = -inf and only masked (-inf) scores,
-        // which a shift of 0 turns into weights 0
-        const float row_lse = ri.valid ? a.lse[ri.out_row] : -INFINITY;
-        const float neg_lse2 = (row_lse == -INFINITY) ? 0.f : -row_lse * kLog2e;
-        bf16x8 qop[D / 32];
-        load_q_tile<D>(a, ri, g, qop);
-        for (int sub0 = 0; sub0 < nt_total; sub0 += sub_len) {
-            const int nsub = min(sub_len, nt_total - sub0);
-            __syncthreads();                     // table, stages and sums of the previous pass are no longer in use
-            const BlockRows rows = make_block_rows<kABlock>(s_row, a.kv, a.sh.n_kv_heads, b, kvh, t0 + sub0, nsub);
-            int pending = -1;                    // step whose per-wave sums wait in s_part[pending & 1]
-            auto fold = [&](int step) {          // one thread per entry, waves added in a fixed order
-                for (int i = tid; i < G * kStepTokens; i += kABlock) {
-                    const int gh = i / kStepTokens, tok = sub0 + step * kStepTokens + i % kStepTokens;
-                    if (tok >= nt_total) continue;
-                    float v = 0.f;
+    const LineCut cut(line, b);
+    int q_held = -1;                             // block of rows that s_q holds
+#pragma unroll 1
+    for (int tier = 0; tier < 2; ++tier) {
+        if (tier && !two_tiers) break;
+        KvDev kv{};                              // field by field: a choice between the structs as a whole would go through scratch memory
+        kv.k = tier ? a2.kv.k : a1.kv.k;
+        kv.seq_lens = tier ? a2.kv.seq_lens : a1.kv.seq_lens;
+        kv.block_table = tier ? a2.kv.block_table : a1.kv.block_table;
+        kv.first_block = tier ? a2.kv.first_block : a1.kv.first_block;
+        kv.cap = tier ? a2.kv.cap : a1.kv.cap;
+        kv.block_size = tier ? a2.kv.block_size : a1.kv.block_size;
+        kv.max_blocks = tier ? a2.kv.max_blocks : a1.kv.max_blocks;
+        const int causal_tail = tier ? a2.causal_tail : a1.causal_tail;
+        const float *lse = tier ? a2.lse : a1.lse;
+        const int len = tier_len(kv, b);
+        float *out = (tier ? a2.a_out : a1.a_out) + ((int64_t)b * a1.sh.n_q_heads + kvh * G) * kv.cap;
+
+        // entries beyond the sequence's length, shared out as well
+        for (int g = 0; g < G; ++g)
+            for (int j = len + share * kWBlock + tid; j < kv.cap; j += line.shares * kWBlock) out[(int64_t)g * kv.cap + j] = 0.f;
+
+        const int first_step = tier ? cut.first_steps : 0, begin = share * cut.share_steps;
+        const int t0 = max(begin - first_step, 0) * kStepTokens;
+        const int t_end = min(max(begin + cut.share_steps - first_step, 0) * kStepTokens, len);
+        if (t0 >= t_end) continue;               // nothing of this tier in the share (uniform over the workgroup)
+        const int pass_len = min(pass_length(kv, t_end - t0), n_qb > 1 ? kWManyRowTokens : INT32_MAX);
+        for (int p0 = t0; p0 < t_end; p0 += pass_len) {
+            const int nt = min(pass_len, t_end - p0), tiles = (nt + kWTile - 1) / kWTile;
+            __syncthreads();                     // the table of the previous pass is no longer in use
+            const BlockRows rows = make_block_rows<kWBlock>(s_row, kv, a1.sh.n_kv_heads, b, kvh, p0, nt);
+            // Requests the K rows of a tile: 16-byte pieces swizzled by the row, as the operand reads want them.
+            auto request = [&](int tile) {
+                constexpr int LOADS = kWTile / S::kGroupRows;
+                const int r = lane / S::kPieces;                 // row inside a load instruction's group
+                if ((tile + 1) * kWTile <= nt) {                 // uniform over the wave
+                    uint32_t base[kWTile / kGranule];            // row of each granule's first token, uniform
 #pragma unroll
-                    for (int ww = 0; ww < kAWaves; ++ww) v += s_part[step & 1][ww][gh][i % kStepTokens];
-                    float *dst = out + (int64_t)gh * a.kv.cap + tok;
-                    *dst = qb == 0 ? v * inv_n : fmaf(v, inv_n, *dst);
+                    for (int g = 0; g < kWTile / kGranule; ++g) base[g] = rows.base + tile * kWTile + g * kGranule;
+                    if (rows.table) {
+#pragma unroll
+                        for (int g = 0; g < kWTile / kGranule; ++g) base[g] = rows.table[tile * (kWTile / kGranule) + g];
+#pragma unroll
+                        for (int g = 0; g < kWTile / kGranule; ++g) base[g] = __builtin_amdgcn_readfirstlane(base[g]);
+                    }
+#pragma unroll
+                    for (int u = 0; u < LOADS; ++u) {
+                        const int row = u * S::kGroupRows;       // of the tile
+                        const uint32_t off = r * S::kRowBytes + 16 * ((lane % S::kPieces) ^ S::swizzle(row % 16 + r));
+                        const char *src = kv.k + (size_t)(base[row / kGranule] + row % kGranule) * S::kRowBytes;
+                        __builtin_amdgcn_global_load_lds((GlobalPtr)(src + off), (LdsPtr)(slot + u * 1024), 16, 0, kNonTemporal);
+                    }
+                } else {                                         // tokens behind the end read the last row
+                    uint32_t at[LOADS];
+#pragma unroll
+                    for (int u = 0; u < LOADS; ++u) {
+                        const uint32_t t = min(tile * kWTile + u * S::kGroupRows + r, nt - 1);
+                        at[u] = rows.table ? rows.table[t / kGranule] + t % kGranule : rows.base + t;
+                    }
+#pragma unroll
+                    for (int u = 0; u < LOADS; ++u) {
+                        const int piece = (lane % S::kPieces) ^ S::swizzle(u * S::kGroupRows + r);
+                        __builtin_amdgcn_global_load_lds((GlobalPtr)(kv.k + (size_t)at[u] * S::kRowBytes + 16 * piece),
+                                                         (LdsPtr)(slot + u * 1024), 16, 0, 0);
+                    }
                 }
             };
-            // Step s reads the stage of its parity and requests the rows of step s + 1 into the other one, which was
-            // last read in step s - 1; the sums of step s - 1 wait in s_part and are folded after the same barrier.
-            const int steps = (nsub + kStepTokens - 1) / kStepTokens;
-            dma_step<D, kAWaves, false>(a.kv, rows, 0, nsub, s_k0, nullptr);
-            auto step = [&](int s, const char *k_cur, char *k_next) {
-                wait_for_own_loads();            // the barrier alone does not wait for LDS-direct loads
+            for (int qb = 0; qb < n_qb; ++qb) {
+                __syncthreads();                 // the queries and shifts of the previous round are no longer in use
+                if (q_held != qb) {              // uniform over the workgroup
+                    for (int g = w; g < kRowsPerBlock / S::kGroupRows; g += kWWaves) {
+                        const int row = g * S::kGroupRows + lane / S::kPieces;
+                        const RowInfo ri = row_info<G>(a1, b, kvh, min(qb * kRowsPerBlock + row, n_rows - 1));
+                        const char *src = static_cast<const char *>(a1.q) + ri.out_row * S::kRowBytes +
+                                          16 * ((lane % S::kPieces) ^ S::swizzle(row));
+                        __builtin_amdgcn_global_load_lds((GlobalPtr)src, (LdsPtr)(s_q + g * 1024), 16, 0, 0);
+                    }
+                    q_held = qb;
+                }
+                if (tid < kRowsPerBlock) {
+                    const RowInfo ri = row_info<G>(a1, b, kvh, qb * kRowsPerBlock + tid);
+                    const float row_lse = ri.valid ? lse[ri.out_row] : -INFINITY;
+                    // a row that sees nothing has lse = -inf; its weights are set to 0 below, whatever the shift
+                    s_shift[tid] = (row_lse == -INFINITY) ? 0.f : -row_lse * kLog2e;
+                }
+                if (w < tiles) request(w);
+                wait_for_own_loads();
                 __syncthreads();
-                if (pending >= 0) fold(pending);                 // written before the barrier above
-                if (s + 1 < steps) dma_step<D, kAWaves, false>(a.kv, rows, s + 1, nsub, k_next, nullptr);
-                float sv[8 * kStepBlocks];
-                const int step0 = sub0 + s * kStepTokens;
-                tile_scores<D, true>(
-                    [&](int t, int kk) {
-                        return *reinterpret_cast<const uint4 *>(k_cur + t * 16 * S::kRowBytes + k_lane[kk]);
-                    },
-                    qop, min(nsub - s * kStepTokens, vis - (t0 + step0)), sv);
+
+                // rows of this block that exist, and the first token that not all of them see
+                const int rows_here = min(n_rows - qb * kRowsPerBlock, kRowsPerBlock);
+                const int seen_by_all = causal_tail ? min(max(len - a1.n_q + qb * kRowsPerBlock / G + 1, 0), len) : len;
+                float done[NS];                  // the sums of the tile before, not stored yet
+                int done_at = -1;
+                auto store = [&]() {             // lane (n, hw) of a half stores every other head of its token (G = 8: its half's heads)
+                    const int t = done_at + n;
+                    if (done_at >= 0 && t < t_end) {
 #pragma unroll
-                for (int e = 0; e < 8 * kStepBlocks; ++e) {
-                    float x = __builtin_amdgcn_exp2f(fmaf(sv[e], scale2, neg_lse2));
-                    // add the rows of the same head: columns n, n + G, n + 2G, ... of the 16-lane row, by rotating
-                    // the row (DPP row_ror) by 8, 4, ... G lanes
-                    if (G <= 8) x += row_rotate<8>(x);
-                    if (G <= 4) x += row_rotate<4>(x);
-                    if (G <= 2) x += row_rotate<2>(x);
-                    if (G <= 1) x += row_rotate<1>(x);
-                    sv[e] = x;
-                }
-                if (n < G) {                     // tokens 16 t + 4 g .. + 3 of the step, head n of the group
+                        for (int g = 0; g < NS; ++g) {
+                            if (G < 8 && NS > 1 && g % 2 != hw) continue;
+                            if (NS == 1 && hw) continue;
+                            float *dst = out + (int64_t)(G == 8 ? 4 * hw + g : g) * kv.cap + t;
+                            *dst = qb == 0 ? done[g] * inv_n : fmaf(done[g], inv_n, *dst);
+                        }
+                    }
+                };
+                for (int tile = w; tile < tiles; tile += kWWaves) {
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // the tile's rows are in the slot
+                    bf16x8 kf[KK];
 #pragma unroll
-                    for (int t = 0; t < 2 * kStepBlocks; ++t)
-                        *reinterpret_cast<float4 *>(&s_part[s & 1][w][n][16 * t + 4 * g]) =
-                            make_float4(sv[4 * t], sv[4 * t + 1], sv[4 * t + 2], sv[4 * t + 3]);
+                    for (int kk = 0; kk < KK; ++kk)
+                        kf[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(slot + (frag0 ^ (32 * kk))));
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // ... and in registers: the slot is free
+                    if (tile + kWWaves < tiles) request(tile + kWWaves);
+                    store();                     // (its write overlaps with this tile's arithmetic)
+                    const int tok0 = p0 + tile * kWTile;
+                    float sum[NS];
+#pragma unroll
+                    for (int g = 0; g < NS; ++g) sum[g] = 0.f;
+                    // c[r] of row tile x is the score of row 32 x + 8 (r / 4) + 4 hw + r % 4 and the lane's token
+                    auto score = [&](int x, int kk, floatx16 &c) {
+                        const uint4 qa = *reinterpret_cast<const uint4 *>(s_q + x * 32 * S::kRowBytes + (frag0 ^ (32 * kk)));
+                        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, qa), kf[kk], c, 0, 0, 0);
+                    };
+                    auto weigh = [&](int x, floatx16 &c) {
+#pragma unroll
+                        for (int q4 = 0; q4 < 4; ++q4) {
+                            const float4 sh = *reinterpret_cast<const float4 *>(s_shift + 32 * x + 8 * q4 + 4 * hw);
+                            const float s4[4] = {sh.x, sh.y, sh.z, sh.w};
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) c[4 * q4 + e] = __builtin_amdgcn_exp2f(fmaf(c[4 * q4 + e], scale2, s4[e]));
+                        }
+                    };
+                    if (rows_here == kRowsPerBlock && tok0 + kWTile <= seen_by_all) {            // uniform over the wave
+                        // straight-line code, two row tiles side by side: their matrix instructions take turns, and the
+                        // vector instructions of one pair run beside the matrix instructions of the other
+#pragma unroll
+                        for (int x = 0; x < RT; x += 2) {
+                            floatx16 c0{}, c1{};
+#pragma unroll
+                            for (int kk = 0; kk < KK; ++kk) {
+                                score(x, kk, c0);
+                                score(x + 1, kk, c1);
+                            }
+                            weigh(x, c0);
+                            weigh(x + 1, c1);
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) sum[r % NS] += c0[r];   // the head of row r is r % G
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) sum[r % NS] += c1[r];
+                        }
+                    } else {
+#pragma unroll 1
+                        for (int x = 0; x < RT && 32 * x < rows_here; ++x) {
+                            floatx16 c{};
+#pragma unroll
+                            for (int kk = 0; kk < KK; ++kk) score(x, kk, c);
+                            weigh(x, c);
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) {
+                                const int row = qb * kRowsPerBlock + 32 * x + 8 * (r / 4) + 4 * hw + r % 4;
+                                const int last = len - (causal_tail ? a1.n_q - row / G : 1);         // last token the row sees
+                                sum[r % NS] += row < n_rows && tok0 + n <= last ? c[r] : 0.f;
+                            }
+                        }
+                    }
+#pragma unroll
+                    for (int g = 0; g < NS; ++g) done[g] = G < 8 ? halves_sum(sum[g]) : sum[g];
+                    done_at = tok0;
                 }
-                pending = s;
-            };
-            for (int s2 = 0; s2 < steps; s2 += 2) {
-                step(s2, s_k0, s_k1);
-                if (s2 + 1 < steps) step(s2 + 1, s_k1, s_k0);
+                store();
             }
-            __syncthreads();
-            if (pending >= 0) fold(pending);
         }
-    }
-    // entries beyond the sequence's length
-    for (int i = tid; i < G * n_here; i += kABlock) {
-        const int gh = i / n_here, j = i % n_here;
-        if (j >= nt_total) out[(int64_t)gh * a.kv.cap + j] = 0.f;
     }
 }
 
@@ -689,13 +764,14 @@ hipError_t launch_attn_group(const AppendArgs &a, const AppendArgs &a2, const Li
 }
 
 template <int D>
-hipError_t launch_weights_group(const AppendArgs &a, const AppendArgs &a2, int n1, dim3 grid, hipStream_t s)
+hipError_t launch_weights_group(const AppendArgs &a, const AppendArgs &a2, const LineDev &line, int two, dim3 grid, hipStream_t s)
 {
+    const dim3 block(kWBlock);
     switch (a.sh.group) {
-    case 1: hipLaunchKernelGGL((append_weights_kernel<D, 1>), grid, dim3(kABlock), 0, s, a, a2, n1); break;
-    case 2: hipLaunchKernelGGL((append_weights_kernel<D, 2>), grid, dim3(kABlock), 0, s, a, a2, n1); break;
-    case 4: hipLaunchKernelGGL((append_weights_kernel<D, 4>), grid, dim3(kABlock), 0, s, a, a2, n1); break;
-    case 8: hipLaunchKernelGGL((append_weights_kernel<D, 8>), grid, dim3(kABlock), 0, s, a, a2, n1); break;
+    case 1: hipLaunchKernelGGL((append_weights_kernel<D, 1>), grid, block, 0, s, a, a2, line, two); break;
+    case 2: hipLaunchKernelGGL((append_weights_kernel<D, 2>), grid, block, 0, s, a, a2, line, two); break;
+    case 4: hipLaunchKernelGGL((append_weights_kernel<D, 4>), grid, block, 0, s, a, a2, line, two); break;
+    case 8: hipLaunchKernelGGL((append_weights_kernel<D, 8>), grid, block, 0, s, a, a2, line, two); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -725,22 +801,20 @@ hipError_t launch_append_attn(int head_dim, const AppendArgs &a, const AppendArg
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_append_weights2(int head_dim, const AppendArgs &a, int n_chunks, const AppendArgs &a2, int n_chunks2,
-                                  hipStream_t s)
+hipError_t launch_append_weights(int head_dim, const AppendArgs &a, const AppendArgs *second, const LineDev &line,
+                                 hipStream_t s)
 {
-    if (a.sh.batch == 0 || n_chunks + n_chunks2 == 0) return hipSuccess;
-    if (n_chunks2 > 0 && (a2.n_q != a.n_q || a2.q != a.q || a2.sh.group != a.sh.group || a2.sh.batch != a.sh.batch ||
-                          a2.sh.n_kv_heads != a.sh.n_kv_heads))
+    if (a.sh.batch == 0 || a.n_q == 0) return hipSuccess;
+    const AppendArgs &a2 = second ? *second : a;
+    if (line.shares <= 0 || a2.n_q != a.n_q || a2.q != a.q || a2.sh.group != a.sh.group || a2.sh.batch != a.sh.batch ||
+        a2.sh.n_kv_heads != a.sh.n_kv_heads)
         return hipErrorInvalidValue;             // the two tiers share the queries and the launch shape
-    dim3 grid(n_chunks + n_chunks2, a.sh.n_kv_heads, a.sh.batch);
-    if (head_dim == 64) return launch_weights_group<64>(a, a2, n_chunks, grid, s);
-    if (head_dim == 128) return launch_weights_group<128>(a, a2, n_chunks, grid, s);
+    const int64_t blocks = (int64_t)line.shares * a.sh.n_kv_heads * a.sh.batch;
+    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)blocks);
+    if (head_dim == 64) return launch_weights_group<64>(a, a2, line, second ? 1 : 0, grid, s);
+    if (head_dim == 128) return launch_weights_group<128>(a, a2, line, second ? 1 : 0, grid, s);
     return hipErrorInvalidValue;
-}
-
-hipError_t launch_append_weights(int head_dim, const AppendArgs &a, int n_chunks, hipStream_t s)
-{
-    return launch_append_weights2(head_dim, a, n_chunks, a, 0, s);
 }
 
 hipError_t launch_append_weights_f32(int head_dim, const AppendArgs &a, hipStream_t s)

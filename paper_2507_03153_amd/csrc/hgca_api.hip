@@ -32,10 +32,6 @@ constexpr size_t kAlign = 256;
 #define HGCA_TARGET_WGS_SPARSE_SCORED 2048
 #endif
 
-// workgroups the append-stage weights pass aims at (its tokens per workgroup are halved from 2048 until it has them)
-#ifndef HGCA_WEIGHTS_TARGET_WGS
-#define HGCA_WEIGHTS_TARGET_WGS 1024
-#endif
 // Workgroups the append-stage attention aims at per launch: what the device holds at once (two per compute unit).
 // Every workgroup writes a partial of 128 rows x d floats (64 KB, read again by the fold: the K/V bytes of four
 // 64-token steps), so splits are as long as filling the device allows.  Measured on the 8B shape, N = 32, with
@@ -917,18 +913,18 @@ int append_want_splits(const hgca_shape *s, int32_t n_q)
 }
 
 // Workgroups that share the `tokens` (by capacity) of a unit, at most `most`: the number for which the launch takes the
-// least time, counted in 64-token steps: rounds of HGCA_APPEND_TARGET_WGS workgroups (what the device holds at once)
+// least time, counted in 64-token steps: rounds of `places` workgroups (what the device holds at once)
 // times the steps of a share, plus what a share costs beside its steps -- loading the queries, the first rows' latency
 // and a partial of 64 KB to write and fold, together about five steps (a step takes 2.8 us, a share's fixed part 15 us
 // on 509 queries x 32 K tokens).
-int append_shares(const hgca_shape *s, int32_t n_q, int64_t tokens, int most)
+int append_shares(const hgca_shape *s, int32_t n_q, int64_t tokens, int most, int places = HGCA_APPEND_TARGET_WGS)
 {
     constexpr int kShareOverhead = 5;
     const int64_t units = append_units(s, n_q), steps = std::max<int64_t>(1, (tokens + kLineStep - 1) / kLineStep);
     int best = 1;
     int64_t best_cost = INT64_MAX;
     for (int n = 1; n <= most && n <= steps; ++n) {
-        const int64_t rounds = (n * units + HGCA_APPEND_TARGET_WGS - 1) / HGCA_APPEND_TARGET_WGS;
+        const int64_t rounds = (n * units + places - 1) / places;
         const int64_t cost = rounds * ((steps + n - 1) / n + kShareOverhead);
         if (cost < best_cost) {
             best_cost = cost;
@@ -1109,22 +1105,26 @@ int hgca_append_attn_tiers(const hgca_shape *shape, const void *q, int32_t n_q, 
 
 namespace {
 
-// Arguments of the weights pass over one tier (bf16) and the number of workgroups along x it takes.
-int weights_args(const hgca_shape *shape, const void *q, int32_t n_q, const hgca_kv_view *tier, int32_t causal_tail,
-                 const float *lse, float *a_out, AppendArgs *a)
+// Arguments of the weights pass over one tier.
+AppendArgs weights_args(const hgca_shape *shape, const void *q, int32_t n_q, const hgca_kv_view *tier, int32_t causal_tail,
+                        const float *lse, float *a_out)
 {
-    a->sh = to_dev(shape);
-    a->q = q;
-    a->kv = to_dev(tier);
-    a->n_q = n_q;
-    a->causal_tail = causal_tail ? 1 : 0;
-    a->lse = lse;
-    a->a_out = a_out;
-    const int64_t units = (int64_t)shape->batch * shape->n_kv_heads;
-    a->chunk = 2048;                                 // tokens per workgroup, halved until the GPU is filled
-    while (a->chunk > 64 && units * n_splits_for(tier->cap, a->chunk) < HGCA_WEIGHTS_TARGET_WGS) a->chunk /= 2;
-    return tier->cap > 0 ? n_splits_for(tier->cap, a->chunk) : 0;
+    AppendArgs a{};
+    a.sh = to_dev(shape);
+    a.q = q;
+    a.kv = to_dev(tier);
+    a.n_q = n_q;
+    a.causal_tail = causal_tail ? 1 : 0;
+    a.lse = lse;
+    a.a_out = a_out;
+    return a;
 }
+
+constexpr int kWeightsPlaces = 256;              // one workgroup of the weights pass per compute unit
+
+// Workgroups per (sequence, KV head) of the weights pass: the rule of append_shares (a share's fixed part is the
+// queries it loads); a workgroup meets all query rows, so the units are the (sequence, KV head) pairs.
+int weights_shares(const hgca_shape *s, int64_t tokens) { return append_shares(s, 1, tokens, kWeightsPlaces, kWeightsPlaces); }
 
 }  // namespace
 
@@ -1139,11 +1139,11 @@ int hgca_append_weights_tiers(const hgca_shape *shape, const void *q, int32_t n_
     if (shape->dtype != HGCA_BF16) return HGCA_ERR_UNSUPPORTED;      // fp32 inputs: one call per tier
     if (shape->batch == 0) return HGCA_OK;
     if ((window->cap > 0 && (!lse_window || !a_gpu)) || (pool->cap > 0 && (!lse_pool || !a_cpu))) return HGCA_ERR_INVALID_ARG;
-    AppendArgs aw{}, ap{};
-    const int n_w = weights_args(shape, q, n_q, window, causal_tail, lse_window, a_gpu, &aw);
-    const int n_p = weights_args(shape, q, n_q, pool, 0, lse_pool, a_cpu, &ap);
-    // the pool's workgroups take the lower block numbers: they are the bulk of the launch
-    return from_hip(launch_append_weights2(shape->head_dim, ap, n_p, aw, n_w, static_cast<hipStream_t>(hip_stream)));
+    const AppendArgs aw = weights_args(shape, q, n_q, window, causal_tail, lse_window, a_gpu);
+    const AppendArgs ap = weights_args(shape, q, n_q, pool, 0, lse_pool, a_cpu);
+    const LineDev line{pool->seq_lens, window->seq_lens, pool->cap, window->cap,
+                       weights_shares(shape, (int64_t)pool->cap + window->cap), 0};
+    return from_hip(launch_append_weights(shape->head_dim, ap, &aw, line, static_cast<hipStream_t>(hip_stream)));
 }
 
 int hgca_append_weights(const hgca_shape *shape, const void *q, int32_t n_q, const hgca_kv_view *tier,
@@ -1154,11 +1154,11 @@ int hgca_append_weights(const hgca_shape *shape, const void *q, int32_t n_q, con
     if (n_q == 0) return HGCA_ERR_INVALID_ARG;       // an average over no query is undefined
     if (shape->batch == 0 || tier->cap == 0) return HGCA_OK;
     if (!lse || !a_out) return HGCA_ERR_INVALID_ARG;
-    AppendArgs a{};
-    const int n_chunks = weights_args(shape, q, n_q, tier, causal_tail, lse, a_out, &a);
+    const AppendArgs a = weights_args(shape, q, n_q, tier, causal_tail, lse, a_out);
     if (shape->dtype == HGCA_F32)
         return from_hip(launch_append_weights_f32(shape->head_dim, a, static_cast<hipStream_t>(hip_stream)));
-    return from_hip(launch_append_weights(shape->head_dim, a, n_chunks, static_cast<hipStream_t>(hip_stream)));
+    const LineDev line{tier->seq_lens, nullptr, tier->cap, 0, weights_shares(shape, tier->cap), 0};
+    return from_hip(launch_append_weights(shape->head_dim, a, nullptr, line, static_cast<hipStream_t>(hip_stream)));
 }
 
 namespace {

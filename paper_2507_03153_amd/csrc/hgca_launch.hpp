@@ -150,7 +150,6 @@ struct AppendArgs {
     int32_t n_q;               // N
     int32_t causal_tail;       // 1: the tier's last N valid tokens are the queries' own; query i sees tokens < len-N+i+1
     int32_t one_part_p;        // 1: the weights enter the second product as one bf16 value instead of a high and a low part
-    int32_t chunk;             // weights: tokens per workgroup, a multiple of 64
     Partials part;             // attention: rows are (b, query, head), one slot per share, or shares + 1 with a second tier
     const float *lse;          // weights: [B, N, Hq], the tier's log-sum-exp per query and head
     float *a_out;              // weights: [B, Hq, cap]
@@ -159,10 +158,9 @@ struct AppendArgs {
 // own view and mask rule; `shares` + 1 slots).
 hipError_t launch_append_attn(int head_dim, const AppendArgs &first, const AppendArgs *second, const LineDev &line,
                               hipStream_t s);
-hipError_t launch_append_weights(int head_dim, const AppendArgs &a, int n_chunks, hipStream_t s);
-// the weights of two tiers (same queries and shape) in one launch
-hipError_t launch_append_weights2(int head_dim, const AppendArgs &a, int n_chunks, const AppendArgs &a2, int n_chunks2,
-                                  hipStream_t s);
+// the weights of one tier (second = nullptr) or of two (same queries and shape), as a line
+hipError_t launch_append_weights(int head_dim, const AppendArgs &first, const AppendArgs *second, const LineDev &line,
+                                 hipStream_t s);
 // the same for fp32 inputs (q [B, N, Hq, d] fp32, fp32 tier): VALU pass, 64 tokens per workgroup
 hipError_t launch_append_weights_f32(int head_dim, const AppendArgs &a, hipStream_t s);
 
