@@ -96,7 +96,7 @@ __global__ __launch_bounds__(kBlock) void dense_attn_mfma_kernel(KernelArgs a)
     __shared__ __attribute__((aligned(16))) char s_lds[DS::kLdsBytes];
     const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
     const int n = tier_len(a.kv, b);
-    const int chunk = even_chunk(a.chunk, n, a.part.n_splits), t0 = split * chunk;
+    const int chunk = even_chunk(a.chunk, n, a.part.n_splits, 16384 / D), t0 = split * chunk;
     if (t0 >= n) {
         write_empty_partial<D, G>(a.part, (int64_t)b * a.sh.n_q_heads + (int64_t)kvh * G, split);
         return;

@@ -50,7 +50,7 @@ __global__ __launch_bounds__(kBlock, HGCA_DG_OCC) void dense_gather_kernel(Kerne
             n = min(max(grown, 0), da.kv.cap);
             takes_token = grown > len;
         }
-        const int chunk = even_chunk(da.chunk, n, dense_splits), t0 = split * chunk;
+        const int chunk = even_chunk(da.chunk, n, dense_splits, 16384 / D), t0 = split * chunk;
         if (takes_token && len >= t0 && len < t0 + chunk) {      // uniform over the workgroup
             // this split owns the token's position: its K and V rows go into the window's block, then the split
             // reads them back like any other row (no other workgroup of the launch touches that position)
