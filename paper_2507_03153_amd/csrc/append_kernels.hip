@@ -58,7 +58,6 @@ template <int BLOCK>
 __device__ __forceinline__ BlockRows make_block_rows(uint32_t *s_tab, const KvDev &kv, int n_kv_heads, int b, int kvh,
                                                      int first, int nt)
 {
-    b = kv_seq(kv, b);
     BlockRows m;
     if (!kv.block_table) {
         m.table = nullptr;
@@ -113,21 +112,25 @@ __device__ __forceinline__ RowInfo row_info(const AppendArgs &a, int b, int kvh,
 //   V: quads of four rows, interleaved in 32-byte chunks ([quad][column chunk][row of the quad][32 bytes]), so that
 //      the 4 rows x 32 bytes a 16-lane group takes with one transpose read are 128 consecutive bytes and the two
 //      groups of a half wave, which take neighbouring chunks, 256.
-template <int D, int NW> struct DmaStage {
-    static constexpr int kPieces = D / 8;                        // 16-byte pieces per row
-    static constexpr int kRowBytes = D * 2;
+// fp32 rows: K as above; V row-major, the 128-byte chunks of every second quad of rows exchanged in pairs, so that the
+// two halves of a wave, which read the same columns of rows four apart, find them on different banks.
+template <typename T, int D, int NW> struct DmaStage {
+    static constexpr bool kF32 = sizeof(T) == 4;
+    static constexpr int kRowBytes = D * sizeof(T);
+    static constexpr int kPieces = kRowBytes / 16;               // 16-byte pieces per row
+    static constexpr int kSwizzled = kPieces < 16 ? kPieces : 16;
     static constexpr int kGroupRows = 1024 / kRowBytes;          // rows per load instruction of a wave
     static constexpr int kGroups = kStepTokens / kGroupRows;     // per step and tensor
     static constexpr int kLoads = kGroups / NW;                  // per wave, step and tensor
     static constexpr int kBytes = kStepTokens * kRowBytes;       // per step and tensor
     static_assert(kGroups % NW == 0 && kLoads >= 1, "the waves share the groups of a step evenly");
 
-    static __device__ __forceinline__ int k_swizzle(int row) { return (row / (16 / kPieces)) % kPieces; }
+    static __device__ __forceinline__ int k_swizzle(int row) { return (row / (16 / kSwizzled)) % kSwizzled; }
     // byte offset, in a K stage, of logical piece `piece` of step row `row`
     static __device__ __forceinline__ int k_offset(int row, int piece) {
         return row * kRowBytes + 16 * (piece ^ k_swizzle(row));
     }
-    // byte offset, in a V stage, of the 32-byte column chunk `dt` of step row `row`
+    // byte offset, in a bf16 V stage, of the 32-byte column chunk `dt` of step row `row`
     static __device__ __forceinline__ int v_offset(int row, int dt) {
         return (row / 4) * (4 * kRowBytes) + dt * 128 + (row % 4) * 32;
     }
@@ -142,23 +145,24 @@ __device__ __forceinline__ void wait_for_own_loads() { __builtin_amdgcn_s_waitcn
 // a full step its address is a scalar (the granule's row) plus an offset that is the lane's for good; only a step
 // that the pass's end cuts computes rows per lane (tokens behind the end read the last row).  The row numbers of a
 // paged tier are looked up before the first load is issued: an LDS read placed after an LDS-direct load waits for it.
-template <int D, int NW, bool WITH_V = true>
+template <typename T, int D, int NW>
 __device__ __forceinline__ void dma_step(const KvDev &kv, const BlockRows &rows, int step, int nsub, char *k_stage,
                                          char *v_stage)
 {
-    using S = DmaStage<D, NW>;
-    static_assert(kGranule % S::kGroupRows == 0 && (NW * S::kGroupRows) % kGranule == 0,
-                  "a load stays inside a granule and all loads of a wave at the same place of theirs");
+    using S = DmaStage<T, D, NW>;
+    static_assert(kGranule % S::kGroupRows == 0, "a load stays inside a granule");
     constexpr int kQuadLanes = 4 * S::kRowBytes / 16;
     const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    // what lands at byte 16 * lane of a group: K row-major with swizzled pieces, V chunk-interleaved
-    const int k_row = lane / S::kPieces, v_row = 4 * (lane / kQuadLanes) + (lane % 8) / 2;   // inside the group
-    const int k_byte = 16 * ((lane % S::kPieces) ^ S::k_swizzle(w * S::kGroupRows + k_row));
-    const int v_byte = 16 * (2 * ((lane % kQuadLanes) / 8) + lane % 2);
+    // what lands at byte 16 * lane of the wave's u-th group: the row inside the group and the byte of the row
+    const int k_row = lane / S::kPieces, v_row = S::kF32 ? k_row : 4 * (lane / kQuadLanes) + (lane % 8) / 2;
+    auto k_byte = [&](int u) { return 16 * ((lane % S::kPieces) ^ S::k_swizzle((w + NW * u) * S::kGroupRows + k_row)); };
+    auto v_byte = [&](int u) {
+        if (S::kF32) return 16 * ((lane % S::kPieces) ^ (8 * (((w + NW * u) * S::kGroupRows + v_row) / 4 % 2)));
+        return 16 * (2 * ((lane % kQuadLanes) / 8) + lane % 2);
+    };
     typedef const __attribute__((address_space(1))) void *GlobalPtr;
     typedef __attribute__((address_space(3))) void *LdsPtr;
     if ((step + 1) * kStepTokens <= nsub) {                      // uniform over the workgroup
-        const uint32_t k_off = k_row * S::kRowBytes + k_byte, v_off = v_row * S::kRowBytes + v_byte;
         const int first = step * kStepTokens + w * S::kGroupRows;                        // of the wave's first load
         uint32_t row[S::kLoads];                                 // uniform over the wave
 #pragma unroll
@@ -167,14 +171,15 @@ __device__ __forceinline__ void dma_step(const KvDev &kv, const BlockRows &rows,
 #pragma unroll
             for (int u = 0; u < S::kLoads; ++u) row[u] = rows.table[(first + NW * S::kGroupRows * u) / kGranule];
 #pragma unroll
-            for (int u = 0; u < S::kLoads; ++u) row[u] = __builtin_amdgcn_readfirstlane(row[u]) + first % kGranule;
+            for (int u = 0; u < S::kLoads; ++u)
+                row[u] = __builtin_amdgcn_readfirstlane(row[u]) + (first + NW * S::kGroupRows * u) % kGranule;
         }
 #pragma unroll
         for (int u = 0; u < S::kLoads; ++u) {
             const size_t at = (size_t)row[u] * S::kRowBytes;
+            const uint32_t k_off = k_row * S::kRowBytes + k_byte(u), v_off = v_row * S::kRowBytes + v_byte(u);
             __builtin_amdgcn_global_load_lds((GlobalPtr)(kv.k + at + k_off), (LdsPtr)(k_stage + (w + NW * u) * 1024), 16, 0, 0);
-            if (WITH_V)
-                __builtin_amdgcn_global_load_lds((GlobalPtr)(kv.v + at + v_off), (LdsPtr)(v_stage + (w + NW * u) * 1024), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((GlobalPtr)(kv.v + at + v_off), (LdsPtr)(v_stage + (w + NW * u) * 1024), 16, 0, 0);
         }
         return;
     }
@@ -188,12 +193,41 @@ __device__ __forceinline__ void dma_step(const KvDev &kv, const BlockRows &rows,
     }
 #pragma unroll
     for (int u = 0; u < S::kLoads; ++u) {
-        __builtin_amdgcn_global_load_lds((GlobalPtr)(kv.k + (size_t)kr[u] * S::kRowBytes + k_byte),
+        __builtin_amdgcn_global_load_lds((GlobalPtr)(kv.k + (size_t)kr[u] * S::kRowBytes + k_byte(u)),
                                          (LdsPtr)(k_stage + (w + NW * u) * 1024), 16, 0, 0);
-        if (WITH_V)
-            __builtin_amdgcn_global_load_lds((GlobalPtr)(kv.v + (size_t)vr[u] * S::kRowBytes + v_byte),
-                                             (LdsPtr)(v_stage + (w + NW * u) * 1024), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((GlobalPtr)(kv.v + (size_t)vr[u] * S::kRowBytes + v_byte(u)),
+                                         (LdsPtr)(v_stage + (w + NW * u) * 1024), 16, 0, 0);
     }
+}
+
+// One 16-byte slice of the score contraction in bf16: C[32 x 32] += A . B over 16 columns.  A lane holds 16 bytes of row
+// lane % 32 of either operand, the lower half of the wave one piece and the upper half the next.
+__device__ __forceinline__ floatx16 score_mfma(const uint4 &a, const uint4 &b, floatx16 c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// The whole contraction of a 32 x 32 tile in fp32 (slices of 8 columns, an instruction per column of a piece).  The
+// instructions go round eight accumulators that are added pairwise: one chain of D / 2 additions would cost the scores
+// three times the rounding error of the tree that a vector dot product forms (weights off by 1e-6 instead of 4e-7).
+template <int KK, typename Piece>
+__device__ __forceinline__ floatx16 score_tile_f32(Piece piece, const uint4 (&b)[KK])
+{
+    constexpr int C = 8;
+    floatx16 c[C];
+#pragma unroll
+    for (int i = 0; i < C; ++i) c[i] = floatx16{};
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+        const floatx4 x = __builtin_bit_cast(floatx4, piece(kk)), y = __builtin_bit_cast(floatx4, b[kk]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) c[(4 * kk + e) % C] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], y[e], c[(4 * kk + e) % C], 0, 0, 0);
+    }
+#pragma unroll
+    for (int n = C / 2; n > 0; n /= 2)
+#pragma unroll
+        for (int i = 0; i < n; ++i) c[i] += c[i + n];
+    return c[0];
 }
 
 constexpr int kAttnWaves = kRowsPerBlock / 32, kAttnBlock = kAttnWaves * kWave;   // a wave owns 32 query rows
@@ -217,18 +251,25 @@ __device__ __forceinline__ float minus_half(uint32_t pair, uint32_t minus_one_at
 //   - the low part of a weight takes one dot instruction;
 //   - a load instruction's address is a scalar plus a constant offset of the lane (dma_step);
 //   about 6 vector instructions per score where the kernel with 16-row tiles took 13.
-// With the line below, 2 x 509 queries x 32 K tokens x 32 heads: 930 -> 760 us (720 TFLOP/s, 1.08 PFLOP/s executed);
+// With the line below, 2 x 509 queries x 32 K tokens x 32 heads: 930 -> 765 us (715 TFLOP/s, 1.07 PFLOP/s executed);
 // 8 x 32 queries x 32 K tokens: 266 -> 250 us, bound by the K/V rows; 48 queries, groups of 8, one part: 320 -> 250 us.
 //
 // A launch may serve TWO tiers (the complete pool and the window of an append turn: Alg. 2 runs the two attentions side
 // by side) as one line of tokens cut into equal shares (LineDev): a workgroup goes through its part of the first tier
 // and its part of the second, usually only one of them, each with the tier's view, mask rule and slot.
-template <int D, int G, bool SPLIT_P>
-__global__ __launch_bounds__(kAttnBlock, 2) void append_attn_kernel(AppendArgs a1, AppendArgs a2,
-                                                                       LineDev line, int two_tiers)
+//
+// fp32 inputs run the same kernel on v_mfma_f32_32x32x2_f32: products and sums in fp32 throughout, the weights as they
+// are (SPLIT_P has no meaning).  Its stages take 128 KB, one workgroup per unit; the pass is bound by the matrix
+// instruction (154 TFLOP/s dense).  2 x 24 queries on 5 K tokens, 32 / 8 heads: 340 us as one-query attention per query,
+// K and V read once per query -> 75 us.
+template <typename T, int D, int G, bool SPLIT_P>
+__global__ __launch_bounds__(kAttnBlock, sizeof(T) == 2 ? 2 : 1) void append_attn_kernel(AppendArgs a1, AppendArgs a2,
+                                                                                          LineDev line, int two_tiers)
 {
+    constexpr bool F32 = sizeof(T) == 4;
     constexpr int NW = kAttnWaves, BLOCK = kAttnBlock;
-    using S = DmaStage<D, NW>;
+    using S = DmaStage<T, D, NW>;
+    constexpr int KK = D * (int)sizeof(T) / 32;                  // slices of the score contraction
     constexpr int DT = D / 32, NT = kStepTokens / 32;            // 32-column tiles of the output, 32-token tiles of a step
     constexpr float kLog2e = 1.4426950408889634f;
     // two stages per tensor as separate arrays: the compiler then knows that a load into one stage does not
@@ -243,24 +284,25 @@ __global__ __launch_bounds__(kAttnBlock, 2) void append_attn_kernel(AppendArgs a
     // head)) read the same rows: they take numbers that are equal modulo the number of XCDs and follow each other
     // there, so that the stream passes through one L2.
     const int n_qb = (a1.n_q * G + kRowsPerBlock - 1) / kRowsPerBlock;
-    const int wg = (int)blockIdx.x;
-    const int stream = n_qb == 1 ? wg : wg % kXcds + kXcds * (wg / kXcds / n_qb);
-    const int qb = n_qb == 1 ? 0 : wg / kXcds % n_qb;
-    if (stream >= line.shares * a1.sh.n_kv_heads * a1.sh.batch) return;          // uniform over the workgroup
-    const int share = stream % line.shares, kvh = stream / line.shares % a1.sh.n_kv_heads,
-              b = stream / line.shares / a1.sh.n_kv_heads;
+    int share = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z, qb = 0;
+    if (n_qb > 1) {                              // uniform over the launch: a flat grid
+        const int wg = (int)blockIdx.x, stream = wg % kXcds + kXcds * (wg / kXcds / n_qb);
+        if (stream >= line.shares * a1.sh.n_kv_heads * a1.sh.batch) return;      // uniform over the workgroup
+        qb = wg / kXcds % n_qb;
+        share = stream % line.shares;
+        kvh = stream / line.shares % a1.sh.n_kv_heads;
+        b = stream / line.shares / a1.sh.n_kv_heads;
+    }
     const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave, n = lane % 32, hw = lane / 32;
 
-    const int row0 = qb * kRowsPerBlock + w * 32;                // first row of the wave
+    const int row0 = qb * kRowsPerBlock + __builtin_amdgcn_readfirstlane(w) * 32;        // first row of the wave
     const bool wave_live = row0 < a1.n_q * G;                    // uniform over the wave
-    const RowInfo ri = row_info<G>(a1, b, kvh, row0 + n);
-    bf16x8 qop[D / 16];                          // B operand: columns 16 kk + 8 hw .. + 7 of the lane's row
+    const bool row_exists = row0 + n < a1.n_q * G;               // lanes without a row repeat the last one and store nothing
+    const RowInfo ri = row_info<G>(a1, b, kvh, min(row0 + n, a1.n_q * G - 1));
+    uint4 qop[KK];                               // B operand: piece 2 kk + hw of the lane's row
 #pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk) {
-        uint4 r = make_uint4(0u, 0u, 0u, 0u);
-        if (ri.valid) r = load16(static_cast<const char *>(a1.q) + (ri.out_row * D + 16 * kk + 8 * hw) * 2);
-        qop[kk] = __builtin_bit_cast(bf16x8, r);
-    }
+    for (int kk = 0; kk < KK; ++kk)
+        qop[kk] = load16(static_cast<const char *>(a1.q) + ri.out_row * S::kRowBytes + 16 * (2 * kk + hw));
     // The running maximum is kept on the RAW scores (the softmax scale is positive, so the order is the same) and
     // the scale, in units of ln 2, is applied inside the exponent: e^{scale (s - m)} = 2^{fma(s, scale2, -m scale2)},
     // one fused multiply-add and one bare v_exp_f32 per score.
@@ -269,10 +311,12 @@ __global__ __launch_bounds__(kAttnBlock, 2) void append_attn_kernel(AppendArgs a
     // offset per 16-column slice because of the swizzle) and of the second.  The V^T operand (8 tokens of one column
     // per lane) comes from two transpose reads: lane j of a 16-lane group points at columns 4(j%4).. of row j/4 of a
     // quad of tokens, the two groups of a half wave at neighbouring column chunks.
-    int k_lane[D / 16];
+    // In fp32 the operand is one float per lane: column n of the 32-column tile, the tile's chunk exchanged with its
+    // neighbour in the upper half's rows.
+    int k_lane[KK];
 #pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk) k_lane[kk] = S::k_offset(n, 2 * kk + hw);
-    const int v_lane = S::v_offset(4 * hw + lane % 16 / 4, lane / 16 % 2) + 8 * (lane % 4);
+    for (int kk = 0; kk < KK; ++kk) k_lane[kk] = S::k_offset(n, 2 * kk + hw);
+    const int v_lane = F32 ? 4 * hw * S::kRowBytes + 4 * n : S::v_offset(4 * hw + lane % 16 / 4, lane / 16 % 2) + 8 * (lane % 4);
     // (-1, 0) and (0, -1) in bf16 for minus_half, in registers: as a literal the second becomes the inline constant
     // -1.0, which the dot product takes as a value of its own width
     uint32_t low_half = 0x0000bf80u, high_half = 0xbf800000u;
@@ -309,12 +353,10 @@ __global__ __launch_bounds__(kAttnBlock, 2) void append_attn_kernel(AppendArgs a
         const int len = tier_len(kv, b);
         const int t0 = step_begin * kStepTokens;
         const int nt_total = min(step_end * kStepTokens, len) - t0;              // <= 0: nothing of the share is valid
-        // tokens [0, vis) of the tier are visible to the row; steps below the wave's smallest vis need no mask
-        const int vis = !ri.valid ? 0 : causal_tail ? min(max(len - a1.n_q + ri.query + 1, 0), len) : len;
-        int vis_min = vis;
-#pragma unroll
-        for (int off = 1; off < 32; off <<= 1) vis_min = min(vis_min, __shfl_xor(vis_min, off, kWave));
-        vis_min = __builtin_amdgcn_readfirstlane(vis_min);           // (the halves of a wave hold the same rows)
+        // tokens [0, vis) of the tier are visible to the row; steps below vis_min, that of the wave's first row (rows are
+        // query-major), need no mask
+        const int vis = causal_tail ? min(max(len - a1.n_q + ri.query + 1, 0), len) : len;
+        const int vis_min = causal_tail ? min(max(len - a1.n_q + min(row0 / G, a1.n_q - 1) + 1, 0), len) : len;
         float m = -INFINITY, shift = 0.f, l = 0.f;               // l: over this lane's tokens only
         floatx16 acc[DT];
 #pragma unroll
@@ -325,13 +367,18 @@ __global__ __launch_bounds__(kAttnBlock, 2) void append_attn_kernel(AppendArgs a
             floatx16 c[NT];
 #pragma unroll
             for (int t = 0; t < NT; ++t) c[t] = floatx16{};
+            auto k_piece = [&](int t, int kk) {
+                return *reinterpret_cast<const uint4 *>(k_stage + t * 32 * S::kRowBytes + k_lane[kk]);
+            };
+            if constexpr (F32) {
 #pragma unroll
-            for (int kk = 0; kk < D / 16; ++kk)
+                for (int t = 0; t < NT; ++t) c[t] = score_tile_f32<KK>([&](int kk) { return k_piece(t, kk); }, qop);
+            } else {
 #pragma unroll
-                for (int t = 0; t < NT; ++t) {       // the accumulators take turns
-                    const uint4 ka = *reinterpret_cast<const uint4 *>(k_stage + t * 32 * S::kRowBytes + k_lane[kk]);
-                    c[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ka), qop[kk], c[t], 0, 0, 0);
-                }
+                for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) c[t] = score_mfma(k_piece(t, kk), qop[kk], c[t]);       // the accumulators take turns
+            }
             if (min(in_split, vis_min - step0) < kStepTokens) {      // uniform over the wave: a length or causal boundary
                 int limit = min(in_split, vis - step0);
                 asm volatile("" : "+v"(limit));                      // a real branch: the selects below are not speculated into every step
@@ -350,13 +397,39 @@ __global__ __launch_bounds__(kAttnBlock, 2) void append_attn_kernel(AppendArgs a
                 const float m_new = fmaxf(m, halves_max(mx));
                 // a row that has seen nothing yet keeps m = -inf: shift by 0 then, every exponent is -inf and gives 0
                 shift = (m_new == -INFINITY) ? 0.f : -m_new * scale2;
-                const float corr = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(fmaf(m, scale2, shift));
+                const float corr = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(F32 ? (m - m_new) * scale2 : fmaf(m, scale2, shift));
                 m = m_new;
                 l *= corr;
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) acc[dt] *= corr;
             }
             float sum[4] = {0.f, 0.f, 0.f, 0.f};     // four chains
+            if constexpr (F32) {
+                // the weight of token 32 t + 8 (r / 4) + 4 hw + r % 4 is the B operand of a two-token contraction as it
+                // stands; s - m first: the difference is exact to its own size
+                const float m0 = m == -INFINITY ? 0.f : m;
+                // a step's products go to sums of their own: shorter chains of additions
+                floatx16 part[DT];
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt) part[dt] = floatx16{};
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const float p = __builtin_amdgcn_exp2f((c[t][r] - m0) * scale2);
+                        sum[r % 4] += p;
+                        const char *v = v_stage + (32 * t + 8 * (r / 4) + r % 4) * S::kRowBytes + v_lane;
+#pragma unroll
+                        for (int dt = 0; dt < DT; ++dt) {
+                            const float x = *reinterpret_cast<const float *>(v + 128 * (dt ^ hw));
+                            part[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(x, p, part[dt], 0, 0, 0);
+                        }
+                    }
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt) acc[dt] += part[dt];
+                l += (sum[0] + sum[1]) + (sum[2] + sum[3]);
+                return;
+            }
             bf16x8 ph[NT][2], pl[NT][2];
 #pragma unroll
             for (int t = 0; t < NT; ++t)
@@ -419,11 +492,11 @@ __global__ __launch_bounds__(kAttnBlock, 2) void append_attn_kernel(AppendArgs a
             // parity, which were last read in step s - 1: the barrier at the top of the step (before which every wave
             // waits for its own loads) orders both.
             const int steps = (nsub + kStepTokens - 1) / kStepTokens;
-            dma_step<D, NW>(kv, rows, 0, nsub, s_k0, s_v0);
+            dma_step<T, D, NW>(kv, rows, 0, nsub, s_k0, s_v0);
             auto step = [&](int s, const char *k_cur, const char *v_cur, char *k_next, char *v_next) {
                 wait_for_own_loads();                // the barrier alone does not wait for LDS-direct loads
                 __syncthreads();
-                if (s + 1 < steps) dma_step<D, NW>(kv, rows, s + 1, nsub, k_next, v_next);
+                if (s + 1 < steps) dma_step<T, D, NW>(kv, rows, s + 1, nsub, k_next, v_next);
                 if (wave_live) step_body(k_cur, v_cur, t0 + sub0 + s * kStepTokens, nsub - s * kStepTokens);
             };
             for (int s2 = 0; s2 < steps; s2 += 2) {
@@ -434,7 +507,7 @@ __global__ __launch_bounds__(kAttnBlock, 2) void append_attn_kernel(AppendArgs a
 
         // partial of every valid row: the lane holds output columns 32 dt + 8 q + 4 hw .. + 3 of its row
         l = halves_sum(l);
-        if (!ri.valid) continue;
+        if (!row_exists) continue;
         const int64_t at = ri.out_row * a1.part.stride + slot;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
@@ -465,26 +538,35 @@ __global__ __launch_bounds__(kAttnBlock, 2) void append_attn_kernel(AppendArgs a
 // streaming policy; more of them in flight, 12 or 15 waves, change nothing), the arithmetic alone 115 us.  The previous
 // kernel (tokens in registers, rows over the lanes) spent two lane exchanges per score and a barrier per 64 tokens,
 // and its 2048-token workgroups came out at 1.2 rounds.
-template <int D> struct WeightsStage {
-    static constexpr int kPieces = D / 8, kRowBytes = D * 2, kGroupRows = 1024 / kRowBytes;
-    static __device__ __forceinline__ int swizzle(int row) { return (row / (16 / kPieces)) % kPieces; }
+//
+// fp32 inputs: the same with v_mfma_f32_32x32x2_f32, four waves (queries and slots take 128 KB).  2 x 24 queries on 5 K
+// tokens: 158 us on the vector units, one tier per launch -> 46 us.
+constexpr int kWTile = 32;
+template <typename T, int D> struct WeightsStage {
+    static constexpr int kWaves = sizeof(T) == 2 ? 8 : 4, kBlock = kWaves * kWave;
+    static constexpr int kRowBytes = D * sizeof(T), kPieces = kRowBytes / 16, kGroupRows = 1024 / kRowBytes;
+    static constexpr int kSwizzled = kPieces < 16 ? kPieces : 16;
+    static __device__ __forceinline__ int swizzle(int row) { return (row / (16 / kSwizzled)) % kSwizzled; }
     static __device__ __forceinline__ int offset(int row, int piece) { return row * kRowBytes + 16 * (piece ^ swizzle(row)); }
 };
-constexpr int kWTile = 32, kWWaves = 8, kWBlock = kWWaves * kWave;
 constexpr int kNonTemporal = 2;                  // cache policy of a load: streamed once
 constexpr int kWManyRowTokens = 512;             // tokens of a block that more than one pass over the rows goes through
 
-template <int D, int G>
-__global__ __launch_bounds__(kWBlock, 2) void append_weights_kernel(AppendArgs a1, AppendArgs a2, LineDev line, int two_tiers)
+template <typename T, int D, int G>
+__global__ __launch_bounds__(sizeof(T) == 2 ? 512 : 256, sizeof(T) == 2 ? 2 : 1) void append_weights_kernel(
+    AppendArgs a1, AppendArgs a2, LineDev line, int two_tiers)
 {
-    using S = WeightsStage<D>;
-    constexpr int KK = D / 16, RT = kRowsPerBlock / 32, NS = G < 4 ? G : 4;
+    using S = WeightsStage<T, D>;
+    static_assert(S::kBlock == (sizeof(T) == 2 ? 512 : 256), "the launch bounds above");
+    constexpr int kWWaves = S::kWaves, kWBlock = S::kBlock;
+    constexpr bool F32 = sizeof(T) == 4;
+    constexpr int KK = S::kRowBytes / 32, RT = kRowsPerBlock / 32, NS = G < 4 ? G : 4;
     constexpr float kLog2e = 1.4426950408889634f;
     typedef const __attribute__((address_space(1))) void *GlobalPtr;
     typedef __attribute__((address_space(3))) void *LdsPtr;
     __shared__ __attribute__((aligned(1024))) char s_q[kRowsPerBlock * S::kRowBytes];
     __shared__ __attribute__((aligned(1024))) char s_k[kWWaves][kWTile * S::kRowBytes];
-    __shared__ __attribute__((aligned(16))) float s_shift[kRowsPerBlock];        // minus the rows' lse in units of ln 2
+    __shared__ __attribute__((aligned(16))) float s_shift[kRowsPerBlock];        // minus the rows' lse, in the exponent's unit
     __shared__ uint32_t s_row[kSub];
 
     const int wg = (int)blockIdx.x;
@@ -492,7 +574,8 @@ __global__ __launch_bounds__(kWBlock, 2) void append_weights_kernel(AppendArgs a
     const int tid = threadIdx.x, lane = tid % kWave, w = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int n = lane % 32, hw = lane / 32;
     const int n_rows = a1.n_q * G, n_qb = (n_rows + kRowsPerBlock - 1) / kRowsPerBlock;
-    const float inv_n = 1.f / (float)a1.n_q, scale2 = a1.sh.sm_scale * kLog2e;
+    // bf16: exponents in units of ln 2 for the bare v_exp_f32; fp32: expf of the scaled score minus lse, rounded once
+    const float unit = F32 ? 1.f : kLog2e, inv_n = 1.f / (float)a1.n_q, scale = a1.sh.sm_scale * unit;
     const int frag0 = S::offset(n, hw);          // operand of row / token n; slice kk is an exclusive-or of 32 kk away
     char *const slot = s_k[w];
 
@@ -579,7 +662,7 @@ __global__ __launch_bounds__(kWBlock, 2) void append_weights_kernel(AppendArgs a
                     const RowInfo ri = row_info<G>(a1, b, kvh, qb * kRowsPerBlock + tid);
                     const float row_lse = ri.valid ? lse[ri.out_row] : -INFINITY;
                     // a row that sees nothing has lse = -inf; its weights are set to 0 below, whatever the shift
-                    s_shift[tid] = (row_lse == -INFINITY) ? 0.f : -row_lse * kLog2e;
+                    s_shift[tid] = (row_lse == -INFINITY) ? 0.f : -row_lse * unit;
                 }
                 if (w < tiles) request(w);
                 wait_for_own_loads();
@@ -604,10 +687,9 @@ __global__ __launch_bounds__(kWBlock, 2) void append_weights_kernel(AppendArgs a
                 };
                 for (int tile = w; tile < tiles; tile += kWWaves) {
                     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // the tile's rows are in the slot
-                    bf16x8 kf[KK];
+                    uint4 kf[KK];
 #pragma unroll
-                    for (int kk = 0; kk < KK; ++kk)
-                        kf[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(slot + (frag0 ^ (32 * kk))));
+                    for (int kk = 0; kk < KK; ++kk) kf[kk] = *reinterpret_cast<const uint4 *>(slot + (frag0 ^ (32 * kk)));
                     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // ... and in registers: the slot is free
                     if (tile + kWWaves < tiles) request(tile + kWWaves);
                     store();                     // (its write overlaps with this tile's arithmetic)
@@ -616,9 +698,18 @@ __global__ __launch_bounds__(kWBlock, 2) void append_weights_kernel(AppendArgs a
 #pragma unroll
                     for (int g = 0; g < NS; ++g) sum[g] = 0.f;
                     // c[r] of row tile x is the score of row 32 x + 8 (r / 4) + 4 hw + r % 4 and the lane's token
-                    auto score = [&](int x, int kk, floatx16 &c) {
-                        const uint4 qa = *reinterpret_cast<const uint4 *>(s_q + x * 32 * S::kRowBytes + (frag0 ^ (32 * kk)));
-                        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, qa), kf[kk], c, 0, 0, 0);
+                    auto q_piece = [&](int x, int kk) {
+                        return *reinterpret_cast<const uint4 *>(s_q + x * 32 * S::kRowBytes + (frag0 ^ (32 * kk)));
+                    };
+                    auto scores = [&](int x) {
+                        floatx16 c{};
+                        if constexpr (F32) {
+                            c = score_tile_f32<KK>([&](int kk) { return q_piece(x, kk); }, kf);
+                        } else {
+#pragma unroll
+                            for (int kk = 0; kk < KK; ++kk) c = score_mfma(q_piece(x, kk), kf[kk], c);
+                        }
+                        return c;
                     };
                     auto weigh = [&](int x, floatx16 &c) {
 #pragma unroll
@@ -626,7 +717,9 @@ __global__ __launch_bounds__(kWBlock, 2) void append_weights_kernel(AppendArgs a
                             const float4 sh = *reinterpret_cast<const float4 *>(s_shift + 32 * x + 8 * q4 + 4 * hw);
                             const float s4[4] = {sh.x, sh.y, sh.z, sh.w};
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) c[4 * q4 + e] = __builtin_amdgcn_exp2f(fmaf(c[4 * q4 + e], scale2, s4[e]));
+                            for (int e = 0; e < 4; ++e)
+                                c[4 * q4 + e] = F32 ? expf(fmaf(c[4 * q4 + e], scale, s4[e]))
+                                                    : __builtin_amdgcn_exp2f(fmaf(c[4 * q4 + e], scale, s4[e]));
                         }
                     };
                     if (rows_here == kRowsPerBlock && tok0 + kWTile <= seen_by_all) {            // uniform over the wave
@@ -635,10 +728,15 @@ __global__ __launch_bounds__(kWBlock, 2) void append_weights_kernel(AppendArgs a
 #pragma unroll
                         for (int x = 0; x < RT; x += 2) {
                             floatx16 c0{}, c1{};
+                            if constexpr (F32) {
+                                c0 = scores(x);
+                                c1 = scores(x + 1);
+                            } else {
 #pragma unroll
-                            for (int kk = 0; kk < KK; ++kk) {
-                                score(x, kk, c0);
-                                score(x + 1, kk, c1);
+                                for (int kk = 0; kk < KK; ++kk) {
+                                    c0 = score_mfma(q_piece(x, kk), kf[kk], c0);
+                                    c1 = score_mfma(q_piece(x + 1, kk), kf[kk], c1);
+                                }
                             }
                             weigh(x, c0);
                             weigh(x + 1, c1);
@@ -650,9 +748,7 @@ __global__ __launch_bounds__(kWBlock, 2) void append_weights_kernel(AppendArgs a
                     } else {
 #pragma unroll 1
                         for (int x = 0; x < RT && 32 * x < rows_here; ++x) {
-                            floatx16 c{};
-#pragma unroll
-                            for (int kk = 0; kk < KK; ++kk) score(x, kk, c);
+                            floatx16 c = scores(x);
                             weigh(x, c);
 #pragma unroll
                             for (int r = 0; r < 16; ++r) {
@@ -672,106 +768,30 @@ __global__ __launch_bounds__(kWBlock, 2) void append_weights_kernel(AppendArgs a
     }
 }
 
-// The same weights for fp32 inputs, on the VALU (the fp32 shapes are the small, exact ones: this pass is written for
-// clarity, not for bandwidth).  One workgroup = 64 tokens of one (sequence, KV head): their K rows are parked in LDS
-// (one pad per row, a thread walks its own row); thread (t, part) adds e^{s_it - lse_i} over the queries
-// i = part, part + 4, ... for every head of the group, the four parts are added through LDS.
-constexpr int kF32Tokens = 64, kF32Block = 256, kF32Parts = kF32Block / kF32Tokens;
-
-template <int D, int G>
-__global__ __launch_bounds__(kF32Block) void append_weights_f32_kernel(AppendArgs a)
-{
-    __shared__ float s_k[kF32Tokens][D + 1];
-    __shared__ float s_q[kF32Parts][D];
-    __shared__ float s_sum[kF32Parts][G][kF32Tokens];
-    __shared__ uint32_t s_row[kF32Tokens];
-
-    const int chunk_id = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
-    const int tid = threadIdx.x, t = tid % kF32Tokens, part = tid / kF32Tokens;
-    const int len = tier_len(a.kv, b);
-    const int t0 = chunk_id * kF32Tokens;
-    const int n_here = min(kF32Tokens, a.kv.cap - t0);           // entries of a_out this workgroup writes
-    const int nt = min(kF32Tokens, len - t0);                    // valid tokens among them (may be <= 0)
-    float *out = a.a_out + ((int64_t)b * a.sh.n_q_heads + kvh * G) * a.kv.cap + t0;
-    if (nt <= 0) {                                               // uniform over the workgroup
-        for (int i = tid; i < G * n_here; i += kF32Block) out[(int64_t)(i / n_here) * a.kv.cap + i % n_here] = 0.f;
-        return;
-    }
-    const RowMap rows = make_row_map<false, kF32Block>(s_row, a.kv, a.sh.n_kv_heads, b, kvh, t0, nt, nullptr);
-    const float *k = reinterpret_cast<const float *>(a.kv.k);
-    for (int i = tid; i < nt * D; i += kF32Block) s_k[i / D][i % D] = k[(int64_t)rows(i / D) * D + i % D];
-    const float *q = static_cast<const float *>(a.q);
-    float acc[G];
-#pragma unroll
-    for (int gh = 0; gh < G; ++gh) acc[gh] = 0.f;
-    const int rounds = (a.n_q + kF32Parts - 1) / kF32Parts;
-    for (int gh = 0; gh < G; ++gh) {
-        const int h = kvh * G + gh;
-        for (int r = 0; r < rounds; ++r) {
-            const int i = r * kF32Parts + part;                  // this part's query of the round
-            __syncthreads();                                     // the K rows are in place; the previous query is done with
-            if (i < a.n_q)
-                for (int e = t; e < D; e += kF32Tokens) s_q[part][e] = q[(((int64_t)b * a.n_q + i) * a.sh.n_q_heads + h) * D + e];
-            __syncthreads();
-            if (i >= a.n_q || t >= nt) continue;                 // no barrier below this line inside the round
-            const int vis = a.causal_tail ? min(max(len - a.n_q + i + 1, 0), len) : len;
-            if (t0 + t >= vis) continue;
-            float dot = 0.f;
-#pragma unroll 8
-            for (int e = 0; e < D; ++e) dot = fmaf(s_q[part][e], s_k[t][e], dot);
-            acc[gh] += expf(dot * a.sh.sm_scale - a.lse[((int64_t)b * a.n_q + i) * a.sh.n_q_heads + h]);
-        }
-    }
-#pragma unroll
-    for (int gh = 0; gh < G; ++gh) s_sum[part][gh][t] = acc[gh];
-    __syncthreads();
-    const float inv_n = 1.f / (float)a.n_q;
-    for (int i = tid; i < G * n_here; i += kF32Block) {
-        const int gh = i / n_here, j = i % n_here;
-        float v = 0.f;
-#pragma unroll
-        for (int p = 0; p < kF32Parts; ++p) v += s_sum[p][gh][j];
-        out[(int64_t)gh * a.kv.cap + j] = j < nt ? v * inv_n : 0.f;
-    }
-}
-
-template <int D>
-hipError_t launch_weights_f32_group(const AppendArgs &a, dim3 grid, hipStream_t s)
-{
-    switch (a.sh.group) {
-    case 1: hipLaunchKernelGGL((append_weights_f32_kernel<D, 1>), grid, dim3(kF32Block), 0, s, a); break;
-    case 2: hipLaunchKernelGGL((append_weights_f32_kernel<D, 2>), grid, dim3(kF32Block), 0, s, a); break;
-    case 4: hipLaunchKernelGGL((append_weights_f32_kernel<D, 4>), grid, dim3(kF32Block), 0, s, a); break;
-    case 8: hipLaunchKernelGGL((append_weights_f32_kernel<D, 8>), grid, dim3(kF32Block), 0, s, a); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
-template <int D, bool SPLIT_P>
+template <typename T, int D, bool SPLIT_P>
 hipError_t launch_attn_group(const AppendArgs &a, const AppendArgs &a2, const LineDev &line, int two, dim3 grid,
                              hipStream_t s)
 {
     const dim3 block(kAttnBlock);
     switch (a.sh.group) {
-    case 1: hipLaunchKernelGGL((append_attn_kernel<D, 1, SPLIT_P>), grid, block, 0, s, a, a2, line, two); break;
-    case 2: hipLaunchKernelGGL((append_attn_kernel<D, 2, SPLIT_P>), grid, block, 0, s, a, a2, line, two); break;
-    case 4: hipLaunchKernelGGL((append_attn_kernel<D, 4, SPLIT_P>), grid, block, 0, s, a, a2, line, two); break;
-    case 8: hipLaunchKernelGGL((append_attn_kernel<D, 8, SPLIT_P>), grid, block, 0, s, a, a2, line, two); break;
+    case 1: hipLaunchKernelGGL((append_attn_kernel<T, D, 1, SPLIT_P>), grid, block, 0, s, a, a2, line, two); break;
+    case 2: hipLaunchKernelGGL((append_attn_kernel<T, D, 2, SPLIT_P>), grid, block, 0, s, a, a2, line, two); break;
+    case 4: hipLaunchKernelGGL((append_attn_kernel<T, D, 4, SPLIT_P>), grid, block, 0, s, a, a2, line, two); break;
+    case 8: hipLaunchKernelGGL((append_attn_kernel<T, D, 8, SPLIT_P>), grid, block, 0, s, a, a2, line, two); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-template <int D>
+template <typename T, int D>
 hipError_t launch_weights_group(const AppendArgs &a, const AppendArgs &a2, const LineDev &line, int two, dim3 grid, hipStream_t s)
 {
-    const dim3 block(kWBlock);
+    const dim3 block(WeightsStage<T, D>::kBlock);
     switch (a.sh.group) {
-    case 1: hipLaunchKernelGGL((append_weights_kernel<D, 1>), grid, block, 0, s, a, a2, line, two); break;
-    case 2: hipLaunchKernelGGL((append_weights_kernel<D, 2>), grid, block, 0, s, a, a2, line, two); break;
-    case 4: hipLaunchKernelGGL((append_weights_kernel<D, 4>), grid, block, 0, s, a, a2, line, two); break;
-    case 8: hipLaunchKernelGGL((append_weights_kernel<D, 8>), grid, block, 0, s, a, a2, line, two); break;
+    case 1: hipLaunchKernelGGL((append_weights_kernel<T, D, 1>), grid, block, 0, s, a, a2, line, two); break;
+    case 2: hipLaunchKernelGGL((append_weights_kernel<T, D, 2>), grid, block, 0, s, a, a2, line, two); break;
+    case 4: hipLaunchKernelGGL((append_weights_kernel<T, D, 4>), grid, block, 0, s, a, a2, line, two); break;
+    case 8: hipLaunchKernelGGL((append_weights_kernel<T, D, 8>), grid, block, 0, s, a, a2, line, two); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -779,7 +799,7 @@ hipError_t launch_weights_group(const AppendArgs &a, const AppendArgs &a2, const
 
 }  // namespace
 
-hipError_t launch_append_attn(int head_dim, const AppendArgs &a, const AppendArgs *second, const LineDev &line,
+hipError_t launch_append_attn(int dtype, int head_dim, const AppendArgs &a, const AppendArgs *second, const LineDev &line,
                               hipStream_t s)
 {
     if (a.sh.batch == 0 || a.n_q == 0) return hipSuccess;
@@ -790,19 +810,23 @@ hipError_t launch_append_attn(int head_dim, const AppendArgs &a, const AppendArg
         return hipErrorInvalidValue;             // the two tiers share the queries, the launch shape and the partials
     const int n_qb = (a.n_q * a.sh.group + kRowsPerBlock - 1) / kRowsPerBlock;
     const int64_t streams = (int64_t)line.shares * a.sh.n_kv_heads * a.sh.batch;
-    const int64_t blocks = n_qb == 1 ? streams : (streams + kXcds - 1) / kXcds * kXcds * n_qb;
+    const int64_t blocks = (streams + kXcds - 1) / kXcds * kXcds * n_qb;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)blocks);
+    const dim3 grid = n_qb == 1 ? dim3(line.shares, a.sh.n_kv_heads, a.sh.batch) : dim3((unsigned)blocks);
     const int two = second ? 1 : 0;
-    if (head_dim == 64)
-        return a.one_part_p ? launch_attn_group<64, false>(a, a2, line, two, grid, s) : launch_attn_group<64, true>(a, a2, line, two, grid, s);
-    if (head_dim == 128)
-        return a.one_part_p ? launch_attn_group<128, false>(a, a2, line, two, grid, s) : launch_attn_group<128, true>(a, a2, line, two, grid, s);
+    if (dtype == 0 && head_dim == 64) return launch_attn_group<float, 64, false>(a, a2, line, two, grid, s);
+    if (dtype == 0 && head_dim == 128) return launch_attn_group<float, 128, false>(a, a2, line, two, grid, s);
+    if (dtype == 1 && head_dim == 64)
+        return a.one_part_p ? launch_attn_group<bf16_t, 64, false>(a, a2, line, two, grid, s)
+                            : launch_attn_group<bf16_t, 64, true>(a, a2, line, two, grid, s);
+    if (dtype == 1 && head_dim == 128)
+        return a.one_part_p ? launch_attn_group<bf16_t, 128, false>(a, a2, line, two, grid, s)
+                            : launch_attn_group<bf16_t, 128, true>(a, a2, line, two, grid, s);
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_append_weights(int head_dim, const AppendArgs &a, const AppendArgs *second, const LineDev &line,
-                                 hipStream_t s)
+hipError_t launch_append_weights(int dtype, int head_dim, const AppendArgs &a, const AppendArgs *second,
+                                 const LineDev &line, hipStream_t s)
 {
     if (a.sh.batch == 0 || a.n_q == 0) return hipSuccess;
     const AppendArgs &a2 = second ? *second : a;
@@ -812,17 +836,11 @@ hipError_t launch_append_weights(int head_dim, const AppendArgs &a, const Append
     const int64_t blocks = (int64_t)line.shares * a.sh.n_kv_heads * a.sh.batch;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks);
-    if (head_dim == 64) return launch_weights_group<64>(a, a2, line, second ? 1 : 0, grid, s);
-    if (head_dim == 128) return launch_weights_group<128>(a, a2, line, second ? 1 : 0, grid, s);
-    return hipErrorInvalidValue;
-}
-
-hipError_t launch_append_weights_f32(int head_dim, const AppendArgs &a, hipStream_t s)
-{
-    if (a.sh.batch == 0 || a.kv.cap == 0) return hipSuccess;
-    dim3 grid((a.kv.cap + kF32Tokens - 1) / kF32Tokens, a.sh.n_kv_heads, a.sh.batch);
-    if (head_dim == 64) return launch_weights_f32_group<64>(a, grid, s);
-    if (head_dim == 128) return launch_weights_f32_group<128>(a, grid, s);
+    const int two = second ? 1 : 0;
+    if (dtype == 0 && head_dim == 64) return launch_weights_group<float, 64>(a, a2, line, two, grid, s);
+    if (dtype == 0 && head_dim == 128) return launch_weights_group<float, 128>(a, a2, line, two, grid, s);
+    if (dtype == 1 && head_dim == 64) return launch_weights_group<bf16_t, 64>(a, a2, line, two, grid, s);
+    if (dtype == 1 && head_dim == 128) return launch_weights_group<bf16_t, 128>(a, a2, line, two, grid, s);
     return hipErrorInvalidValue;
 }
 

@@ -107,12 +107,12 @@ __global__ __launch_bounds__(kBlock) void dense_attn_mfma_kernel(KernelArgs a)
 // ---- combine and merge ------------------------------------------------------------------------------
 
 // One workgroup folds one (b, h) row (fold_device.hpp); lse_p, if given, receives the log-sum-exp of set p alone.
-template <int D, bool OUT_BF16>
+template <int D, bool OUT_BF16, bool LINE>
 __global__ __launch_bounds__(kFoldBlock) void combine_kernel(Partials p, Partials q, void *o, float *lse, float *lse_p,
                                                              float *lse_q, LineDev line)
 {
     __shared__ FoldShared<D> sh;
-    if (line.shares) line_sets<D>(line, Partials(p), blockIdx.x, p, q);          // uniform over the launch
+    if (LINE) line_sets<D>(line, Partials(p), blockIdx.x, p, q);
     if (lse_p) fold_row<D, OUT_BF16, true>(sh, p, q, o, lse, lse_p, blockIdx.x, lse_q);   // uniform over the launch
     else fold_row<D, OUT_BF16, false>(sh, p, q, o, lse, nullptr, blockIdx.x);
 }
@@ -120,7 +120,7 @@ __global__ __launch_bounds__(kFoldBlock) void combine_kernel(Partials p, Partial
 // The same fold for MANY rows with few splits each (the append stage: B * N * Hq rows): a workgroup per row would be
 // thousands of workgroups of a few KB each.  Here a thread owns four columns of one row and walks the row's splits
 // itself, so a workgroup folds kFoldBlock / (D / 4) rows and needs neither LDS nor a barrier.
-template <int D, bool OUT_BF16>
+template <int D, bool OUT_BF16, bool LINE>
 __global__ __launch_bounds__(kFoldBlock) void combine_rows_kernel(Partials p, Partials q, void *o, float *lse, float *lse_p,
                                                                   float *lse_q, int64_t n_rows, LineDev line)
 {
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(kFoldBlock) void combine_rows_kernel(Partials p, Pa
     const int64_t row = (int64_t)blockIdx.x * R + threadIdx.x / C4;
     const int c4 = threadIdx.x % C4;
     if (row >= n_rows) return;
-    if (line.shares) line_sets<D>(line, Partials(p), row, p, q);                 // uniform over the launch
+    if (LINE) line_sets<D>(line, Partials(p), row, p, q);
     const int np = p.n_splits, nq = q.n_splits, n = np + nq;
     auto m_of = [&](int s) { return s < np ? p.m[row * p.stride + s] : q.m[row * q.stride + (s - np)]; };
     auto l_of = [&](int s) { return s < np ? p.l[row * p.stride + s] : q.l[row * q.stride + (s - np)]; };
@@ -345,6 +345,7 @@ hipError_t launch_combine(int head_dim, int64_t n_rows, const Partials &p, float
 
 namespace {
 
+template <bool LINE>
 hipError_t launch_fold(int head_dim, int64_t n_rows, const Partials &p, const Partials &q, const LineDev &line, int n_slots,
                        void *o, int o_dtype, float *lse, float *lse_p, float *lse_q, hipStream_t s)
 {
@@ -354,8 +355,8 @@ hipError_t launch_fold(int head_dim, int64_t n_rows, const Partials &p, const Pa
     const dim3 grid((unsigned)((n_rows + rows_per_wg - 1) / rows_per_wg)), block(kFoldBlock);
 #define HGCA_FOLD_CASE(D, BF)                                                                                             \
     if (head_dim == D && o_dtype == (BF ? 1 : 0)) {                                                                       \
-        if (many) HGCA_LAUNCH((combine_rows_kernel<D, BF>), grid, block, s, p, q, o, lse, lse_p, lse_q, n_rows, line);    \
-        else HGCA_LAUNCH((combine_kernel<D, BF>), grid, block, s, p, q, o, lse, lse_p, lse_q, line);                      \
+        if (many) HGCA_LAUNCH((combine_rows_kernel<D, BF, LINE>), grid, block, s, p, q, o, lse, lse_p, lse_q, n_rows, line);    \
+        else HGCA_LAUNCH((combine_kernel<D, BF, LINE>), grid, block, s, p, q, o, lse, lse_p, lse_q, line);                \
         return hipGetLastError();                                                                                         \
     }
     HGCA_FOLD_CASE(64, false) HGCA_FOLD_CASE(64, true) HGCA_FOLD_CASE(128, false) HGCA_FOLD_CASE(128, true)
@@ -369,7 +370,7 @@ hipError_t launch_combine2(int head_dim, int64_t n_rows, const Partials &p, cons
                            float *lse, hipStream_t s, float *lse_p, float *lse_q)
 {
     if (lse_q && !lse_p) return hipErrorInvalidValue;
-    return launch_fold(head_dim, n_rows, p, q, LineDev{}, p.n_splits + q.n_splits, o, o_dtype, lse, lse_p, lse_q, s);
+    return launch_fold<false>(head_dim, n_rows, p, q, LineDev{}, p.n_splits + q.n_splits, o, o_dtype, lse, lse_p, lse_q, s);
 }
 
 hipError_t launch_combine_line(int head_dim, int64_t n_rows, const Partials &t, const LineDev &line, float *o, float *lse,
@@ -377,7 +378,7 @@ hipError_t launch_combine_line(int head_dim, int64_t n_rows, const Partials &t, 
 {
     if (line.shares <= 0 || t.stride != line.shares + 1 || line.rows_per_seq <= 0 || (lse_first && !lse_second))
         return hipErrorInvalidValue;
-    return launch_fold(head_dim, n_rows, t, Partials{}, line, t.stride, o, 0, lse, lse_second, lse_first, s);
+    return launch_fold<true>(head_dim, n_rows, t, Partials{}, line, t.stride, o, 0, lse, lse_second, lse_first, s);
 }
 
 hipError_t launch_merge(int head_dim, int64_t n_rows, const float *o_a, const float *lse_a, const float *o_b,

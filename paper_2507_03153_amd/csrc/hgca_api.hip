@@ -918,26 +918,32 @@ int append_want_splits(const hgca_shape *s, int32_t n_q)
     return (int)std::max<int64_t>(1, HGCA_APPEND_TARGET_WGS / append_units(s, n_q));
 }
 
-// Workgroups that share the `tokens` (by capacity) of a unit, at most `most`: the number for which the launch takes the
-// least time, counted in 64-token steps: rounds of `places` workgroups (what the device holds at once)
-// times the steps of a share, plus what a share costs beside its steps -- loading the queries, the first rows' latency
-// and a partial of 64 KB to write and fold, together about five steps (a step takes 2.8 us, a share's fixed part 15 us
-// on 509 queries x 32 K tokens).
-int append_shares(const hgca_shape *s, int32_t n_q, int64_t tokens, int most, int places = HGCA_APPEND_TARGET_WGS)
+// Workgroups that share the `tokens` (by capacity) of each of `units`, at most `most`: the number for which the launch
+// takes the least time, counted in 64-token steps: rounds of `places` workgroups (what the device holds at once) times
+// the steps of a share and what a share costs beside them (`overhead` steps).
+int line_shares(int64_t units, int64_t tokens, int most, int places, int overhead)
 {
-    constexpr int kShareOverhead = 5;
-    const int64_t units = append_units(s, n_q), steps = std::max<int64_t>(1, (tokens + kLineStep - 1) / kLineStep);
+    const int64_t steps = std::max<int64_t>(1, (tokens + kLineStep - 1) / kLineStep);
     int best = 1;
     int64_t best_cost = INT64_MAX;
     for (int n = 1; n <= most && n <= steps; ++n) {
         const int64_t rounds = (n * units + places - 1) / places;
-        const int64_t cost = rounds * ((steps + n - 1) / n + kShareOverhead);
+        const int64_t cost = rounds * ((steps + n - 1) / n + overhead);
         if (cost < best_cost) {
             best_cost = cost;
             best = n;
         }
     }
     return best;
+}
+
+// The attention: in bf16 two workgroups per unit and about five steps for loading the queries, the first rows' latency
+// and a partial of 64 KB to write and fold (a step takes 2.8 us, the fixed part 15 us on 509 queries x 32 K tokens); in
+// fp32 one workgroup per unit, whose steps are four times as long.
+int append_shares(const hgca_shape *s, int32_t n_q, int64_t tokens, int most)
+{
+    const bool f32 = s->dtype == HGCA_F32;
+    return line_shares(append_units(s, n_q), tokens, most, f32 ? HGCA_APPEND_TARGET_WGS / 2 : HGCA_APPEND_TARGET_WGS, f32 ? 1 : 5);
 }
 
 struct AppendWs {
@@ -994,32 +1000,8 @@ int hgca_append_attn(const hgca_shape *shape, const void *q, int32_t n_q, const 
     if (!ws || ws_bytes < w.total || !aligned16(ws)) return HGCA_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
 
-    if (shape->dtype == HGCA_F32) {
-        // fp32 inputs: every (sequence, query) pair is a one-query attention over the tokens that query sees, so the
-        // split kernels of the decode path serve, on a batch of B * n_q queries that share their sequence's rows
-        if ((int64_t)shape->batch * n_q > 65535) return HGCA_ERR_UNSUPPORTED;
-        AttnArgs d{};
-        d.sh = to_dev(shape);
-        d.sh.batch = shape->batch * n_q;
-        d.q = q;
-        d.kv = to_dev(tier);
-        d.kv.n_q = n_q;
-        d.kv.causal_tail = (flags & HGCA_APPEND_CAUSAL_TAIL) ? 1 : 0;
-        d.chunk = pick_chunk(tier->cap, (int64_t)d.sh.batch * shape->n_kv_heads, HGCA_TARGET_WGS_DENSE);
-        char *base = static_cast<char *>(ws);
-        d.part.o = reinterpret_cast<float *>(base + w.o);
-        d.part.m = reinterpret_cast<float *>(base + w.m);
-        d.part.l = reinterpret_cast<float *>(base + w.l);
-        d.part.n_splits = d.part.stride = std::max(1, n_splits_for(tier->cap, d.chunk));
-        if (d.part.n_splits > w.max_splits) return HGCA_ERR_WORKSPACE;
-        const int64_t rows = (int64_t)d.sh.batch * shape->n_q_heads;
-        if (tier->cap == 0) {                    // nothing to attend to: the fold of one empty split writes O = 0, lse = -inf
-            Partials none{};
-            return from_hip(launch_combine2(shape->head_dim, rows, none, none, o_out, 0, lse_out, s));
-        }
-        if ((rc = from_hip(launch_attn_partial_dense(shape->dtype, shape->head_dim, d, s))) != HGCA_OK) return rc;
-        return from_hip(launch_combine(shape->head_dim, rows, d.part, o_out, lse_out, s));
-    }
+    // (a limit of the fp32 calls that callers may rely on as part of the interface)
+    if (shape->dtype == HGCA_F32 && (int64_t)shape->batch * n_q > 65535) return HGCA_ERR_UNSUPPORTED;
     AppendArgs a{};
     a.sh = to_dev(shape);
     a.q = q;
@@ -1031,7 +1013,7 @@ int hgca_append_attn(const hgca_shape *shape, const void *q, int32_t n_q, const 
     char *base = static_cast<char *>(ws);
     a.part = Partials{reinterpret_cast<float *>(base + w.o), reinterpret_cast<float *>(base + w.m),
                       reinterpret_cast<float *>(base + w.l), line.shares, line.shares};
-    if ((rc = from_hip(launch_append_attn(shape->head_dim, a, nullptr, line, s))) != HGCA_OK) return rc;
+    if ((rc = from_hip(launch_append_attn(shape->dtype, shape->head_dim, a, nullptr, line, s))) != HGCA_OK) return rc;
     const int64_t rows = (int64_t)shape->batch * n_q * shape->n_q_heads;
     return from_hip(launch_combine(shape->head_dim, rows, a.part, o_out, lse_out, s));
 }
@@ -1070,7 +1052,10 @@ size_t hgca_append_tiers_workspace_bytes(const hgca_shape *shape, int32_t n_q, i
     return tiers_layout(shape, n_q, window_cap, pool_cap).total;
 }
 
-int hgca_append_attn_tiers(const hgca_shape *shape, const void *q, int32_t n_q, const hgca_kv_view *window,
+namespace {
+
+// Both tiers of an append turn, either type (the exported call takes bf16 only; a turn over the managed cache both).
+int append_attn_tiers(const hgca_shape *shape, const void *q, int32_t n_q, const hgca_kv_view *window,
                            const hgca_kv_view *pool, int32_t flags, float *o_out, float *lse_out, float *lse_window_out,
                            float *lse_pool_out, void *ws, size_t ws_bytes, void *hip_stream)
 {
@@ -1078,7 +1063,6 @@ int hgca_append_attn_tiers(const hgca_shape *shape, const void *q, int32_t n_q, 
     if (rc != HGCA_OK) return rc;
     if ((rc = check_append(shape, q, n_q, pool, true)) != HGCA_OK) return rc;
     if (flags & ~(HGCA_APPEND_CAUSAL_TAIL | HGCA_APPEND_ONE_PART_P)) return HGCA_ERR_INVALID_ARG;
-    if (shape->dtype != HGCA_BF16) return HGCA_ERR_UNSUPPORTED;      // fp32 inputs: one call per tier and hgca_lse_merge
     if (shape->batch == 0 || n_q == 0) return HGCA_OK;
     if (!o_out || !lse_out || !aligned16(o_out)) return HGCA_ERR_INVALID_ARG;
     if ((int64_t)shape->n_kv_heads * (((int64_t)n_q * group_of(shape) + 127) / 128) > 65535) return HGCA_ERR_UNSUPPORTED;
@@ -1099,7 +1083,7 @@ int hgca_append_attn_tiers(const hgca_shape *shape, const void *q, int32_t n_q, 
     aw.part = ap.part = Partials{reinterpret_cast<float *>(base + w.o), reinterpret_cast<float *>(base + w.m),
                                  reinterpret_cast<float *>(base + w.l), w.shares + 1, w.shares + 1};
     const LineDev line{pool->seq_lens, window->seq_lens, pool->cap, window->cap, w.shares, n_q * shape->n_q_heads};
-    if ((rc = from_hip(launch_append_attn(shape->head_dim, ap, &aw, line, s))) != HGCA_OK) return rc;
+    if ((rc = from_hip(launch_append_attn(shape->dtype, shape->head_dim, ap, &aw, line, s))) != HGCA_OK) return rc;
     // merge_state over the partials of both tiers at once; each tier's own lse comes out of the same fold
     const int64_t rows = (int64_t)shape->batch * n_q * shape->n_q_heads;
     float *lse_w = lse_window_out ? lse_window_out : reinterpret_cast<float *>(base + w.lse_w);
@@ -1107,6 +1091,21 @@ int hgca_append_attn_tiers(const hgca_shape *shape, const void *q, int32_t n_q, 
     const bool want_tiers = lse_window_out || lse_pool_out;
     return from_hip(launch_combine_line(shape->head_dim, rows, ap.part, line, o_out, lse_out, want_tiers ? lse_p : nullptr,
                                         want_tiers ? lse_w : nullptr, s));
+}
+
+}  // namespace
+
+int hgca_append_attn_tiers(const hgca_shape *shape, const void *q, int32_t n_q, const hgca_kv_view *window,
+                           const hgca_kv_view *pool, int32_t flags, float *o_out, float *lse_out, float *lse_window_out,
+                           float *lse_pool_out, void *ws, size_t ws_bytes, void *hip_stream)
+{
+    int rc = check_append(shape, q, n_q, window, true);
+    if (rc != HGCA_OK) return rc;
+    if ((rc = check_append(shape, q, n_q, pool, true)) != HGCA_OK) return rc;
+    if (flags & ~(HGCA_APPEND_CAUSAL_TAIL | HGCA_APPEND_ONE_PART_P)) return HGCA_ERR_INVALID_ARG;
+    if (shape->dtype != HGCA_BF16) return HGCA_ERR_UNSUPPORTED;      // fp32 inputs: one call per tier and hgca_lse_merge
+    return append_attn_tiers(shape, q, n_q, window, pool, flags, o_out, lse_out, lse_window_out, lse_pool_out, ws, ws_bytes,
+                             hip_stream);
 }
 
 namespace {
@@ -1126,11 +1125,33 @@ AppendArgs weights_args(const hgca_shape *shape, const void *q, int32_t n_q, con
     return a;
 }
 
-constexpr int kWeightsPlaces = 256;              // one workgroup of the weights pass per compute unit
+// Workgroups per (sequence, KV head) of the weights pass: one per compute unit, each meets all query rows.
+int weights_shares(const hgca_shape *s, int64_t tokens)
+{
+    constexpr int kPlaces = 256;
+    return line_shares((int64_t)s->batch * s->n_kv_heads, tokens, kPlaces, kPlaces, s->dtype == HGCA_F32 ? 1 : 5);
+}
 
-// Workgroups per (sequence, KV head) of the weights pass: the rule of append_shares (a share's fixed part is the
-// queries it loads); a workgroup meets all query rows, so the units are the (sequence, KV head) pairs.
-int weights_shares(const hgca_shape *s, int64_t tokens) { return append_shares(s, 1, tokens, kWeightsPlaces, kWeightsPlaces); }
+}  // namespace
+
+namespace {
+
+int append_weights_tiers(const hgca_shape *shape, const void *q, int32_t n_q, const hgca_kv_view *window,
+                              const hgca_kv_view *pool, int32_t causal_tail, const float *lse_window, const float *lse_pool,
+                              float *a_gpu, float *a_cpu, void *hip_stream)
+{
+    int rc = check_append(shape, q, n_q, window, false);
+    if (rc != HGCA_OK) return rc;
+    if ((rc = check_append(shape, q, n_q, pool, false)) != HGCA_OK) return rc;
+    if (n_q == 0) return HGCA_ERR_INVALID_ARG;       // an average over no query is undefined
+    if (shape->batch == 0) return HGCA_OK;
+    if ((window->cap > 0 && (!lse_window || !a_gpu)) || (pool->cap > 0 && (!lse_pool || !a_cpu))) return HGCA_ERR_INVALID_ARG;
+    const AppendArgs aw = weights_args(shape, q, n_q, window, causal_tail, lse_window, a_gpu);
+    const AppendArgs ap = weights_args(shape, q, n_q, pool, 0, lse_pool, a_cpu);
+    const LineDev line{pool->seq_lens, window->seq_lens, pool->cap, window->cap,
+                       weights_shares(shape, (int64_t)pool->cap + window->cap), 0};
+    return from_hip(launch_append_weights(shape->dtype, shape->head_dim, ap, &aw, line, static_cast<hipStream_t>(hip_stream)));
+}
 
 }  // namespace
 
@@ -1143,13 +1164,7 @@ int hgca_append_weights_tiers(const hgca_shape *shape, const void *q, int32_t n_
     if ((rc = check_append(shape, q, n_q, pool, false)) != HGCA_OK) return rc;
     if (n_q == 0) return HGCA_ERR_INVALID_ARG;       // an average over no query is undefined
     if (shape->dtype != HGCA_BF16) return HGCA_ERR_UNSUPPORTED;      // fp32 inputs: one call per tier
-    if (shape->batch == 0) return HGCA_OK;
-    if ((window->cap > 0 && (!lse_window || !a_gpu)) || (pool->cap > 0 && (!lse_pool || !a_cpu))) return HGCA_ERR_INVALID_ARG;
-    const AppendArgs aw = weights_args(shape, q, n_q, window, causal_tail, lse_window, a_gpu);
-    const AppendArgs ap = weights_args(shape, q, n_q, pool, 0, lse_pool, a_cpu);
-    const LineDev line{pool->seq_lens, window->seq_lens, pool->cap, window->cap,
-                       weights_shares(shape, (int64_t)pool->cap + window->cap), 0};
-    return from_hip(launch_append_weights(shape->head_dim, ap, &aw, line, static_cast<hipStream_t>(hip_stream)));
+    return append_weights_tiers(shape, q, n_q, window, pool, causal_tail, lse_window, lse_pool, a_gpu, a_cpu, hip_stream);
 }
 
 int hgca_append_weights(const hgca_shape *shape, const void *q, int32_t n_q, const hgca_kv_view *tier,
@@ -1161,17 +1176,15 @@ int hgca_append_weights(const hgca_shape *shape, const void *q, int32_t n_q, con
     if (shape->batch == 0 || tier->cap == 0) return HGCA_OK;
     if (!lse || !a_out) return HGCA_ERR_INVALID_ARG;
     const AppendArgs a = weights_args(shape, q, n_q, tier, causal_tail, lse, a_out);
-    if (shape->dtype == HGCA_F32)
-        return from_hip(launch_append_weights_f32(shape->head_dim, a, static_cast<hipStream_t>(hip_stream)));
     const LineDev line{tier->seq_lens, nullptr, tier->cap, 0, weights_shares(shape, tier->cap), 0};
-    return from_hip(launch_append_weights(shape->head_dim, a, nullptr, line, static_cast<hipStream_t>(hip_stream)));
+    return from_hip(launch_append_weights(shape->dtype, shape->head_dim, a, nullptr, line, static_cast<hipStream_t>(hip_stream)));
 }
 
 namespace {
 
-// Workspace of hgca_managed_append_step: [scratch of hgca_append_attn | O, lse of the window part | O, lse of the pool part]
+// Workspace of hgca_managed_append_step: [scratch of the two-tier attention | lse of the window part | lse of the pool part]
 struct ManagedAppendWs {
-    size_t attn, o_w, lse_w, o_p, lse_p, total;
+    size_t attn, lse_w, lse_p, total;
     size_t attn_bytes;
 };
 
@@ -1179,13 +1192,10 @@ ManagedAppendWs managed_append_layout(const hgca_shape *s, int32_t n_q, int32_t 
 {
     ManagedAppendWs w{};
     const size_t rows = (size_t)s->batch * n_q * s->n_q_heads;
-    w.attn_bytes = std::max(append_layout(s, n_q, std::max(win_cap, pool_cap)).total,
-                            tiers_layout(s, n_q, win_cap, pool_cap).total);
+    w.attn_bytes = tiers_layout(s, n_q, win_cap, pool_cap).total;
     size_t at = 0;
     w.attn = at; at += align_up(w.attn_bytes);
-    w.o_w = at; at += align_up(rows * s->head_dim * sizeof(float));
     w.lse_w = at; at += align_up(rows * sizeof(float));
-    w.o_p = at; at += align_up(rows * s->head_dim * sizeof(float));
     w.lse_p = at; at += align_up(rows * sizeof(float));
     w.total = std::max<size_t>(at, kAlign);
     return w;
@@ -1234,8 +1244,7 @@ int hgca_managed_append_step(const hgca_shape *shape, const hgca_cache_state *ca
     const ManagedAppendWs w = managed_append_layout(shape, n_q, c.win_cap, c.pool_cap);
     if (!ws || ws_bytes < w.total || !aligned16(ws)) return HGCA_ERR_WORKSPACE;
     char *base = static_cast<char *>(ws);
-    float *o_w = reinterpret_cast<float *>(base + w.o_w), *lse_w = reinterpret_cast<float *>(base + w.lse_w);
-    float *o_p = reinterpret_cast<float *>(base + w.o_p), *lse_p = reinterpret_cast<float *>(base + w.lse_p);
+    float *lse_w = reinterpret_cast<float *>(base + w.lse_w), *lse_p = reinterpret_cast<float *>(base + w.lse_p);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const int32_t row_bytes = shape->head_dim * (shape->dtype == HGCA_BF16 ? 2 : 4);
 
@@ -1243,30 +1252,13 @@ int hgca_managed_append_step(const hgca_shape *shape, const hgca_cache_state *ca
     if ((rc = from_hip(launch_kv_append(c, k_in, v_in, nullptr, shape->batch, shape->n_kv_heads, row_bytes, n_q, s))) != HGCA_OK)
         return rc;
     // gpu_attention over the window (causal among the incoming tokens), cpu_attention over the complete offloaded
-    // cache, merge_state per (sequence, query, head): bf16 as one launch for both tiers and one fold; fp32 as a call
-    // per tier and a merge
-    if (shape->dtype == HGCA_BF16) {
-        if ((rc = hgca_append_attn_tiers(shape, q, n_q, &window, &pool, flags | HGCA_APPEND_CAUSAL_TAIL, o_out, lse_out,
-                                         lse_w, lse_p, base + w.attn, w.attn_bytes, hip_stream)) != HGCA_OK)
-            return rc;
-    } else {
-        if ((rc = hgca_append_attn(shape, q, n_q, &window, flags | HGCA_APPEND_CAUSAL_TAIL, o_w, lse_w, base + w.attn,
-                                   w.attn_bytes, hip_stream)) != HGCA_OK)
-            return rc;
-        if ((rc = hgca_append_attn(shape, q, n_q, &pool, flags, o_p, lse_p, base + w.attn, w.attn_bytes, hip_stream)) != HGCA_OK)
-            return rc;
-        hgca_shape merged = *shape;
-        merged.batch = shape->batch * n_q;
-        if ((rc = hgca_lse_merge(&merged, o_p, lse_p, o_w, lse_w, o_out, HGCA_F32, lse_out, hip_stream)) != HGCA_OK) return rc;
-    }
-    // A_gpu, A_cpu: the query-averaged weights of the two parts (bf16: one launch for both)
-    if (shape->dtype == HGCA_BF16) {
-        if ((rc = hgca_append_weights_tiers(shape, q, n_q, &window, &pool, 1, lse_w, lse_p, a_gpu, a_cpu, hip_stream)) != HGCA_OK)
-            return rc;
-    } else {
-        if ((rc = hgca_append_weights(shape, q, n_q, &window, 1, lse_w, a_gpu, hip_stream)) != HGCA_OK) return rc;
-        if ((rc = hgca_append_weights(shape, q, n_q, &pool, 0, lse_p, a_cpu, hip_stream)) != HGCA_OK) return rc;
-    }
+    // cache, merge_state per (sequence, query, head): one launch for both tiers and one fold
+    if ((rc = append_attn_tiers(shape, q, n_q, &window, &pool, flags | HGCA_APPEND_CAUSAL_TAIL, o_out, lse_out, lse_w, lse_p,
+                                base + w.attn, w.attn_bytes, hip_stream)) != HGCA_OK)
+        return rc;
+    // A_gpu, A_cpu: the query-averaged weights of the two parts, one launch for both
+    if ((rc = append_weights_tiers(shape, q, n_q, &window, &pool, 1, lse_w, lse_p, a_gpu, a_cpu, hip_stream)) != HGCA_OK)
+        return rc;
     // Alg. 1: moving averages (the n_q new entries take their first observed weight), re-evaluation of the salient
     // lists (Sec. 3.2.2: ids = A_cpu > beta / A_cpu.size), eviction of as many whole blocks as it takes: per row, one launch
     if (HGCA_FUSE_APPEND_TAIL)

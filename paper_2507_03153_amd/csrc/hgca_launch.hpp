@@ -139,13 +139,13 @@ struct ThresholdArgs {
 };
 hipError_t launch_threshold_select(const ThresholdArgs &a, int64_t n_rows, hipStream_t s);
 
-// ---- append stage: N queries per sequence over one tier (bf16, MFMA) ----
+// ---- append stage: N queries per sequence over one tier or two (matrix cores, either type) ----
 
 constexpr int kMaxAppendChunk = 8192;   // tokens of capacity per share of the append-stage attention at most, where shares are counted
 
 struct AppendArgs {
     ShapeDev sh;
-    const void *q;             // [B, N, Hq, d] bf16
+    const void *q;             // [B, N, Hq, d]
     KvDev kv;
     int32_t n_q;               // N
     int32_t causal_tail;       // 1: the tier's last N valid tokens are the queries' own; query i sees tokens < len-N+i+1
@@ -156,14 +156,11 @@ struct AppendArgs {
 };
 // One tier (second = nullptr, `shares` slots) or two as a line (same queries, shape and partials; each tier with its
 // own view and mask rule; `shares` + 1 slots).
-hipError_t launch_append_attn(int head_dim, const AppendArgs &first, const AppendArgs *second, const LineDev &line,
+hipError_t launch_append_attn(int dtype, int head_dim, const AppendArgs &first, const AppendArgs *second, const LineDev &line,
                               hipStream_t s);
 // the weights of one tier (second = nullptr) or of two (same queries and shape), as a line
-hipError_t launch_append_weights(int head_dim, const AppendArgs &first, const AppendArgs *second, const LineDev &line,
+hipError_t launch_append_weights(int dtype, int head_dim, const AppendArgs &first, const AppendArgs *second, const LineDev &line,
                                  hipStream_t s);
-// the same for fp32 inputs (q [B, N, Hq, d] fp32, fp32 tier): VALU pass, 64 tokens per workgroup
-hipError_t launch_append_weights_f32(int head_dim, const AppendArgs &a, hipStream_t s);
-
 // ---- KV manager over a block pool (mirrors hgca_cache_state; all pointers device memory) ----
 
 constexpr int32_t kCacheWindowFull = 1, kCacheContextFull = 2, kCacheListFull = 4;   // sticky bits of *status
