@@ -8,8 +8,13 @@ namespace hgca {
 
 namespace {
 
-// 16-byte loads per thread that make up the pre-filter's sample in the 512-thread workgroups (1: 2 048 scores, so
-// rows from 4 096 scores on are served; with 2 the ragged batch of 2048 rows is 3 us slower, the others the same)
+// 16-byte loads per thread that make up the pre-filter's sample: in the 1024-thread workgroups 2, 8 192 scores (8 before:
+// rows below 65 536 scores could not use the filter, and the sample cost more than the entries it kept out of the lists:
+// 256 rows of 122 880, k = 4096, 45.6 -> 41.7 us; with 1 or 4 loads 42.0 and 44.1); in the 512-thread workgroups 1, 2 048 scores (rows from 4 096 scores on
+// are served; with 2 the ragged batch of 2048 rows is 3 us slower, the others the same)
+#ifndef HGCA_SEL_LARGE_SAMPLE_LOADS
+#define HGCA_SEL_LARGE_SAMPLE_LOADS 2
+#endif
 #ifndef HGCA_SEL_SMALL_SAMPLE_LOADS
 #define HGCA_SEL_SMALL_SAMPLE_LOADS 1
 #endif
@@ -50,10 +55,16 @@ struct Binning {
 // scores NaN.  Infinite scores (a caller's masked positions, say) then fall into the end bins by clamping.
 __device__ __forceinline__ float finite_or(float s, float otherwise) { return fabsf(s) < INFINITY ? s : otherwise; }
 
-// Four consecutive scores starting at position t (a multiple of 4); positions at or beyond n read -inf.
-__device__ __forceinline__ float4 load4_padded(const float *sc, bool sc_vec, int t, int n)
+// Four consecutive scores starting at position t (a multiple of 4); positions at or beyond n read -inf.  A row starts
+// on any multiple of 4 bytes (the capacity may be odd), which is all a 16-byte load asks for: rows of 61 003 scores,
+// loaded score by score where the row was not 16-byte aligned, 40.4 -> 22.2 us together with the smaller sample.
+__device__ __forceinline__ float4 load4_padded(const float *sc, int t, int n)
 {
-    if (sc_vec && t + 3 < n) return *reinterpret_cast<const float4 *>(sc + t);
+    if (t + 3 < n) {
+        typedef float unaligned4 __attribute__((ext_vector_type(4), aligned(4)));
+        const unaligned4 v = *reinterpret_cast<const unaligned4 *>(sc + t);
+        return make_float4(v.x, v.y, v.z, v.w);
+    }
     float4 v = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
     if (t < n) v.x = sc[t];
     if (t + 1 < n) v.y = sc[t + 1];
@@ -170,7 +181,6 @@ struct Sel {
     template <bool CACHED>
     struct Row {
         const float *sc, *cache;
-        bool sc_vec;
         int n, seg;
         __device__ __forceinline__ int padded() const { return (n + seg - 1) / seg * seg; }
         __device__ __forceinline__ int steps() const {             // uniform over a wave
@@ -181,7 +191,7 @@ struct Sel {
         }
         __device__ __forceinline__ float4 at(int t) const {
             if (CACHED) return *reinterpret_cast<const float4 *>(cache + t);
-            return load4_padded(sc, sc_vec, min(t, (n + 3) / 4 * 4), n);    // clamp: far padding needs no address
+            return load4_padded(sc, min(t, (n + 3) / 4 * 4), n);    // clamp: far padding needs no address
         }
     };
 
@@ -197,7 +207,6 @@ struct Sel {
                                                                    int32_t *out, int n, int k, int64_t bh)
     {
         const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
-        const bool sc_vec = (a.kv.cap & 3) == 0;     // rows start 16-byte aligned
         const int seg = segment_length(n);
         const int padded = (n + seg - 1) / seg * seg;
         const int steps = w * seg < padded ? seg / kStep : 0;        // uniform over a wave
@@ -207,7 +216,7 @@ struct Sel {
 #pragma unroll
         for (int i = 0; i < STEPS; ++i) {
             v[i] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-            if (i < steps) v[i] = load4_padded(sc, sc_vec, min(pos0 + kStep * i, (n + 3) / 4 * 4), n);
+            if (i < steps) v[i] = load4_padded(sc, min(pos0 + kStep * i, (n + 3) / 4 * 4), n);
         }
         float mn = INFINITY, mx = -INFINITY;
 #pragma unroll
@@ -364,7 +373,7 @@ struct Sel {
     // score costs one compare, and nothing of the row but the retained entries is written anywhere.  The estimate
     // is only a filter: if fewer than k entries pass it, a wave's list overflows or the threshold bin is crowded,
     // the function returns false before it has written any output and the caller runs select_row.  `lists` is the workgroup's dynamic LDS (list_bytes of it).
-    // kSampleLoads 16-byte loads per thread make up the sample (8 for the large workgroups: 32 768 scores).
+    // kSampleLoads 16-byte loads per thread make up the sample.
     static constexpr int kSampleChunk = 256;                     // scores of one run of the sample: what a wave takes with one load
     template <int kSampleLoads>
     static __device__ __forceinline__ bool select_row_prefiltered(const SelectArgs &a, SelShared &sh, float *lists,
@@ -375,7 +384,6 @@ struct Sel {
         constexpr int kSample = kSampleChunks * kSampleChunk;
         static_assert(kSampleChunks >= 2, "the sample is spread over the row");
         const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
-        const bool sc_vec = (a.kv.cap & 3) == 0;     // rows start 16-byte aligned
         const int cap_w = list_bytes / (kSelWaves * 8);              // entries of one wave's list
         // the fraction of the row asked for, raised by six standard deviations of its estimate from the sample
         const float p = (float)k / (float)n;
@@ -390,7 +398,7 @@ struct Sel {
             const int j = u * kSelBlock + tid;                       // float4 of the sample
             const int c = j / (kSampleChunk / 4);
             const int start = (int)((int64_t)c * (n - kSampleChunk) / (kSampleChunks - 1)) & ~3;
-            v[u] = load4_padded(sc, sc_vec, start + 4 * (j % (kSampleChunk / 4)), n);
+            v[u] = load4_padded(sc, start + 4 * (j % (kSampleChunk / 4)), n);
         }
         float mn = INFINITY, mx = -INFINITY;
 #pragma unroll
@@ -442,7 +450,7 @@ struct Sel {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 r[u] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-                if (i0 + u < steps) r[u] = load4_padded(sc, sc_vec, min(pos0 + kStep * (i0 + u), (n + 3) / 4 * 4), n);
+                if (i0 + u < steps) r[u] = load4_padded(sc, min(pos0 + kStep * (i0 + u), (n + 3) / 4 * 4), n);
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -588,7 +596,6 @@ struct Sel {
         Row<CACHED> row;
         row.sc = sc;
         row.cache = cache;
-        row.sc_vec = (a.kv.cap & 3) == 0;            // rows start 16-byte aligned
         row.n = n;
         row.seg = segment_length(n);
         const int padded = row.padded();             // >= n, <= kSelWaves * seg
@@ -607,7 +614,7 @@ struct Sel {
                 float4 v[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u)
-                    v[u] = load4_padded(sc, row.sc_vec, 4 * min(base + u * kSelBlock + tid, n4 - 1), n);
+                    v[u] = load4_padded(sc, 4 * min(base + u * kSelBlock + tid, n4 - 1), n);
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const int i = base + u * kSelBlock + tid;
@@ -943,7 +950,7 @@ __device__ __forceinline__ void select_row_any(const SelectArgs &a, typename Sel
         if (S::template select_row_in_registers<(REG_STEPS > 0 ? REG_STEPS : 1)>(a, sh, sc, out, n, k, bh)) return;
         __syncthreads();                         // the general path starts over on the shared state
     } else if (list_bytes > 0 && S::padded_length(n) > cache_floats) {     // too long for LDS as fp32: pre-filter
-        if (S::template select_row_prefiltered<(BLOCK == kLargeBlock ? 8 : HGCA_SEL_SMALL_SAMPLE_LOADS)>(a, sh, cache, list_bytes, sc,
+        if (S::template select_row_prefiltered<(BLOCK == kLargeBlock ? HGCA_SEL_LARGE_SAMPLE_LOADS : HGCA_SEL_SMALL_SAMPLE_LOADS)>(a, sh, cache, list_bytes, sc,
                                                                                                        out, n, k, bh))
             return;
         __syncthreads();                         // the general path starts over on the shared state

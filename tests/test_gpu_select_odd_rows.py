@@ -1,0 +1,44 @@
+"""Selection on rows of odd capacity (a row then starts on any multiple of 4 bytes) and of the lengths at which the
+selection changes its way of holding a row: bit-exact against the oracle's selection on the same fp32 scores."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rows,cap,k", [(3, 16381, 700), (2, 33793, 1500), (4, 33795, 2000), (5, 61003, 2048), (2, 65537, 300),
+                                        (300, 4099, 200), (300, 14337, 700), (2, 135171, 4000)])
+def test_odd_capacities(oracle, rows, cap, k):
+    import torch
+    from paper_2507_03153_amd import hgca
+    rng = np.random.default_rng(cap + rows)
+    scores = (rng.standard_normal((1, rows, cap)) + 2.5 * (rng.random((1, rows, cap)) < 0.01)).astype(np.float32)
+    scores[0, 0] = np.round(scores[0, 0] * 8) / 8                # ties everywhere in one row
+    shape = hgca.Shape(hgca.F32, 1, rows, rows, 128, 1.0)
+    d = torch.from_numpy(scores).cuda()
+    idx = torch.full((1, rows, k), -7, dtype=torch.int32, device="cuda")
+    cnt, sel = torch.zeros(1, rows, dtype=torch.int32, device="cuda"), torch.zeros(1, rows, k, device="cuda")
+    hgca.select_topk(shape, d, None, cap, k, k, idx, cnt, sel_scores_out=sel)
+    torch.cuda.synchronize()
+    want, want_cnt = oracle.select_given(scores, k, k)
+    assert np.array_equal(cnt.cpu().numpy(), want_cnt) and np.array_equal(idx.cpu().numpy(), want)
+    assert np.array_equal(sel.cpu().numpy(), np.take_along_axis(scores, want.astype(np.int64), axis=2))
+
+
+@pytest.mark.parametrize("cap", [1021, 2054, 131])
+def test_scores_of_odd_capacities(oracle, cap):
+    """The score pass writes whole rows of an odd capacity: every score, nothing behind them."""
+    import torch
+    from paper_2507_03153_amd import hgca
+    B, Hq, Hkv, d = 2, 8, 2, 128
+    g = torch.Generator().manual_seed(cap)
+    q = torch.randn(B, Hq, d, generator=g).to(torch.bfloat16)
+    k = torch.randn(B, Hkv, cap, d, generator=g).to(torch.bfloat16)
+    shape = hgca.Shape(hgca.BF16, B, Hq, Hkv, d, d ** -0.5)
+    out = torch.full((B * Hq * cap + 64,), -9.0, device="cuda")
+    hgca.pool_scores(shape, q.cuda(), hgca.Tier(k.cuda(), None, cap), out)
+    torch.cuda.synchronize()
+    want = torch.einsum("bghd,bgtd->bght", q.double().view(B, Hkv, Hq // Hkv, d), k.double()) * d ** -0.5
+    got = out.cpu()
+    assert torch.all(got[B * Hq * cap:] == -9.0)
+    assert float((got[:B * Hq * cap].double().view(B, Hkv, Hq // Hkv, cap) - want).abs().max()) <= 1e-5
