@@ -517,10 +517,9 @@ int hgca_ctx_compact(const hgca_shape *shape, const hgca_kv_view *pool,
                      int32_t ctx_cap, int32_t *cnt_out, void *hip_stream);
 
 /* ---- Append stage (Sec. 2.1: N incoming tokens, Q in R^{h x N x d}; Alg. 2,
- * append branch).  bf16 inputs run both contractions on the matrix cores;
- * fp32 inputs (the exact shapes) run on the vector units: every (sequence,
- * query) pair is then a one-query attention over the tokens that query sees,
- * served by the split kernels of the decode path (B * n_q <= 65 535). ----
+ * append branch).  Both contractions run on the matrix cores: bf16 inputs on
+ * the bf16 instructions, fp32 inputs (the exact shapes; B * n_q <= 65 535) on
+ * the fp32 ones, products and sums in fp32 throughout. ----
  *
  * q is [B, N, Hq, d].  Attention of all N queries over one tier; the two parts
  * of the hybrid step are two calls (the window with HGCA_APPEND_CAUSAL_TAIL,
@@ -556,9 +555,9 @@ int hgca_append_attn(const hgca_shape *shape, const void *q, int32_t n_q,
  * window) and over the COMPLETE older pool, merged per (sequence, query, head)
  * with merge_state.  The same results as hgca_append_attn on each tier and
  * hgca_lse_merge (up to the order of fp32 additions), in two launches instead
- * of five: the splits of both tiers share one launch and one split size, and
- * one fold of all split partials yields the merged output together with each
- * tier's own log-sum-exp.  o_out fp32 [B, N, Hq, d], lse_out fp32 [B, N, Hq];
+ * of five: pool and window are one line of tokens that the workgroups of one
+ * launch share evenly, and one fold of all partials yields the merged output
+ * together with each tier's own log-sum-exp.  o_out fp32 [B, N, Hq, d], lse_out fp32 [B, N, Hq];
  * lse_window_out / lse_pool_out (fp32 [B, N, Hq], optional) receive the
  * per-tier lse that hgca_append_weights normalises with.  bf16 inputs only
  * (HGCA_ERR_UNSUPPORTED for fp32: use the per-tier calls).  ws needs
