@@ -375,6 +375,25 @@ struct Sel {
     // the function returns false before it has written any output and the caller runs select_row.  `lists` is the workgroup's dynamic LDS (list_bytes of it).
     // kSampleLoads 16-byte loads per thread make up the sample.
     static constexpr int kSampleChunk = 256;                     // scores of one run of the sample: what a wave takes with one load
+
+    // The fraction of a row the pre-filter asks for, raised by six standard deviations of its estimate from the sample.
+    template <int kSampleLoads>
+    static __device__ __forceinline__ float prefilter_fraction(int n, int k)
+    {
+        constexpr float kSample = (float)(kSelBlock * kSampleLoads * 4);
+        const float p = (float)k / (float)n;
+        return p + 6.f * sqrtf(p / kSample) + 8.f / kSample;
+    }
+
+    // Not worth it (or no room) unless the retained entries are few: uniform over the workgroup.
+    template <int kSampleLoads>
+    static __device__ __forceinline__ bool prefilter_fits(int n, int k, int list_bytes)
+    {
+        const int room = list_bytes / (kSelWaves * 8) * kSelWaves;
+        const float p_est = prefilter_fraction<kSampleLoads>(n, k);
+        return n >= 2 * kSelBlock * kSampleLoads * 4 && p_est * (float)n * 1.25f <= (float)room && p_est <= 0.2f;
+    }
+
     template <int kSampleLoads>
     static __device__ __forceinline__ bool select_row_prefiltered(const SelectArgs &a, SelShared &sh, float *lists,
                                                                   int list_bytes, const float *sc, int32_t *out, int n,
@@ -385,11 +404,7 @@ struct Sel {
         static_assert(kSampleChunks >= 2, "the sample is spread over the row");
         const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
         const int cap_w = list_bytes / (kSelWaves * 8);              // entries of one wave's list
-        // the fraction of the row asked for, raised by six standard deviations of its estimate from the sample
-        const float p = (float)k / (float)n;
-        const float p_est = p + 6.f * sqrtf(p / (float)kSample) + 8.f / (float)kSample;
-        // not worth it (or no room) unless the retained entries are few: uniform over the workgroup
-        if (n < 2 * kSample || p_est * (float)n * 1.25f > (float)(cap_w * kSelWaves) || p_est > 0.2f) return false;
+        const float p_est = prefilter_fraction<kSampleLoads>(n, k);
 
         // ---- the sample: range, histogram, the estimate ---------------------------------------------------
         float4 v[kSampleLoads];
@@ -950,10 +965,17 @@ __device__ __forceinline__ void select_row_any(const SelectArgs &a, typename Sel
         if (S::template select_row_in_registers<(REG_STEPS > 0 ? REG_STEPS : 1)>(a, sh, sc, out, n, k, bh)) return;
         __syncthreads();                         // the general path starts over on the shared state
     } else if (list_bytes > 0 && S::padded_length(n) > cache_floats) {     // too long for LDS as fp32: pre-filter
-        if (S::template select_row_prefiltered<(BLOCK == kLargeBlock ? HGCA_SEL_LARGE_SAMPLE_LOADS : HGCA_SEL_SMALL_SAMPLE_LOADS)>(a, sh, cache, list_bytes, sc,
-                                                                                                       out, n, k, bh))
-            return;
-        __syncthreads();                         // the general path starts over on the shared state
+        // A row with many of its entries asked for may fit the lists only with a larger sample's tighter estimate:
+        // 24 rows of 101 388, k = 12 163, hold 14 593 entries with 8 192 samples and 13 348 with 32 768, room 13 516.
+        constexpr int kLoads = BLOCK == kLargeBlock ? HGCA_SEL_LARGE_SAMPLE_LOADS : HGCA_SEL_SMALL_SAMPLE_LOADS;
+        constexpr int kMoreLoads = BLOCK == kLargeBlock ? 4 * kLoads : kLoads;
+        if (S::template prefilter_fits<kLoads>(n, k, list_bytes)) {
+            if (S::template select_row_prefiltered<kLoads>(a, sh, cache, list_bytes, sc, out, n, k, bh)) return;
+            __syncthreads();                     // the general path starts over on the shared state
+        } else if (kMoreLoads > kLoads && S::template prefilter_fits<kMoreLoads>(n, k, list_bytes)) {
+            if (S::template select_row_prefiltered<kMoreLoads>(a, sh, cache, list_bytes, sc, out, n, k, bh)) return;
+            __syncthreads();
+        }
     }
     if (S::padded_length(n) <= cache_floats) S::template select_row<kCachedScores>(a, sh, cache, sc, out, n, k, bh);
     else if (S::padded_length(n) <= cache_bytes) S::template select_row<kCachedBins>(a, sh, cache, sc, out, n, k, bh);

@@ -7,7 +7,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("rows,cap,k", [(3, 16381, 700), (2, 33793, 1500), (4, 33795, 2000), (5, 61003, 2048), (2, 65537, 300),
-                                        (300, 4099, 200), (300, 14337, 700), (2, 135171, 4000)])
+                                        (300, 4099, 200), (300, 14337, 700), (2, 135171, 4000),
+                                        # only the larger sample leaves room for them in the lists, or is sure enough
+                                        (3, 101388, 12163), (2, 65537, 12000)])
 def test_odd_capacities(oracle, rows, cap, k):
     import torch
     from paper_2507_03153_amd import hgca
