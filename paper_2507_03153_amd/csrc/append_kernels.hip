@@ -252,7 +252,7 @@ __device__ __forceinline__ float minus_half(uint32_t pair, uint32_t minus_one_at
 //   - a load instruction's address is a scalar plus a constant offset of the lane (dma_step);
 //   about 6 vector instructions per score where the kernel with 16-row tiles took 13.
 // With the line below, 2 x 509 queries x 32 K tokens x 32 heads: 930 -> 765 us (715 TFLOP/s, 1.07 PFLOP/s executed);
-// 8 x 32 queries x 32 K tokens: 266 -> 250 us, bound by the K/V rows; 48 queries, groups of 8, one part: 320 -> 250 us.
+// 8 x 32 queries x 32 K tokens: 265 us before and after (bound by the K/V rows in flight); 48 queries, groups of 8, one part: 320 -> 250 us.
 //
 // A launch may serve TWO tiers (the complete pool and the window of an append turn: Alg. 2 runs the two attentions side
 // by side) as one line of tokens cut into equal shares (LineDev): a workgroup goes through its part of the first tier

@@ -37,8 +37,8 @@ constexpr size_t kAlign = 256;
 
 // Workgroups the append-stage attention aims at per launch: what the device holds at once (two per compute unit).
 // Every workgroup writes a partial of 128 rows x d floats (64 KB, read again by the fold: the K/V bytes of four
-// 64-token steps), so splits are as long as filling the device allows.  Measured on the 8B shape, N = 32, with
-// 512 / 768 / 1024 / 1536: window 55.7 / 61.0 / 66.0 / 74.8 us, pool 258.5 / 273.4 / 266.6 / 288.1 us.
+// 64-token steps), so splits are as long as filling the device allows.  Measured on the 8B shape, N = 32 (by a kernel
+// with 16-row tiles), with 512 / 768 / 1024 / 1536: window 55.7 / 61.0 / 66.0 / 74.8 us, pool 258.5 / 273.4 / 266.6 / 288.1 us.
 #ifndef HGCA_APPEND_TARGET_WGS
 #define HGCA_APPEND_TARGET_WGS 512
 #endif
@@ -539,8 +539,10 @@ int hgca_sparse_attn_grouped(const hgca_shape *shape, const void *q, const hgca_
     // Deferred, the split size is hgca_sparse_attn's (hgca_lse_merge_splits derives the split count from k_max alone).
     // Folded here, there are a group's times fewer lists and workgroups, so the splits are that much shorter (64 lists
     // of 2 048 entries for groups of 4: 27.0 -> 22.6 us with 1024 workgroups; with 2048, two partials per 64 rows, 26.6).
-    a.chunk = pick_chunk(k_max, (int64_t)shape->batch * (deferred ? shape->n_q_heads : shape->n_kv_heads),
-                         deferred ? HGCA_TARGET_WGS_SPARSE : HGCA_TARGET_WGS_GROUPED);
+    // Without groups there are as many lists as heads, and nothing to shorten.
+    const bool own_split = !deferred && shape->n_q_heads > shape->n_kv_heads;
+    a.chunk = pick_chunk(k_max, (int64_t)shape->batch * (own_split ? shape->n_kv_heads : shape->n_q_heads),
+                         own_split ? HGCA_TARGET_WGS_GROUPED : HGCA_TARGET_WGS_SPARSE);
     a.part = partials_at(ws, w, std::max(1, n_splits_for(k_max, a.chunk)));
     const int64_t rows = (int64_t)shape->batch * shape->n_q_heads;
     if ((rc = from_hip(launch_attn_partial_gather(shape->dtype, shape->head_dim, a, s))) != HGCA_OK) return rc;
