@@ -537,7 +537,10 @@ int hgca_ctx_compact(const hgca_shape *shape, const hgca_kv_view *pool,
  * stay fp32 throughout.)
  * Other bits are rejected.  shape.sm_scale must be positive and finite for the
  * append entry points.  o_out is fp32 [B, N, Hq, d], lse_out fp32
- * [B, N, Hq]; a query that sees nothing gives O = 0, lse = -inf.  ws needs
+ * [B, N, Hq]; a query that sees nothing gives O = 0, lse = -inf.  In fp32 a
+ * row that a query does not see has no part in its O, whatever the row holds;
+ * in bf16 the V rows of a tier's valid tokens have to be finite (an infinity or
+ * NaN in one may reach earlier queries too).  ws needs
  * hgca_append_workspace_bytes(shape, n_q, tier->cap) bytes.  n_q <= 4096. */
 enum {
     HGCA_APPEND_CAUSAL_TAIL = 1,

@@ -240,6 +240,46 @@ __device__ __forceinline__ float minus_half(uint32_t pair, uint32_t minus_one_at
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), __builtin_bit_cast(bf16x2, minus_one_at), p, false);
 }
 
+// The sums of a wave's rows over the tier positions [begin, end) -- of a row only [begin, row_end) -- on the vector
+// units, one token after the other.  As in the kernel below, the two halves of a wave hold the even and the odd 16-byte
+// pieces of their row's query and the output columns 32 dt + 8 (i / 4) + 4 hw + i % 4; all lanes of the wave take part.
+template <int D>
+__device__ __forceinline__ void append_sums_again(const KvDev &kv, int n_kv_heads, int b, int kvh, int begin, int row_end,
+                                                  int end, const uint4 (&q)[D / 8], int hw, float m0, float scale2,
+                                                  floatx16 (&acc)[D / 32])
+{
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt) acc[dt] = floatx16{};
+    const int32_t *blocks = kv.block_table ? kv.block_table + (int64_t)b * kv.max_blocks + (kv.first_block ? kv.first_block[b] : 0)
+                                           : nullptr;
+#pragma unroll 1
+    for (int tok = begin; tok < end; ++tok) {
+        const int64_t row = blocks ? ((int64_t)blocks[tok / kv.block_size] * n_kv_heads + kvh) * kv.block_size + tok % kv.block_size
+                                   : ((int64_t)b * n_kv_heads + kvh) * kv.cap + tok;
+        const char *k = kv.k + row * (D * 4), *v = kv.v + row * (D * 4) + 16 * hw;
+        float s = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < D / 8; ++kk) {
+            const float4 x = *reinterpret_cast<const float4 *>(k + 16 * (2 * kk + hw));
+            const floatx4 y = __builtin_bit_cast(floatx4, q[kk]);
+            s = fmaf(x.w, y[3], fmaf(x.z, y[2], fmaf(x.y, y[1], fmaf(x.x, y[0], s))));
+        }
+        s = halves_sum(s);
+        if (tok >= row_end) continue;
+        const float p = __builtin_amdgcn_exp2f((s - m0) * scale2);
+#pragma unroll
+        for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const float4 x = *reinterpret_cast<const float4 *>(v + 128 * dt + 32 * q4);
+                acc[dt][4 * q4] = fmaf(p, x.x, acc[dt][4 * q4]);
+                acc[dt][4 * q4 + 1] = fmaf(p, x.y, acc[dt][4 * q4 + 1]);
+                acc[dt][4 * q4 + 2] = fmaf(p, x.z, acc[dt][4 * q4 + 2]);
+                acc[dt][4 * q4 + 3] = fmaf(p, x.w, acc[dt][4 * q4 + 3]);
+            }
+    }
+}
+
 // A workgroup: four waves of 32 query rows over one share of the tokens of one (sequence, KV head).  The scores come
 // from v_mfma_f32_32x32x16_bf16, whose result gives a lane 16 scores of ONE row per 32 tokens (the other 16 are the
 // lane's partner's, 32 lanes away), so a step's softmax is one chain per lane over 32 scores.  What the pass follows is
@@ -503,6 +543,24 @@ __global__ __launch_bounds__(kAttnBlock, sizeof(T) == 2 ? 2 : 1) void append_att
                 step(s2, s_k0, s_v0, s_k1, s_v1);
                 if (s2 + 1 < steps) step(s2 + 1, s_k1, s_v1, s_k0, s_v0);
             }
+        }
+
+        // A weight of 0 keeps a V row out of the products above only while the row is finite (0 * inf is NaN).  Where that
+        // may have happened -- steps with tokens that some rows do not see, and sums that are not finite -- the wave forms its
+        // sums again on the vector units, every row from what it sees and nothing else (m and l do not depend on V).  In bf16 the
+        // V rows of every token of a tier have to be finite.
+        if constexpr (F32) {
+            bool again = false;
+            if (wave_live && (nt_total % kStepTokens != 0 || vis_min < t0 + nt_total)) {         // uniform over the wave
+                bool finite = true;
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) finite &= fabsf(acc[dt][i]) < INFINITY;
+                again = __any(!finite);
+            }
+            if (again) append_sums_again<D>(kv, a1.sh.n_kv_heads, b, kvh, t0, min(t0 + nt_total, vis), t0 + nt_total, qop, hw,
+                                            m == -INFINITY ? 0.f : m, scale2, acc);
         }
 
         // partial of every valid row: the lane holds output columns 32 dt + 8 q + 4 hw .. + 3 of its row

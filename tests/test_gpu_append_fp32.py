@@ -1,0 +1,66 @@
+"""fp32 append stage on the matrix instructions, against a 64-bit reference that gives every query exactly the tokens
+it sees."""
+import numpy as np
+import pytest
+
+from test_gpu_append import gpu, to_paged  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def reference(q, K, V, lens, scale, causal):
+    """O and lse in 64 bits, each query over the rows it sees and no others (a row holding inf or NaN then reaches the
+    queries that see it and no others)."""
+    B, N, Hq, d = q.shape
+    G = Hq // K.shape[1]
+    o, lse = np.zeros((B, N, Hq, d)), np.full((B, N, Hq), -np.inf)
+    for b in range(B):
+        for i in range(N):
+            n = max(int(lens[b]) - N + i + 1, 0) if causal else int(lens[b])
+            for h in range(Hq):
+                if n == 0:
+                    continue
+                k, v = K[b, h // G, :n].astype(np.float64), V[b, h // G, :n].astype(np.float64)
+                s = (k @ q[b, i, h].astype(np.float64)) * scale
+                p = np.exp(s - s.max())
+                lse[b, i, h] = s.max() + np.log(p.sum())
+                with np.errstate(invalid="ignore"):
+                    o[b, i, h] = (p[:, None] * v).sum(0) / p.sum()
+    return o, lse
+
+
+@pytest.mark.parametrize("causal", [True, False], ids=["causal", "whole"])
+@pytest.mark.parametrize("kw", [
+    dict(B=2, N=40, Hq=8, Hkv=2, d=128, cap=203, lens=(203, 70)),            # two blocks of rows, steps cut by the length
+    dict(B=2, N=20, Hq=4, Hkv=4, d=64, cap=128, lens=(128, 65)),
+    dict(B=1, N=33, Hq=8, Hkv=1, d=128, cap=192, lens=(192,), paged=True),
+], ids=["gqa4", "mha_d64", "gqa8_paged"])
+def test_rows_a_query_does_not_see_may_hold_anything(gpu, kw, causal):  # noqa: F811
+    """Infinities and NaNs in V rows behind a query's causal limit, and in the last row of a tier whose length is no
+    whole number of steps: O of a query is what its own rows give."""
+    torch, hgca, runner = gpu
+    B, N, Hq, Hkv, d, cap, lens = (kw[x] for x in ("B", "N", "Hq", "Hkv", "d", "cap", "lens"))
+    lens = np.array(lens, np.int32)
+    rng = np.random.default_rng(3)
+    q, K, V = (rng.standard_normal(s).astype(np.float32) for s in ((B, N, Hq, d), (B, Hkv, cap, d), (B, Hkv, cap, d)))
+    for b, n in enumerate(lens):
+        V[b, :, n - 1, ::2] = np.inf                             # seen by the last query only, where causal
+        V[b, 0, n - 3, 1::4] = np.nan
+        V[b, -1, n - N // 2, :5] = -np.inf
+        V[b, :, n:] = np.nan                                     # behind the end: nobody's
+        K[b, :, n:] = np.nan
+    g = lambda a: runner._to_gpu(a, "cuda:0")
+    shape = hgca.Shape(hgca.F32, B, Hq, Hkv, d, d ** -0.5)
+    tier = to_paged(runner, hgca, torch, K, V, lens, cap, 16, 4, "cuda:0") if kw.get("paged") else \
+        hgca.Tier(g(K), g(V), cap, g(lens))
+    o, lse = torch.zeros(B, N, Hq, d, device="cuda:0"), torch.zeros(B, N, Hq, device="cuda:0")
+    hgca.append_attn(shape, g(q), tier, causal, o, lse, hgca.append_workspace(shape, N, cap, "cuda:0"))
+    torch.cuda.synchronize()
+    o_ref, l_ref = reference(q, K, V, lens, d ** -0.5, causal)
+    o, lse = o.cpu().numpy().astype(np.float64), lse.cpu().numpy().astype(np.float64)
+    assert np.max(np.abs(lse - l_ref)) <= 1e-5
+    finite = np.isfinite(o_ref)
+    assert finite.any() and not finite.all()
+    assert np.array_equal(np.isfinite(o), finite), f"{np.sum(np.isfinite(o) != finite)} of {o.size} outputs differ in kind"
+    assert np.array_equal(np.isnan(o), np.isnan(o_ref)) and np.array_equal(o[np.isinf(o_ref)], o_ref[np.isinf(o_ref)])
+    assert np.max(np.abs(o[finite] - o_ref[finite])) <= 1e-5
