@@ -436,8 +436,11 @@ __global__ __launch_bounds__(kAttnBlock, sizeof(T) == 2 ? 2 : 1) void append_att
             if (__any(mx > m)) {                     // uniform over the wave
                 const float m_new = fmaxf(m, halves_max(mx));
                 // a row that has seen nothing yet keeps m = -inf: shift by 0 then, every exponent is -inf and gives 0
-                shift = (m_new == -INFINITY) ? 0.f : -m_new * scale2;
-                const float corr = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(F32 ? (m - m_new) * scale2 : fmaf(m, scale2, shift));
+                const float shift_new = (m_new == -INFINITY) ? 0.f : -m_new * scale2;
+                // exactly 1 for a row whose maximum stands, however many other rows of the wave find new ones: in bf16 the
+                // difference of the two shifts as the weights have them (rounded), in fp32 they are not used
+                const float corr = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(F32 ? (m - m_new) * scale2 : shift_new - shift);
+                shift = shift_new;
                 m = m_new;
                 l *= corr;
 #pragma unroll
