@@ -630,8 +630,7 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 512 : 256, sizeof(T) == 2 ? 2 : 1)
     __shared__ __attribute__((aligned(16))) float s_shift[kRowsPerBlock];        // minus the rows' lse, in the exponent's unit
     __shared__ uint32_t s_row[kSub];
 
-    const int wg = (int)blockIdx.x;
-    const int share = wg % line.shares, kvh = wg / line.shares % a1.sh.n_kv_heads, b = wg / line.shares / a1.sh.n_kv_heads;
+    const int share = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
     const int tid = threadIdx.x, lane = tid % kWave, w = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int n = lane % 32, hw = lane / 32;
     const int n_rows = a1.n_q * G, n_qb = (n_rows + kRowsPerBlock - 1) / kRowsPerBlock;
@@ -894,9 +893,8 @@ hipError_t launch_append_weights(int dtype, int head_dim, const AppendArgs &a, c
     if (line.shares <= 0 || a2.n_q != a.n_q || a2.q != a.q || a2.sh.group != a.sh.group || a2.sh.batch != a.sh.batch ||
         a2.sh.n_kv_heads != a.sh.n_kv_heads)
         return hipErrorInvalidValue;             // the two tiers share the queries and the launch shape
-    const int64_t blocks = (int64_t)line.shares * a.sh.n_kv_heads * a.sh.batch;
-    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)blocks);
+    // (a flat grid would be short of numbers: its threads are counted in 32 bits per dimension)
+    const dim3 grid(line.shares, a.sh.n_kv_heads, a.sh.batch);
     const int two = second ? 1 : 0;
     if (dtype == 0 && head_dim == 64) return launch_weights_group<float, 64>(a, a2, line, two, grid, s);
     if (dtype == 0 && head_dim == 128) return launch_weights_group<float, 128>(a, a2, line, two, grid, s);

@@ -391,3 +391,17 @@ def test_reevaluation_threshold_on_a_cpu(gpu, oracle):
     say(f"    kept per head {cnt_ref.min()}..{cnt_ref.max()} of {p_lens.tolist()}; decided differently inside the "
         f"rounding band: {differing}")
     assert 0 < cnt_ref.min() and cnt_ref.max() < p_lens.min()
+
+
+def test_append_weights_of_as_many_heads_as_the_shape_allows(gpu):
+    """65 535 sequences x 256 KV heads of one token each: more (sequence, KV head) pairs than a flat launch of 512-thread
+    workgroups can number (2^23)."""
+    torch, hgca, runner = gpu
+    B, H, d = 65535, 256, 64
+    say(f"\n[case] append weights B={B} Hq={H} Hkv={H} d={d}, one token each")
+    k = torch.zeros(B, H, 1, d, dtype=torch.bfloat16, device="cuda:0")
+    q, lse = k.view(B, 1, H, d), torch.zeros(B, 1, H, device="cuda:0")
+    a = torch.full((B, H, 1), float("nan"), device="cuda:0")
+    hgca.append_weights(hgca.Shape(hgca.BF16, B, H, H, d, 1.0), q, hgca.Tier(k, None, 1), False, lse, a)
+    torch.cuda.synchronize()
+    assert bool((a == 1.0).all())
