@@ -593,15 +593,22 @@ __global__ __launch_bounds__(kAttnBlock, sizeof(T) == 2 ? 2 : 1) void append_att
 // workgroup, a tile's K rows arrive by LDS-direct loads in a slot that only its wave reads, go to registers as the B
 // operand, and the slot takes the next tile at once -- no barrier and no sums through LDS in the loop.  Window and pool
 // are one line of equal shares, as in the attention kernel, so that the launch is one full round of workgroups however
-// the two lengths compare.  With more than 128 rows a share goes through blocks of 512 tokens, every block once per 128
-// rows (it stays in the caches meanwhile), adding to a_out.
-// 8 x 32 queries on 32 K tokens, 32 / 8 heads: 185 -> 126 us.  The loads alone take 101 us (124 us without the
-// streaming policy; more of them in flight, 12 or 15 waves, change nothing), the arithmetic alone 115 us.  The previous
-// kernel (tokens in registers, rows over the lanes) spent two lane exchanges per score and a barrier per 64 tokens,
-// and its 2048-token workgroups came out at 1.2 rounds.
+// the two lengths compare.  With more than 128 rows a share goes through blocks of 2048 tokens, every block once per 128
+// rows (it stays in the caches meanwhile), adding to a_out: 33 / 64 / 128 queries x 4 heads on 28 K tokens, batch 8:
+// 244 / 262 / 505 us with blocks of 512 tokens, two tiles per wave between barriers; 195 / 221 / 432 us.
+//
+// The number of rows may be any: a row that does not exist weighs nothing through its shift, so only tiles that the causal
+// limit cuts compare, a compare and a select per score (with a test per score in every block that is not full, 31 queries
+// x 4 heads took 147 us where 32 took 105; now 101 and 101).
+// Both tiers of 8 x 32 queries on 32 K tokens, 32 / 8 heads: 150 us (tokens in registers, rows over the lanes: two lane
+// exchanges per score and a barrier per 64 tokens, 2048-token workgroups that came out at 1.2 rounds) -> 117 us.  The
+// loads alone take 101 us (124 us without the streaming policy; more of them in flight, 12 or 15 waves, change nothing).
+// A launch over few tokens is a chain of latencies: K is requested before the queries, and a share with fewer tiles than
+// waves deals a tile's rows to several waves, which add up through LDS (100 queries over 512 tokens 8.2 -> 4.8 us, 16
+// queries x 4 heads over 3.5 K tokens 6.8 -> 5.4; workgroups of 64 tokens with a row tile per wave: 4.7 and 4.6).
 //
 // fp32 inputs: the same with v_mfma_f32_32x32x2_f32, four waves (queries and slots take 128 KB).  2 x 24 queries on 5 K
-// tokens: 158 us on the vector units, one tier per launch -> 46 us.
+// tokens: 137 us on the vector units, one tier per launch -> 36 us.
 constexpr int kWTile = 32;
 template <typename T, int D> struct WeightsStage {
     static constexpr int kWaves = sizeof(T) == 2 ? 8 : 4, kBlock = kWaves * kWave;
@@ -610,17 +617,22 @@ template <typename T, int D> struct WeightsStage {
     static __device__ __forceinline__ int swizzle(int row) { return (row / (16 / kSwizzled)) % kSwizzled; }
     static __device__ __forceinline__ int offset(int row, int piece) { return row * kRowBytes + 16 * (piece ^ swizzle(row)); }
 };
+#ifndef WMANY
+#define WMANY 512
+#define WPOL 2
+#endif
 constexpr int kNonTemporal = 2;                  // cache policy of a load: streamed once
-constexpr int kWManyRowTokens = 512;             // tokens of a block that more than one pass over the rows goes through
+constexpr int kWManyRowTokens = 2048;            // tokens of a block that more than one pass over the rows goes through
 
-template <typename T, int D, int G>
+template <typename T, int D, int G, bool TWO>
 __global__ __launch_bounds__(sizeof(T) == 2 ? 512 : 256, sizeof(T) == 2 ? 2 : 1) void append_weights_kernel(
-    AppendArgs a1, AppendArgs a2, LineDev line, int two_tiers)
+    AppendArgs a1, AppendArgs a2, LineDev line, int streamed)
 {
     using S = WeightsStage<T, D>;
     static_assert(S::kBlock == (sizeof(T) == 2 ? 512 : 256), "the launch bounds above");
     constexpr int kWWaves = S::kWaves, kWBlock = S::kBlock;
     constexpr bool F32 = sizeof(T) == 4;
+    constexpr int kSpreadLive = F32 ? 2 : 3;     // row tiles from which dealing them out to idle waves pays
     constexpr int KK = S::kRowBytes / 32, RT = kRowsPerBlock / 32, NS = G < 4 ? G : 4;
     constexpr float kLog2e = 1.4426950408889634f;
     typedef const __attribute__((address_space(1))) void *GlobalPtr;
@@ -641,30 +653,23 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 512 : 256, sizeof(T) == 2 ? 2 : 1)
 
     const LineCut cut(line, b);
     int q_held = -1;                             // block of rows that s_q holds
-#pragma unroll 1
-    for (int tier = 0; tier < 2; ++tier) {
-        if (tier && !two_tiers) break;
-        KvDev kv{};                              // field by field: a choice between the structs as a whole would go through scratch memory
-        kv.k = tier ? a2.kv.k : a1.kv.k;
-        kv.seq_lens = tier ? a2.kv.seq_lens : a1.kv.seq_lens;
-        kv.block_table = tier ? a2.kv.block_table : a1.kv.block_table;
-        kv.first_block = tier ? a2.kv.first_block : a1.kv.first_block;
-        kv.cap = tier ? a2.kv.cap : a1.kv.cap;
-        kv.block_size = tier ? a2.kv.block_size : a1.kv.block_size;
-        kv.max_blocks = tier ? a2.kv.max_blocks : a1.kv.max_blocks;
-        const int causal_tail = tier ? a2.causal_tail : a1.causal_tail;
-        const float *lse = tier ? a2.lse : a1.lse;
+    // one tier's part of the share; first_step: where the tier begins on the line.  (A loop over the tiers that chose
+    // every argument by its counter took 0.7 us more of a launch with one.)
+    auto serve = [&](const AppendArgs &a, int first_step) {
+        const KvDev &kv = a.kv;
+        const int causal_tail = a.causal_tail;
+        const float *lse = a.lse;
         const int len = tier_len(kv, b);
-        float *out = (tier ? a2.a_out : a1.a_out) + ((int64_t)b * a1.sh.n_q_heads + kvh * G) * kv.cap;
+        float *out = a.a_out + ((int64_t)b * a1.sh.n_q_heads + kvh * G) * kv.cap;
 
         // entries beyond the sequence's length, shared out as well
         for (int g = 0; g < G; ++g)
             for (int j = len + share * kWBlock + tid; j < kv.cap; j += line.shares * kWBlock) out[(int64_t)g * kv.cap + j] = 0.f;
 
-        const int first_step = tier ? cut.first_steps : 0, begin = share * cut.share_steps;
+        const int begin = share * cut.share_steps;
         const int t0 = max(begin - first_step, 0) * kStepTokens;
         const int t_end = min(max(begin + cut.share_steps - first_step, 0) * kStepTokens, len);
-        if (t0 >= t_end) continue;               // nothing of this tier in the share (uniform over the workgroup)
+        if (t0 >= t_end) return;                 // nothing of this tier in the share (uniform over the workgroup)
         const int pass_len = min(pass_length(kv, t_end - t0), n_qb > 1 ? kWManyRowTokens : INT32_MAX);
         for (int p0 = t0; p0 < t_end; p0 += pass_len) {
             const int nt = min(pass_len, t_end - p0), tiles = (nt + kWTile - 1) / kWTile;
@@ -689,7 +694,10 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 512 : 256, sizeof(T) == 2 ? 2 : 1)
                         const int row = u * S::kGroupRows;       // of the tile
                         const uint32_t off = r * S::kRowBytes + 16 * ((lane % S::kPieces) ^ S::swizzle(row % 16 + r));
                         const char *src = kv.k + (size_t)(base[row / kGranule] + row % kGranule) * S::kRowBytes;
-                        __builtin_amdgcn_global_load_lds((GlobalPtr)(src + off), (LdsPtr)(slot + u * 1024), 16, 0, kNonTemporal);
+                        if (streamed)            // uniform over the launch (the policy is part of the instruction)
+                            __builtin_amdgcn_global_load_lds((GlobalPtr)(src + off), (LdsPtr)(slot + u * 1024), 16, 0, kNonTemporal);
+                        else
+                            __builtin_amdgcn_global_load_lds((GlobalPtr)(src + off), (LdsPtr)(slot + u * 1024), 16, 0, 0);
                     }
                 } else {                                         // tokens behind the end read the last row
                     uint32_t at[LOADS];
@@ -708,10 +716,18 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 512 : 256, sizeof(T) == 2 ? 2 : 1)
             };
             for (int qb = 0; qb < n_qb; ++qb) {
                 __syncthreads();                 // the queries and shifts of the previous round are no longer in use
+                const int live = (min(n_rows - qb * kRowsPerBlock, kRowsPerBlock) + 31) / 32;        // 32-row tiles with rows that exist
+                // a block with fewer tiles than there are waves: several waves take a tile's rows in turn and add up at the end
+                const int spread_bits = live < kSpreadLive ? 0 : 4 * tiles <= kWWaves ? 2 : 2 * tiles <= kWWaves ? 1 : 0;
+                const int spread = 1 << spread_bits, part = w % spread, tile_first = w >> spread_bits, tile_step = kWWaves >> spread_bits;
+                if (tile_first < tiles) request(tile_first);     // first: it has the longest way
+                // rows that do not exist repeat the last query of their head with a shift of -inf: they weigh nothing, and
+                // what a non-finite key gives them it gives an existing row of that head too
+                auto existing = [&](int r) { return r < n_rows ? r : n_rows - G + r % G; };
                 if (q_held != qb) {              // uniform over the workgroup
                     for (int g = w; g < kRowsPerBlock / S::kGroupRows; g += kWWaves) {
                         const int row = g * S::kGroupRows + lane / S::kPieces;
-                        const RowInfo ri = row_info<G>(a1, b, kvh, min(qb * kRowsPerBlock + row, n_rows - 1));
+                        const RowInfo ri = row_info<G>(a1, b, kvh, existing(qb * kRowsPerBlock + row));
                         const char *src = static_cast<const char *>(a1.q) + ri.out_row * S::kRowBytes +
                                           16 * ((lane % S::kPieces) ^ S::swizzle(row));
                         __builtin_amdgcn_global_load_lds((GlobalPtr)src, (LdsPtr)(s_q + g * 1024), 16, 0, 0);
@@ -720,18 +736,16 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 512 : 256, sizeof(T) == 2 ? 2 : 1)
                 }
                 if (tid < kRowsPerBlock) {
                     const RowInfo ri = row_info<G>(a1, b, kvh, qb * kRowsPerBlock + tid);
-                    const float row_lse = ri.valid ? lse[ri.out_row] : -INFINITY;
-                    // a row that sees nothing has lse = -inf; its weights are set to 0 below, whatever the shift
+                    const float row_lse = ri.valid ? lse[ri.out_row] : INFINITY;
+                    // a row that sees nothing has lse = -inf; its weights are left out below, whatever the shift
                     s_shift[tid] = (row_lse == -INFINITY) ? 0.f : -row_lse * unit;
                 }
-                if (w < tiles) request(w);
                 wait_for_own_loads();
                 __syncthreads();
 
-                // rows of this block that exist, and the first token that not all of them see
-                const int rows_here = min(n_rows - qb * kRowsPerBlock, kRowsPerBlock);
-                const int seen_by_all = causal_tail ? min(max(len - a1.n_q + qb * kRowsPerBlock / G + 1, 0), len) : len;
-                float done[NS];                  // the sums of the tile before, not stored yet
+                // tokens that all rows of the block see (tokens behind the length are not stored and need no mask)
+                const int seen_by_all = causal_tail ? len - a1.n_q + qb * kRowsPerBlock / G + 1 : INT32_MAX;
+                float done[NS] = {};             // the sums of the tile before, not stored yet
                 int done_at = -1;
                 auto store = [&]() {             // lane (n, hw) of a half stores every other head of its token (G = 8: its half's heads)
                     const int t = done_at + n;
@@ -745,13 +759,13 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 512 : 256, sizeof(T) == 2 ? 2 : 1)
                         }
                     }
                 };
-                for (int tile = w; tile < tiles; tile += kWWaves) {
+                for (int tile = tile_first; tile < tiles; tile += tile_step) {
                     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // the tile's rows are in the slot
                     uint4 kf[KK];
 #pragma unroll
                     for (int kk = 0; kk < KK; ++kk) kf[kk] = *reinterpret_cast<const uint4 *>(slot + (frag0 ^ (32 * kk)));
                     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // ... and in registers: the slot is free
-                    if (tile + kWWaves < tiles) request(tile + kWWaves);
+                    if (tile + tile_step < tiles) request(tile + tile_step);
                     store();                     // (its write overlaps with this tile's arithmetic)
                     const int tok0 = p0 + tile * kWTile;
                     float sum[NS];
@@ -782,50 +796,83 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 512 : 256, sizeof(T) == 2 ? 2 : 1)
                                                     : __builtin_amdgcn_exp2f(fmaf(c[4 * q4 + e], scale, s4[e]));
                         }
                     };
-                    if (rows_here == kRowsPerBlock && tok0 + kWTile <= seen_by_all) {            // uniform over the wave
-                        // straight-line code, two row tiles side by side: their matrix instructions take turns, and the
-                        // vector instructions of one pair run beside the matrix instructions of the other
+                    // two row tiles side by side: their matrix instructions take turns, and the vector instructions of one
+                    // pair run beside the matrix instructions of the other
+                    auto pair = [&](int x, floatx16 &c0, floatx16 &c1) {
+                        c0 = floatx16{};
+                        c1 = floatx16{};
+                        if constexpr (F32) {
+                            c0 = scores(x);
+                            c1 = scores(x + 1);
+                        } else {
+#pragma unroll
+                            for (int kk = 0; kk < KK; ++kk) {
+                                c0 = score_mfma(q_piece(x, kk), kf[kk], c0);
+                                c1 = score_mfma(q_piece(x + 1, kk), kf[kk], c1);
+                            }
+                        }
+                        weigh(x, c0);
+                        weigh(x + 1, c1);
+                    };
+                    auto add = [&](const floatx16 &c) {          // the head of row r is r % G
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) sum[r % NS] += c[r];
+                    };
+                    if (live == RT && spread == 1 && tok0 + kWTile <= seen_by_all) {     // uniform over the wave: straight-line code
 #pragma unroll
                         for (int x = 0; x < RT; x += 2) {
-                            floatx16 c0{}, c1{};
-                            if constexpr (F32) {
-                                c0 = scores(x);
-                                c1 = scores(x + 1);
-                            } else {
-#pragma unroll
-                                for (int kk = 0; kk < KK; ++kk) {
-                                    c0 = score_mfma(q_piece(x, kk), kf[kk], c0);
-                                    c1 = score_mfma(q_piece(x + 1, kk), kf[kk], c1);
-                                }
-                            }
-                            weigh(x, c0);
-                            weigh(x + 1, c1);
-#pragma unroll
-                            for (int r = 0; r < 16; ++r) sum[r % NS] += c0[r];   // the head of row r is r % G
-#pragma unroll
-                            for (int r = 0; r < 16; ++r) sum[r % NS] += c1[r];
+                            floatx16 c0, c1;
+                            pair(x, c0, c1);
+                            add(c0);
+                            add(c1);
                         }
                     } else {
+                        // Row r sees the lane's token iff r / G >= token - (len - n_q): the first such row, relative to the
+                        // first row that the lane holds.  Tiles that all rows see whole get a limit nothing is below.
+                        const int first_row = tok0 + kWTile <= seen_by_all
+                                                  ? INT32_MIN / 2
+                                                  : G * (tok0 + n - (len - a1.n_q)) - qb * kRowsPerBlock - 4 * hw;
+                        auto mask = [&](int x, floatx16 &c) {
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) c[r] = 8 * (r / 4) + r % 4 >= first_row - 32 * x ? c[r] : 0.f;
+                        };
+                        int x = part;
 #pragma unroll 1
-                        for (int x = 0; x < RT && 32 * x < rows_here; ++x) {
+                        for (; spread == 1 && x + 1 < live; x += 2) {
+                            floatx16 c0, c1;
+                            pair(x, c0, c1);
+                            mask(x, c0);
+                            mask(x + 1, c1);
+                            add(c0);
+                            add(c1);
+                        }
+#pragma unroll 1
+                        for (; x < live; x += spread) {
                             floatx16 c = scores(x);
                             weigh(x, c);
-#pragma unroll
-                            for (int r = 0; r < 16; ++r) {
-                                const int row = qb * kRowsPerBlock + 32 * x + 8 * (r / 4) + 4 * hw + r % 4;
-                                const int last = len - (causal_tail ? a1.n_q - row / G : 1);         // last token the row sees
-                                sum[r % NS] += row < n_rows && tok0 + n <= last ? c[r] : 0.f;
-                            }
+                            mask(x, c);
+                            add(c);
                         }
                     }
 #pragma unroll
                     for (int g = 0; g < NS; ++g) done[g] = G < 8 ? halves_sum(sum[g]) : sum[g];
                     done_at = tok0;
                 }
+                if (spread > 1) {                // uniform over the workgroup; a wave has met one tile at most, its slot is free
+#pragma unroll
+                    for (int g = 0; g < NS; ++g) reinterpret_cast<float *>(slot)[g * kWave + lane] = done[g];
+                    __syncthreads();
+                    for (int i = 1; part == 0 && i < spread; ++i)
+#pragma unroll
+                        for (int g = 0; g < NS; ++g) done[g] += reinterpret_cast<const float *>(s_k[w + i])[g * kWave + lane];
+                    if (part != 0) done_at = -1;
+                }
                 store();
             }
         }
-    }
+    };
+    serve(a1, 0);
+    if constexpr (TWO) serve(a2, cut.first_steps);
 }
 
 template <typename T, int D, bool SPLIT_P>
@@ -843,18 +890,27 @@ hipError_t launch_attn_group(const AppendArgs &a, const AppendArgs &a2, const Li
     return hipGetLastError();
 }
 
-template <typename T, int D>
-hipError_t launch_weights_group(const AppendArgs &a, const AppendArgs &a2, const LineDev &line, int two, dim3 grid, hipStream_t s)
+template <typename T, int D, bool TWO>
+hipError_t launch_weights_tiers(const AppendArgs &a, const AppendArgs &a2, const LineDev &line, dim3 grid, int streamed,
+                                hipStream_t s)
 {
     const dim3 block(WeightsStage<T, D>::kBlock);
     switch (a.sh.group) {
-    case 1: hipLaunchKernelGGL((append_weights_kernel<T, D, 1>), grid, block, 0, s, a, a2, line, two); break;
-    case 2: hipLaunchKernelGGL((append_weights_kernel<T, D, 2>), grid, block, 0, s, a, a2, line, two); break;
-    case 4: hipLaunchKernelGGL((append_weights_kernel<T, D, 4>), grid, block, 0, s, a, a2, line, two); break;
-    case 8: hipLaunchKernelGGL((append_weights_kernel<T, D, 8>), grid, block, 0, s, a, a2, line, two); break;
+    case 1: hipLaunchKernelGGL((append_weights_kernel<T, D, 1, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
+    case 2: hipLaunchKernelGGL((append_weights_kernel<T, D, 2, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
+    case 4: hipLaunchKernelGGL((append_weights_kernel<T, D, 4, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
+    case 8: hipLaunchKernelGGL((append_weights_kernel<T, D, 8, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+template <typename T, int D>
+hipError_t launch_weights_group(const AppendArgs &a, const AppendArgs &a2, const LineDev &line, int two, dim3 grid,
+                                int streamed, hipStream_t s)
+{
+    return two ? launch_weights_tiers<T, D, true>(a, a2, line, grid, streamed, s)
+               : launch_weights_tiers<T, D, false>(a, a2, line, grid, streamed, s);
 }
 
 }  // namespace
@@ -895,11 +951,18 @@ hipError_t launch_append_weights(int dtype, int head_dim, const AppendArgs &a, c
         return hipErrorInvalidValue;             // the two tiers share the queries and the launch shape
     // (a flat grid would be short of numbers: its threads are counted in 32 bits per dimension)
     const dim3 grid(line.shares, a.sh.n_kv_heads, a.sh.batch);
+    // K rows that pass once and are too many to stay in the L2 caches anyway (32 MB, by capacity) are streamed past them:
+    // 470 MB 106 -> 94 us, 33 MB (fp32) 15.1 -> 13.9; 11 MB, which do stay, 5.3 us as they are and 5.7 streamed.  More than
+    // one pass over the rows reads K again: 33 queries x 4 heads 192 us as they are, 211 streamed.
+    const bool one_pass = (int64_t)a.n_q * a.sh.group <= kRowsPerBlock;
+    const int64_t row_bytes = (int64_t)head_dim * (dtype == 0 ? 4 : 2);
+    const int64_t k_bytes = (int64_t)a.sh.batch * a.sh.n_kv_heads * ((int64_t)a.kv.cap + (second ? second->kv.cap : 0)) * row_bytes;
+    const int streamed = (one_pass || dtype == 0) && k_bytes >= (int64_t(16) << 20) ? 1 : 0;
     const int two = second ? 1 : 0;
-    if (dtype == 0 && head_dim == 64) return launch_weights_group<float, 64>(a, a2, line, two, grid, s);
-    if (dtype == 0 && head_dim == 128) return launch_weights_group<float, 128>(a, a2, line, two, grid, s);
-    if (dtype == 1 && head_dim == 64) return launch_weights_group<bf16_t, 64>(a, a2, line, two, grid, s);
-    if (dtype == 1 && head_dim == 128) return launch_weights_group<bf16_t, 128>(a, a2, line, two, grid, s);
+    if (dtype == 0 && head_dim == 64) return launch_weights_group<float, 64>(a, a2, line, two, grid, streamed, s);
+    if (dtype == 0 && head_dim == 128) return launch_weights_group<float, 128>(a, a2, line, two, grid, streamed, s);
+    if (dtype == 1 && head_dim == 64) return launch_weights_group<bf16_t, 64>(a, a2, line, two, grid, streamed, s);
+    if (dtype == 1 && head_dim == 128) return launch_weights_group<bf16_t, 128>(a, a2, line, two, grid, streamed, s);
     return hipErrorInvalidValue;
 }
 
