@@ -617,10 +617,6 @@ template <typename T, int D> struct WeightsStage {
     static __device__ __forceinline__ int swizzle(int row) { return (row / (16 / kSwizzled)) % kSwizzled; }
     static __device__ __forceinline__ int offset(int row, int piece) { return row * kRowBytes + 16 * (piece ^ swizzle(row)); }
 };
-#ifndef WMANY
-#define WMANY 512
-#define WPOL 2
-#endif
 constexpr int kNonTemporal = 2;                  // cache policy of a load: streamed once
 constexpr int kWManyRowTokens = 2048;            // tokens of a block that more than one pass over the rows goes through
 
