@@ -302,9 +302,9 @@ __device__ __forceinline__ void append_sums_again(const KvDev &kv, int n_kv_head
 // are (SPLIT_P has no meaning).  Its stages take 128 KB, one workgroup per unit; the pass is bound by the matrix
 // instruction (154 TFLOP/s dense).  2 x 24 queries on 5 K tokens, 32 / 8 heads: 340 us as one-query attention per query,
 // K and V read once per query -> 75 us.
-template <typename T, int D, int G, bool SPLIT_P>
+template <typename T, int D, int G, bool SPLIT_P, bool TWO>
 __global__ __launch_bounds__(kAttnBlock, sizeof(T) == 2 ? 2 : 1) void append_attn_kernel(AppendArgs a1, AppendArgs a2,
-                                                                                          LineDev line, int two_tiers)
+                                                                                          LineDev line)
 {
     constexpr bool F32 = sizeof(T) == 4;
     constexpr int NW = kAttnWaves, BLOCK = kAttnBlock;
@@ -363,33 +363,10 @@ __global__ __launch_bounds__(kAttnBlock, sizeof(T) == 2 ? 2 : 1) void append_att
     asm volatile("" : "+v"(low_half), "+v"(high_half));
 
     const LineCut cut(line, b);
-#pragma unroll 1
-    for (int tier = 0; tier < 2; ++tier) {
-        // the share's steps of the line inside this tier, and the slot they go to (see LineDev); all uniform
-        const int begin = share * cut.share_steps, end = begin + cut.share_steps;
-        int step_begin, step_end, slot;
-        if (tier == 0) {
-            if (two_tiers && begin > cut.first_steps) continue;
-            step_begin = begin;
-            step_end = end;
-            slot = share;
-        } else {
-            if (!two_tiers || (end <= cut.first_steps && share != line.shares - 1)) continue;
-            step_begin = max(begin - cut.first_steps, 0);
-            step_end = max(end - cut.first_steps, 0);
-            slot = share + 1;
-        }
-        // field by field: a choice between the two argument structs as a whole would put them into scratch memory
-        KvDev kv{};
-        kv.k = tier ? a2.kv.k : a1.kv.k;
-        kv.v = tier ? a2.kv.v : a1.kv.v;
-        kv.seq_lens = tier ? a2.kv.seq_lens : a1.kv.seq_lens;
-        kv.block_table = tier ? a2.kv.block_table : a1.kv.block_table;
-        kv.first_block = tier ? a2.kv.first_block : a1.kv.first_block;
-        kv.cap = tier ? a2.kv.cap : a1.kv.cap;
-        kv.block_size = tier ? a2.kv.block_size : a1.kv.block_size;
-        kv.max_blocks = tier ? a2.kv.max_blocks : a1.kv.max_blocks;
-        const int causal_tail = tier ? a2.causal_tail : a1.causal_tail;
+    // one tier's part of the share: steps [step_begin, step_end) of the tier, which go to `slot` (see LineDev); all uniform
+    auto serve = [&](const AppendArgs &a, int step_begin, int step_end, int slot) {
+        const KvDev &kv = a.kv;
+        const int causal_tail = a.causal_tail;
         const int len = tier_len(kv, b);
         const int t0 = step_begin * kStepTokens;
         const int nt_total = min(step_end * kStepTokens, len) - t0;              // <= 0: nothing of the share is valid
@@ -568,7 +545,7 @@ __global__ __launch_bounds__(kAttnBlock, sizeof(T) == 2 ? 2 : 1) void append_att
 
         // partial of every valid row: the lane holds output columns 32 dt + 8 q + 4 hw .. + 3 of its row
         l = halves_sum(l);
-        if (!row_exists) continue;
+        if (!row_exists) return;
         const int64_t at = ri.out_row * a1.part.stride + slot;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
@@ -580,7 +557,12 @@ __global__ __launch_bounds__(kAttnBlock, sizeof(T) == 2 ? 2 : 1) void append_att
             a1.part.m[at] = (m == -INFINITY) ? -INFINITY : m * a1.sh.sm_scale;         // the shift of the weights, in scaled scores
             a1.part.l[at] = l;
         }
-    }
+    };
+    const int begin = share * cut.share_steps, end = begin + cut.share_steps;
+    if (!TWO || begin <= cut.first_steps) serve(a1, begin, end, share);
+    if constexpr (TWO)
+        if (end > cut.first_steps || share == line.shares - 1)
+            serve(a2, max(begin - cut.first_steps, 0), max(end - cut.first_steps, 0), share + 1);
 }
 
 // Query-averaged softmax weights of a tier: a_out[b, h, t] = (1/N) sum_i e^{s_it - lse_i} over the queries i that see
@@ -871,19 +853,26 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 512 : 256, sizeof(T) == 2 ? 2 : 1)
     if constexpr (TWO) serve(a2, cut.first_steps);
 }
 
+template <typename T, int D, bool SPLIT_P, bool TWO>
+hipError_t launch_attn_tiers(const AppendArgs &a, const AppendArgs &a2, const LineDev &line, dim3 grid, hipStream_t s)
+{
+    const dim3 block(kAttnBlock);
+    switch (a.sh.group) {
+    case 1: hipLaunchKernelGGL((append_attn_kernel<T, D, 1, SPLIT_P, TWO>), grid, block, 0, s, a, a2, line); break;
+    case 2: hipLaunchKernelGGL((append_attn_kernel<T, D, 2, SPLIT_P, TWO>), grid, block, 0, s, a, a2, line); break;
+    case 4: hipLaunchKernelGGL((append_attn_kernel<T, D, 4, SPLIT_P, TWO>), grid, block, 0, s, a, a2, line); break;
+    case 8: hipLaunchKernelGGL((append_attn_kernel<T, D, 8, SPLIT_P, TWO>), grid, block, 0, s, a, a2, line); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
 template <typename T, int D, bool SPLIT_P>
 hipError_t launch_attn_group(const AppendArgs &a, const AppendArgs &a2, const LineDev &line, int two, dim3 grid,
                              hipStream_t s)
 {
-    const dim3 block(kAttnBlock);
-    switch (a.sh.group) {
-    case 1: hipLaunchKernelGGL((append_attn_kernel<T, D, 1, SPLIT_P>), grid, block, 0, s, a, a2, line, two); break;
-    case 2: hipLaunchKernelGGL((append_attn_kernel<T, D, 2, SPLIT_P>), grid, block, 0, s, a, a2, line, two); break;
-    case 4: hipLaunchKernelGGL((append_attn_kernel<T, D, 4, SPLIT_P>), grid, block, 0, s, a, a2, line, two); break;
-    case 8: hipLaunchKernelGGL((append_attn_kernel<T, D, 8, SPLIT_P>), grid, block, 0, s, a, a2, line, two); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    return two ? launch_attn_tiers<T, D, SPLIT_P, true>(a, a2, line, grid, s)
+               : launch_attn_tiers<T, D, SPLIT_P, false>(a, a2, line, grid, s);
 }
 
 template <typename T, int D, bool TWO>

@@ -939,13 +939,33 @@ int line_shares(int64_t units, int64_t tokens, int most, int places, int overhea
     return best;
 }
 
-// The attention: in bf16 two workgroups per unit and about five steps for loading the queries, the first rows' latency
-// and a partial of 64 KB to write and fold (a step takes 2.8 us, the fixed part 15 us on 509 queries x 32 K tokens); in
-// fp32 one workgroup per unit, whose steps are four times as long.
+// Shares of the attention.  In bf16 a compute unit holds two workgroups: a 64-token step of both takes 2.8 us, of one alone
+// 1.6, so two long shares are better than one of twice the length, but short ones pay for their start, 3 us, and for
+// their partial, which is written and read again by the fold (64 KB for 128 rows of 128 columns, 5 TB/s).  Times in 0.1 us;
+// only the smallest number of shares of each length in steps is looked at.  64 queries x 4 heads over 8 K tokens: 31.3 us
+// with 16 shares per unit (one workgroup per compute unit), 34.9 with 32; 55 queries over 5.6 K tokens 15.8 with 32, 18.6
+// with 45; 8 x 32 queries x 4 heads over 32 K tokens 260 with 8 (two workgroups per compute unit), 282 with 4.
+// In fp32 a compute unit holds one workgroup, whose steps are several times as long as its start and its partial.
 int append_shares(const hgca_shape *s, int32_t n_q, int64_t tokens, int most)
 {
-    const bool f32 = s->dtype == HGCA_F32;
-    return line_shares(append_units(s, n_q), tokens, most, f32 ? HGCA_APPEND_TARGET_WGS / 2 : HGCA_APPEND_TARGET_WGS, f32 ? 1 : 5);
+    const int64_t units = append_units(s, n_q);
+    if (s->dtype == HGCA_F32) return line_shares(units, tokens, most, HGCA_APPEND_TARGET_WGS / 2, 1);
+    constexpr int64_t kUnits = HGCA_APPEND_TARGET_WGS / 2, kStepOfTwo = 28, kStepAlone = 16, kStart = 30;
+    const int64_t steps = std::max<int64_t>(1, (tokens + kLineStep - 1) / kLineStep);
+    const int64_t partial = std::min<int64_t>(128, (int64_t)n_q * group_of(s)) * s->head_dim * 8;        // bytes, written and read
+    int64_t best = 1, best_cost = INT64_MAX;
+    for (int64_t n = 1; n <= most && n <= steps;) {
+        const int64_t len = (steps + n - 1) / n, load = (n * units + kUnits - 1) / kUnits;
+        const int64_t cost = load / 2 * (len * kStepOfTwo + kStart) + load % 2 * (len * kStepAlone + kStart) +
+                             n * units * partial / 500000;
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = n;
+        }
+        if (len == 1) break;
+        n = (steps + len - 2) / (len - 1);       // the smallest number whose shares are shorter
+    }
+    return (int)best;
 }
 
 struct AppendWs {

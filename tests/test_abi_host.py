@@ -509,3 +509,22 @@ def test_managed_decode_step_rejects_bad_arguments(hg):
     assert step(wd_bytes=hg.workspace_bytes(sh, 32, 0, 0) - 1) == hg.ERR_WORKSPACE
     assert step(wsp_bytes=hg.workspace_bytes(sh, 0, 0, 32) - 1) == hg.ERR_WORKSPACE
     assert step(shape=hg.Shape(hg.BF16, 0, 8, 2, 128, 0.088), q=None, o=None, a=None) == hg.OK
+
+
+@pytest.mark.parametrize("shape,n_q,window,pool,shares", [
+    ((1, 32, 8, 128), 64, 1000, 7000, 16),                    # 16 units: one workgroup per compute unit
+    ((2, 4, 4, 128), 55, 836, 4759, 30),                      # 8 units, 89 steps in threes
+    ((2, 4, 4, 128), 100, 512, 5632, 32),
+    ((8, 32, 8, 128), 32, 4096, 28672, 8),                    # 64 units, long shares: two workgroups per compute unit
+    ((2, 32, 8, 128), 509, 4096, 28672, 2),
+    ((64, 64, 64, 128), 509, 4096, 28672, 1),                 # far more units than places
+], ids=["n64", "n55", "n100", "n32", "n509", "many_units"])
+def test_shares_of_an_append_call(hg, shape, n_q, window, pool, shares):
+    """The number of shares an append call is cut into, as its workspace shows it: shares + 1 slots of one output row and
+    two statistics per (sequence, query, head), and two log-sum-exp rows."""
+    b, hq, hkv, d = shape
+    rows = b * n_q * hq
+    got = hg.lib().hgca_append_tiers_workspace_bytes(ctypes.byref(hg.Shape(hg.BF16, b, hq, hkv, d, 1.0)), n_q, window, pool)
+    up = lambda x: (x + 255) // 256 * 256
+    want = [up(rows * n * d * 4) + 2 * up(rows * n * 4) + 2 * up(rows * 4) for n in range(1, 66)]
+    assert got in want and want.index(got) == shares
