@@ -519,7 +519,8 @@ int hgca_ctx_compact(const hgca_shape *shape, const hgca_kv_view *pool,
 /* ---- Append stage (Sec. 2.1: N incoming tokens, Q in R^{h x N x d}; Alg. 2,
  * append branch).  Both contractions run on the matrix cores: bf16 inputs on
  * the bf16 instructions, fp32 inputs (the exact shapes; B * n_q <= 65 535) on
- * the fp32 ones, products and sums in fp32 throughout. ----
+ * the fp32 ones, products and sums in fp32 throughout; a few fp32 queries over
+ * one tier run one by one on the vector units where that is faster. ----
  *
  * q is [B, N, Hq, d].  Attention of all N queries over one tier; the two parts
  * of the hybrid step are two calls (the window with HGCA_APPEND_CAUSAL_TAIL,

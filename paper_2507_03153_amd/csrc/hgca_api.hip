@@ -968,6 +968,26 @@ int append_shares(const hgca_shape *s, int32_t n_q, int64_t tokens, int most)
     return (int)best;
 }
 
+// fp32, few queries: one-query attention per (sequence, query) with the split kernels of the decode path, which read K and V
+// once per query and work out no more than its rows, against the matrix instructions, which work out 32 rows whatever
+// there are.  The lower estimate has it, in us: query by query 6 + 1.5 per head of a group, and the K and V bytes of all
+// queries at what the vector units take (28 TB/s over the heads of a group) or the rows come from (20 TB/s out of L2,
+// 13.7 out of the last cache, 7.6 out of memory); on the matrix instructions 7, and the steps of a workgroup, one at a time
+// per compute unit, 9.8 each (head_dim 128).  Measured, query by query against matrix: 4 sequences, 32 heads, 4 K tokens,
+// 1 / 4 / 5 queries 80 : 314, 278 : 315, 351 : 316 us; 2 sequences, 32 / 8 heads, 4 K tokens, 2 / 4 / 8 queries 30 : 47,
+// 49 : 48, 86 : 48; one sequence, 4 heads of 64, 2 K tokens, 8 / 32 queries 8.2 : 11.3, 12.2 : 11.7.
+bool f32_query_by_query(const hgca_shape *s, int32_t n_q, int64_t tokens, int most)
+{
+    const int g = group_of(s);
+    const double set = (double)s->batch * s->n_kv_heads * tokens * s->head_dim * 8;              // bytes of K and V
+    const double source = set <= 16e6 ? 20e6 : set <= 256e6 ? 13.7e6 : 7.6e6;                    // bytes per us
+    const double by_query = 6 + 1.5 * g + set * n_q / std::min(28e6 / g, source);
+    const int64_t shares = append_shares(s, n_q, tokens, most), places = HGCA_APPEND_TARGET_WGS / 2;
+    const int64_t steps = (tokens + kLineStep - 1) / kLineStep;
+    const int64_t turns = (shares * append_units(s, n_q) + places - 1) / places * ((steps + shares - 1) / shares);
+    return by_query < 7 + turns * 9.8 * s->head_dim / 128;
+}
+
 struct AppendWs {
     size_t o, m, l, total;
     int max_splits;
@@ -976,7 +996,7 @@ struct AppendWs {
 AppendWs append_layout(const hgca_shape *s, int32_t n_q, int64_t max_tokens)
 {
     AppendWs w{};
-    // bf16: splits of up to kMaxAppendChunk tokens; fp32 runs on the one-query kernels, whose splits hold kMaxChunk
+    // shares of up to kMaxAppendChunk tokens; fp32 may run on the one-query kernels, whose splits hold kMaxChunk
     w.max_splits = std::max(append_want_splits(s, n_q), n_splits_for(std::max<int64_t>(max_tokens, 1),
                                                                      s->dtype == HGCA_F32 ? kMaxChunk : kMaxAppendChunk));
     const size_t rows = (size_t)s->batch * n_q * s->n_q_heads;
@@ -1022,8 +1042,31 @@ int hgca_append_attn(const hgca_shape *shape, const void *q, int32_t n_q, const 
     if (!ws || ws_bytes < w.total || !aligned16(ws)) return HGCA_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
 
-    // (a limit of the fp32 calls that callers may rely on as part of the interface)
-    if (shape->dtype == HGCA_F32 && (int64_t)shape->batch * n_q > 65535) return HGCA_ERR_UNSUPPORTED;
+    if (shape->dtype == HGCA_F32) {
+        // batch * n_q sequences of one query each, as one of the two routes has it, are a grid dimension
+        if ((int64_t)shape->batch * n_q > 65535) return HGCA_ERR_UNSUPPORTED;
+        if (tier->cap > 0 && f32_query_by_query(shape, n_q, tier->cap, w.max_splits)) {
+            // splits no shorter than the workspace has slots for
+            const int chunk = std::max(pick_chunk(tier->cap, (int64_t)shape->batch * n_q * shape->n_kv_heads, HGCA_TARGET_WGS_DENSE),
+                                       (n_splits_for(tier->cap, w.max_splits) + 63) / 64 * 64);
+            const int n_splits = n_splits_for(tier->cap, chunk);
+            if (chunk > kMaxChunk || n_splits > w.max_splits) return HGCA_ERR_WORKSPACE;
+            AttnArgs d{};
+            d.sh = to_dev(shape);
+            d.sh.batch = shape->batch * n_q;
+            d.q = q;
+            d.kv = to_dev(tier);
+            d.kv.n_q = n_q;
+            d.kv.causal_tail = (flags & HGCA_APPEND_CAUSAL_TAIL) ? 1 : 0;
+            d.chunk = chunk;
+            char *base = static_cast<char *>(ws);
+            d.part = Partials{reinterpret_cast<float *>(base + w.o), reinterpret_cast<float *>(base + w.m),
+                              reinterpret_cast<float *>(base + w.l), n_splits, n_splits};
+            const int64_t rows = (int64_t)d.sh.batch * shape->n_q_heads;
+            if ((rc = from_hip(launch_attn_partial_dense(shape->dtype, shape->head_dim, d, s))) != HGCA_OK) return rc;
+            return from_hip(launch_combine(shape->head_dim, rows, d.part, o_out, lse_out, s));
+        }
+    }
     AppendArgs a{};
     a.sh = to_dev(shape);
     a.q = q;
