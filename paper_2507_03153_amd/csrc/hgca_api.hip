@@ -538,11 +538,18 @@ int hgca_sparse_attn_grouped(const hgca_shape *shape, const void *q, const hgca_
     a.grouped = 1;
     // Deferred, the split size is hgca_sparse_attn's (hgca_lse_merge_splits derives the split count from k_max alone).
     // Folded here, there are a group's times fewer lists and workgroups, so the splits are that much shorter (64 lists
-    // of 2 048 entries for groups of 4: 27.0 -> 22.6 us with 1024 workgroups; with 2048, two partials per 64 rows, 26.6).
+    // of 2 048 entries for groups of 4: 27.0 -> 22.6 us with 1024 workgroups; with 2048, two partials per 64 rows, 26.6),
+    // but no shorter than 16 KB of K each (64 lists of 900 entries of dimension 64 in bf16: 13.1 us in splits of 128, 15.6
+    // in splits of 64), and the bf16 kernel for groups of 8, whose workgroups write eight rows of partials each, gets half as
+    // many (64 lists of 900 entries, dimension 64 / 128: 20.8 / 26.8 us with 512 workgroups, 34.5 / 34.6 with 960).
     // Without groups there are as many lists as heads, and nothing to shorten.
-    const bool own_split = !deferred && shape->n_q_heads > shape->n_kv_heads;
-    a.chunk = pick_chunk(k_max, (int64_t)shape->batch * (own_split ? shape->n_kv_heads : shape->n_q_heads),
-                         own_split ? HGCA_TARGET_WGS_GROUPED : HGCA_TARGET_WGS_SPARSE);
+    const int group = group_of(shape), row_bytes = shape->head_dim * (shape->dtype == HGCA_BF16 ? 2 : 4);
+    if (deferred || group == 1) {
+        a.chunk = pick_chunk(k_max, (int64_t)shape->batch * shape->n_q_heads, HGCA_TARGET_WGS_SPARSE);
+    } else {
+        const int target = shape->dtype == HGCA_BF16 && group == 8 ? HGCA_TARGET_WGS_GROUPED / 2 : HGCA_TARGET_WGS_GROUPED;
+        a.chunk = std::max(pick_chunk(k_max, (int64_t)shape->batch * shape->n_kv_heads, target), 16384 / row_bytes);
+    }
     a.part = partials_at(ws, w, std::max(1, n_splits_for(k_max, a.chunk)));
     const int64_t rows = (int64_t)shape->batch * shape->n_q_heads;
     if ((rc = from_hip(launch_attn_partial_gather(shape->dtype, shape->head_dim, a, s))) != HGCA_OK) return rc;

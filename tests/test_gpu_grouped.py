@@ -133,3 +133,39 @@ def test_union_longer_than_its_row_is_cut_and_flagged(gpu, oracle):
     hgca.union_lists(sh, idx, cnt, 3, 64, out, out_cnt, 5, status)
     torch.cuda.synchronize()
     assert out.cpu().tolist() == [[[0, 1, 2, 3, 10]]] and int(out_cnt.cpu()[0, 0]) == 5 and int(status.cpu()[0]) == 1
+
+
+@pytest.mark.parametrize("dtype,heads,kv,d,k_max", [
+    ("bf16", 64, 8, 64, 900), ("bf16", 64, 8, 128, 2048), ("bf16", 32, 8, 64, 900), ("bf16", 16, 8, 64, 700), ("f32", 64, 8, 128, 900),
+    ("f32", 32, 8, 64, 900),
+])
+def test_shared_lists_at_the_edges_of_their_splits(gpu, dtype, heads, kv, d, k_max):
+    """Lists folded at once, of every length around the splits' ends (64, 128, 256 and 512 entries by shape and type), against
+    attention over the listed rows in 64 bits."""
+    torch, hgca, _ = gpu
+    dev = "cuda:0"
+    counts = [k_max, k_max - 1, 513, 512, 257, 128, 127, 65, 64, 63, 1, 0]
+    say(f"\n[case] shared lists {dtype} {heads}/{kv} d={d} k_max={k_max} counts={counts}")
+    B, P, G = len(counts), 3000, heads // kv
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device=dev).manual_seed(d + k_max)
+    q, k, v = (torch.randn(*s, generator=g, device=dev).to(dt) for s in ((B, heads, d), (B, kv, P, d), (B, kv, P, d)))
+    idx = torch.full((B, kv, k_max), -1, dtype=torch.int32, device=dev)
+    for b, n in enumerate(counts):
+        idx[b, :, :n] = torch.rand(kv, P, generator=g, device=dev).topk(n, -1).indices.sort(-1).values.int()
+    cnt = torch.tensor(counts, dtype=torch.int32, device=dev).view(B, 1).expand(B, kv).contiguous()
+    shape = hgca.Shape(hgca.BF16 if dtype == "bf16" else hgca.F32, B, heads, kv, d, d ** -0.5)
+    o, lse = torch.full((B, heads, d), float("nan"), device=dev), torch.full((B, heads), float("nan"), device=dev)
+    hgca.sparse_attn_grouped(shape, q, hgca.Tier(k, v, P), idx, cnt, k_max, o, lse, hgca.alloc_workspace(shape, 0, 0, k_max, dev))
+    torch.cuda.synchronize()
+    tol = 2e-4 if dtype == "bf16" else 1e-5                      # the bars of test_gpu_parity
+    for b, n in enumerate(counts):
+        if n == 0:
+            assert bool((o[b] == 0).all()) and bool((lse[b] == float("-inf")).all())
+            continue
+        at = idx[b, :, :n].long()[..., None].expand(kv, n, d)
+        kk, vv = k[b].gather(1, at).double(), v[b].gather(1, at).double()
+        s = torch.matmul(q[b].view(kv, G, d).double(), kk.transpose(1, 2).contiguous()) * d ** -0.5
+        want = torch.matmul(s.softmax(-1), vv).view(heads, d)
+        assert float((o[b].double() - want).abs().max()) <= tol, n
+        assert float((lse[b].double() - s.logsumexp(-1).view(heads)).abs().max()) <= tol, n
