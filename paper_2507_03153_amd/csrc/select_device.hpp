@@ -43,6 +43,11 @@ __device__ __forceinline__ float key_to_score(uint32_t key) {
 }
 
 
+struct ScoreRange {
+    float lo = INFINITY, hi = -INFINITY;
+    bool enough = false;                         // else the first scores of the row are still to be met
+};
+
 struct Binning {
     float lo, inv_w;
     __device__ __forceinline__ float scaled(float s) const { return (s - lo) * inv_w; }
@@ -375,6 +380,7 @@ struct Sel {
     // the function returns false before it has written any output and the caller runs select_row.  `lists` is the workgroup's dynamic LDS (list_bytes of it).
     // kSampleLoads 16-byte loads per thread make up the sample.
     static constexpr int kSampleChunk = 256;                     // scores of one run of the sample: what a wave takes with one load
+    static constexpr int kRangeLoads = 8;                        // 16-byte loads per thread that the byte mode's range is taken over
 
     // The fraction of a row the pre-filter asks for, raised by six standard deviations of its estimate from the sample.
     template <int kSampleLoads>
@@ -394,10 +400,19 @@ struct Sel {
         return n >= 2 * kSelBlock * kSampleLoads * 4 && p_est * (float)n * 1.25f <= (float)room && p_est <= 0.2f;
     }
 
-    template <int kSampleLoads>
+    // GUARDED (rows that the byte mode holds, which costs them less than a filter that fails): the estimate is trusted only
+    // if no run of the sample holds many more of its high scores than chance would give it.  Where high scores stand
+    // together the estimate is a matter of how many groups the sample met, and the lists of single waves overflow; such rows
+    // are left to the byte mode at once, which also takes the sample into its range (it met the first 32 768 scores only, and
+    // a row that rises towards its end crowded the topmost bin).  32 rows of 122 880 scores, 2048 wanted, in groups of 64 / at
+    // the end of the row: 51.6 / 180 us with the filter tried in full, 41.2 / 43.2.  Rows below 65 536 scores, which the byte mode
+    // serves almost as fast as the filter, load the rest of that range with the sample (1.5 us): 32 rows of 61 004, 2048 wanted,
+    // no groups 26.4 us in the byte mode, 18.1 with the filter, 19.7 with the filter and the range; in groups of 64: 24.4, 33.6
+    // and 27.3.
+    template <int kSampleLoads, bool GUARDED>
     static __device__ __forceinline__ bool select_row_prefiltered(const SelectArgs &a, SelShared &sh, float *lists,
                                                                   int list_bytes, const float *sc, int32_t *out, int n,
-                                                                  int k, int64_t bh)
+                                                                  int k, int64_t bh, ScoreRange &range)
     {
         constexpr int kSampleChunks = kSelBlock * kSampleLoads * 4 / kSampleChunk;
         constexpr int kSample = kSampleChunks * kSampleChunk;
@@ -416,12 +431,21 @@ struct Sel {
             v[u] = load4_padded(sc, start + 4 * (j % (kSampleChunk / 4)), n);
         }
         float mn = INFINITY, mx = -INFINITY;
-#pragma unroll
-        for (int u = 0; u < kSampleLoads; ++u) {
-            const float s[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+        auto widen = [&](const float4 &x) {
+            const float s[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
             for (int e = 0; e < 4; ++e) { mx = fmaxf(mx, finite_or(s[e], -INFINITY)); mn = fminf(mn, finite_or(s[e], INFINITY)); }
+        };
+        const bool with_range = GUARDED && n < 65536;        // uniform: the range of the byte mode, too
+        if (with_range) {
+            float4 first[kRangeLoads];
+#pragma unroll
+            for (int u = 0; u < kRangeLoads; ++u) first[u] = load4_padded(sc, min(4 * (u * kSelBlock + tid), (n + 3) / 4 * 4), n);
+#pragma unroll
+            for (int u = 0; u < kRangeLoads; ++u) widen(first[u]);
         }
+#pragma unroll
+        for (int u = 0; u < kSampleLoads; ++u) widen(v[u]);
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) {
             mn = fminf(mn, __shfl_xor(mn, off, kWave));
@@ -435,6 +459,7 @@ struct Sel {
 #pragma unroll
         for (int i = 0; i < kSelWaves; ++i) { mn = fminf(mn, sh.wave_min[i]); mx = fmaxf(mx, sh.wave_max[i]); }
         if (!(mx > mn)) return false;                // a constant sample, or nothing finite in it (uniform)
+        if (GUARDED) range = ScoreRange{mn, mx, with_range};
         Binning bin;
         bin.lo = mn;
         bin.inv_w = (float)kBins / (mx - mn);
@@ -448,7 +473,18 @@ struct Sel {
         __syncthreads();
         locate_rank(sh, kBins, (uint32_t)min(kSample, (int)ceilf(p_est * (float)kSample)));
         const float floor_score = mn + (float)sh.found[0] * ((mx - mn) / (float)kBins);   // lower edge of that bin
-        __syncthreads();
+        if (GUARDED) {
+            constexpr float kRun = (float)kSampleChunk;
+            const int most = (int)(p_est * kRun + 5.5f * sqrtf(p_est * kRun) + 2.f);     // of a run; chance: 1 in 10^6
+            bool crowded = false;
+#pragma unroll
+            for (int u = 0; u < kSampleLoads; ++u)               // a wave's load is one run
+                crowded |= __popcll(__ballot(v[u].x >= floor_score)) + __popcll(__ballot(v[u].y >= floor_score)) +
+                               __popcll(__ballot(v[u].z >= floor_score)) + __popcll(__ballot(v[u].w >= floor_score)) > most;
+            if (__syncthreads_or(crowded)) return false;
+        } else {
+            __syncthreads();
+        }
 
         // ---- the row, once: entries at or above the estimate go to the wave's list, in position order -------
         const int seg = segment_length(n);
@@ -601,9 +637,10 @@ struct Sel {
         return true;
     }
 
+    // known (kCachedBins): the range of a sample that the caller has met, or an empty one.
     template <int MODE>
-    static __device__ __forceinline__ void select_row(const SelectArgs &a, SelShared &sh, float *cache,
-                                                      const float *sc, int32_t *out, int n, int k, int64_t bh)
+    static __device__ __forceinline__ void select_row(const SelectArgs &a, SelShared &sh, float *cache, const float *sc,
+                                                      int32_t *out, int n, int k, int64_t bh, ScoreRange known = ScoreRange{})
     {
         constexpr bool CACHED = MODE == kCachedScores, BINS = MODE == kCachedBins;
         uint8_t *cbin = reinterpret_cast<uint8_t *>(cache);         // kCachedBins: one byte per position of the padded row
@@ -617,11 +654,11 @@ struct Sel {
         const int steps = row.steps();
 
         // ---- pass 0: range of the row; the padded row goes to LDS ---------------------------------------
-        float mn = INFINITY, mx = -INFINITY;
-        {
-            constexpr int U = 8;                     // 16-byte loads in flight per lane
+        float mn = known.lo, mx = known.hi;
+        if (!(BINS && known.enough)) {
+            constexpr int U = kRangeLoads;           // 16-byte loads in flight per lane
             const int n4 = padded / 4;
-            // kCachedBins: the range is taken from the first kSelBlock * U * 4 scores only.  Any range gives a correct
+            // kCachedBins: the range is taken from the first kSelBlock * U * 4 scores and the sample only.  Any range gives a correct
             // selection (scores beyond it land in the end bins, and a threshold bin that turns out crowded is resolved
             // exactly below); a range that misses part of the row only makes the end bins fuller.
             const int n4_range = BINS ? min(n4, kSelBlock * U) : n4;
@@ -961,6 +998,7 @@ __device__ __forceinline__ void select_row_any(const SelectArgs &a, typename Sel
                                                int cache_floats, int cache_bytes, int list_bytes)
 {
     using S = Sel<BLOCK>;
+    ScoreRange range;
     if (REG_STEPS > 0 && S::segment_length(n) <= REG_STEPS * kStep) {      // the row fits the lanes' registers
         if (S::template select_row_in_registers<(REG_STEPS > 0 ? REG_STEPS : 1)>(a, sh, sc, out, n, k, bh)) return;
         __syncthreads();                         // the general path starts over on the shared state
@@ -969,16 +1007,19 @@ __device__ __forceinline__ void select_row_any(const SelectArgs &a, typename Sel
         // 24 rows of 101 388, k = 12 163, hold 14 593 entries with 8 192 samples and 13 348 with 32 768, room 13 516.
         constexpr int kLoads = BLOCK == kLargeBlock ? HGCA_SEL_LARGE_SAMPLE_LOADS : HGCA_SEL_SMALL_SAMPLE_LOADS;
         constexpr int kMoreLoads = BLOCK == kLargeBlock ? 4 * kLoads : kLoads;
+        const bool in_bytes = BLOCK == kLargeBlock && S::padded_length(n) <= cache_bytes;          // guarded
         if (S::template prefilter_fits<kLoads>(n, k, list_bytes)) {
-            if (S::template select_row_prefiltered<kLoads>(a, sh, cache, list_bytes, sc, out, n, k, bh)) return;
+            if (in_bytes ? S::template select_row_prefiltered<kLoads, true>(a, sh, cache, list_bytes, sc, out, n, k, bh, range)
+                         : S::template select_row_prefiltered<kLoads, false>(a, sh, cache, list_bytes, sc, out, n, k, bh, range))
+                return;
             __syncthreads();                     // the general path starts over on the shared state
         } else if (kMoreLoads > kLoads && S::template prefilter_fits<kMoreLoads>(n, k, list_bytes)) {
-            if (S::template select_row_prefiltered<kMoreLoads>(a, sh, cache, list_bytes, sc, out, n, k, bh)) return;
+            if (S::template select_row_prefiltered<kMoreLoads, false>(a, sh, cache, list_bytes, sc, out, n, k, bh, range)) return;
             __syncthreads();
         }
     }
     if (S::padded_length(n) <= cache_floats) S::template select_row<kCachedScores>(a, sh, cache, sc, out, n, k, bh);
-    else if (S::padded_length(n) <= cache_bytes) S::template select_row<kCachedBins>(a, sh, cache, sc, out, n, k, bh);
+    else if (S::padded_length(n) <= cache_bytes) S::template select_row<kCachedBins>(a, sh, cache, sc, out, n, k, bh, range);
     else S::template select_row<kFromMemory>(a, sh, cache, sc, out, n, k, bh);
 }
 

@@ -44,3 +44,30 @@ def test_scores_of_odd_capacities(oracle, cap):
     got = out.cpu()
     assert torch.all(got[B * Hq * cap:] == -9.0)
     assert float((got[:B * Hq * cap].double().view(B, Hkv, Hq // Hkv, cap) - want).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("cap,k", [(33800, 1500), (40000, 1024), (61003, 2048), (65536, 3000), (70001, 2500), (135100, 4000)])
+def test_high_scores_that_stand_together(oracle, cap, k):
+    """Rows whose high scores are not spread by chance, which the sampled pre-filter leaves to the mode that holds a row as
+    bytes: in groups of 8, 64 and 512 consecutive positions, rising towards the end, all at the end, one far above a flat
+    row, two levels, and infinite ones among them."""
+    import torch
+    from paper_2507_03153_amd import hgca
+    rng = np.random.default_rng(cap)
+    pos = np.arange(cap)
+    rows = [rng.standard_normal(cap) + 5.0 * np.repeat(rng.random(-(-cap // g)) < 1.2 * k / cap, g)[:cap] for g in (8, 64, 512)]
+    rows += [rng.standard_normal(cap) + 6.0 * pos / cap, rng.standard_normal(cap) - 4.0 * np.log(cap - pos)]
+    rows += [np.where(pos == 5, 1e6, rng.standard_normal(cap)), np.where(pos // 700 % 5 == 0, 1.0, 0.0)]
+    rows += [np.where(pos % 9001 < 40, np.inf, rng.standard_normal(cap)), np.where(pos < cap // 2, -np.inf, rng.standard_normal(cap))]
+    scores = np.stack(rows).astype(np.float32)[None]
+    n = scores.shape[1]
+    shape = hgca.Shape(hgca.F32, 1, n, n, 128, 1.0)
+    idx = torch.full((1, n, k), -7, dtype=torch.int32, device="cuda")
+    cnt, sel = torch.zeros(1, n, dtype=torch.int32, device="cuda"), torch.zeros(1, n, k, device="cuda")
+    hgca.select_topk(shape, torch.from_numpy(scores).cuda(), None, cap, k, k, idx, cnt, sel_scores_out=sel)
+    torch.cuda.synchronize()
+    want, want_cnt = oracle.select_given(scores, k, k)
+    assert np.array_equal(cnt.cpu().numpy(), want_cnt)
+    for r in range(n):
+        assert np.array_equal(idx.cpu().numpy()[0, r], want[0, r]), r
+    assert np.array_equal(sel.cpu().numpy(), np.take_along_axis(scores, want.astype(np.int64), axis=2))
