@@ -111,3 +111,20 @@ def test_few_queries_over_more_splits_than_the_workspace_holds(gpu):  # noqa: F8
     torch.cuda.synchronize()
     o_ref, l_ref = reference(q.cpu().numpy(), k.cpu().numpy(), v.cpu().numpy(), [cap] * B, d ** -0.5, False)
     assert np.max(np.abs(o.cpu().numpy() - o_ref)) <= 1e-5 and np.max(np.abs(lse.cpu().numpy() - l_ref)) <= 1e-5
+
+
+@pytest.mark.parametrize("kw", [
+    dict(B=2, Hq=8, Hkv=2, d=128, seed=41), dict(B=1, Hq=16, Hkv=2, d=128, seed=42), dict(B=2, Hq=4, Hkv=4, d=64, seed=43),
+], ids=["gqa4", "gqa8", "mha_d64"])
+def test_turns_over_a_long_line(kw):
+    """Managed turns: pool and window as one line of tokens in fp32, an empty pool at first and some thousand tokens at last,
+    up to 8000 query rows per KV head (the weights pass adds to its output block after block of them)."""
+    import torch
+    from paper_2507_03153_amd import cache, hgca, runner
+    from test_gpu_kv_turns import run_turns
+    hgca.lib()
+    prefill = (0, 100)[:kw["B"]]
+    _, _, status, st = run_turns((torch, hgca, runner, cache), block_size=16, win_blocks=8, max_blocks=200, k_max=2900,
+                                 turns=[("a", 1000), ("a", 900), ("d", 3), ("a", 700), ("a", 40), ("a", 33)], alpha=0.3, beta=1.0,
+                                 prefill=prefill, fp32=True, **kw)
+    assert status == 0 and st["evicted_blocks"] >= 40

@@ -43,3 +43,22 @@ def test_block_sizes_read_the_same_rows(gpu, block):  # noqa: F811
     torch.cuda.synchronize()
     for x, y in zip(*out):
         assert torch.isfinite(x).all() and torch.equal(x, y)
+
+
+def test_one_part_repeats_itself(gpu):  # noqa: F811
+    """Weights rounded once to bf16: O depends on how the line is cut (a weight is rounded relative to the maximum of its
+    share), and on nothing else: the same call gives the same bits, into a workspace that held something else."""
+    torch, hgca, runner = gpu
+    B, N, Hq, Hkv, d, W, P, dev = 2, 48, 64, 8, 128, 1024, 7000, "cuda:0"
+    g = torch.Generator(device=dev).manual_seed(8)
+    r = lambda *s: torch.randn(*s, generator=g, device=dev).to(torch.bfloat16)
+    q, win, pool = r(B, N, Hq, d), hgca.Tier(r(B, Hkv, W, d), r(B, Hkv, W, d), W), hgca.Tier(r(B, Hkv, P, d), r(B, Hkv, P, d), P)
+    shape = hgca.Shape(hgca.BF16, B, Hq, Hkv, d, d ** -0.5)
+    out = []
+    for fill in (0, 255):
+        o, lse = torch.zeros(B, N, Hq, d, device=dev), torch.zeros(B, N, Hq, device=dev)
+        ws = hgca.append_tiers_workspace(shape, N, W, P, dev).fill_(fill)
+        hgca.append_attn_tiers(shape, q, win, pool, o, lse, ws, one_part_p=True)
+        out.append((o, lse))
+    torch.cuda.synchronize()
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
