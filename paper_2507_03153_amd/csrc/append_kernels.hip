@@ -1,5 +1,6 @@
 // Append stage: N queries per sequence attend to one KV tier (Sec. 2.1: S = Q K^T, A = softmax(S),
-// O = A V with Q in R^{h x N x d}; Alg. 2, append branch).  bf16 inputs, both contractions on the matrix cores.
+// O = A V with Q in R^{h x N x d}; Alg. 2, append branch), or to two.  Both contractions on the matrix
+// cores, bf16 and fp32.
 //
 // Work unit of the attention kernel: one workgroup = one share of the tokens of one (sequence, KV head) and up to 128
 // query rows (a row = one query x one head of the GQA group, query-major).  Every wave owns 32 rows, so nothing is
@@ -13,8 +14,8 @@
 // In both results a lane's column is the query row lane % 32, so the running maximum, the running sum and the
 // rescaling factor of a row live in the lanes that hold its scores AND its output columns: the online softmax needs
 // one lane exchange per row statistic and no LDS.  The probabilities go from the score registers straight into the B
-// operand of the second contraction (the contraction index is matched by reading V^T in the same token order); they
-// are rounded to bf16 there, as a high and a low part (two MFMAs, fp32-level accuracy) or, on request, as one part.
+// operand of the second contraction (the contraction index is matched by reading V^T in the same token order); in bf16
+// they are rounded there, as a high and a low part (two MFMAs, fp32-level accuracy) or, on request, as one part.
 //
 // The weights kernel brings its K rows in the same way (it has no second contraction).
 #include "hgca_launch.hpp"
@@ -27,12 +28,10 @@ namespace {
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float float2v __attribute__((ext_vector_type(2)));
 
-constexpr int kABlock = 512;
-constexpr int kAWaves = kABlock / kWave;
 constexpr int kStepBlocks = 2;                   // 32-token contraction blocks per step
 constexpr int kStepTokens = 32 * kStepBlocks;
-constexpr int kRowsPerBlock = 128;               // query rows per workgroup = 8 tiles of 16, one per wave
-static_assert(kRowsPerBlock == 16 * kAWaves, "one row tile per wave");
+constexpr int kRowsPerBlock = 128;               // query rows of a workgroup
+constexpr int kAttnWaves = kRowsPerBlock / 32, kAttnBlock = kAttnWaves * kWave;   // of the attention: a wave owns 32 of them
 constexpr int kSub = kMaxChunk;                  // entries of the table of rows (paged tiers)
 static_assert(kStepTokens == kLineStep, "shares of a line are whole steps");
 static_assert(kSub * 16 % kStepTokens == 0, "a pass is a whole number of steps");
@@ -88,7 +87,7 @@ __device__ __forceinline__ float halves_sum(float x) {
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
-// Row bookkeeping of one 16-row tile for this lane (column n = lane % 16).
+// Where a query row of a (sequence, KV head) pair lives: query r / G, head r % G of the group.
 struct RowInfo {
     bool valid;
     int query;
@@ -230,7 +229,6 @@ __device__ __forceinline__ floatx16 score_tile_f32(Piece piece, const uint4 (&b)
     return c[0];
 }
 
-constexpr int kAttnWaves = kRowsPerBlock / 32, kAttnBlock = kAttnWaves * kWave;   // a wave owns 32 query rows
 constexpr int kXcds = 8;
 
 // p - (one half of a packed pair of bf16): the multiply-adds of the dot product are exact here (p and its rounded

@@ -45,8 +45,9 @@ struct KernelArgs {
 // Tokens per split of a set of n tokens that n_splits workgroups share: the host fixes the number of splits from
 // the CAPACITY (lengths and list counts are device memory), so a set that fills half of its capacity would leave half
 // of its workgroups empty and the others with twice the work.  A whole number of 64-token rounds, at most `chunk`.
-// Parts below 32 KB of K and V each are not worth a workgroup (min_tokens, 16 384 / head_dim): 280 heads of dimension 64
-// with 766 listed entries in room for 1 563 came out 1 % slower in six parts of 128 than in three of 256.
+// Parts below min_tokens = 16 384 / head_dim -- 32 KB of K and as many of V in bf16, 64 KB in fp32 -- are left as they are: they
+// cost a workgroup its start and a partial.  (One measurement stands behind the figure: 280 heads of dimension 64 with 766
+// listed entries in room for 1 563, bf16, came out 1 % slower in six parts of 128 than in three of 256.)
 // Measured: managed decode step with 2 007 listed entries per head and room for 4 096 (batch 8, 32 heads, window
 // 4 096) 96.9 -> 71.4 us; sets that fill their capacity are cut as before.
 __device__ __forceinline__ int even_chunk(int chunk, int n, int n_splits, int min_tokens)

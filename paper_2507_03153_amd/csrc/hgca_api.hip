@@ -35,10 +35,11 @@ constexpr size_t kAlign = 256;
 #define HGCA_TARGET_WGS_SPARSE_SCORED 2048
 #endif
 
-// Workgroups the append-stage attention aims at per launch: what the device holds at once (two per compute unit).
-// Every workgroup writes a partial of 128 rows x d floats (64 KB, read again by the fold: the K/V bytes of four
-// 64-token steps), so splits are as long as filling the device allows.  Measured on the 8B shape, N = 32 (by a kernel
-// with 16-row tiles), with 512 / 768 / 1024 / 1536: window 55.7 / 61.0 / 66.0 / 74.8 us, pool 258.5 / 273.4 / 266.6 / 288.1 us.
+// Workgroups of the append-stage attention that the device holds at once (two per compute unit in bf16), and the most
+// shares it is cut into where the tokens do not ask for more (append_shares): every workgroup writes a partial of 128 rows x d
+// floats (64 KB, read again by the fold: the K/V bytes of four 64-token steps).  More than a full round of them was no
+// better even with long pools: 8B shape, N = 32, 512 / 768 / 1024 / 1536 workgroups of an earlier kernel (16-row tiles):
+// window 55.7 / 61.0 / 66.0 / 74.8 us, pool 258.5 / 273.4 / 266.6 / 288.1 us.
 #ifndef HGCA_APPEND_TARGET_WGS
 #define HGCA_APPEND_TARGET_WGS 512
 #endif
@@ -1043,7 +1044,7 @@ int hgca_append_attn(const hgca_shape *shape, const void *q, int32_t n_q, const 
     if (flags & ~(HGCA_APPEND_CAUSAL_TAIL | HGCA_APPEND_ONE_PART_P)) return HGCA_ERR_INVALID_ARG;
     if (shape->batch == 0 || n_q == 0) return HGCA_OK;
     if (!o_out || !lse_out || !aligned16(o_out)) return HGCA_ERR_INVALID_ARG;
-    // (KV head, block of 128 query rows) pairs are one grid dimension of the launch
+    // a limit of the interface (once the grid dimension of the (KV head, block of 128 query rows) pairs)
     if ((int64_t)shape->n_kv_heads * (((int64_t)n_q * group_of(shape) + 127) / 128) > 65535) return HGCA_ERR_UNSUPPORTED;
     const AppendWs w = append_layout(shape, n_q, tier->cap);
     if (!ws || ws_bytes < w.total || !aligned16(ws)) return HGCA_ERR_WORKSPACE;
@@ -1309,7 +1310,7 @@ int hgca_managed_append_step(const hgca_shape *shape, const hgca_cache_state *ca
     pool.cap = cache->pool_cap;
     if ((rc = check_append(shape, q, n_q, &window, true)) != HGCA_OK) return rc;
     if ((rc = check_append(shape, q, n_q, &pool, true)) != HGCA_OK) return rc;
-    if ((int64_t)shape->batch * n_q > 65535) return HGCA_ERR_UNSUPPORTED;        // the merge runs on batch * n_q rows
+    if ((int64_t)shape->batch * n_q > 65535) return HGCA_ERR_UNSUPPORTED;        // a limit of the interface
     if (!k_in || !v_in || !aligned16(k_in) || !aligned16(v_in) || !a_gpu || (cache->pool_cap > 0 && !a_cpu) || !o_out ||
         !lse_out || !aligned16(o_out))
         return HGCA_ERR_INVALID_ARG;
