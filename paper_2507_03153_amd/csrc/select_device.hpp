@@ -45,7 +45,6 @@ __device__ __forceinline__ float key_to_score(uint32_t key) {
 
 struct ScoreRange {
     float lo = INFINITY, hi = -INFINITY;
-    bool enough = false;                         // else the first scores of the row are still to be met
 };
 
 struct Binning {
@@ -380,7 +379,6 @@ struct Sel {
     // the function returns false before it has written any output and the caller runs select_row.  `lists` is the workgroup's dynamic LDS (list_bytes of it).
     // kSampleLoads 16-byte loads per thread make up the sample.
     static constexpr int kSampleChunk = 256;                     // scores of one run of the sample: what a wave takes with one load
-    static constexpr int kRangeLoads = 8;                        // 16-byte loads per thread that the byte mode's range is taken over
 
     // The fraction of a row the pre-filter asks for, raised by six standard deviations of its estimate from the sample.
     template <int kSampleLoads>
@@ -405,10 +403,9 @@ struct Sel {
     // together the estimate is a matter of how many groups the sample met, and the lists of single waves overflow; such rows
     // are left to the byte mode at once, which also takes the sample into its range (it met the first 32 768 scores only, and
     // a row that rises towards its end crowded the topmost bin).  32 rows of 122 880 scores, 2048 wanted, in groups of 64 / at
-    // the end of the row: 51.6 / 180 us with the filter tried in full, 41.2 / 43.2.  Rows below 65 536 scores, which the byte mode
-    // serves almost as fast as the filter, load the rest of that range with the sample (1.5 us): 32 rows of 61 004, 2048 wanted,
-    // no groups 26.4 us in the byte mode, 18.1 with the filter, 19.7 with the filter and the range; in groups of 64: 24.4, 33.6
-    // and 27.3.
+    // the end of the row: 51.6 / 180 us with the filter tried in full, 41.2 / 43.2; 32 rows of 61 004, 2048 wanted, in groups of
+    // 64: 33.6 and 28.3 (24.4 in the byte mode alone), no groups 18.1 and 18.8 (26.4).  To take all of that range with the sample
+    // saves a row that is left 0.9 us and costs one that is not as much.
     template <int kSampleLoads, bool GUARDED>
     static __device__ __forceinline__ bool select_row_prefiltered(const SelectArgs &a, SelShared &sh, float *lists,
                                                                   int list_bytes, const float *sc, int32_t *out, int n,
@@ -431,21 +428,12 @@ struct Sel {
             v[u] = load4_padded(sc, start + 4 * (j % (kSampleChunk / 4)), n);
         }
         float mn = INFINITY, mx = -INFINITY;
-        auto widen = [&](const float4 &x) {
-            const float s[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+        for (int u = 0; u < kSampleLoads; ++u) {
+            const float s[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
 #pragma unroll
             for (int e = 0; e < 4; ++e) { mx = fmaxf(mx, finite_or(s[e], -INFINITY)); mn = fminf(mn, finite_or(s[e], INFINITY)); }
-        };
-        const bool with_range = GUARDED && n < 65536;        // uniform: the range of the byte mode, too
-        if (with_range) {
-            float4 first[kRangeLoads];
-#pragma unroll
-            for (int u = 0; u < kRangeLoads; ++u) first[u] = load4_padded(sc, min(4 * (u * kSelBlock + tid), (n + 3) / 4 * 4), n);
-#pragma unroll
-            for (int u = 0; u < kRangeLoads; ++u) widen(first[u]);
         }
-#pragma unroll
-        for (int u = 0; u < kSampleLoads; ++u) widen(v[u]);
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) {
             mn = fminf(mn, __shfl_xor(mn, off, kWave));
@@ -459,7 +447,7 @@ struct Sel {
 #pragma unroll
         for (int i = 0; i < kSelWaves; ++i) { mn = fminf(mn, sh.wave_min[i]); mx = fmaxf(mx, sh.wave_max[i]); }
         if (!(mx > mn)) return false;                // a constant sample, or nothing finite in it (uniform)
-        if (GUARDED) range = ScoreRange{mn, mx, with_range};
+        if (GUARDED) range = ScoreRange{mn, mx};
         Binning bin;
         bin.lo = mn;
         bin.inv_w = (float)kBins / (mx - mn);
@@ -655,8 +643,8 @@ struct Sel {
 
         // ---- pass 0: range of the row; the padded row goes to LDS ---------------------------------------
         float mn = known.lo, mx = known.hi;
-        if (!(BINS && known.enough)) {
-            constexpr int U = kRangeLoads;           // 16-byte loads in flight per lane
+        {
+            constexpr int U = 8;                     // 16-byte loads in flight per lane
             const int n4 = padded / 4;
             // kCachedBins: the range is taken from the first kSelBlock * U * 4 scores and the sample only.  Any range gives a correct
             // selection (scores beyond it land in the end bins, and a threshold bin that turns out crowded is resolved
