@@ -565,7 +565,8 @@ int hgca_append_attn(const hgca_shape *shape, const void *q, int32_t n_q,
  * lse_window_out / lse_pool_out (fp32 [B, N, Hq], optional) receive the
  * per-tier lse that hgca_append_weights normalises with.  bf16 inputs only
  * (HGCA_ERR_UNSUPPORTED for fp32: use the per-tier calls).  ws needs
- * hgca_append_tiers_workspace_bytes(shape, n_q, window->cap, pool->cap). */
+ * hgca_append_tiers_workspace_bytes(shape, n_q, window->cap, pool->cap) bytes,
+ * which also serve calls whose tiers have smaller capacities. */
 size_t hgca_append_tiers_workspace_bytes(const hgca_shape *shape, int32_t n_q,
                                          int32_t window_cap, int32_t pool_cap);
 int hgca_append_attn_tiers(const hgca_shape *shape, const void *q, int32_t n_q,

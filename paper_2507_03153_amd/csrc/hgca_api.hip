@@ -1100,13 +1100,15 @@ struct TiersWs {
     int shares;
 };
 
-TiersWs tiers_layout(const hgca_shape *s, int32_t n_q, int64_t win_cap, int64_t pool_cap)
+// reusable: the size the queries return, which also serves tiers of smaller capacities (these may be cut into more shares).
+TiersWs tiers_layout(const hgca_shape *s, int32_t n_q, int64_t win_cap, int64_t pool_cap, bool reusable = false)
 {
     TiersWs w{};
     const int64_t tokens = (win_cap + kLineStep - 1) / kLineStep * kLineStep + (pool_cap + kLineStep - 1) / kLineStep * kLineStep;
     const int most = std::max(append_want_splits(s, n_q), n_splits_for(std::max<int64_t>(tokens, 1), kMaxAppendChunk));
     w.shares = append_shares(s, n_q, tokens, most);
-    const size_t rows = (size_t)s->batch * n_q * s->n_q_heads, slots = w.shares + 1;
+    const int64_t most_of_any = std::min<int64_t>(most, std::max<int64_t>(1, tokens / kLineStep));
+    const size_t rows = (size_t)s->batch * n_q * s->n_q_heads, slots = (reusable ? most_of_any : w.shares) + 1;
     size_t at = 0;
     w.o = at; at += align_up(rows * slots * s->head_dim * sizeof(float));
     w.m = at; at += align_up(rows * slots * sizeof(float));
@@ -1122,7 +1124,7 @@ TiersWs tiers_layout(const hgca_shape *s, int32_t n_q, int64_t win_cap, int64_t 
 size_t hgca_append_tiers_workspace_bytes(const hgca_shape *shape, int32_t n_q, int32_t window_cap, int32_t pool_cap)
 {
     if (check_shape(shape) != HGCA_OK || n_q < 0 || window_cap < 0 || pool_cap < 0) return 0;
-    return tiers_layout(shape, n_q, window_cap, pool_cap).total;
+    return tiers_layout(shape, n_q, window_cap, pool_cap, true).total;
 }
 
 namespace {
@@ -1261,11 +1263,11 @@ struct ManagedAppendWs {
     size_t attn_bytes;
 };
 
-ManagedAppendWs managed_append_layout(const hgca_shape *s, int32_t n_q, int32_t win_cap, int32_t pool_cap)
+ManagedAppendWs managed_append_layout(const hgca_shape *s, int32_t n_q, int32_t win_cap, int32_t pool_cap, bool reusable = false)
 {
     ManagedAppendWs w{};
     const size_t rows = (size_t)s->batch * n_q * s->n_q_heads;
-    w.attn_bytes = tiers_layout(s, n_q, win_cap, pool_cap).total;
+    w.attn_bytes = tiers_layout(s, n_q, win_cap, pool_cap, reusable).total;
     size_t at = 0;
     w.attn = at; at += align_up(w.attn_bytes);
     w.lse_w = at; at += align_up(rows * sizeof(float));
@@ -1283,7 +1285,7 @@ size_t hgca_managed_append_workspace_bytes(const hgca_shape *shape, const hgca_c
     host_only.batch = shape ? std::min(shape->batch, 0) : 0;     // sizing needs no device pointers
     if (!shape || !cache || n_q < 0 || n_q > 4096 || check_shape(shape) != HGCA_OK || check_cache(&host_only, cache, &c) != HGCA_OK)
         return 0;
-    return managed_append_layout(shape, n_q, c.win_cap, c.pool_cap).total;
+    return managed_append_layout(shape, n_q, c.win_cap, c.pool_cap, true).total;
 }
 
 int hgca_managed_append_step(const hgca_shape *shape, const hgca_cache_state *cache, const void *q, const void *k_in,

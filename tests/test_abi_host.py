@@ -511,20 +511,16 @@ def test_managed_decode_step_rejects_bad_arguments(hg):
     assert step(shape=hg.Shape(hg.BF16, 0, 8, 2, 128, 0.088), q=None, o=None, a=None) == hg.OK
 
 
-@pytest.mark.parametrize("shape,n_q,window,pool,shares", [
-    ((1, 32, 8, 128), 64, 1000, 7000, 16),                    # 16 units: one workgroup per compute unit
-    ((2, 4, 4, 128), 55, 836, 4759, 30),                      # 8 units, 89 steps in threes
-    ((2, 4, 4, 128), 100, 512, 5632, 32),
-    ((8, 32, 8, 128), 32, 4096, 28672, 8),                    # 64 units, long shares: two workgroups per compute unit
-    ((2, 32, 8, 128), 509, 4096, 28672, 2),
-    ((64, 64, 64, 128), 509, 4096, 28672, 1),                 # far more units than places
-], ids=["n64", "n55", "n100", "n32", "n509", "many_units"])
-def test_shares_of_an_append_call(hg, shape, n_q, window, pool, shares):
-    """The number of shares an append call is cut into, as its workspace shows it: shares + 1 slots of one output row and
-    two statistics per (sequence, query, head), and two log-sum-exp rows."""
-    b, hq, hkv, d = shape
-    rows = b * n_q * hq
-    got = hg.lib().hgca_append_tiers_workspace_bytes(ctypes.byref(hg.Shape(hg.BF16, b, hq, hkv, d, 1.0)), n_q, window, pool)
-    up = lambda x: (x + 255) // 256 * 256
-    want = [up(rows * n * d * 4) + 2 * up(rows * n * 4) + 2 * up(rows * 4) for n in range(1, 66)]
-    assert got in want and want.index(got) == shares
+
+def test_append_workspace_serves_smaller_tiers(hg):
+    """The workspace of the two-tier append call for given capacities is enough for tiers of any smaller ones (which may be cut
+    into more shares): no query for smaller capacities asks for more."""
+    import random
+    rng = random.Random(3)
+    size = hg.lib().hgca_append_tiers_workspace_bytes
+    for _ in range(3000):
+        hq, hkv = rng.choice([(4, 4), (32, 8), (64, 8), (40, 40), (16, 8)])
+        sh = hg.Shape(rng.choice([hg.F32, hg.BF16]), rng.choice([1, 2, 3, 8, 16]), hq, hkv, rng.choice([64, 128]), 1.0)
+        n, window, pool = rng.randint(1, 200), rng.randint(0, 8000), rng.randint(0, 60000)
+        w, p = rng.randint(0, window), rng.randint(0, pool)
+        assert size(ctypes.byref(sh), n, w, p) <= size(ctypes.byref(sh), n, window, pool), (n, (w, p), (window, pool))

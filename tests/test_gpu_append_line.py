@@ -62,3 +62,26 @@ def test_one_part_repeats_itself(gpu):  # noqa: F811
         out.append((o, lse))
     torch.cuda.synchronize()
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,N,W,P,shares", [
+    (1, 32, 8, 64, 1000, 7000, 16),                              # 16 units: one workgroup per compute unit
+    (2, 4, 4, 55, 836, 4759, 30),                                # 8 units, 89 steps in threes
+    (2, 4, 4, 100, 512, 5632, 32),
+    (8, 32, 8, 32, 4096, 28672, 8),                              # 64 units, long shares: two workgroups per compute unit
+    (2, 32, 8, 509, 4096, 28672, 2),
+], ids=["n64", "n55", "n100", "n32", "n509"])
+def test_number_of_shares(gpu, B, Hq, Hkv, N, W, P, shares):  # noqa: F811
+    """The number of shares a call is cut into, as the partials in its workspace show it: shares + 1 slots of a row of
+    outputs and two statistics per (sequence, query, head), every one of them written."""
+    torch, hgca, runner = gpu
+    d, dev = 128, "cuda:0"
+    z = lambda *s: torch.zeros(*s, dtype=torch.bfloat16, device=dev)
+    shape = hgca.Shape(hgca.BF16, B, Hq, Hkv, d, 1.0)
+    o, lse = torch.zeros(B, N, Hq, d, device=dev), torch.zeros(B, N, Hq, device=dev)
+    ws = hgca.append_tiers_workspace(shape, N, W, P, dev).fill_(255)             # NaN everywhere
+    win, pool = hgca.Tier(z(B, Hkv, W, d), z(B, Hkv, W, d), W), hgca.Tier(z(B, Hkv, P, d), z(B, Hkv, P, d), P)
+    hgca.append_attn_tiers(shape, z(B, N, Hq, d), win, pool, o, lse, ws)
+    torch.cuda.synchronize()
+    written = int((~torch.isnan(ws.view(torch.float32))).sum())
+    assert written == B * N * Hq * (shares + 1) * (d + 2)
