@@ -953,6 +953,8 @@ int line_shares(int64_t units, int64_t tokens, int most, int places, int overhea
 // only the smallest number of shares of each length in steps is looked at.  64 queries x 4 heads over 8 K tokens: 31.3 us
 // with 16 shares per unit (one workgroup per compute unit), 34.9 with 32; 55 queries over 5.6 K tokens 15.8 with 32, 18.6
 // with 45; 8 x 32 queries x 4 heads over 32 K tokens 260 with 8 (two workgroups per compute unit), 282 with 4.
+// (With the weights rounded to bf16, fewer shares also mean fewer weights that are exactly 1: 55 queries over 5.6 K tokens 6.7e-4
+// off with 30 shares, 6.3e-4 with 45.)
 // In fp32 a compute unit holds one workgroup, whose steps are several times as long as its start and its partial.
 int append_shares(const hgca_shape *s, int32_t n_q, int64_t tokens, int most)
 {
