@@ -30,63 +30,12 @@ __global__ __launch_bounds__(kBlock) void attn_split_kernel(KernelArgs a)
     SV::run(a, s_lds, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
-#ifndef HGCA_SCORE_PLAIN_STORES_FROM
-#define HGCA_SCORE_PLAIN_STORES_FROM 8           // heads per group from which the scores leave with ordinary stores
-#endif
-#ifndef HGCA_SCORE_WAVES
-#define HGCA_SCORE_WAVES 4
-#endif
-constexpr int kScoreWaves = HGCA_SCORE_WAVES;    // waves per workgroup of the score pass
-constexpr int kScoreBlock = kScoreWaves * kWave;
-
 template <int D, int G>
 __global__ __launch_bounds__(kScoreBlock) void pool_scores_mfma_kernel(KernelArgs a)
 {
-    __shared__ uint4 s_stage[kScoreWaves * Stage<D>::kWaveVecs];
-    __shared__ __attribute__((aligned(16))) float s_sc[G][kMaxScoreChunk];
-    __shared__ uint32_t s_row[kMaxScoreChunk];
-
-    const int chunk_id = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
-    const int n = tier_len(a.kv, b);
-    const int t0 = chunk_id * a.chunk;
-    if (t0 >= n) return;
-    const int nt = min(a.chunk, n - t0);
-    const int64_t bh0 = (int64_t)b * a.sh.n_q_heads + (int64_t)kvh * G;
-    const RowMap rows = make_row_map<false, kScoreBlock>(s_row, a.kv, a.sh.n_kv_heads, b, kvh, t0, nt, nullptr);
-    mfma_scores<D, G, kMaxScoreChunk, kScoreWaves>(a, s_stage, s_sc, bh0, nt, rows);
-    __syncthreads();
-
-    // coalesced streaming stores, 16 bytes per lane where the row alignment allows it
-    const int64_t cap = a.kv.cap;
-    const bool vec_ok = (cap % 4) == 0;
-    const int n4 = (nt + 3) / 4;
-    const int n_out = a.group_max ? 1 : G;       // rows written: one per KV head, or one per head
-    float *out = a.scores + (a.group_max ? bh0 / G : bh0) * cap + t0;
-    for (int i = threadIdx.x; i < n_out * n4; i += kScoreBlock) {
-        const int g = i / n4, j = 4 * (i % n4);
-        float4 v = *reinterpret_cast<const float4 *>(&s_sc[g][j]);
-        if (a.group_max) {
-#pragma unroll
-            for (int gg = 1; gg < G; ++gg) {
-                const float4 u = *reinterpret_cast<const float4 *>(&s_sc[gg][j]);
-                v = make_float4(fmaxf(v.x, u.x), fmaxf(v.y, u.y), fmaxf(v.z, u.z), fmaxf(v.w, u.w));
-            }
-        }
-        float *o = out + g * cap + j;
-        if (vec_ok && j + 3 < nt) {              // one 16-byte streaming store
-            const floatx4 vv = {v.x, v.y, v.z, v.w};
-            // Groups of 8 write an eighth of what they read; their scores leave with ordinary stores (measured on
-            // the 70B shape: 321 against 332 us per step), smaller groups with non-temporal ones (8B shape: 145
-            // against 148 us; MHA: 1040 against 1086 us)
-            if (G >= HGCA_SCORE_PLAIN_STORES_FROM) *reinterpret_cast<floatx4 *>(o) = vv;
-            else __builtin_nontemporal_store(vv, reinterpret_cast<floatx4 *>(o));
-        } else {
-            if (j < nt) o[0] = v.x;
-            if (j + 1 < nt) o[1] = v.y;
-            if (j + 2 < nt) o[2] = v.z;
-            if (j + 3 < nt) o[3] = v.w;
-        }
-    }
+    using SS = ScoreSplit<D, G>;
+    __shared__ __attribute__((aligned(16))) char s_lds[SS::kLdsBytes];
+    SS::run(a, s_lds, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 template <int D, int G>

@@ -4,9 +4,28 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "hgca_device.hpp"
 
 namespace hgca {
+
+// Allows launches of a kernel with up to `bytes` of dynamic LDS, once per device (the attribute belongs to a device's copy of
+// the kernel; the limit without it is 64 KiB).
+template <auto Kernel>
+hipError_t lift_lds_limit(int bytes)
+{
+    constexpr int kMaxDevices = 64;
+    static std::atomic<bool> lifted[kMaxDevices];                // zero-initialised
+    int dev = 0;
+    hipError_t rc = hipGetDevice(&dev);
+    if (rc != hipSuccess) return rc;
+    const bool tracked = dev >= 0 && dev < kMaxDevices;
+    if (tracked && lifted[dev].load(std::memory_order_acquire)) return hipSuccess;
+    rc = hipFuncSetAttribute(reinterpret_cast<const void *>(Kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (rc == hipSuccess && tracked) lifted[dev].store(true, std::memory_order_release);
+    return rc;
+}
 
 constexpr int kMaxChunk = 512;     // tokens of one split (one workgroup) at most
 constexpr int kMaxScoreChunk = 128;   // same for the MFMA score pass, which wants many small workgroups
@@ -99,6 +118,15 @@ struct SelectArgs {
     float *sel_scores;     // optional [B, Hq, k_max]: score of every kept entry, in idx order
 };
 hipError_t launch_select(const SelectArgs &a, hipStream_t s);
+
+// A short decode step in two launches (same results as the launches above up to the order of the fp32 sums):
+// the window's split kernels and the score pass (no group_max), ...
+hipError_t launch_window_scores(int dtype, int head_dim, const AttnArgs &dense, const ScoreArgs &scores, hipStream_t s);
+// ... and per row the selection (idx, cnt and sel_scores are written as by launch_select), attention over the selected V rows
+// and the fold with the window's partials.  Lists of up to kMaxShortList entries; a.kv is the pool with its V rows.
+constexpr int kMaxShortList = 16384;
+hipError_t launch_select_attend(int dtype, int head_dim, const SelectArgs &a, const Partials &window, void *o, int o_dtype,
+                                float *lse, hipStream_t s);
 
 // The window's split kernels and the per-head gather's split kernels (launch_attn_partial_dense and
 // launch_attn_partial_gather with the same arguments) as one launch; bf16, groups of 1, 2 or 4, per-head lists.

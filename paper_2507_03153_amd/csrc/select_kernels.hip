@@ -32,7 +32,6 @@
 #include "select_device.hpp"
 
 #include <algorithm>
-#include <atomic>
 
 namespace hgca {
 
@@ -87,19 +86,8 @@ hipError_t launch_select_block(const SelectArgs &a, int64_t rows, int max_cache_
     const int cache_floats = padded <= max_cache_floats ? padded : 0;
     // longer rows, up to four times the large cache: one byte per score
     const int cache_bytes = cache_floats == 0 && padded <= 4 * kMaxCacheFloats ? padded : 0;
-    // once per device: lift the dynamic LDS limit of the kernel (the attribute belongs to a device's copy of it)
-    constexpr int kMaxDevices = 64;
-    static std::atomic<bool> limit_lifted[kMaxDevices];          // zero-initialised
-    int dev = 0;
-    hipError_t rc = hipGetDevice(&dev);
+    const hipError_t rc = lift_lds_limit<select_topk_kernel<BLOCK>>(kMaxCacheFloats * (int)sizeof(float));
     if (rc != hipSuccess) return rc;
-    const bool tracked = dev >= 0 && dev < kMaxDevices;
-    if (!tracked || !limit_lifted[dev].load(std::memory_order_acquire)) {
-        rc = hipFuncSetAttribute(reinterpret_cast<const void *>(select_topk_kernel<BLOCK>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, kMaxCacheFloats * (int)sizeof(float));
-        if (rc != hipSuccess) return rc;
-        if (tracked) limit_lifted[dev].store(true, std::memory_order_release);
-    }
     // rows that do not fit as fp32 try the pre-filter first when the workgroup is alone on its unit: its lists take
     // the whole dynamic allocation (the byte cache of the general path, if that runs after all, uses the same memory)
     // (the small workgroups, when asked to, keep their lists in the allocation of their byte cache)
