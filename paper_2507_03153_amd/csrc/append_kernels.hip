@@ -21,6 +21,8 @@
 #include "hgca_launch.hpp"
 #include "row_map.hpp"
 
+#include <type_traits>
+
 namespace hgca {
 
 namespace {
@@ -233,6 +235,7 @@ __device__ __forceinline__ floatx16 score_tile_f32(Piece piece, const uint4 (&b)
 }
 
 constexpr int kXcds = 8;
+constexpr int kWAhead = 2;                       // query pieces of the weights pass that are read ahead
 constexpr int kAhead = 2;                        // slices of the score contraction whose K pieces are read ahead
 
 // The sums of a wave's rows over the tier positions [begin, end) -- of a row only [begin, row_end) -- on the vector
@@ -607,6 +610,9 @@ __global__ __launch_bounds__(kAttnBlock, sizeof(T) == 2 ? 2 : 1) void append_att
 // The number of rows may be any: a row that does not exist weighs nothing through its shift, so only tiles that the causal
 // limit cuts compare, a compare and a select per score (with a test per score in every block that is not full, 31 queries
 // x 4 heads took 147 us where 32 took 105; now 101 and 101).
+// A tile's query pieces come from LDS well before their products, and a pair of row tiles is weighed beside the products of the
+// next: with every read right before its use each of the 32 matrix instructions of a tile waited for LDS (whole turns: 8 x 32
+// queries 387 -> 380 us, 4 x 128 queries 697 -> 677, 3 x 55 queries on 17 K tokens 173.5 -> 170.8; 8 x 9 queries unchanged).
 // Both tiers of 8 x 32 queries on 32 K tokens, 32 / 8 heads: 150 us (tokens in registers, rows over the lanes: two lane
 // exchanges per score and a barrier per 64 tokens, 2048-token workgroups that came out at 1.2 rounds) -> 117 us.  The
 // loads alone take 101 us (124 us without the streaming policy; more of them in flight, 12 or 15 waves, change nothing).
@@ -777,57 +783,81 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 512 : 256, sizeof(T) == 2 ? 2 : 1)
                     auto q_piece = [&](int x, int kk) {
                         return *reinterpret_cast<const uint4 *>(s_q + x * 32 * S::kRowBytes + (frag0 ^ (32 * kk)));
                     };
-                    auto scores = [&](int x) {
-                        floatx16 c{};
-                        if constexpr (F32) {
-                            c = score_tile_f32<KK>([&](int kk) { return q_piece(x, kk); }, kf);
-                        } else {
+                    auto scores = [&](int x) { return score_tile_f32<KK>([&](int kk) { return q_piece(x, kk); }, kf); };
+                    auto shift_of = [&](int x, int q4) {         // of rows 32 x + 8 q4 + 4 hw .. + 3
+                        return *reinterpret_cast<const float4 *>(s_shift + 32 * x + 8 * q4 + 4 * hw);
+                    };
+                    auto weigh_quad = [&](floatx16 &c, int q4, const float4 &sh) {
+                        const float s4[4] = {sh.x, sh.y, sh.z, sh.w};
 #pragma unroll
-                            for (int kk = 0; kk < KK; ++kk) c = score_mfma(q_piece(x, kk), kf[kk], c);
-                        }
-                        return c;
+                        for (int e = 0; e < 4; ++e)
+                            c[4 * q4 + e] = F32 ? expf(fmaf(c[4 * q4 + e], scale, s4[e]))
+                                                : __builtin_amdgcn_exp2f(fmaf(c[4 * q4 + e], scale, s4[e]));
                     };
                     auto weigh = [&](int x, floatx16 &c) {
 #pragma unroll
-                        for (int q4 = 0; q4 < 4; ++q4) {
-                            const float4 sh = *reinterpret_cast<const float4 *>(s_shift + 32 * x + 8 * q4 + 4 * hw);
-                            const float s4[4] = {sh.x, sh.y, sh.z, sh.w};
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                c[4 * q4 + e] = F32 ? expf(fmaf(c[4 * q4 + e], scale, s4[e]))
-                                                    : __builtin_amdgcn_exp2f(fmaf(c[4 * q4 + e], scale, s4[e]));
-                        }
+                        for (int q4 = 0; q4 < 4; ++q4) weigh_quad(c, q4, shift_of(x, q4));
                     };
-                    // two row tiles side by side: their matrix instructions take turns, and the vector instructions of one
-                    // pair run beside the matrix instructions of the other
-                    auto pair = [&](int x, floatx16 &c0, floatx16 &c1) {
-                        c0 = floatx16{};
-                        c1 = floatx16{};
+                    // NP row tiles from x on, two at a time side by side so that their matrix instructions take turns.  The
+                    // query pieces are read kWAhead before the instructions that take them (left alone the scheduler reads
+                    // each right before its use, and every matrix instruction waits for LDS); a pair of tiles is weighed
+                    // beside the products of the next pair.
+                    auto tiles_of = [&](int x, auto count, floatx16 (&c)[decltype(count)::value]) {
+                        constexpr int NP = decltype(count)::value, ALL = NP * KK, W = NP > 1 ? 2 : 1;
                         if constexpr (F32) {
-                            c0 = scores(x);
-                            c1 = scores(x + 1);
-                        } else {
 #pragma unroll
-                            for (int kk = 0; kk < KK; ++kk) {
-                                c0 = score_mfma(q_piece(x, kk), kf[kk], c0);
-                                c1 = score_mfma(q_piece(x + 1, kk), kf[kk], c1);
+                            for (int i = 0; i < NP; ++i) {
+                                c[i] = scores(x + i);
+                                weigh(x + i, c[i]);
                             }
+                        } else {
+                            uint4 qf[ALL];
+                            auto read = [&](int i) {             // the i-th piece in the order of use
+                                if (i < ALL) qf[i] = q_piece(x + i / (W * KK) * W + i % W, i / W % KK);
+                            };
+#pragma unroll
+                            for (int i = 0; i < kWAhead; ++i) read(i);
+                            constexpr int QUADS = 4 * W > KK ? 4 * W / KK : 1;           // weighed beside a slice's products
+                            float4 sh[4 * W];
+#pragma unroll
+                            for (int t0 = 0; t0 < NP; t0 += W) {
+#pragma unroll
+                                for (int i = 0; i < W; ++i) c[t0 + i] = floatx16{};
+#pragma unroll
+                                for (int kk = 0; kk < KK; ++kk) {
+                                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                                    for (int i = 0; i < W; ++i) read(W * (t0 / W * KK + kk) + i + kWAhead);
+                                    if (t0 > 0 && kk * QUADS < 4 * W) {
+#pragma unroll
+                                        for (int i = 0; i < QUADS; ++i) {
+                                            const int j = kk * QUADS + i;
+                                            weigh_quad(c[t0 - W + j / 4], j % 4, sh[j]);
+                                        }
+                                    }
+#pragma unroll
+                                    for (int i = 0; i < W; ++i)
+                                        c[t0 + i] = score_mfma(qf[W * (t0 / W * KK + kk) + i], kf[kk], c[t0 + i]);
+                                    if (kk == KK - 1) {          // the pair's shifts, for its turn to be weighed
+#pragma unroll
+                                        for (int j = 0; j < 4 * W; ++j) sh[j] = shift_of(x + t0 + j / 4, j % 4);
+                                    }
+                                }
+                            }
+                            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                            for (int j = 0; j < 4 * W; ++j) weigh_quad(c[NP - W + j / 4], j % 4, sh[j]);
                         }
-                        weigh(x, c0);
-                        weigh(x + 1, c1);
                     };
                     auto add = [&](const floatx16 &c) {          // the head of row r is r % G
 #pragma unroll
                         for (int r = 0; r < 16; ++r) sum[r % NS] += c[r];
                     };
                     if (live == RT && spread == 1 && tok0 + kWTile <= seen_by_all) {     // uniform over the wave: straight-line code
+                        floatx16 c[RT];
+                        tiles_of(0, std::integral_constant<int, RT>{}, c);
 #pragma unroll
-                        for (int x = 0; x < RT; x += 2) {
-                            floatx16 c0, c1;
-                            pair(x, c0, c1);
-                            add(c0);
-                            add(c1);
-                        }
+                        for (int x = 0; x < RT; ++x) add(c[x]);
                     } else {
                         // Row r sees the lane's token iff r / G >= token - (len - n_q): the first such row, relative to the
                         // first row that the lane holds.  Tiles that all rows see whole get a limit nothing is below.
@@ -841,19 +871,19 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 512 : 256, sizeof(T) == 2 ? 2 : 1)
                         int x = part;
 #pragma unroll 1
                         for (; spread == 1 && x + 1 < live; x += 2) {
-                            floatx16 c0, c1;
-                            pair(x, c0, c1);
-                            mask(x, c0);
-                            mask(x + 1, c1);
-                            add(c0);
-                            add(c1);
+                            floatx16 c[2];
+                            tiles_of(x, std::integral_constant<int, 2>{}, c);
+                            mask(x, c[0]);
+                            mask(x + 1, c[1]);
+                            add(c[0]);
+                            add(c[1]);
                         }
 #pragma unroll 1
                         for (; x < live; x += spread) {
-                            floatx16 c = scores(x);
-                            weigh(x, c);
-                            mask(x, c);
-                            add(c);
+                            floatx16 c[1];
+                            tiles_of(x, std::integral_constant<int, 1>{}, c);
+                            mask(x, c[0]);
+                            add(c[0]);
                         }
                     }
 #pragma unroll
