@@ -218,6 +218,14 @@ struct SplitValu {
     // lds: kLdsBytes, 16-byte aligned; a workgroup of kBlock threads
     static __device__ __forceinline__ void run(const KernelArgs &a, char *lds, int split, int unit, int b)
     {
+        constexpr bool GATHER = MODE == kGather || MODE == kGatherScored || MODE == kGatherGroup;
+        const int64_t list = MODE == kGatherGroup ? (int64_t)b * a.sh.n_kv_heads + unit : (int64_t)b * a.sh.n_q_heads + unit;
+        run_of(a, lds, split, unit, b, GATHER ? (a.kv.cap > 0 ? min(a.cnt[list], a.k_max) : 0) : tier_len(a.kv, b));
+    }
+
+    // the same for a set of n tokens
+    static __device__ __forceinline__ void run_of(const KernelArgs &a, char *lds, int split, int unit, int b, int n)
+    {
         constexpr int EPL = Elem<T>::kPerLoad;
         constexpr int LPR = D / EPL;
         constexpr int RPW = kWave / LPR;
@@ -239,7 +247,6 @@ struct SplitValu {
 
         const int64_t bh0 = (int64_t)b * Hq + h0;
         const int64_t list = PER_HEAD_LIST ? bh0 : (int64_t)b * Hkv + unit;      // row of idx / cnt
-        const int n = GATHER ? (a.kv.cap > 0 ? min(a.cnt[list], a.k_max) : 0) : tier_len(a.kv, b);
         const int chunk = MODE == kScores ? a.chunk : even_chunk(a.chunk, n, a.part.n_splits, 16384 / D);
         const int t0 = split * chunk;
 

@@ -1,6 +1,8 @@
 // Independent kernels of a decode step as ONE launch.
 #include "attn_device.hpp"
 
+#include <type_traits>
+
 namespace hgca {
 
 namespace {
@@ -13,6 +15,8 @@ namespace {
 // workgroups drain (or the other way round).  Roles by blockIdx; measured on the 8B shape: with K and V gathered
 // (270 MB against the window's 134 MB) the gather's workgroups go first (68.0 against 69.2 us per step), with V
 // alone gathered (135 MB) the window's (145.8 against 148.3 us per step with a selection).
+// fp32 takes both parts on the vector units; there and in small steps a launch saved is what counts (managed decode loop of one
+// sequence, fp32, 32 / 8 heads of 64, per step: insert, window, gather and tail 24.8 us, in two launches 18.2).
 #ifndef HGCA_DG_OCC
 #define HGCA_DG_OCC 5                            // waves per SIMD the register budget is set for
 #endif
@@ -24,14 +28,16 @@ namespace {
 #define HGCA_DG_UNROLL 4                         // V loads a lane of a window split keeps in flight
 #endif
 
-template <int D, int G, int GMODE, int LD>
-__global__ __launch_bounds__(kBlock, HGCA_DG_OCC) void dense_gather_kernel(KernelArgs da, KernelArgs ga, int n_dense,
+template <typename T, int D, int G, int GMODE, int LD>
+__global__ __launch_bounds__(kBlock, sizeof(T) == 2 && G < 8 ? HGCA_DG_OCC : 1) void dense_gather_kernel(KernelArgs da, KernelArgs ga, int n_dense,
                                                                           int dense_splits, int gather_splits,
                                                                           int gather_first, const char *k_new,
                                                                           const char *v_new)
 {
-    using DS = DenseSplit<D, G, kBlock, HGCA_DG_UNROLL, LD>;   // LDS sized for window splits of up to LD tokens
-    using GS = SplitValu<bf16_t, D, 1, GMODE, HGCA_DG_GATHER_UNROLL>;
+    constexpr bool F32 = sizeof(T) == 4;
+    // bf16: the window on the matrix cores, LDS sized for splits of up to LD tokens; fp32: on the vector units
+    using DS = std::conditional_t<F32, SplitValu<T, D, G, kDense>, DenseSplit<D, G, kBlock, HGCA_DG_UNROLL, LD>>;
+    using GS = SplitValu<T, D, 1, GMODE, F32 ? kUnroll : HGCA_DG_GATHER_UNROLL>;
     constexpr int kLds = DS::kLdsBytes > GS::kLdsBytes ? DS::kLdsBytes : GS::kLdsBytes;
     __shared__ __attribute__((aligned(16))) char s_lds[kLds];
     // the part with more bytes to move takes the lower block numbers and starts first (the other fills in behind it)
@@ -54,7 +60,7 @@ __global__ __launch_bounds__(kBlock, HGCA_DG_OCC) void dense_gather_kernel(Kerne
         if (takes_token && len >= t0 && len < t0 + chunk) {      // uniform over the workgroup
             // this split owns the token's position: its K and V rows go into the window's block, then the split
             // reads them back like any other row (no other workgroup of the launch touches that position)
-            constexpr int kPieces = D * 2 / 16, kRow = D * 2;
+            constexpr int kRow = D * (int)sizeof(T), kPieces = kRow / 16;
             if (threadIdx.x < 2 * kPieces) {
                 const bool is_v = threadIdx.x >= kPieces;
                 const int piece = threadIdx.x % kPieces;
@@ -66,11 +72,12 @@ __global__ __launch_bounds__(kBlock, HGCA_DG_OCC) void dense_gather_kernel(Kerne
             }
             __syncthreads();
         }
-        if (t0 >= n) {
-            write_empty_partial<D, G>(da.part, (int64_t)b * da.sh.n_q_heads + (int64_t)kvh * G, split);
-            return;
+        if constexpr (F32) {
+            DS::run_of(da, s_lds, split, kvh, b, n);
+        } else {
+            if (t0 >= n) write_empty_partial<D, G>(da.part, (int64_t)b * da.sh.n_q_heads + (int64_t)kvh * G, split);
+            else DS::run(da, s_lds, split, kvh, b, t0, min(chunk, n - t0));
         }
-        DS::run(da, s_lds, split, kvh, b, t0, min(chunk, n - t0));
         return;
     }
     GS::run(ga, s_lds, u % gather_splits, (u / gather_splits) % ga.sh.n_q_heads, u / (gather_splits * ga.sh.n_q_heads));
@@ -80,7 +87,7 @@ __global__ __launch_bounds__(kBlock, HGCA_DG_OCC) void dense_gather_kernel(Kerne
 
 bool dense_gather_fusable(int dtype, int head_dim, int group)
 {
-    return dtype == 1 && (head_dim == 64 || head_dim == 128) && (group == 1 || group == 2 || group == 4);
+    return (dtype == 0 || dtype == 1) && (head_dim == 64 || head_dim == 128) && (group == 1 || group == 2 || group == 4 || group == 8);
 }
 
 hipError_t launch_dense_gather(int dtype, int head_dim, const AttnArgs &dense, const AttnArgs &gather, hipStream_t s,
@@ -111,23 +118,26 @@ hipError_t launch_dense_gather(int dtype, int head_dim, const AttnArgs &dense, c
     const dim3 grid((unsigned)(n_dense + n_gather)), block(kBlock);
     const int g = dense.sh.group;
     // the window's splits size the launch's LDS: the common 256-token splits leave room for seven workgroups per unit
-#define HGCA_DG_LAUNCH(D, G, GMODE, LD, FIRST)                                                                      \
-    hipLaunchKernelGGL((dense_gather_kernel<D, G, GMODE, LD>), grid, block, 0, s, da, ga, (int)n_dense,             \
+#define HGCA_DG_LAUNCH(T, D, G, GMODE, LD, FIRST)                                                                   \
+    hipLaunchKernelGGL((dense_gather_kernel<T, D, G, GMODE, LD>), grid, block, 0, s, da, ga, (int)n_dense,          \
                        dense.part.n_splits, gather.part.n_splits, FIRST, static_cast<const char *>(k_new),        \
                        static_cast<const char *>(v_new))
 #define HGCA_DG_CASE(D, G)                                                                                          \
     if (head_dim == D && g == G) {                                                                                  \
-        if (gather.sel_scores) {                                                                                    \
-            if (dense.chunk <= 256) HGCA_DG_LAUNCH(D, G, kGatherScored, 256, 0);                                    \
-            else HGCA_DG_LAUNCH(D, G, kGatherScored, kMaxChunk, 0);                                                 \
+        if (dtype == 0) {                                                                                           \
+            if (gather.sel_scores) HGCA_DG_LAUNCH(float, D, G, kGatherScored, kMaxChunk, 0);                        \
+            else HGCA_DG_LAUNCH(float, D, G, kGather, kMaxChunk, 1);                                                \
+        } else if (gather.sel_scores) {                                                                             \
+            if (dense.chunk <= 256) HGCA_DG_LAUNCH(bf16_t, D, G, kGatherScored, 256, 0);                            \
+            else HGCA_DG_LAUNCH(bf16_t, D, G, kGatherScored, kMaxChunk, 0);                                         \
         } else {                                                                                                    \
-            if (dense.chunk <= 256) HGCA_DG_LAUNCH(D, G, kGather, 256, 1);                                          \
-            else HGCA_DG_LAUNCH(D, G, kGather, kMaxChunk, 1);                                                       \
+            if (dense.chunk <= 256) HGCA_DG_LAUNCH(bf16_t, D, G, kGather, 256, 1);                                  \
+            else HGCA_DG_LAUNCH(bf16_t, D, G, kGather, kMaxChunk, 1);                                               \
         }                                                                                                           \
         return hipGetLastError();                                                                                   \
     }
-    HGCA_DG_CASE(64, 1) HGCA_DG_CASE(64, 2) HGCA_DG_CASE(64, 4)
-    HGCA_DG_CASE(128, 1) HGCA_DG_CASE(128, 2) HGCA_DG_CASE(128, 4)
+    HGCA_DG_CASE(64, 1) HGCA_DG_CASE(64, 2) HGCA_DG_CASE(64, 4) HGCA_DG_CASE(64, 8)
+    HGCA_DG_CASE(128, 1) HGCA_DG_CASE(128, 2) HGCA_DG_CASE(128, 4) HGCA_DG_CASE(128, 8)
 #undef HGCA_DG_CASE
 #undef HGCA_DG_LAUNCH
     return hipErrorInvalidValue;

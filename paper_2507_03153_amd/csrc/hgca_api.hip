@@ -138,13 +138,38 @@ int pick_chunk(int64_t n, int64_t units, int target, int max_chunk = kMaxChunk)
 
 int n_splits_for(int64_t n, int chunk) { return (int)((n + chunk - 1) / chunk); }
 
+// Whether the window's splits and the sparse part's splits share a launch, and the window split's tokens there (below).
+// fp32 and groups of up to 4 always do.  Measured, two launches : one, us: fp32 steady steps 1 sequence, 32 / 8 heads of 128,
+// window 2048, 1900 listed 29.3 : 22.6, 4 sequences 63.9 : 60.4; decode loops, which insert the token in the same launch, per
+// step 37.2 : 29.4 and 58.2 : 53.2.  The window body of groups of 8 leaves room for two (head_dim 128) or three workgroups per
+// unit, so the launch pays where the gather's workgroups come to about one round, or two with a token to insert: steady, heads of
+// 128, 256 workgroups 18.2 : 15.8, 960 19.0 : 22.1, 1920 25.3 : 35.0; heads of 64, 960 17.9 : 15.6, 1920 19.6 : 22.1; loops, heads of
+// 128, 640 workgroups 24.5 : 18.2 per step, 1280 29.3 : 29.7, 2048 38.5 : 39.8; heads of 64, 2048 25.7 : 20.9 and 43.2 : 36.2, 8700 137.6 : 144.6.
+bool shares_launch(const hgca_shape *s, int64_t window, int64_t pool, int64_t k_max, int gather_chunk, bool scored, bool token)
+{
+    if (!HGCA_FUSE_DENSE_GATHER || window <= 0 || pool <= 0 || k_max <= 0 ||
+        !dense_gather_fusable(s->dtype, s->head_dim, group_of(s)))
+        return false;
+    const int64_t wgs = (int64_t)s->batch * s->n_q_heads * n_splits_for(k_max, gather_chunk);
+    const int64_t window_wgs = (int64_t)s->batch * s->n_kv_heads * n_splits_for(window, kMinChunk);
+    if (wgs + window_wgs > int64_t(1) << 23) return false;       // threads of a flat grid are counted in 32 bits
+    if (s->dtype == HGCA_F32 || group_of(s) < 8) return true;
+    if (scored) return false;
+    return wgs <= (s->head_dim == 64 ? (token ? 4096 : 1024) : (token ? 1024 : 512));
+}
+
 // Tokens per window split: in a launch of its own the window wants about HGCA_TARGET_WGS_DENSE workgroups; in a launch
 // it shares with the sparse part's splits, which fill the device anyway, longer splits (half as many partials to write
 // and fold) are better.  Measured on the 8B shape: full step 145.2 -> 143.8 us, steady 67.9 -> 67.6 us; on its own the
 // window is 1 us slower with them.
-int dense_chunk(const hgca_shape *s, int64_t cap, bool shares_launch)
+// fp32 beside a gather of K and V, whose splits are as long as the window's on the vector units: shorter ones as long as the units
+// do not fill the device by themselves (4 sequences, 64 / 8 heads of 128, window 2048, 1900 listed: 97.3 -> 84.5 us; 8 sequences of 40
+// heads 79.4 -> 85.1).
+int dense_chunk(const hgca_shape *s, int64_t cap, bool shared, bool scored = true)
 {
-    return pick_chunk(cap, (int64_t)s->batch * s->n_kv_heads, shares_launch ? HGCA_TARGET_WGS_DENSE_SHARED : HGCA_TARGET_WGS_DENSE);
+    const int64_t units = (int64_t)s->batch * s->n_kv_heads;
+    if (s->dtype == HGCA_F32 && !scored && units <= 256) shared = false;
+    return pick_chunk(cap, units, shared ? HGCA_TARGET_WGS_DENSE_SHARED : HGCA_TARGET_WGS_DENSE);
 }
 
 // Tokens per workgroup of the score pass over a pool of `cap` tokens.  Groups of 8 heads take half the tokens per
@@ -658,8 +683,8 @@ int hgca_hybrid_decode_step(const hgca_shape *shape, const void *q, const hgca_k
     }
     // The window's splits and the sparse part's splits are two streaming passes that need nothing from each other:
     // where the shapes allow they share one launch (after the selection), so the second needs no ramp-up of its own.
-    const bool fuse_gather = HGCA_FUSE_DENSE_GATHER && pool->cap > 0 && window->cap > 0 && k_max > 0 &&
-                             dense_gather_fusable(shape->dtype, shape->head_dim, group_of(shape));
+    const int gather_chunk = pick_chunk(k_max, (int64_t)shape->batch * shape->n_q_heads, HGCA_TARGET_WGS_SPARSE_SCORED);
+    const bool fuse_gather = shares_launch(shape, window->cap, pool->cap, k_max, gather_chunk, true, false);
     da.chunk = dense_chunk(shape, window->cap, fuse_gather);
     da.part = partials_at(ws_dense, wd, n_splits_for(window->cap, da.chunk));
 
@@ -678,7 +703,7 @@ int hgca_hybrid_decode_step(const hgca_shape *shape, const void *q, const hgca_k
     ga.cnt = cnt_out;
     ga.sel_scores = sel;
     ga.k_max = k_max;
-    ga.chunk = pick_chunk(k_max, (int64_t)shape->batch * shape->n_q_heads, HGCA_TARGET_WGS_SPARSE_SCORED);
+    ga.chunk = gather_chunk;
     ga.part = partials_at(ws_sparse, wsp, std::max(1, n_splits_for(k_max, ga.chunk)));
     if (fuse_gather) rc = from_hip(launch_dense_gather(shape->dtype, shape->head_dim, da, ga, s));
     else rc = from_hip(launch_attn_partial_gather(shape->dtype, shape->head_dim, ga, s));
@@ -713,9 +738,10 @@ int hgca_hybrid_decode_step_selected(const hgca_shape *shape, const void *q, con
     da.sh = to_dev(shape);
     da.q = q;
     da.kv = to_dev(window);
-    const bool one_launch = HGCA_FUSE_DENSE_GATHER && window->cap > 0 && k_max > 0 && pool->cap > 0 &&
-                            dense_gather_fusable(shape->dtype, shape->head_dim, group_of(shape));
-    da.chunk = dense_chunk(shape, window->cap, one_launch);
+    const int gather_chunk = pick_chunk(k_max, (int64_t)shape->batch * shape->n_q_heads, HGCA_TARGET_WGS_SPARSE);
+    const bool scored = sel_scores != nullptr;
+    const bool one_launch = shares_launch(shape, window->cap, pool->cap, k_max, gather_chunk, scored, false);
+    da.chunk = dense_chunk(shape, window->cap, one_launch, scored);
     da.part = partials_at(ws_dense, wd, n_splits_for(window->cap, da.chunk));
     AttnArgs ga{};
     ga.sh = da.sh;
@@ -725,7 +751,7 @@ int hgca_hybrid_decode_step_selected(const hgca_shape *shape, const void *q, con
     ga.cnt = cnt;
     ga.sel_scores = sel_scores;
     ga.k_max = k_max;
-    ga.chunk = pick_chunk(k_max, (int64_t)shape->batch * shape->n_q_heads, HGCA_TARGET_WGS_SPARSE);
+    ga.chunk = gather_chunk;
     ga.part = partials_at(ws_sparse, wsp, std::max(1, n_splits_for(k_max, ga.chunk)));
     // gpu_attention over the window and cpu_attention over the listed entries: one launch where the shapes allow
     if (one_launch) {
@@ -861,11 +887,12 @@ int hgca_managed_decode_step(const hgca_shape *shape, const hgca_cache_state *ca
     const int64_t rows = (int64_t)shape->batch * shape->n_q_heads;
     const int32_t row_bytes = shape->head_dim * (shape->dtype == HGCA_BF16 ? 2 : 4);
 
-    const bool one_launch = HGCA_FUSE_DENSE_GATHER && window.cap > 0 && cache->k_max > 0 && cache->pool_cap > 0 &&
-                            dense_gather_fusable(shape->dtype, shape->head_dim, group_of(shape));
+    const bool token_may_join = HGCA_FUSE_KV_APPEND && HGCA_FUSE_DECODE_TAIL;
+    const int gather_chunk = pick_chunk(cache->k_max, rows, HGCA_TARGET_WGS_SPARSE);
+    const bool one_launch = shares_launch(shape, window.cap, cache->pool_cap, cache->k_max, gather_chunk, false, token_may_join);
     // Alg. 2: KV_gpu' = concat(KV_gpu, KV_in): a launch of its own, or (token_joins_in_split) the window split that
     // owns the token's position writes its rows and the step's last launch stores the new length
-    const bool token_joins_in_split = HGCA_FUSE_KV_APPEND && HGCA_FUSE_DECODE_TAIL && one_launch;
+    const bool token_joins_in_split = token_may_join && one_launch;
     if (!token_joins_in_split &&
         (rc = from_hip(launch_kv_append(c, k_in, v_in, nullptr, shape->batch, shape->n_kv_heads, row_bytes, 1, s))) != HGCA_OK)
         return rc;
@@ -874,7 +901,7 @@ int hgca_managed_decode_step(const hgca_shape *shape, const hgca_cache_state *ca
     da.sh = to_dev(shape);
     da.q = q;
     da.kv = to_dev(&window);
-    da.chunk = dense_chunk(shape, window.cap, one_launch);
+    da.chunk = dense_chunk(shape, window.cap, one_launch, false);
     da.part = partials_at(ws_dense, wd, n_splits_for(window.cap, da.chunk));
     da.raw_scores = a_gpu;
     // cpu_attention over KV_ctx: split kernels over each head's list of salient pool positions
@@ -885,7 +912,7 @@ int hgca_managed_decode_step(const hgca_shape *shape, const hgca_cache_state *ca
     ga.idx = cache->ctx_idx;
     ga.cnt = cache->ctx_cnt;
     ga.k_max = cache->k_max;
-    ga.chunk = pick_chunk(cache->k_max, rows, HGCA_TARGET_WGS_SPARSE);
+    ga.chunk = gather_chunk;
     ga.part = partials_at(ws_sparse, wsp, std::max(1, n_splits_for(cache->k_max, ga.chunk)));
     // the two parts need nothing from each other: one launch where the shapes allow
     if (one_launch) {

@@ -129,7 +129,7 @@ hipError_t launch_select_attend(int dtype, int head_dim, const SelectArgs &a, co
                                 float *lse, hipStream_t s);
 
 // The window's split kernels and the per-head gather's split kernels (launch_attn_partial_dense and
-// launch_attn_partial_gather with the same arguments) as one launch; bf16, groups of 1, 2 or 4, per-head lists.
+// launch_attn_partial_gather with the same arguments) as one launch; per-head lists.
 bool dense_gather_fusable(int dtype, int head_dim, int group);
 // With k_new / v_new ([B, Hkv, row], paged window with a per-sequence first block only) the window takes one more
 // token per sequence in the same launch: the split that owns its position writes its rows into the window's block
