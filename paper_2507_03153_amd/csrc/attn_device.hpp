@@ -38,9 +38,40 @@ struct KernelArgs {
     Partials part;
     float *scores;
     int32_t group_max;     // score pass: write one row per KV head, the maximum over the group's heads
+    int32_t by_group;      // gather through per-head lists: order of the workgroups (GatherPlace)
 };
 
 // ---- pieces shared by all split kernels ---------------------------------------------------
+
+constexpr int kXcds = 8;                         // workgroups of a launch are dealt to the XCDs in turn
+
+// Which split of which head's list the v-th workgroup of a gather serves.  The heads of a group list many of the same
+// tokens, and split i of their lists covers about the same part of the pool: with by_group the workgroups of a (sequence, KV
+// head, split) take numbers that are equal modulo the number of XCDs and follow each other there, so that a row that several of
+// them want comes into that XCD's L2 once.  The launch holds gather_blocks() workgroups; those without a split return false.
+struct GatherPlace {
+    int split, head, b;
+    __device__ __forceinline__ bool find(int v, const ShapeDev &sh, int n_splits, int by_group) {
+        if (!by_group) {                         // uniform over the launch
+            split = v % n_splits;
+            head = v / n_splits % sh.n_q_heads;
+            b = v / (n_splits * sh.n_q_heads);
+            return true;
+        }
+        const int r = v / kXcds, unit = r / sh.group * kXcds + v % kXcds;
+        if (unit >= sh.batch * sh.n_kv_heads * n_splits) return false;
+        split = unit % n_splits;
+        head = unit / n_splits % sh.n_kv_heads * sh.group + r % sh.group;
+        b = unit / (n_splits * sh.n_kv_heads);
+        return true;
+    }
+};
+inline int64_t gather_blocks(const ShapeDev &sh, int n_splits, int by_group)
+{
+    if (!by_group) return (int64_t)sh.batch * sh.n_q_heads * n_splits;
+    const int64_t units = (int64_t)sh.batch * sh.n_kv_heads * n_splits;
+    return (units + kXcds - 1) / kXcds * kXcds * sh.group;
+}
 
 // Tokens per split of a set of n tokens that n_splits workgroups share: the host fixes the number of splits from
 // the CAPACITY (lengths and list counts are device memory), so a set that fills half of its capacity would leave half
@@ -90,9 +121,13 @@ __device__ __forceinline__ void split_softmax(float (*s_p)[LD], float *s_m, floa
 }
 
 // o[g][:] = sum_j p[g][j] v_j over the split, reduced over the workgroup and written as a partial.
+// A 16-byte piece of a K or V row: streamed past the caches, or kept.
+template <bool KEEP>
+__device__ __forceinline__ uint4 load16_row(const char *p) { return KEEP ? load16(p) : load16_stream(p); }
+
 // The first UNROLL loads of a lane's V pass (the rows value_pass takes first), for a caller that wants them in
 // flight before the weights are ready: the addresses depend on the row map only.
-template <typename T, int D, int BLOCK = kBlock, int UNROLL = kUnroll>
+template <typename T, int D, int BLOCK = kBlock, int UNROLL = kUnroll, bool KEEP = false>
 __device__ __forceinline__ void value_prefetch(const KernelArgs &a, int nt, const RowMap &rows, uint4 (&vr)[UNROLL])
 {
     constexpr int LPR = D / Elem<T>::kPerLoad, RPW = kWave / LPR, RPI = (BLOCK / kWave) * RPW;
@@ -102,13 +137,14 @@ __device__ __forceinline__ void value_prefetch(const KernelArgs &a, int nt, cons
     for (int u = 0; u < UNROLL; ++u) {
         const int j = min(u * RPI + w * RPW + r, nt - 1);
         vr[u] = make_uint4(0u, 0u, 0u, 0u);
-        if (nt > 0) vr[u] = load16_stream(a.kv.v + rows(j) * ROW_BYTES + c * 16);   // (uniform; a split is never empty here)
+        if (nt > 0) vr[u] = load16_row<KEEP>(a.kv.v + rows(j) * ROW_BYTES + c * 16);   // (uniform; a split is never empty here)
     }
 }
 
 // V pass of a split: o = sum_j p_j v_j per head, reduced over the workgroup, and the split's partial (m, l, o).
 // With PRE the first UNROLL loads of every lane have been issued by value_prefetch (`first`).
-template <typename T, int D, int NH, bool GATHER, int BLOCK = kBlock, int UNROLL = kUnroll, int LD = kMaxChunk, bool PRE = false>
+template <typename T, int D, int NH, bool GATHER, int BLOCK = kBlock, int UNROLL = kUnroll, int LD = kMaxChunk, bool PRE = false,
+          bool KEEP = false>
 __device__ __forceinline__ void value_pass(const KernelArgs &a, float (*s_p)[LD],
                                            float (*s_red)[NH][D], const float *s_m, const float *s_l,
                                            int64_t bh0, int split, int nt, const RowMap &rows,
@@ -155,7 +191,7 @@ __device__ __forceinline__ void value_pass(const KernelArgs &a, float (*s_p)[LD]
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
             const int j = min(base + u * RPI + w * RPW + r, nt - 1);
-            vr[u] = load16_stream(a.kv.v + rows(j) * ROW_BYTES + c * 16);
+            vr[u] = load16_row<KEEP>(a.kv.v + rows(j) * ROW_BYTES + c * 16);
         }
         consume(base, vr);
     }
@@ -209,8 +245,9 @@ __device__ __forceinline__ void store_split_scores(const KernelArgs &a, const fl
 
 // One split of softmax attention on the VALU path (any dtype and head_dim): dense over a tier, gathered through a
 // list of positions, or the score pass alone.  `unit` is the query head (per-head lists) or the KV head.
-// UNROLL: 16-byte loads a lane keeps in flight in the K and V passes.
-template <typename T, int D, int NH, int MODE, int UNROLL = kUnroll>
+// UNROLL: 16-byte loads a lane keeps in flight in the K and V passes.  KEEP: rows stay in the cache for the other heads of the
+// group that list them (see GatherPlace).
+template <typename T, int D, int NH, int MODE, int UNROLL = kUnroll, bool KEEP = false>
 struct SplitValu {
     static constexpr int kPBytes = NH * kMaxChunk * 4, kRowBytes = kMaxChunk * 4, kRedBytes = kWaves * NH * D * 4;
     static constexpr int kLdsBytes = kPBytes + kRowBytes + kRedBytes + 64;
@@ -274,7 +311,7 @@ struct SplitValu {
     #pragma unroll
             for (int u = 0; u < UNROLL; ++u) {
                 const int j = min(base + u * RPI + w * RPW + r, nt - 1);
-                kr[u] = load16_stream(a.kv.k + rows(j) * ROW_BYTES + c * 16);
+                kr[u] = load16_row<KEEP>(a.kv.k + rows(j) * ROW_BYTES + c * 16);
             }
     #pragma unroll
             for (int u = 0; u < UNROLL; ++u) {
@@ -299,15 +336,15 @@ struct SplitValu {
 
         if (HGCA_V_PREFETCH && GATHER) {             // the first V rows travel while the softmax statistics are formed
             uint4 first[UNROLL];
-            value_prefetch<T, D, kBlock, UNROLL>(a, nt, rows, first);
+            value_prefetch<T, D, kBlock, UNROLL, KEEP>(a, nt, rows, first);
             split_softmax<NH>(s_p, s_m, s_l, nt);
             __syncthreads();
-            value_pass<T, D, NH, GATHER, kBlock, UNROLL, kMaxChunk, true>(a, s_p, s_red, s_m, s_l, bh0, split, nt, rows, first);
+            value_pass<T, D, NH, GATHER, kBlock, UNROLL, kMaxChunk, true, KEEP>(a, s_p, s_red, s_m, s_l, bh0, split, nt, rows, first);
             return;
         }
         split_softmax<NH>(s_p, s_m, s_l, nt);
         __syncthreads();
-        value_pass<T, D, NH, GATHER, kBlock, UNROLL>(a, s_p, s_red, s_m, s_l, bh0, split, nt, rows);
+        value_pass<T, D, NH, GATHER, kBlock, UNROLL, kMaxChunk, false, KEEP>(a, s_p, s_red, s_m, s_l, bh0, split, nt, rows);
     }
 };
 

@@ -22,11 +22,16 @@ namespace {
 
 // ---- VALU path -----------------------------------------------------------------------------
 
-template <typename T, int D, int NH, int MODE>
+template <typename T, int D, int NH, int MODE, bool KEEP = false>
 __global__ __launch_bounds__(kBlock) void attn_split_kernel(KernelArgs a)
 {
-    using SV = SplitValu<T, D, NH, MODE>;
+    using SV = SplitValu<T, D, NH, MODE, kUnroll, KEEP>;
     __shared__ __attribute__((aligned(16))) char s_lds[SV::kLdsBytes];
+    if ((MODE == kGather || MODE == kGatherScored) && a.by_group) {      // a flat grid
+        GatherPlace at;
+        if (at.find(blockIdx.x, a.sh, a.part.n_splits, a.by_group)) SV::run(a, s_lds, at.split, at.head, at.b);
+        return;
+    }
     SV::run(a, s_lds, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
@@ -221,6 +226,7 @@ KernelArgs to_kernel_args(const AttnArgs &a)
     ka.chunk = a.chunk;
     ka.part = a.part;
     ka.scores = a.raw_scores;
+    ka.by_group = a.by_group;
     return ka;
 }
 
@@ -258,10 +264,15 @@ hipError_t launch_attn_partial_gather(int dtype, int head_dim, const AttnArgs &a
         if (dtype == 1 && head_dim == 128) return launch_gather_group<bf16_t, 128>(ka, a.sh.group, grid, s);
         return hipErrorInvalidValue;
     }
-    dim3 grid(a.part.n_splits, a.sh.n_q_heads, a.sh.batch);
-    const KernelArgs ka = to_kernel_args(a);
-#define HGCA_GATHER_CASE(T, D)                                                                              \
-    if (a.sel_scores) HGCA_LAUNCH((attn_split_kernel<T, D, 1, kGatherScored>), grid, dim3(kBlock), s, ka);  \
+    // by_group: a flat grid, whose threads are counted in 32 bits; more workgroups than that go without its order
+    const int64_t blocks = gather_blocks(a.sh, a.part.n_splits, 1);
+    const bool by_group = a.by_group && blocks < int64_t(1) << 23;
+    const dim3 grid = by_group ? dim3((unsigned)blocks) : dim3(a.part.n_splits, a.sh.n_q_heads, a.sh.batch);
+    KernelArgs ka = to_kernel_args(a);
+    ka.by_group = by_group ? 1 : 0;
+#define HGCA_GATHER_CASE(T, D)                                                                                      \
+    if (a.sel_scores) HGCA_LAUNCH((attn_split_kernel<T, D, 1, kGatherScored>), grid, dim3(kBlock), s, ka);          \
+    else if (a.keep) HGCA_LAUNCH((attn_split_kernel<T, D, 1, kGather, true>), grid, dim3(kBlock), s, ka);           \
     else HGCA_LAUNCH((attn_split_kernel<T, D, 1, kGather>), grid, dim3(kBlock), s, ka)
     if (dtype == 0 && head_dim == 64) { HGCA_GATHER_CASE(float, 64); }
     else if (dtype == 0 && head_dim == 128) { HGCA_GATHER_CASE(float, 128); }

@@ -158,6 +158,22 @@ bool shares_launch(const hgca_shape *s, int64_t window, int64_t pool, int64_t k_
     return wgs <= (s->head_dim == 64 ? (token ? 4096 : 1024) : (token ? 1024 : 512));
 }
 
+// Whether the gather's workgroups run by groups of heads and keep their rows for each other (GatherPlace): by how much of the
+// pool a group's lists would cover if they shared nothing, group * k_max / cap.  Heads of a group list many of the same tokens; what
+// comes in once for several of them is worth more than the rows' way past the caches only where there is enough of it.  Measured, as
+// before : by groups : and kept, us.  Managed loops, per step: groups of 4, 8 sequences, pool 28 672 71.8 : 72.3 : 67.9, 60 000 134 : 120 :
+// 111; of 8, 60 000 245 : 196 : 174; of 2, 14 336 37.5 : 37.5 : 35.6.  Steady: groups of 4, 64 ragged sequences (40 %) 219 : 202 : 190;
+// 8 sequences, 14 % 34.4 : 34.7 : 33.3, 12 % 65.9 : 66.4 : 67.2; of 8, 24 % 46.7 : 41.5 : 42.0 and 28 % 47.3 : 44.6 : 46.2; of 2, 20 %
+// 35.7 : 33.9 : 35.6, 7 % 24.1 : 24.5 : 23.5.  With the scores given only V comes in, behind a pass over the pool: groups of 4, 40 % 231 : 224 :
+// 223 and 84.8 : 84.9 : 85.5, 28 % 141.0 : 141.3 : 141.9; of 8, 90 % 225 : 204 : 202, 80 % 114 : 111 : 117, 28 % 41.2 : 42.2 : 41.7.
+void order_gather(AttnArgs &ga, bool managed)
+{
+    const int64_t g = ga.sh.group, percent = ga.kv.cap > 0 ? 100 * g * ga.k_max / ga.kv.cap : 0;
+    if (g == 1) return;
+    ga.by_group = managed || percent >= (ga.sel_scores ? 40 : g == 2 ? 16 : 13);
+    ga.keep = !ga.sel_scores && (managed || (ga.by_group && g > 2));
+}
+
 // Tokens per window split: in a launch of its own the window wants about HGCA_TARGET_WGS_DENSE workgroups; in a launch
 // it shares with the sparse part's splits, which fill the device anyway, longer splits (half as many partials to write
 // and fold) are better.  Measured on the 8B shape: full step 145.2 -> 143.8 us, steady 67.9 -> 67.6 us; on its own the
@@ -705,6 +721,7 @@ int hgca_hybrid_decode_step(const hgca_shape *shape, const void *q, const hgca_k
     ga.k_max = k_max;
     ga.chunk = gather_chunk;
     ga.part = partials_at(ws_sparse, wsp, std::max(1, n_splits_for(k_max, ga.chunk)));
+    order_gather(ga, false);
     if (fuse_gather) rc = from_hip(launch_dense_gather(shape->dtype, shape->head_dim, da, ga, s));
     else rc = from_hip(launch_attn_partial_gather(shape->dtype, shape->head_dim, ga, s));
     if (rc != HGCA_OK) return rc;
@@ -753,6 +770,7 @@ int hgca_hybrid_decode_step_selected(const hgca_shape *shape, const void *q, con
     ga.k_max = k_max;
     ga.chunk = gather_chunk;
     ga.part = partials_at(ws_sparse, wsp, std::max(1, n_splits_for(k_max, ga.chunk)));
+    order_gather(ga, false);
     // gpu_attention over the window and cpu_attention over the listed entries: one launch where the shapes allow
     if (one_launch) {
         if ((rc = from_hip(launch_dense_gather(shape->dtype, shape->head_dim, da, ga, s))) != HGCA_OK) return rc;
@@ -914,6 +932,7 @@ int hgca_managed_decode_step(const hgca_shape *shape, const hgca_cache_state *ca
     ga.k_max = cache->k_max;
     ga.chunk = gather_chunk;
     ga.part = partials_at(ws_sparse, wsp, std::max(1, n_splits_for(cache->k_max, ga.chunk)));
+    order_gather(ga, true);
     // the two parts need nothing from each other: one launch where the shapes allow
     if (one_launch) {
         if ((rc = from_hip(launch_dense_gather(shape->dtype, shape->head_dim, da, ga, s, token_joins_in_split ? k_in : nullptr,

@@ -77,6 +77,8 @@ struct AttnArgs {
     Partials part;
     float *raw_scores;     // dense only, optional: [B, Hq, cap], receives the scaled score of every valid token
     int32_t grouped;       // gather only: idx is [B, Hkv, k_max], cnt [B, Hkv]; the heads of a group share the list
+    int32_t by_group;      // per-head lists: the workgroups of a group's heads run side by side on one XCD (GatherPlace), ...
+    int32_t keep;          // ... and rows stay in its cache for the other heads instead of being streamed past it
 };
 
 // dtype: 0 fp32, 1 bf16; head_dim 64|128.  Dense handles the `group` query heads
