@@ -38,26 +38,20 @@ struct KernelArgs {
     Partials part;
     float *scores;
     int32_t group_max;     // score pass: write one row per KV head, the maximum over the group's heads
-    int32_t by_group;      // gather through per-head lists: order of the workgroups (GatherPlace)
+    int32_t by_group;      // gather in a launch of its own: workgroups by groups of heads (GatherPlace)
 };
 
 // ---- pieces shared by all split kernels ---------------------------------------------------
 
 constexpr int kXcds = 8;                         // workgroups of a launch are dealt to the XCDs in turn
 
-// Which split of which head's list the v-th workgroup of a gather serves.  The heads of a group list many of the same
-// tokens, and split i of their lists covers about the same part of the pool: with by_group the workgroups of a (sequence, KV
+// Which split of which head's list the v-th workgroup of a gather by groups serves.  The heads of a group list many of the same
+// tokens, and split i of their lists covers about the same part of the pool: the workgroups of a (sequence, KV
 // head, split) take numbers that are equal modulo the number of XCDs and follow each other there, so that a row that several of
 // them want comes into that XCD's L2 once.  The launch holds gather_blocks() workgroups; those without a split return false.
 struct GatherPlace {
     int split, head, b;
-    __device__ __forceinline__ bool find(int v, const ShapeDev &sh, int n_splits, int by_group) {
-        if (!by_group) {                         // uniform over the launch
-            split = v % n_splits;
-            head = v / n_splits % sh.n_q_heads;
-            b = v / (n_splits * sh.n_q_heads);
-            return true;
-        }
+    __device__ __forceinline__ bool find(int v, const ShapeDev &sh, int n_splits) {
         const int r = v / kXcds, unit = r / sh.group * kXcds + v % kXcds;
         if (unit >= sh.batch * sh.n_kv_heads * n_splits) return false;
         split = unit % n_splits;
@@ -66,9 +60,8 @@ struct GatherPlace {
         return true;
     }
 };
-inline int64_t gather_blocks(const ShapeDev &sh, int n_splits, int by_group)
+inline int64_t gather_blocks(const ShapeDev &sh, int n_splits)
 {
-    if (!by_group) return (int64_t)sh.batch * sh.n_q_heads * n_splits;
     const int64_t units = (int64_t)sh.batch * sh.n_kv_heads * n_splits;
     return (units + kXcds - 1) / kXcds * kXcds * sh.group;
 }

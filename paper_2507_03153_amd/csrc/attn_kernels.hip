@@ -29,7 +29,7 @@ __global__ __launch_bounds__(kBlock) void attn_split_kernel(KernelArgs a)
     __shared__ __attribute__((aligned(16))) char s_lds[SV::kLdsBytes];
     if ((MODE == kGather || MODE == kGatherScored) && a.by_group) {      // a flat grid
         GatherPlace at;
-        if (at.find(blockIdx.x, a.sh, a.part.n_splits, a.by_group)) SV::run(a, s_lds, at.split, at.head, at.b);
+        if (at.find(blockIdx.x, a.sh, a.part.n_splits)) SV::run(a, s_lds, at.split, at.head, at.b);
         return;
     }
     SV::run(a, s_lds, blockIdx.x, blockIdx.y, blockIdx.z);
@@ -265,7 +265,7 @@ hipError_t launch_attn_partial_gather(int dtype, int head_dim, const AttnArgs &a
         return hipErrorInvalidValue;
     }
     // by_group: a flat grid, whose threads are counted in 32 bits; more workgroups than that go without its order
-    const int64_t blocks = gather_blocks(a.sh, a.part.n_splits, 1);
+    const int64_t blocks = gather_blocks(a.sh, a.part.n_splits);
     const bool by_group = a.by_group && blocks < int64_t(1) << 23;
     const dim3 grid = by_group ? dim3((unsigned)blocks) : dim3(a.part.n_splits, a.sh.n_q_heads, a.sh.batch);
     KernelArgs ka = to_kernel_args(a);

@@ -28,7 +28,8 @@ namespace {
 #define HGCA_DG_UNROLL 4                         // V loads a lane of a window split keeps in flight
 #endif
 
-template <typename T, int D, int G, int GMODE, int LD, bool KEEP>
+// ORDER of the gather's workgroups: 0 head by head, 1 by groups of heads, 2 the same with the rows kept for each other.
+template <typename T, int D, int G, int GMODE, int LD, int ORDER>
 __global__ __launch_bounds__(kBlock, sizeof(T) == 2 && G < 8 ? HGCA_DG_OCC : 1) void dense_gather_kernel(KernelArgs da, KernelArgs ga, int n_dense,
                                                                           int dense_splits, int gather_splits,
                                                                           int gather_first, const char *k_new,
@@ -37,7 +38,7 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 2 && G < 8 ? HGCA_DG_OCC : 1) 
     constexpr bool F32 = sizeof(T) == 4;
     // bf16: the window on the matrix cores, LDS sized for splits of up to LD tokens; fp32: on the vector units
     using DS = std::conditional_t<F32, SplitValu<T, D, G, kDense>, DenseSplit<D, G, kBlock, HGCA_DG_UNROLL, LD>>;
-    using GS = SplitValu<T, D, 1, GMODE, F32 ? kUnroll : HGCA_DG_GATHER_UNROLL, KEEP>;
+    using GS = SplitValu<T, D, 1, GMODE, F32 ? kUnroll : HGCA_DG_GATHER_UNROLL, ORDER == 2>;
     constexpr int kLds = DS::kLdsBytes > GS::kLdsBytes ? DS::kLdsBytes : GS::kLdsBytes;
     __shared__ __attribute__((aligned(16))) char s_lds[kLds];
     // the part with more bytes to move takes the lower block numbers and starts first (the other fills in behind it)
@@ -45,7 +46,7 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 2 && G < 8 ? HGCA_DG_OCC : 1) 
     const bool dense_role = gather_first ? (int)blockIdx.x >= n_gather : (int)blockIdx.x < n_dense;
     const int u = (int)blockIdx.x - (dense_role ? (gather_first ? n_gather : 0) : (gather_first ? 0 : n_dense));
     if (dense_role) {                            // uniform over the workgroup
-        if (u >= da.sh.batch * da.sh.n_kv_heads * dense_splits) return;          // padding
+        if (ORDER > 0 && u >= da.sh.batch * da.sh.n_kv_heads * dense_splits) return;         // padding
         const int split = u % dense_splits, kvh = (u / dense_splits) % da.sh.n_kv_heads,
                   b = u / (dense_splits * da.sh.n_kv_heads);
         int n = tier_len(da.kv, b), len = 0, first = 0;
@@ -81,8 +82,12 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 2 && G < 8 ? HGCA_DG_OCC : 1) 
         }
         return;
     }
+    if (ORDER == 0) {
+        GS::run(ga, s_lds, u % gather_splits, (u / gather_splits) % ga.sh.n_q_heads, u / (gather_splits * ga.sh.n_q_heads));
+        return;
+    }
     GatherPlace at;
-    if (at.find(u, ga.sh, gather_splits, ga.by_group)) GS::run(ga, s_lds, at.split, at.head, at.b);
+    if (at.find(u, ga.sh, gather_splits)) GS::run(ga, s_lds, at.split, at.head, at.b);
 }
 
 }  // namespace
@@ -98,9 +103,12 @@ hipError_t launch_dense_gather(int dtype, int head_dim, const AttnArgs &dense, c
     if (!dense_gather_fusable(dtype, head_dim, dense.sh.group) || gather.grouped) return hipErrorInvalidValue;
     if ((k_new != nullptr) != (v_new != nullptr)) return hipErrorInvalidValue;
     if (k_new && (!dense.kv.block_table || !dense.kv.first_block || !dense.kv.seq_lens)) return hipErrorInvalidValue;
-    // (the first part's number is a multiple of the number of XCDs, so that the second part's numbers go round them as they count)
-    const int64_t n_dense = ((int64_t)dense.sh.batch * dense.sh.n_kv_heads * dense.part.n_splits + kXcds - 1) / kXcds * kXcds;
-    const int64_t n_gather = gather_blocks(gather.sh, gather.part.n_splits, gather.by_group);
+    const int order = dense.sh.group == 1 || !gather.by_group ? 0 : gather.keep && !gather.sel_scores ? 2 : 1;
+    // (by groups, the first part's number is a multiple of the number of XCDs, so that the second part's go round them as they count)
+    const int64_t n_window = (int64_t)dense.sh.batch * dense.sh.n_kv_heads * dense.part.n_splits;
+    const int64_t n_dense = order ? (n_window + kXcds - 1) / kXcds * kXcds : n_window;
+    const int64_t n_gather = order ? gather_blocks(gather.sh, gather.part.n_splits)
+                                   : (int64_t)gather.sh.batch * gather.sh.n_q_heads * gather.part.n_splits;
     if (n_dense + n_gather == 0) return hipSuccess;
     if (n_dense + n_gather > 0x7fffffff) return hipErrorInvalidValue;
     auto to_ka = [](const AttnArgs &a) {
@@ -115,31 +123,35 @@ hipError_t launch_dense_gather(int dtype, int head_dim, const AttnArgs &dense, c
         ka.chunk = a.chunk;
         ka.part = a.part;
         ka.scores = a.raw_scores;
-        ka.by_group = a.by_group;
         return ka;
     };
     const KernelArgs da = to_ka(dense), ga = to_ka(gather);
     const dim3 grid((unsigned)(n_dense + n_gather)), block(kBlock);
     const int g = dense.sh.group;
     // the window's splits size the launch's LDS: the common 256-token splits leave room for seven workgroups per unit
-#define HGCA_DG_LAUNCH(T, D, G, GMODE, LD, KEEP, FIRST)                                                             \
-    hipLaunchKernelGGL((dense_gather_kernel<T, D, G, GMODE, LD, KEEP>), grid, block, 0, s, da, ga, (int)n_dense,    \
+#define HGCA_DG_LAUNCH(T, D, G, GMODE, LD, ORDER, FIRST)                                                            \
+    hipLaunchKernelGGL((dense_gather_kernel<T, D, G, GMODE, LD, ORDER>), grid, block, 0, s, da, ga, (int)n_dense,   \
                        dense.part.n_splits, gather.part.n_splits, FIRST, static_cast<const char *>(k_new),        \
                        static_cast<const char *>(v_new))
-    // rows are kept for the other heads of a group only where K and V are gathered (the one caller's choice that gains)
+#define HGCA_DG_SCORED(T, D, G, LD)                                                                                 \
+    do {                                                                                                            \
+        if (order) HGCA_DG_LAUNCH(T, D, G, kGatherScored, LD, (G > 1 ? 1 : 0), 0);                                  \
+        else HGCA_DG_LAUNCH(T, D, G, kGatherScored, LD, 0, 0);                                                      \
+    } while (0)
 #define HGCA_DG_GATHER(T, D, G, LD)                                                                                 \
     do {                                                                                                            \
-        if (G > 1 && gather.keep) HGCA_DG_LAUNCH(T, D, G, kGather, LD, (G > 1), 1);                                 \
-        else HGCA_DG_LAUNCH(T, D, G, kGather, LD, false, 1);                                                        \
+        if (order == 2) HGCA_DG_LAUNCH(T, D, G, kGather, LD, (G > 1 ? 2 : 0), 1);                                   \
+        else if (order) HGCA_DG_LAUNCH(T, D, G, kGather, LD, (G > 1 ? 1 : 0), 1);                                   \
+        else HGCA_DG_LAUNCH(T, D, G, kGather, LD, 0, 1);                                                            \
     } while (0)
 #define HGCA_DG_CASE(D, G)                                                                                          \
     if (head_dim == D && g == G) {                                                                                  \
         if (dtype == 0) {                                                                                           \
-            if (gather.sel_scores) HGCA_DG_LAUNCH(float, D, G, kGatherScored, kMaxChunk, false, 0);                 \
+            if (gather.sel_scores) HGCA_DG_SCORED(float, D, G, kMaxChunk);                                          \
             else HGCA_DG_GATHER(float, D, G, kMaxChunk);                                                            \
         } else if (gather.sel_scores) {                                                                             \
-            if (dense.chunk <= 256) HGCA_DG_LAUNCH(bf16_t, D, G, kGatherScored, 256, false, 0);                     \
-            else HGCA_DG_LAUNCH(bf16_t, D, G, kGatherScored, kMaxChunk, false, 0);                                  \
+            if (dense.chunk <= 256) HGCA_DG_SCORED(bf16_t, D, G, 256);                                              \
+            else HGCA_DG_SCORED(bf16_t, D, G, kMaxChunk);                                                           \
         } else {                                                                                                    \
             if (dense.chunk <= 256) HGCA_DG_GATHER(bf16_t, D, G, 256);                                              \
             else HGCA_DG_GATHER(bf16_t, D, G, kMaxChunk);                                                           \
@@ -150,6 +162,7 @@ hipError_t launch_dense_gather(int dtype, int head_dim, const AttnArgs &dense, c
     HGCA_DG_CASE(128, 1) HGCA_DG_CASE(128, 2) HGCA_DG_CASE(128, 4) HGCA_DG_CASE(128, 8)
 #undef HGCA_DG_CASE
 #undef HGCA_DG_GATHER
+#undef HGCA_DG_SCORED
 #undef HGCA_DG_LAUNCH
     return hipErrorInvalidValue;
 }
