@@ -138,6 +138,21 @@ int pick_chunk(int64_t n, int64_t units, int target, int max_chunk = kMaxChunk)
 
 int n_splits_for(int64_t n, int chunk) { return (int)((n + chunk - 1) / chunk); }
 
+// Windows and lists long enough to make 8 or 16 splits of 128 are not cut into splits of 64, however few sequences there are: more
+// partials than the fold takes in one round trip.  One sequence, 32 / 8 heads of 128, window 4096: steady step, 2000 listed 21.8 ->
+// 17.7 us, decode loop 25.0 -> 21.5 us per step, step with a selection 41.0 -> 37.0, of 61 003 tokens 62.0 -> 58.4; a window of 512
+// is better in splits of 64 (step 29.9 : 31.1, loop of 3 sequences 21.7 : 23.1), a list of 600 the same in both.
+int no_shorter(int chunk, int64_t n, int64_t from) { return n >= from ? std::max(chunk, 128) : chunk; }
+constexpr int64_t kLongWindow = 2048, kLongList = 1024;
+// ... and lists only as long as the splits of 128 come to a workgroup per compute unit, two where a row has 512 bytes, of which a
+// workgroup has half as many in flight (fp32, 16 lists of 2285 entries of dimension 128: loop 18.4 -> 19.4 us per step)
+int gather_split(const hgca_shape *s, int64_t k_max, int target)
+{
+    const int64_t rows = (int64_t)s->batch * s->n_q_heads, row_bytes = s->head_dim * (s->dtype == HGCA_BF16 ? 2 : 4);
+    const int chunk = pick_chunk(k_max, rows, target);
+    return rows * n_splits_for(k_max, 128) >= 256 * std::max<int64_t>(1, row_bytes / 256) ? no_shorter(chunk, k_max, kLongList) : chunk;
+}
+
 // Whether the window's splits and the sparse part's splits share a launch, and the window split's tokens there (below).
 // fp32 and groups of up to 4 always do.  Measured, two launches : one, us: fp32 steady steps 1 sequence, 32 / 8 heads of 128,
 // window 2048, 1900 listed 29.3 : 22.6, 4 sequences 63.9 : 60.4; decode loops, which insert the token in the same launch, per
@@ -185,7 +200,8 @@ int dense_chunk(const hgca_shape *s, int64_t cap, bool shared, bool scored = tru
 {
     const int64_t units = (int64_t)s->batch * s->n_kv_heads;
     if (s->dtype == HGCA_F32 && !scored && units <= 256) shared = false;
-    return pick_chunk(cap, units, shared ? HGCA_TARGET_WGS_DENSE_SHARED : HGCA_TARGET_WGS_DENSE);
+    if (!shared) return pick_chunk(cap, units, HGCA_TARGET_WGS_DENSE);
+    return no_shorter(pick_chunk(cap, units, HGCA_TARGET_WGS_DENSE_SHARED), cap, kLongWindow);
 }
 
 // Tokens per workgroup of the score pass over a pool of `cap` tokens.  Groups of 8 heads take half the tokens per
@@ -699,7 +715,7 @@ int hgca_hybrid_decode_step(const hgca_shape *shape, const void *q, const hgca_k
     }
     // The window's splits and the sparse part's splits are two streaming passes that need nothing from each other:
     // where the shapes allow they share one launch (after the selection), so the second needs no ramp-up of its own.
-    const int gather_chunk = pick_chunk(k_max, (int64_t)shape->batch * shape->n_q_heads, HGCA_TARGET_WGS_SPARSE_SCORED);
+    const int gather_chunk = gather_split(shape, k_max, HGCA_TARGET_WGS_SPARSE_SCORED);
     const bool fuse_gather = shares_launch(shape, window->cap, pool->cap, k_max, gather_chunk, true, false);
     da.chunk = dense_chunk(shape, window->cap, fuse_gather);
     da.part = partials_at(ws_dense, wd, n_splits_for(window->cap, da.chunk));
@@ -755,7 +771,7 @@ int hgca_hybrid_decode_step_selected(const hgca_shape *shape, const void *q, con
     da.sh = to_dev(shape);
     da.q = q;
     da.kv = to_dev(window);
-    const int gather_chunk = pick_chunk(k_max, (int64_t)shape->batch * shape->n_q_heads, HGCA_TARGET_WGS_SPARSE);
+    const int gather_chunk = gather_split(shape, k_max, HGCA_TARGET_WGS_SPARSE);
     const bool scored = sel_scores != nullptr;
     const bool one_launch = shares_launch(shape, window->cap, pool->cap, k_max, gather_chunk, scored, false);
     da.chunk = dense_chunk(shape, window->cap, one_launch, scored);
@@ -906,7 +922,7 @@ int hgca_managed_decode_step(const hgca_shape *shape, const hgca_cache_state *ca
     const int32_t row_bytes = shape->head_dim * (shape->dtype == HGCA_BF16 ? 2 : 4);
 
     const bool token_may_join = HGCA_FUSE_KV_APPEND && HGCA_FUSE_DECODE_TAIL;
-    const int gather_chunk = pick_chunk(cache->k_max, rows, HGCA_TARGET_WGS_SPARSE);
+    const int gather_chunk = gather_split(shape, cache->k_max, HGCA_TARGET_WGS_SPARSE);
     const bool one_launch = shares_launch(shape, window.cap, cache->pool_cap, cache->k_max, gather_chunk, false, token_may_join);
     // Alg. 2: KV_gpu' = concat(KV_gpu, KV_in): a launch of its own, or (token_joins_in_split) the window split that
     // owns the token's position writes its rows and the step's last launch stores the new length
