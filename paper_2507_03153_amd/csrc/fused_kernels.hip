@@ -103,7 +103,8 @@ hipError_t launch_dense_gather(int dtype, int head_dim, const AttnArgs &dense, c
     if (!dense_gather_fusable(dtype, head_dim, dense.sh.group) || gather.grouped) return hipErrorInvalidValue;
     if ((k_new != nullptr) != (v_new != nullptr)) return hipErrorInvalidValue;
     if (k_new && (!dense.kv.block_table || !dense.kv.first_block || !dense.kv.seq_lens)) return hipErrorInvalidValue;
-    const int order = dense.sh.group == 1 || !gather.by_group ? 0 : gather.keep && !gather.sel_scores ? 2 : 1;
+    // by groups without keeping the rows is a choice of groups of 2 and of given scores (order_gather); the others keep them
+    const int order = dense.sh.group == 1 || !gather.by_group ? 0 : !gather.sel_scores && (gather.keep || dense.sh.group > 2) ? 2 : 1;
     // (by groups, the first part's number is a multiple of the number of XCDs, so that the second part's go round them as they count)
     const int64_t n_window = (int64_t)dense.sh.batch * dense.sh.n_kv_heads * dense.part.n_splits;
     const int64_t n_dense = order ? (n_window + kXcds - 1) / kXcds * kXcds : n_window;
@@ -128,6 +129,7 @@ hipError_t launch_dense_gather(int dtype, int head_dim, const AttnArgs &dense, c
     const KernelArgs da = to_ka(dense), ga = to_ka(gather);
     const dim3 grid((unsigned)(n_dense + n_gather)), block(kBlock);
     const int g = dense.sh.group;
+    if (dtype == 1 && g == 8 && gather.sel_scores) return hipErrorInvalidValue;  // not built: its callers use two launches
     // the window's splits size the launch's LDS: the common 256-token splits leave room for seven workgroups per unit
 #define HGCA_DG_LAUNCH(T, D, G, GMODE, LD, ORDER, FIRST)                                                            \
     hipLaunchKernelGGL((dense_gather_kernel<T, D, G, GMODE, LD, ORDER>), grid, block, 0, s, da, ga, (int)n_dense,   \
@@ -141,7 +143,7 @@ hipError_t launch_dense_gather(int dtype, int head_dim, const AttnArgs &dense, c
 #define HGCA_DG_GATHER(T, D, G, LD)                                                                                 \
     do {                                                                                                            \
         if (order == 2) HGCA_DG_LAUNCH(T, D, G, kGather, LD, (G > 1 ? 2 : 0), 1);                                   \
-        else if (order) HGCA_DG_LAUNCH(T, D, G, kGather, LD, (G > 1 ? 1 : 0), 1);                                   \
+        else if (order) HGCA_DG_LAUNCH(T, D, G, kGather, LD, (G == 2 ? 1 : G > 1 ? 2 : 0), 1);                      \
         else HGCA_DG_LAUNCH(T, D, G, kGather, LD, 0, 1);                                                            \
     } while (0)
 #define HGCA_DG_CASE(D, G)                                                                                          \
@@ -150,8 +152,8 @@ hipError_t launch_dense_gather(int dtype, int head_dim, const AttnArgs &dense, c
             if (gather.sel_scores) HGCA_DG_SCORED(float, D, G, kMaxChunk);                                          \
             else HGCA_DG_GATHER(float, D, G, kMaxChunk);                                                            \
         } else if (gather.sel_scores) {                                                                             \
-            if (dense.chunk <= 256) HGCA_DG_SCORED(bf16_t, D, G, 256);                                              \
-            else HGCA_DG_SCORED(bf16_t, D, G, kMaxChunk);                                                           \
+            if (dense.chunk <= 256) HGCA_DG_SCORED(bf16_t, D, (G < 8 ? G : 4), 256);                                \
+            else HGCA_DG_SCORED(bf16_t, D, (G < 8 ? G : 4), kMaxChunk);                                             \
         } else {                                                                                                    \
             if (dense.chunk <= 256) HGCA_DG_GATHER(bf16_t, D, G, 256);                                              \
             else HGCA_DG_GATHER(bf16_t, D, G, kMaxChunk);                                                           \
