@@ -21,8 +21,8 @@ namespace {
 // or table row cannot take all of them receives none (status bit).  gridDim.y workgroups share a sequence's rows
 // (16-byte pieces dealt round-robin, four loads in flight per thread); the last of them to finish (an arrival counter
 // in plan[4b + 3], left at zero) stores the new length: by then every workgroup of the sequence has read the old one.
-// A chain of round trips (state, block table, rows, arrival): the rows are requested first, 32 tokens x 8 sequences 9.6 -> 6.5 us
-// (with 1024 threads and fewer arrivals 6.8; 24 tokens x 2 sequences, fp32, 3.5 us more than with 256).
+// A chain of round trips (state, block table, rows, arrival): the rows are requested first, 32 tokens x 8 sequences 9.6 -> 5.7 us
+// (with 1024 threads and fewer arrivals 6.8; 24 tokens x 2 sequences, fp32, 9.1 -> 4.7, with 1024 threads 7.6).
 __global__ __launch_bounds__(kRowBlock) void kv_append_kernel(CacheDev c, const char *k_in, const char *v_in,
                                                               const int32_t *active, int32_t n_kv_heads,
                                                               int32_t row_bytes, int32_t n_tokens)
