@@ -91,14 +91,17 @@ __global__ __launch_bounds__(kLargeBlock) void select_attend_kernel(SelectArgs a
     for (int s = sg + SG; s < np; s += SG) mx = fmaxf(mx, win.m[first + s]);
 
     __syncthreads();                             // the list is written (by this workgroup) and the selection's LDS is free
+    const int n = tier_len(a.kv, b);
     int k = a.k_per_seq ? a.k_per_seq[b] : a.k_uniform;
-    k = max(0, min(min(k, tier_len(a.kv, b)), a.k_max));
+    k = max(0, min(min(k, n), a.k_max));
     float *s_p = s_dyn;
     uint32_t *s_row = reinterpret_cast<uint32_t *>(s_dyn + a.k_max);
     const int32_t *blocks = kv.block_table ? kv.block_table + (int64_t)b * kv.max_blocks + (kv.first_block ? kv.first_block[b] : 0)
                                            : nullptr;
     for (int j = tid; j < k; j += kLargeBlock) {
-        const int tok = a.idx[bh * a.k_max + j];
+        // a position that is none of the sequence's (a row with NaN scores need not fill its list) is clamped into it, as in
+        // make_row_map: no address is formed that the tier or its block table does not hold
+        const int tok = min(max(a.idx[bh * a.k_max + j], 0), n - 1);
         s_row[j] = blocks ? (uint32_t)(((int64_t)blocks[tok / kv.block_size] * a.sh.n_kv_heads + kvh) * kv.block_size + tok % kv.block_size)
                           : (uint32_t)(((int64_t)b * a.sh.n_kv_heads + kvh) * kv.cap + tok);
         const float s = a.sel_scores[bh * a.k_max + j];

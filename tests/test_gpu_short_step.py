@@ -57,3 +57,35 @@ def test_short_step_equals_the_oracle(oracle, name, kw, W, P, k_max):
         assert np.max(np.abs(got_l[some] - lse[some])) <= tol
         bar = tol if o_dtype == torch.float32 else tol + np.max(np.abs(o)) * 2.0 ** -8   # one rounding to bf16
         assert np.max(np.abs(out.double().cpu().numpy() - o)) <= bar
+
+
+@pytest.mark.parametrize("name,kw,W,P,k_max", [
+    ("C2", dict(Hq=8, Hkv=2), 300, 900, 200), ("C5", dict(Hq=4, Hkv=2), 100, 1700, 130), ("C1", dict(Hq=8, Hkv=2), 90, 2000, 129),
+    ("C2", dict(Hq=4, Hkv=4, d=64), 100, 36000, 300),
+], ids=["bf16", "bf16_paged", "f32", "bf16_long_rows"])
+def test_queries_that_are_not_numbers(name, kw, W, P, k_max):
+    """One head's query is NaN, and so is every score of its row: the positions in its list and the rows that are read stay
+    inside the sequence whatever the list held before, and the other heads' results are those without it, bit for bit."""
+    import torch
+    from paper_2507_03153_amd import hgca, runner
+    p_lens = [P, 65, k_max, 1, 0]                # with 1 and k_max valid positions every one is kept
+    cfg = wl.scaled(wl.CONFIGS[name], B=len(p_lens), W=W, P=P, k=16, ragged=None, **kw)
+    L = wl.make_layer(cfg)
+    L.pool.seq_lens = np.array(p_lens, np.int32)
+    D = runner.DeviceLayer.upload(L)
+    step = runner.HybridStep(D.shape, cfg.W, cfg.P, k_max)
+    bad = 1
+    outs = []
+    for q, left in ((D.q, -1), (D.q.clone(), -1), (D.q.clone(), 0x7fffff00), (D.q.clone(), -0x7fffff00)):
+        if outs:
+            q[:, bad] = float("nan")
+        step.idx.fill_(left)
+        hgca.hybrid_decode_step(D.shape, q, D.window, D.pool, min(k_max, P), k_max, step.idx, step.cnt, step.o, step.lse,
+                                step.ws_dense, step.ws_sparse)
+        torch.cuda.synchronize()
+        outs.append([t.clone() for t in (step.idx, step.cnt, step.o, step.lse)])
+    good = [h for h in range(cfg.Hq) if h != bad]
+    for got in outs[1:]:
+        for x, want in zip(got, outs[0]):
+            assert torch.equal(x[:, good], want[:, good])
+        assert torch.equal(got[1], outs[0][1])
