@@ -160,7 +160,7 @@ int hgca_select_salient(const hgca_shape *shape, const void *q,
  * keeps): per (b, h) row of scores (device fp32 [B,Hq,cap], 16-byte aligned;
  * +inf and -inf are ordinary values here, e.g. -inf for positions a caller has
  * masked: they rank above / below every finite score, ties among them by
- * position; with NaN the selection is unspecified) keep
+ * position; NaN ranks as -inf does) keep
  * the k_b = min(k, len_b) largest of the first len_b = seq_lens[b] entries (all
  * `cap` if seq_lens is NULL).  Tie rule, budgets,
  * k_max, idx_out, cnt_out and sel_scores_out as in hgca_select_salient.  Only

@@ -59,6 +59,11 @@ struct Binning {
 // scores NaN.  Infinite scores (a caller's masked positions, say) then fall into the end bins by clamping.
 __device__ __forceinline__ float finite_or(float s, float otherwise) { return fabsf(s) < INFINITY ? s : otherwise; }
 
+// NaN ranks as -inf.  The passes over whole rows need no test for it (it is counted into bin 0 and fails every compare with a
+// threshold above -inf); the places that rank entries one by one, or keep ties of -inf, take scores through this, so that as
+// many entries are kept as were asked for and every place of the list is written.
+__device__ __forceinline__ float number_or_least(float s) { return s == s ? s : -INFINITY; }
+
 // Four consecutive scores starting at position t (a multiple of 4); positions at or beyond n read -inf.  A row starts
 // on any multiple of 4 bytes (the capacity may be odd), which is all a 16-byte load asks for: rows of 61 003 scores,
 // loaded score by score where the row was not 16-byte aligned, 40.4 -> 22.2 us together with the smaller sample.
@@ -732,7 +737,7 @@ struct Sel {
             }
             if (inside) {
                 const uint32_t slot = atomicAdd(&sh.n_cand, 1u);
-                if (slot < (uint32_t)kMaxCand) { sh.cand_score()[slot] = sc_e; sh.cand_idx()[slot] = pos; }
+                if (slot < (uint32_t)kMaxCand) { sh.cand_score()[slot] = number_or_least(sc_e); sh.cand_idx()[slot] = pos; }
             }
             return over;
         };
@@ -846,7 +851,7 @@ struct Sel {
                     const float s[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        const uint32_t key = order_key(s[e]);
+                        const uint32_t key = order_key(number_or_least(s[e]));
                         if (t + e < n && bin(s[e]) == tb && (key & mask) == prefix)
                             atomicAdd(&sh.hist[(key >> shift) & (uint32_t)(nb - 1)], 1u);
                     }
@@ -868,7 +873,7 @@ struct Sel {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     my_gt += t + e < n && s[e] > thr;
-                    my_eq += t + e < n && s[e] == thr;
+                    my_eq += t + e < n && number_or_least(s[e]) == thr;
                 }
             }
             my_gt = (uint32_t)wave_sum((float)my_gt);
@@ -951,7 +956,7 @@ struct Sel {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 gt[e] = s[e] > thr;
-                eq[e] = s[e] == thr && !(pad_ties && t + e >= n);
+                eq[e] = number_or_least(s[e]) == thr && !(pad_ties && t + e >= n);
                 const unsigned long long m_gt = __ballot(gt[e]), m_eq = __ballot(eq[e]);
                 gt_before += lanes_below(m_gt);
                 eq_before += lanes_below(m_eq);
