@@ -103,7 +103,7 @@ hipError_t launch_dense_gather(int dtype, int head_dim, const AttnArgs &dense, c
     if (!dense_gather_fusable(dtype, head_dim, dense.sh.group) || gather.grouped) return hipErrorInvalidValue;
     if ((k_new != nullptr) != (v_new != nullptr)) return hipErrorInvalidValue;
     if (k_new && (!dense.kv.block_table || !dense.kv.first_block || !dense.kv.seq_lens)) return hipErrorInvalidValue;
-    // by groups without keeping the rows is a choice of groups of 2 and of given scores (order_gather); the others keep them
+    // by groups without keeping the rows is built for groups of 2 and for given scores; the others keep them here
     const int order = dense.sh.group == 1 || !gather.by_group ? 0 : !gather.sel_scores && (gather.keep || dense.sh.group > 2) ? 2 : 1;
     // (by groups, the first part's number is a multiple of the number of XCDs, so that the second part's go round them as they count)
     const int64_t n_window = (int64_t)dense.sh.batch * dense.sh.n_kv_heads * dense.part.n_splits;

@@ -9,6 +9,7 @@
 #include <cstdint>
 
 #include "hgca_launch.hpp"
+#include "routes.hpp"
 
 namespace {
 
@@ -173,20 +174,11 @@ bool shares_launch(const hgca_shape *s, int64_t window, int64_t pool, int64_t k_
     return wgs <= (s->head_dim == 64 ? (token ? 4096 : 1024) : (token ? 1024 : 512));
 }
 
-// Whether the gather's workgroups run by groups of heads and keep their rows for each other (GatherPlace): by how much of the
-// pool a group's lists would cover if they shared nothing, group * k_max / cap.  Heads of a group list many of the same tokens; what
-// comes in once for several of them is worth more than the rows' way past the caches only where there is enough of it.  Measured, as
-// before : by groups : and kept, us.  Managed loops, per step: groups of 4, 8 sequences, pool 28 672 71.8 : 72.3 : 67.9, 60 000 134 : 120 :
-// 111; of 8, 60 000 245 : 196 : 174; of 2, 14 336 37.5 : 37.5 : 35.6.  Steady: groups of 4, 64 ragged sequences (40 %) 219 : 202 : 190;
-// 8 sequences, 29 %, lists of a selection with little in common 67.1 kept 70.9; 12 % 65.9 : 66.4 : 67.2; of 8, 28 % 47.3 : 44.6 : 46.2; of 2, 20 %
-// 35.7 : 33.9 : 35.6, 7 % 24.1 : 24.5 : 23.5.  With the scores given only V comes in, behind a pass over the pool: groups of 4, 40 % 231 : 224 :
-// 223 and 84.8 : 84.9 : 85.5, 28 % 141.0 : 141.3 : 141.9; of 8, 90 % 225 : 204 : 202, 80 % 114 : 111 : 117, 28 % 41.2 : 42.2 : 41.7.
 void order_gather(AttnArgs &ga, bool managed)
 {
-    const int64_t g = ga.sh.group, percent = ga.kv.cap > 0 ? 100 * g * ga.k_max / ga.kv.cap : 0;
-    if (g == 1) return;
-    ga.by_group = managed || percent >= (!ga.sel_scores && g == 2 ? 16 : 40);
-    ga.keep = !ga.sel_scores && (managed || (ga.by_group && g > 2));
+    const GatherOrder o = gather_order(ga.sh.group, ga.k_max, ga.kv.cap, ga.sel_scores != nullptr);
+    ga.by_group = (managed && ga.sh.group > 1) || o.by_group;
+    ga.keep = (managed && ga.sh.group > 1) || o.keep;
 }
 
 // Tokens per window split: in a launch of its own the window wants about HGCA_TARGET_WGS_DENSE workgroups; in a launch

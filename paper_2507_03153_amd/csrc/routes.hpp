@@ -1,0 +1,32 @@
+// Rules by which the entry points choose among paths that give the same results: plain functions of sizes, without HIP.
+#pragma once
+
+#include <stdint.h>
+
+namespace hgca {
+
+// Whether the workgroups of a gather run by groups of heads (GatherPlace), and whether the rows of K and V stay in the cache for
+// the group's other heads or are streamed past it: by how much of the pool a group's lists would cover if they shared nothing,
+// group * k_max / pool.  Heads of a group may list many of the same tokens or hardly any; the limits lie where lists that
+// share no more than chance gives them lose nothing to speak of.  Measured, in percent of what the order head by head takes, groups
+// of 4, lists that share nothing / a quarter of their entries at 7 % of the pool:
+//   kept        coverage 20 % 107 / 105   29 % 101 / 89   36 % 99 / 85   48 % 102 / 95   60 % 92 / 76   (8 sequences, 28 672 tokens)
+//               29 % 98 / 88   34 % 98 / 87   40 % 98 / 87                                    (64 sequences of 2 K to 16 K tokens in blocks)
+//   lists of a selection on random keys, 29 %: 67.1 -> 70.9 us per step; fp32 28 % 105 / 100, 40 % 101 / 90, 60 % 95 / 84
+// Groups of 8 by groups: 28 % 98 / 93, 40 % 97 / 91, 60 % 92 / 79; kept 40 % 105 / 89, 60 % 96 / 76; where the window shares their
+// launch only the kept order is built: in small bf16 steps no order matters; fp32, 45 %, 16 sequences kept 99 / 86, 4 104 / 101.  Groups of 2 by groups: 16 % 100 /
+// 100, 30 % 98 / 94; kept 106 / 103, 103 / 94.
+// With the scores given only V comes in, behind a pass over the pool: by groups 36 % 96.5 .. 101, 45 % 96 .. 101, 90 % 92 .. 101 (groups
+// of 2, 4 and 8, 2 to 32 sequences of 6 K to 40 K tokens).
+struct GatherOrder {
+    bool by_group, keep;
+};
+inline GatherOrder gather_order(int64_t group, int64_t k_max, int64_t pool, bool scored)
+{
+    if (group <= 1 || pool <= 0) return {false, false};
+    const int64_t covered = 100 * group * k_max;
+    const bool by_group = covered >= (group == 2 && !scored ? 16 : 36) * pool;
+    return {by_group, by_group && !scored && (group == 4 || (group == 8 && covered >= 50 * pool))};
+}
+
+}  // namespace hgca

@@ -1,0 +1,56 @@
+"""The rules that choose among paths with the same results (csrc/routes.hpp), compiled for the host: the sizes that a rule was
+placed by fall on the side they were measured for."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include <cstdio>
+#include <cstring>
+#include "routes.hpp"
+int main(int argc, char **argv)
+{
+    long long v[8];
+    char what[32];
+    while (std::scanf("%31s", what) == 1) {
+        if (!std::strcmp(what, "order")) {
+            for (int i = 0; i < 4; ++i) if (std::scanf("%lld", v + i) != 1) return 1;
+            const hgca::GatherOrder o = hgca::gather_order(v[0], v[1], v[2], v[3] != 0);
+            std::printf("%d\n", o.keep ? 2 : o.by_group ? 1 : 0);
+        }
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("routes")
+    src, exe = d / "routes.cpp", d / "routes"
+    src.write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I" + os.path.join(ROOT, "paper_2507_03153_amd", "csrc"),
+                    "-I" + os.path.join(ROOT, "include"), str(src), "-o", str(exe)], check=True)
+
+    def ask(*lines):
+        out = subprocess.run([str(exe)], input="\n".join(lines), capture_output=True, text=True, check=True).stdout
+        return [int(x) for x in out.split()]
+    return ask
+
+
+# group, k_max, pool, scores given -> 0 head by head, 1 by groups, 2 by groups with the rows kept
+ORDER = [
+    # 64 sequences of 2 K to 16 K tokens, a tenth of each pool listed: lists of 1405 to 1433 for a pool of 14 336, 39.2 to 40 %
+    ((4, 1405, 14336, 0), 2), ((4, 1433, 14336, 0), 2), ((4, 1433, 14336, 1), 1), ((4, 1405, 14336, 1), 1),
+    ((4, 2048, 28672, 0), 0), ((4, 2048, 28672, 1), 0),                  # 28.6 %, lists of a selection
+    ((8, 1434, 28672, 0), 1), ((8, 2048, 28672, 1), 1), ((8, 2150, 28672, 0), 2), ((8, 1720, 28672, 0), 1), ((8, 4096, 122880, 0), 0),
+    ((2, 1146, 14336, 0), 0), ((2, 1147, 14336, 0), 1), ((2, 14336, 14336, 0), 1), ((2, 2000, 14336, 1), 0),
+    ((1, 14336, 14336, 0), 0), ((4, 100, 0, 0), 0), ((4, 0, 14336, 0), 0), ((8, 2147483647, 2147483647, 0), 2),
+]
+
+
+def test_order_of_the_gather(rules):
+    got = rules(*("order %d %d %d %d" % a for a, _ in ORDER))
+    assert got == [want for _, want in ORDER]
