@@ -174,11 +174,12 @@ bool shares_launch(const hgca_shape *s, int64_t window, int64_t pool, int64_t k_
     return wgs <= (s->head_dim == 64 ? (token ? 4096 : 1024) : (token ? 1024 : 512));
 }
 
-void order_gather(AttnArgs &ga, bool managed)
+// pool: tokens the pool can hold (a managed pool's capacity may count the window's blocks)
+void order_gather(AttnArgs &ga, int64_t pool, bool managed)
 {
-    const GatherOrder o = gather_order(ga.sh.group, ga.k_max, ga.kv.cap, ga.sel_scores != nullptr);
-    ga.by_group = (managed && ga.sh.group > 1) || o.by_group;
-    ga.keep = (managed && ga.sh.group > 1) || o.keep;
+    const GatherOrder o = gather_order(ga.sh.group, ga.k_max, pool, ga.sel_scores != nullptr, managed);
+    ga.by_group = o.by_group;
+    ga.keep = o.keep;
 }
 
 // Tokens per window split: in a launch of its own the window wants about HGCA_TARGET_WGS_DENSE workgroups; in a launch
@@ -729,7 +730,7 @@ int hgca_hybrid_decode_step(const hgca_shape *shape, const void *q, const hgca_k
     ga.k_max = k_max;
     ga.chunk = gather_chunk;
     ga.part = partials_at(ws_sparse, wsp, std::max(1, n_splits_for(k_max, ga.chunk)));
-    order_gather(ga, false);
+    order_gather(ga, pool->cap, false);
     if (fuse_gather) rc = from_hip(launch_dense_gather(shape->dtype, shape->head_dim, da, ga, s));
     else rc = from_hip(launch_attn_partial_gather(shape->dtype, shape->head_dim, ga, s));
     if (rc != HGCA_OK) return rc;
@@ -778,7 +779,7 @@ int hgca_hybrid_decode_step_selected(const hgca_shape *shape, const void *q, con
     ga.k_max = k_max;
     ga.chunk = gather_chunk;
     ga.part = partials_at(ws_sparse, wsp, std::max(1, n_splits_for(k_max, ga.chunk)));
-    order_gather(ga, false);
+    order_gather(ga, pool->cap, false);
     // gpu_attention over the window and cpu_attention over the listed entries: one launch where the shapes allow
     if (one_launch) {
         if ((rc = from_hip(launch_dense_gather(shape->dtype, shape->head_dim, da, ga, s))) != HGCA_OK) return rc;
@@ -940,7 +941,7 @@ int hgca_managed_decode_step(const hgca_shape *shape, const hgca_cache_state *ca
     ga.k_max = cache->k_max;
     ga.chunk = gather_chunk;
     ga.part = partials_at(ws_sparse, wsp, std::max(1, n_splits_for(cache->k_max, ga.chunk)));
-    order_gather(ga, true);
+    order_gather(ga, std::min<int64_t>(pool.cap, (int64_t)(cache->max_blocks - cache->win_blocks) * cache->block_size), true);
     // the two parts need nothing from each other: one launch where the shapes allow
     if (one_launch) {
         if ((rc = from_hip(launch_dense_gather(shape->dtype, shape->head_dim, da, ga, s, token_joins_in_split ? k_in : nullptr,

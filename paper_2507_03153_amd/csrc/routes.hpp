@@ -16,17 +16,23 @@ namespace hgca {
 // Groups of 8 by groups: 28 % 98 / 93, 40 % 97 / 91, 60 % 92 / 79; kept 40 % 105 / 89, 60 % 96 / 76; where the window shares their
 // launch only the kept order is built: in small bf16 steps no order matters; fp32, 45 %, 16 sequences kept 99 / 86, 4 104 / 101.  Groups of 2 by groups: 16 % 100 /
 // 100, 30 % 98 / 94; kept 106 / 103, 103 / 94.
+// Managed lists have room to grow and are rarely full: the coverage by their capacity says less, and the limit is lower.  Loops,
+// kept, lists that share nothing / a quarter: groups of 4, coverage by capacity 12 %, half full 103, 103, 100 / 100, 100, 99 and 20 %
+// 103, 100, 102 / 102, 94, 98, nearly full 101, 98, 100 / 98, 86, 94, 32 % 100, 105, 96 / 96, 82, 88 (8 sequences, 28 672 tokens; 6,
+// 60 032; 8, 14 336); room for a seventh of the pool, 57 %, filled to 30, 50 and 85 %: 8 sequences, 28 672 101, 99, 107 / 95, 95, 95; 6,
+// 63 424 97, 105, 103 / 90, 87, 88; groups of 8, 114 %: 14 336 100, 95, 95 / 90, 85, 76, 28 672 100, 107, 105 (shared, 50 %: 92); groups
+// of 2 by groups, 28 %: 8 sequences, 20 000 93, 94, 99 / 92, 91, 96, 5, 48 960 103, 99, 99 / 102, 97, 95.
 // With the scores given only V comes in, behind a pass over the pool: by groups 36 % 96.5 .. 101, 45 % 96 .. 101, 90 % 92 .. 101 (groups
 // of 2, 4 and 8, 2 to 32 sequences of 6 K to 40 K tokens).
 struct GatherOrder {
     bool by_group, keep;
 };
-inline GatherOrder gather_order(int64_t group, int64_t k_max, int64_t pool, bool scored)
+inline GatherOrder gather_order(int64_t group, int64_t k_max, int64_t pool, bool scored, bool managed)
 {
     if (group <= 1 || pool <= 0) return {false, false};
     const int64_t covered = 100 * group * k_max;
-    const bool by_group = covered >= (group == 2 && !scored ? 16 : 36) * pool;
-    return {by_group, by_group && !scored && (group == 4 || (group == 8 && covered >= 50 * pool))};
+    const bool by_group = covered >= (group == 2 && !scored ? 16 : managed ? 20 : 36) * pool;
+    return {by_group, by_group && !scored && (group == 4 || (group == 8 && (managed || covered >= 50 * pool)))};
 }
 
 }  // namespace hgca

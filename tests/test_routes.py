@@ -17,8 +17,8 @@ int main(int argc, char **argv)
     char what[32];
     while (std::scanf("%31s", what) == 1) {
         if (!std::strcmp(what, "order")) {
-            for (int i = 0; i < 4; ++i) if (std::scanf("%lld", v + i) != 1) return 1;
-            const hgca::GatherOrder o = hgca::gather_order(v[0], v[1], v[2], v[3] != 0);
+            for (int i = 0; i < 5; ++i) if (std::scanf("%lld", v + i) != 1) return 1;
+            const hgca::GatherOrder o = hgca::gather_order(v[0], v[1], v[2], v[3] != 0, v[4] != 0);
             std::printf("%d\n", o.keep ? 2 : o.by_group ? 1 : 0);
         }
     }
@@ -40,17 +40,20 @@ def rules(tmp_path_factory):
     return ask
 
 
-# group, k_max, pool, scores given -> 0 head by head, 1 by groups, 2 by groups with the rows kept
+# group, k_max, pool, scores given, managed -> 0 head by head, 1 by groups, 2 by groups with the rows kept
 ORDER = [
     # 64 sequences of 2 K to 16 K tokens, a tenth of each pool listed: lists of 1405 to 1433 for a pool of 14 336, 39.2 to 40 %
-    ((4, 1405, 14336, 0), 2), ((4, 1433, 14336, 0), 2), ((4, 1433, 14336, 1), 1), ((4, 1405, 14336, 1), 1),
-    ((4, 2048, 28672, 0), 0), ((4, 2048, 28672, 1), 0),                  # 28.6 %, lists of a selection
-    ((8, 1434, 28672, 0), 1), ((8, 2048, 28672, 1), 1), ((8, 2150, 28672, 0), 2), ((8, 1720, 28672, 0), 1), ((8, 4096, 122880, 0), 0),
-    ((2, 1146, 14336, 0), 0), ((2, 1147, 14336, 0), 1), ((2, 14336, 14336, 0), 1), ((2, 2000, 14336, 1), 0),
-    ((1, 14336, 14336, 0), 0), ((4, 100, 0, 0), 0), ((4, 0, 14336, 0), 0), ((8, 2147483647, 2147483647, 0), 2),
+    ((4, 1405, 14336, 0, 0), 2), ((4, 1433, 14336, 0, 0), 2), ((4, 1433, 14336, 1, 0), 1), ((4, 1405, 14336, 1, 0), 1),
+    ((4, 2048, 28672, 0, 0), 0), ((4, 2048, 28672, 1, 0), 0),                  # 28.6 %, lists of a selection
+    ((8, 1434, 28672, 0, 0), 1), ((8, 2048, 28672, 1, 0), 1), ((8, 2150, 28672, 0, 0), 2), ((8, 1720, 28672, 0, 0), 1), ((8, 4096, 122880, 0, 0), 0),
+    ((2, 1146, 14336, 0, 0), 0), ((2, 1147, 14336, 0, 0), 1), ((2, 14336, 14336, 0, 0), 1), ((2, 2000, 14336, 1, 0), 0),
+    # managed loops: room for a seventh of the pool, for 2480 entries, for a twentieth
+    ((4, 4096, 28704, 0, 1), 2), ((8, 8576, 60064, 0, 1), 2), ((2, 4096, 28704, 0, 1), 1), ((4, 2480, 29168, 0, 1), 2),
+    ((4, 1434, 28672, 0, 1), 2), ((4, 1433, 28672, 0, 1), 0), ((8, 700, 28672, 0, 1), 0), ((2, 700, 28672, 0, 1), 0),
+    ((1, 14336, 14336, 0, 0), 0), ((4, 100, 0, 0, 0), 0), ((4, 0, 14336, 0, 0), 0), ((8, 2147483647, 2147483647, 0, 0), 2),
 ]
 
 
 def test_order_of_the_gather(rules):
-    got = rules(*("order %d %d %d %d" % a for a, _ in ORDER))
+    got = rules(*("order %d %d %d %d %d" % a for a, _ in ORDER))
     assert got == [want for _, want in ORDER]
