@@ -1,5 +1,6 @@
 // Independent kernels of a decode step as ONE launch.
 #include "attn_device.hpp"
+#include "routes.hpp"
 
 #include <type_traits>
 
@@ -11,10 +12,8 @@ namespace {
 //
 // Both are streaming passes that need nothing from each other (Alg. 2 runs gpu_attention and cpu_attention side by
 // side); as two launches of one stream the second waits for the last workgroup of the first, and each pays its own
-// ramp-up and tail.  In one grid the workgroups of the sparse part take over compute units as the window's
-// workgroups drain (or the other way round).  Roles by blockIdx; measured on the 8B shape: with K and V gathered
-// (270 MB against the window's 134 MB) the gather's workgroups go first (68.0 against 69.2 us per step), with V
-// alone gathered (135 MB) the window's (145.8 against 148.3 us per step with a selection).
+// ramp-up and tail.  In one grid the workgroups of one part take over compute units as the other's drain.  Roles by
+// blockIdx; which part starts first is window_first's to say.
 // fp32 takes both parts on the vector units; there and in small steps a launch saved is what counts (managed decode loop of one
 // sequence, fp32, 32 / 8 heads of 64, per step: insert, window, gather and tail 24.8 us, in two launches 18.2).
 #ifndef HGCA_DG_OCC
@@ -41,7 +40,7 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 2 && G < 8 ? HGCA_DG_OCC : 1) 
     using GS = SplitValu<T, D, 1, GMODE, F32 ? kUnroll : HGCA_DG_GATHER_UNROLL, ORDER == 2>;
     constexpr int kLds = DS::kLdsBytes > GS::kLdsBytes ? DS::kLdsBytes : GS::kLdsBytes;
     __shared__ __attribute__((aligned(16))) char s_lds[kLds];
-    // the part with more bytes to move takes the lower block numbers and starts first (the other fills in behind it)
+    // one part takes the lower block numbers and starts first, the other fills in behind it (window_first)
     const int n_gather = (int)gridDim.x - n_dense;
     const bool dense_role = gather_first ? (int)blockIdx.x >= n_gather : (int)blockIdx.x < n_dense;
     const int u = (int)blockIdx.x - (dense_role ? (gather_first ? n_gather : 0) : (gather_first ? 0 : n_dense));
@@ -129,22 +128,23 @@ hipError_t launch_dense_gather(int dtype, int head_dim, const AttnArgs &dense, c
     const KernelArgs da = to_ka(dense), ga = to_ka(gather);
     const dim3 grid((unsigned)(n_dense + n_gather)), block(kBlock);
     const int g = dense.sh.group;
+    const int gather_first = window_first(dtype == 0, g, dense.kv.cap, gather.k_max, gather.sel_scores != nullptr) ? 0 : 1;
     if (dtype == 1 && g == 8 && gather.sel_scores) return hipErrorInvalidValue;  // not built: its callers use two launches
     // the window's splits size the launch's LDS: the common 256-token splits leave room for seven workgroups per unit
-#define HGCA_DG_LAUNCH(T, D, G, GMODE, LD, ORDER, FIRST)                                                            \
+#define HGCA_DG_LAUNCH(T, D, G, GMODE, LD, ORDER)                                                                   \
     hipLaunchKernelGGL((dense_gather_kernel<T, D, G, GMODE, LD, ORDER>), grid, block, 0, s, da, ga, (int)n_dense,   \
-                       dense.part.n_splits, gather.part.n_splits, FIRST, static_cast<const char *>(k_new),        \
+                       dense.part.n_splits, gather.part.n_splits, gather_first, static_cast<const char *>(k_new), \
                        static_cast<const char *>(v_new))
 #define HGCA_DG_SCORED(T, D, G, LD)                                                                                 \
     do {                                                                                                            \
-        if (order) HGCA_DG_LAUNCH(T, D, G, kGatherScored, LD, (G > 1 ? 1 : 0), 0);                                  \
-        else HGCA_DG_LAUNCH(T, D, G, kGatherScored, LD, 0, 0);                                                      \
+        if (order) HGCA_DG_LAUNCH(T, D, G, kGatherScored, LD, (G > 1 ? 1 : 0));                                     \
+        else HGCA_DG_LAUNCH(T, D, G, kGatherScored, LD, 0);                                                         \
     } while (0)
 #define HGCA_DG_GATHER(T, D, G, LD)                                                                                 \
     do {                                                                                                            \
-        if (order == 2) HGCA_DG_LAUNCH(T, D, G, kGather, LD, (G > 1 ? 2 : 0), 1);                                   \
-        else if (order) HGCA_DG_LAUNCH(T, D, G, kGather, LD, (G == 2 ? 1 : G > 1 ? 2 : 0), 1);                      \
-        else HGCA_DG_LAUNCH(T, D, G, kGather, LD, 0, 1);                                                            \
+        if (order == 2) HGCA_DG_LAUNCH(T, D, G, kGather, LD, (G > 1 ? 2 : 0));                                      \
+        else if (order) HGCA_DG_LAUNCH(T, D, G, kGather, LD, (G == 2 ? 1 : G > 1 ? 2 : 0));                         \
+        else HGCA_DG_LAUNCH(T, D, G, kGather, LD, 0);                                                               \
     } while (0)
 #define HGCA_DG_CASE(D, G)                                                                                          \
     if (head_dim == D && g == G) {                                                                                  \

@@ -186,14 +186,14 @@ void order_gather(AttnArgs &ga, int64_t pool, bool managed)
 // it shares with the sparse part's splits, which fill the device anyway, longer splits (half as many partials to write
 // and fold) are better.  Measured on the 8B shape: full step 145.2 -> 143.8 us, steady 67.9 -> 67.6 us; on its own the
 // window is 1 us slower with them.
-// fp32 beside a gather of K and V, whose splits are as long as the window's on the vector units: shorter ones as long as the units
-// do not fill the device by themselves (4 sequences, 64 / 8 heads of 128, window 2048, 1900 listed: 97.3 -> 84.5 us; 8 sequences of 40
-// heads 79.4 -> 85.1).
-int dense_chunk(const hgca_shape *s, int64_t cap, bool shared, bool scored = true)
+// fp32 windows run on the vector units, several times as long per token as the gather's splits: theirs are as short as in a
+// launch of their own (with the longer ones, where a window may be a single split: 40 sequences, 32 / 8 heads of 128, window 512, pool
+// 2500, 60 listed: steady 58 us in two launches, 91 in one; 60 with short splits, 48 with the window's workgroups first as well; step
+// with a selection 170 : 201 : 162.  8 sequences, 64 / 8 heads, window 2048, pool 4096, 100 listed: step 142 : 156 : 140).
+int dense_chunk(const hgca_shape *s, int64_t cap, bool shared)
 {
     const int64_t units = (int64_t)s->batch * s->n_kv_heads;
-    if (s->dtype == HGCA_F32 && !scored && units <= 256) shared = false;
-    if (!shared) return pick_chunk(cap, units, HGCA_TARGET_WGS_DENSE);
+    if (!shared || s->dtype == HGCA_F32) return pick_chunk(cap, units, HGCA_TARGET_WGS_DENSE);
     return no_shorter(pick_chunk(cap, units, HGCA_TARGET_WGS_DENSE_SHARED), cap, kLongWindow);
 }
 
@@ -701,7 +701,7 @@ int hgca_hybrid_decode_step(const hgca_shape *shape, const void *q, const hgca_k
     if (short_step(shape, window->cap, pool->cap, k_max)) {
         // window splits as in the launch shared with the gather; in fp32, on the vector units, half as long (4 sequences, 64 / 8
         // heads, window 8192: 146 -> 117 us; bf16, 1 sequence, 32 / 8 heads, the other way round 24.6 : 27.0)
-        da.chunk = dense_chunk(shape, window->cap, shape->dtype == HGCA_BF16);
+        da.chunk = dense_chunk(shape, window->cap, true);
         da.part = partials_at(ws_dense, wd, n_splits_for(window->cap, da.chunk));
         if ((rc = from_hip(launch_window_scores(shape->dtype, shape->head_dim, da, sa, s))) != HGCA_OK) return rc;
         return from_hip(launch_select_attend(shape->dtype, shape->head_dim, se, da.part, o_out, o_dtype, lse_out, s));
@@ -767,7 +767,7 @@ int hgca_hybrid_decode_step_selected(const hgca_shape *shape, const void *q, con
     const int gather_chunk = gather_split(shape, k_max, HGCA_TARGET_WGS_SPARSE);
     const bool scored = sel_scores != nullptr;
     const bool one_launch = shares_launch(shape, window->cap, pool->cap, k_max, gather_chunk, scored, false);
-    da.chunk = dense_chunk(shape, window->cap, one_launch, scored);
+    da.chunk = dense_chunk(shape, window->cap, one_launch);
     da.part = partials_at(ws_dense, wd, n_splits_for(window->cap, da.chunk));
     AttnArgs ga{};
     ga.sh = da.sh;
@@ -928,7 +928,7 @@ int hgca_managed_decode_step(const hgca_shape *shape, const hgca_cache_state *ca
     da.sh = to_dev(shape);
     da.q = q;
     da.kv = to_dev(&window);
-    da.chunk = dense_chunk(shape, window.cap, one_launch, false);
+    da.chunk = dense_chunk(shape, window.cap, one_launch);
     da.part = partials_at(ws_dense, wd, n_splits_for(window.cap, da.chunk));
     da.raw_scores = a_gpu;
     // cpu_attention over KV_ctx: split kernels over each head's list of salient pool positions

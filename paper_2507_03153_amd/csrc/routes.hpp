@@ -35,4 +35,16 @@ inline GatherOrder gather_order(int64_t group, int64_t k_max, int64_t pool, bool
     return {by_group, by_group && !scored && (group == 4 || (group == 8 && (managed || covered >= 50 * pool)))};
 }
 
+// Whether the window's splits take the lower block numbers of a launch that they share with the gather, and so start first; the
+// other part fills in behind.  With the scores given the gather brings V alone and starts second.  With K and V gathered it has more
+// to bring, in bf16 (8B shape, 270 MB against 134: 68.0 against 69.2 us per step).  In fp32 a window split takes longer than any of the
+// gather's, and started last they are what the launch waits for: 12 sequences, 32 / 8 heads of 128, window 4096, 600 listed 133 : 107
+// us, window 1024, 1900 listed 133 : 134; one sequence, 64 / 8 heads of 64, window 1024, 1900 listed 20.0 : 16.5; over 220 shapes 0.95
+// times, at worst 1.05.  Without groups the two kinds of splits are alike and the bytes decide: 4 sequences, 40 heads of 128, 600
+// listed, window 4096 137 : 123, loops with lists half full, window 256 34.3 : 35.8 per step, 1024 55.9 : 57.3, 2048 86.0 : 83.3.
+inline bool window_first(bool f32, int64_t group, int64_t window, int64_t k_max, bool scored)
+{
+    return scored || (f32 && (group > 1 || window >= 2 * k_max));
+}
+
 }  // namespace hgca

@@ -20,6 +20,9 @@ int main(int argc, char **argv)
             for (int i = 0; i < 5; ++i) if (std::scanf("%lld", v + i) != 1) return 1;
             const hgca::GatherOrder o = hgca::gather_order(v[0], v[1], v[2], v[3] != 0, v[4] != 0);
             std::printf("%d\n", o.keep ? 2 : o.by_group ? 1 : 0);
+        } else if (!std::strcmp(what, "first")) {
+            for (int i = 0; i < 5; ++i) if (std::scanf("%lld", v + i) != 1) return 1;
+            std::printf("%d\n", hgca::window_first(v[0] != 0, v[1], v[2], v[3], v[4] != 0) ? 1 : 0);
         }
     }
 }
@@ -57,3 +60,13 @@ ORDER = [
 def test_order_of_the_gather(rules):
     got = rules(*("order %d %d %d %d %d" % a for a, _ in ORDER))
     assert got == [want for _, want in ORDER]
+
+
+# fp32, group, window, k_max, scores given -> the window's workgroups start first
+FIRST = [((0, 4, 4096, 2048, 0), 0), ((0, 4, 4096, 2048, 1), 1), ((0, 1, 8192, 16, 0), 0), ((1, 4, 512, 60, 0), 1), ((1, 8, 1024, 1900, 0), 1),
+         ((1, 1, 4096, 600, 0), 1), ((1, 1, 1024, 585, 0), 0), ((1, 1, 256, 1800, 0), 0), ((1, 1, 256, 1800, 1), 1)]
+
+
+def test_which_part_of_a_shared_launch_starts_first(rules):
+    got = rules(*("first %d %d %d %d %d" % a for a, _ in FIRST))
+    assert got == [want for _, want in FIRST]
