@@ -21,7 +21,8 @@ namespace hgca {
 // 103, 100, 102 / 102, 94, 98, nearly full 101, 98, 100 / 98, 86, 94, 32 % 100, 105, 96 / 96, 82, 88 (8 sequences, 28 672 tokens; 6,
 // 60 032; 8, 14 336); room for a seventh of the pool, 57 %, filled to 30, 50 and 85 %: 8 sequences, 28 672 101, 99, 107 / 95, 95, 95; 6,
 // 63 424 97, 105, 103 / 90, 87, 88; groups of 8, 114 %: 14 336 100, 95, 95 / 90, 85, 76, 28 672 100, 107, 105 (shared, 50 %: 92); groups
-// of 2 by groups, 28 %: 8 sequences, 20 000 93, 94, 99 / 92, 91, 96, 5, 48 960 103, 99, 99 / 102, 97, 95.
+// of 2, 28 %: 8 sequences, 20 000 92, 96, 100 / 91, 93, 96, 5 sequences, 48 960 104, 101, 97 / 103, 99, 92 (by groups without keeping
+// the rows within 3 % of that; fp32 loops kept 0.98 times that, 30 shapes).
 // With the scores given only V comes in, behind a pass over the pool: by groups 36 % 96.5 .. 101, 45 % 96 .. 101, 90 % 92 .. 101 (groups
 // of 2, 4 and 8, 2 to 32 sequences of 6 K to 40 K tokens).
 struct GatherOrder {
@@ -32,7 +33,7 @@ inline GatherOrder gather_order(int64_t group, int64_t k_max, int64_t pool, bool
     if (group <= 1 || pool <= 0) return {false, false};
     const int64_t covered = 100 * group * k_max;
     const bool by_group = covered >= (group == 2 && !scored ? 16 : managed ? 20 : 36) * pool;
-    return {by_group, by_group && !scored && (group == 4 || (group == 8 && (managed || covered >= 50 * pool)))};
+    return {by_group, by_group && !scored && (managed || group == 4 || (group == 8 && covered >= 50 * pool))};
 }
 
 // Whether the window's splits take the lower block numbers of a launch that they share with the gather, and so start first; the

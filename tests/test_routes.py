@@ -51,7 +51,7 @@ ORDER = [
     ((8, 1434, 28672, 0, 0), 1), ((8, 2048, 28672, 1, 0), 1), ((8, 2150, 28672, 0, 0), 2), ((8, 1720, 28672, 0, 0), 1), ((8, 4096, 122880, 0, 0), 0),
     ((2, 1146, 14336, 0, 0), 0), ((2, 1147, 14336, 0, 0), 1), ((2, 14336, 14336, 0, 0), 1), ((2, 2000, 14336, 1, 0), 0),
     # managed loops: room for a seventh of the pool, for 2480 entries, for a twentieth
-    ((4, 4096, 28704, 0, 1), 2), ((8, 8576, 60064, 0, 1), 2), ((2, 4096, 28704, 0, 1), 1), ((4, 2480, 29168, 0, 1), 2),
+    ((4, 4096, 28704, 0, 1), 2), ((8, 8576, 60064, 0, 1), 2), ((2, 4096, 28704, 0, 1), 2), ((4, 2480, 29168, 0, 1), 2),
     ((4, 1434, 28672, 0, 1), 2), ((4, 1433, 28672, 0, 1), 0), ((8, 700, 28672, 0, 1), 0), ((2, 700, 28672, 0, 1), 0),
     ((1, 14336, 14336, 0, 0), 0), ((4, 100, 0, 0, 0), 0), ((4, 0, 14336, 0, 0), 0), ((8, 2147483647, 2147483647, 0, 0), 2),
 ]
