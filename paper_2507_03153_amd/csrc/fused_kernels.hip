@@ -1,6 +1,5 @@
 // Independent kernels of a decode step as ONE launch.
 #include "attn_device.hpp"
-#include "routes.hpp"
 
 #include <type_traits>
 

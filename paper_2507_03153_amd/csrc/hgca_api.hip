@@ -9,7 +9,6 @@
 #include <cstdint>
 
 #include "hgca_launch.hpp"
-#include "routes.hpp"
 
 namespace {
 
@@ -203,23 +202,6 @@ int score_chunk(const hgca_shape *s, int64_t cap)
 {
     const int target = HGCA_TARGET_WGS_SCORES * (s->n_q_heads / s->n_kv_heads >= 8 ? 2 : 1);
     return pick_chunk(cap, (int64_t)s->batch * s->n_kv_heads, target, s->dtype == HGCA_BF16 ? kMaxScoreChunk : kMaxChunk);
-}
-
-// Whether a step with a selection runs as the two launches of short_step_kernels.hip.  They save two or three dependent
-// launches of 3 to 5 us each; against that a row's list is read by one compute unit alone (its V rows at about 60 GB/s ... 512 KB
-// take 8 us), and a score pass that shares its launch with the window has the window's registers and LDS.  One row per compute
-// unit at most; then, general path : this one, in us
-//   V rows of a list, bf16: 102 KB (k 400) 21.4 : 20.0, 154 KB (k 1207) 32.9 : 33.9, 512 KB (k 2000) 25.5 : 31.8; fp32, which has one
-//   launch more in the general path: 16 KB 24.7 : 15.9, 358 KB 27.9 : 26.6, 512 KB 27.7 : 30.5, 1 MB 34.4 : 43.0
-//   keys of the pool, bf16, groups of up to 4: 164 MB 57.1 : 57.2, 205 MB 76.0 : 73.1, 410 MB 110.6 : 112.0 and 103.6 : 105.7;
-//   groups of 8, whose window takes 70 KB of LDS: 20 MB 30.6 : 27.0, 33 MB 37.5 : 37.0, 51 MB 40.3 : 43.4, 82 MB 46.4 : 53.4
-bool short_step(const hgca_shape *s, int64_t window, int64_t pool, int64_t k_max)
-{
-    if (window <= 0 || pool <= 0 || k_max <= 0 || k_max > kMaxShortList) return false;
-    if ((int64_t)s->batch * s->n_q_heads > 256) return false;
-    const int64_t row = s->head_dim * (s->dtype == HGCA_BF16 ? 2 : 4);
-    if (s->dtype == HGCA_F32) return k_max * row <= 384 << 10;
-    return k_max * row <= 128 << 10 && s->batch * s->n_kv_heads * pool * row <= int64_t(group_of(s) == 8 ? 32 : 256) << 20;
 }
 
 // Workspace layout: [partials o | partials m | partials l | one float per row | scores | scores of the kept entries].
@@ -698,7 +680,7 @@ int hgca_hybrid_decode_step(const hgca_shape *shape, const void *q, const hgca_k
     se.idx = idx_out;
     se.cnt = cnt_out;
     se.sel_scores = sel;
-    if (short_step(shape, window->cap, pool->cap, k_max)) {
+    if (short_step(shape->dtype == HGCA_F32, shape->head_dim, (int64_t)shape->batch * shape->n_kv_heads, group_of(shape), window->cap, pool->cap, k_max)) {
         // window splits as in the launch shared with the gather; in fp32, on the vector units, half as long (4 sequences, 64 / 8
         // heads, window 8192: 146 -> 117 us; bf16, 1 sequence, 32 / 8 heads, the other way round 24.6 : 27.0)
         da.chunk = dense_chunk(shape, window->cap, true);

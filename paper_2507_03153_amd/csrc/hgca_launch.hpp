@@ -7,6 +7,7 @@
 #include <atomic>
 
 #include "hgca_device.hpp"
+#include "routes.hpp"
 
 namespace hgca {
 
@@ -126,7 +127,6 @@ hipError_t launch_select(const SelectArgs &a, hipStream_t s);
 hipError_t launch_window_scores(int dtype, int head_dim, const AttnArgs &dense, const ScoreArgs &scores, hipStream_t s);
 // ... and per row the selection (idx, cnt and sel_scores are written as by launch_select), attention over the selected V rows
 // and the fold with the window's partials.  Lists of up to kMaxShortList entries; a.kv is the pool with its V rows.
-constexpr int kMaxShortList = 16384;
 hipError_t launch_select_attend(int dtype, int head_dim, const SelectArgs &a, const Partials &window, void *o, int o_dtype,
                                 float *lse, hipStream_t s);
 

@@ -23,6 +23,9 @@ int main(int argc, char **argv)
         } else if (!std::strcmp(what, "first")) {
             for (int i = 0; i < 5; ++i) if (std::scanf("%lld", v + i) != 1) return 1;
             std::printf("%d\n", hgca::window_first(v[0] != 0, v[1], v[2], v[3], v[4] != 0) ? 1 : 0);
+        } else if (!std::strcmp(what, "short")) {
+            for (int i = 0; i < 7; ++i) if (std::scanf("%lld", v + i) != 1) return 1;
+            std::printf("%d\n", hgca::short_step(v[0] != 0, v[1], v[2], v[3], v[4], v[5], v[6]) ? 1 : 0);
         }
     }
 }
@@ -70,3 +73,23 @@ FIRST = [((0, 4, 4096, 2048, 0), 0), ((0, 4, 4096, 2048, 1), 1), ((0, 1, 8192, 1
 def test_which_part_of_a_shared_launch_starts_first(rules):
     got = rules(*("first %d %d %d %d %d" % a for a, _ in FIRST))
     assert got == [want for _, want in FIRST]
+
+
+# fp32, head_dim, sequences * KV heads, group, window, pool, k_max -> the step takes two launches
+SHORT = [
+    ((1, 64, 4, 1, 256, 2048, 64), 1), ((0, 128, 8, 4, 256, 2048, 512), 1), ((0, 128, 8, 4, 256, 2048, 513), 0),
+    ((1, 128, 8, 4, 256, 2048, 768), 1), ((1, 128, 8, 4, 256, 2048, 769), 0), ((1, 64, 8, 4, 256, 4096, 1536), 1), ((1, 64, 8, 4, 256, 4096, 1537), 0),
+    ((0, 64, 64, 4, 256, 2048, 64), 1), ((0, 64, 65, 4, 256, 2048, 64), 0), ((0, 64, 32, 8, 256, 2048, 64), 1), ((0, 64, 33, 8, 256, 2048, 64), 0),
+    ((0, 128, 8, 4, 256, 131072, 64), 1), ((0, 128, 8, 4, 256, 131073, 64), 0), ((0, 128, 8, 8, 256, 16384, 64), 1), ((0, 128, 8, 8, 256, 16385, 64), 0),
+    # fp32 heads of 64 in groups of 8: the pool's keys and the list together
+    ((1, 64, 8, 8, 1024, 16384, 1536), 1), ((1, 64, 8, 8, 1024, 32768, 1536), 0), ((1, 64, 32, 8, 1024, 12800, 64), 1), ((1, 64, 32, 8, 1024, 12800, 640), 0),
+    ((1, 128, 32, 8, 1024, 64000, 768), 1), ((1, 64, 64, 4, 1024, 64000, 1536), 1),
+    # more workgroups than a flat grid has numbers for
+    ((1, 64, 256, 1, 256, 2000000, 64), 1), ((1, 64, 256, 1, 256, 2200000, 64), 0),
+    ((1, 64, 4, 1, 0, 2048, 64), 0), ((1, 64, 4, 1, 256, 0, 64), 0), ((1, 64, 4, 1, 256, 2048, 0), 0),
+]
+
+
+def test_short_steps(rules):
+    got = rules(*("short %d %d %d %d %d %d %d" % a for a, _ in SHORT))
+    assert got == [want for _, want in SHORT]
