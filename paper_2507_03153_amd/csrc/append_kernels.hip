@@ -416,7 +416,12 @@ __global__ __launch_bounds__(kAttnBlock, sizeof(T) == 2 ? 2 : 1) void append_att
                     x[dt] = __builtin_bit_cast(bf16x8, both);
                 }
             };
-            if constexpr (!F32) {                    // the first V rows travel while the maxima are formed
+            // With the weights in two parts, heads of 64 are better without the reads ahead: the fences between the groups cost more than
+            // they save where several blocks of rows share K and V (5 sequences of 40 heads, 144 queries, whole turn 497 -> 520 us, 480 without;
+            // 200 queries x 4 heads 529 -> 546, 492; one block of rows the same within 1 %).  In one part heads of 64 gain 2 to 5 % from them,
+            // heads of 128 1 to 3 %.
+            constexpr bool kReadAheadV = !F32 && (D > 64 || !SPLIT_P);
+            if constexpr (kReadAheadV) {             // the first V rows travel while the maxima are formed
                 read_v(0, vop[0]);
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -498,12 +503,16 @@ __global__ __launch_bounds__(kAttnBlock, sizeof(T) == 2 ? 2 : 1) void append_att
                 ph = __builtin_bit_cast(bf16x8, make_uint4(hi[0], hi[1], hi[2], hi[3]));
                 pl = __builtin_bit_cast(bf16x8, make_uint4(lo[0], lo[1], lo[2], lo[3]));
             };
-            // O^T += V^T P^T: the V rows of the next group are read, and its weights formed, beside a group's products
+            // O^T += V^T P^T: with kReadAheadV the V rows of the next group are read, and its weights formed, beside a group's products
             weigh(0);
 #pragma unroll
             for (int g = 0; g < 2 * NT; ++g) {
-                __builtin_amdgcn_sched_barrier(0);
-                if (g + 1 < 2 * NT) read_v(g + 1, vop[(g + 1) % 2]);
+                if constexpr (kReadAheadV) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (g + 1 < 2 * NT) read_v(g + 1, vop[(g + 1) % 2]);
+                } else {
+                    read_v(g, vop[g % 2]);
+                }
                 const bf16x8 ph_g = ph, pl_g = pl;
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt)
