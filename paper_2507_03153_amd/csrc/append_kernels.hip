@@ -548,7 +548,9 @@ __global__ __launch_bounds__(kAttnBlock, sizeof(T) == 2 ? 2 : 1) void append_att
                 __syncthreads();
                 if (s + 1 < steps) request(s + 1, k_next, v_next);
                 // Two workgroups share a unit, and the older one's waves go first: it would be done after two thirds of the
-                // launch and leave the other alone.  The further a workgroup is, the lower its priority.
+                // launch and leave the other alone.  The further a workgroup is in its pass over a tier, the lower its priority.
+                // (A share is one pass, but for the one that holds the end of the pool and the start of the window and for tiers
+                // in blocks so small that their table takes several passes: those start over.)
                 const int left = steps - s;
                 if (2 * left > steps) __builtin_amdgcn_s_setprio(3);
                 else if (4 * left > steps) __builtin_amdgcn_s_setprio(2);
