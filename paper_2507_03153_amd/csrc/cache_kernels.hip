@@ -35,11 +35,13 @@ __global__ __launch_bounds__(kRowBlock) void kv_append_kernel(CacheDev c, const 
     constexpr int U = 4;
     uint4 kr[U], vr[U];
     int i0 = (int)blockIdx.y * kRowBlock + (int)threadIdx.x;
+    if (n_tokens <= c.win_cap) {                               // else no window takes them, and nothing of them is read
 #pragma unroll
-    for (int u = 0; u < U; ++u) {                              // the first rows travel while the sequence's state is looked up
-        const int64_t at = (src + min(i0 + u * stride, total - 1)) * 16;
-        kr[u] = load16(k_in + at);
-        vr[u] = load16(v_in + at);
+        for (int u = 0; u < U; ++u) {                          // the first rows travel while the sequence's state is looked up
+            const int64_t at = (src + min(i0 + u * stride, total - 1)) * 16;
+            kr[u] = load16(k_in + at);
+            vr[u] = load16(v_in + at);
+        }
     }
     if (active && !active[b]) return;
     const int len = c.win_lens[b];

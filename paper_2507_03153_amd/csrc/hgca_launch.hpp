@@ -201,7 +201,7 @@ constexpr int32_t kCacheWindowFull = 1, kCacheContextFull = 2, kCacheListFull = 
 __device__ __forceinline__ int pending_window_len(int len, int first_block, int n_new, int cap, int block_size,
                                                   int max_blocks, int32_t *fail_bits)
 {
-    const bool no_room = len + n_new > cap;
+    const bool no_room = len >= 0 && n_new > cap - len;          // (no sum of the two, which may be no int)
     if (len < 0 || no_room || first_block + (len + n_new - 1) / block_size >= max_blocks) {
         if (fail_bits) *fail_bits = no_room ? kCacheWindowFull : kCacheContextFull;
         return len;
