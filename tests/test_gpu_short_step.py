@@ -10,7 +10,8 @@ from paper_2507_03153_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
 
-# 128 rows and budgets of up to 128 KB (bf16) or 384 KB (fp32) of V rows take the short path; "over" cases lie behind the edge
+# up to 256 rows and budgets of up to 128 KB (bf16) or 384 KB (fp32) of V rows take the short path; "over" cases lie behind the edge of
+# the budget (the edges of the rows and of the keys are in test_gpu_step_routes)
 CASES = [
     ("bf16_gqa4", "C2", dict(Hq=8, Hkv=2), 1024, 3000, 512),
     ("bf16_gqa4_over", "C2", dict(Hq=8, Hkv=2), 1024, 3000, 513),
