@@ -448,8 +448,8 @@ int hgca_kv_evict(const hgca_shape *shape, const hgca_cache_state *cache,
  * sparsification with beta where a window has reached l_max).  The same
  * results as hgca_kv_append, hgca_dense_window_attn_maw, hgca_sparse_attn on
  * (ctx_idx, ctx_cnt), hgca_lse_merge_splits and hgca_kv_evict in that order,
- * in two launches where the shapes allow (bf16, groups of 1, 2 or 4): the
- * window split that owns the token's position writes its rows, the splits of
+ * in two launches where the shapes allow (all but large steps of groups of 8
+ * in bf16): the window split that owns the token's position writes its rows, the splits of
  * window and salient lists share the launch, and one launch per (sequence,
  * head) row folds the partials, forms A_gpu with the window's own lse from
  * the same fold, updates A_maw, evicts and stores the window's new length.
