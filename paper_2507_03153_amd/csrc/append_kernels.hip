@@ -643,8 +643,15 @@ template <typename T, int D> struct WeightsStage {
 };
 constexpr int kWManyRowTokens = 2048;            // tokens of a block that more than one pass over the rows goes through
 
+// Heads of 64 in groups of up to 4 leave room for two workgroups on a unit (128 registers, 52 KB): row tiles are worked off pair by
+// pair there.  Four at a time, a pair weighed beside the next one's products, take 166 to 175 registers and the second workgroup:
+// 12 sequences, 16 / 8 heads, 14 K tokens, 48 / 100 queries 43.0 -> 47.8, 84.9 -> 96.6 us, with a window as well 54.2 -> 66.3, 109 ->
+// 125; 3 sequences of 40 heads, up to 24 queries 36.1 -> 38.9; pair by pair 43.2, 84.1, 54.0, 106 and 36.1.  (Groups of 4 over two tiers and
+// groups of 8 never had the room.  The registers of groups of 2 over two tiers come to 150 left alone, 125 when they are bounded; the
+// others stay below by themselves, and 3 sequences of 40 heads take 38.6 us with the bound.)
+template <int D, int G, bool TWO> constexpr bool kWTwoPerUnit = D == 64 && (G < 4 || (G == 4 && !TWO));
 template <typename T, int D, int G, bool TWO>
-__global__ __launch_bounds__(sizeof(T) == 2 ? 512 : 256, sizeof(T) == 2 ? 2 : 1) void append_weights_kernel(
+__global__ __launch_bounds__(sizeof(T) == 2 ? 512 : 256, sizeof(T) == 2 ? (D == 64 && G == 2 && TWO ? 4 : 2) : 1) void append_weights_kernel(
     AppendArgs a1, AppendArgs a2, LineDev line, int streamed)
 {
     using S = WeightsStage<T, D>;
@@ -821,6 +828,27 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 512 : 256, sizeof(T) == 2 ? 2 : 1)
                                 c[i] = scores(x + i);
                                 weigh(x + i, c[i]);
                             }
+                        } else if constexpr (kWTwoPerUnit<D, G, TWO>) {
+                            static_assert(NP <= W, "pair by pair");
+                            uint4 qf[ALL];
+                            auto read = [&](int i) {             // the i-th piece in the order of use
+                                if (i < ALL) qf[i] = q_piece(x + i % W, i / W);
+                            };
+#pragma unroll
+                            for (int i = 0; i < kWAhead; ++i) read(i);
+#pragma unroll
+                            for (int i = 0; i < W; ++i) c[i] = floatx16{};
+#pragma unroll
+                            for (int kk = 0; kk < KK; ++kk) {
+                                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                                for (int i = 0; i < W; ++i) read(W * kk + i + kWAhead);
+#pragma unroll
+                                for (int i = 0; i < W; ++i) c[i] = score_mfma(qf[W * kk + i], kf[kk], c[i]);
+                            }
+                            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                            for (int i = 0; i < W; ++i) weigh(x + i, c[i]);
                         } else {
                             uint4 qf[ALL];
                             auto read = [&](int i) {             // the i-th piece in the order of use
@@ -865,10 +893,14 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 512 : 256, sizeof(T) == 2 ? 2 : 1)
                         for (int r = 0; r < 16; ++r) sum[r % NS] += c[r];
                     };
                     if (live == RT && spread == 1 && tok0 + kWTile <= seen_by_all) {     // uniform over the wave: straight-line code
-                        floatx16 c[RT];
-                        tiles_of(0, std::integral_constant<int, RT>{}, c);
+                        constexpr int NP = !F32 && kWTwoPerUnit<D, G, TWO> ? 2 : RT;
 #pragma unroll
-                        for (int x = 0; x < RT; ++x) add(c[x]);
+                        for (int x = 0; x < RT; x += NP) {
+                            floatx16 c[NP];
+                            tiles_of(x, std::integral_constant<int, NP>{}, c);
+#pragma unroll
+                            for (int i = 0; i < NP; ++i) add(c[i]);
+                        }
                     } else {
                         // Row r sees the lane's token iff r / G >= token - (len - n_q): the first such row, relative to the
                         // first row that the lane holds.  Tiles that all rows see whole get a limit nothing is below.
