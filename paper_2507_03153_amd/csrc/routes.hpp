@@ -57,15 +57,16 @@ inline bool window_first(bool f32, int64_t group, int64_t window, int64_t k_max,
 //   keys of the pool, bf16, groups of up to 4: 164 MB 57.1 : 57.2, 205 MB 76.0 : 73.1, 410 MB 110.6 : 112.0 and 103.6 : 105.7;
 //   groups of 8, whose window takes 70 KB of LDS: 20 MB 30.6 : 27.0, 33 MB 37.5 : 37.0, 51 MB 40.3 : 43.4, 82 MB 46.4 : 53.4
 //   fp32, 350 MB to 1 GB: groups of up to 4, and of 8 with heads of 128, 0.98 to 1.12 times as fast, so no limit there; groups of 8
-//   with heads of 64, whose window takes 84 registers and 26 KB: 100 MB, list of 16 KB 72.6 : 67.7, 128 KB 66.2 : 67.6, 320 KB 77.5 : 81.3;
-//   64 MB, 205 KB 59.5 : 59.1, 384 KB 62.1 : 64.1; 32 MB, 384 KB 49.6 : 48.2: keys and 256 times the list in 128 MB.
+//   with heads of 64, whose window takes 84 registers and 26 KB: 100 MB, list of 16 KB 72.6 : 67.7, 160 KB 75.7 : 78.6, 320 KB 77.5 : 81.3;
+//   126 MB, 35 KB 62.8 : 58.1; 200 MB, 16 KB 123.9 : 119.3; 128 MB, 100 KB 89.5 : 89.3; 80 MB, 128 KB 67.7 : 67.3, 256 KB 66.2 : 67.6; 64 MB,
+//   205 KB 59.5 : 59.1, 384 KB 62.1 : 64.1; 32 MB, 384 KB 49.6 : 48.2; 312 MB, 175 KB 167.5 : 172.8: by keys times list, up to 256 MB.
 constexpr int64_t kMaxShortList = 1536;          // entries that the limits in bytes leave room for (fp32, heads of 64)
 inline bool short_step(bool f32, int64_t head_dim, int64_t units, int64_t group, int64_t window, int64_t pool, int64_t k_max)
 {
     if (window <= 0 || pool <= 0 || k_max <= 0 || k_max > kMaxShortList || units * group > 256) return false;
     if (units * (window / 64 + pool / 64 + 2) > int64_t(1) << 23) return false;  // threads of a flat grid are counted in 32 bits
     const int64_t row = head_dim * (f32 ? 4 : 2), list = k_max * row, keys = units * pool * row;
-    if (f32) return list <= 384 << 10 && (group < 8 || head_dim > 64 || keys + 256 * list <= 128 << 20);
+    if (f32) return list <= 384 << 10 && (group < 8 || head_dim > 64 || (keys <= 256 << 20 && keys * list <= int64_t(13000) << 30));
     return list <= 128 << 10 && keys <= int64_t(group == 8 ? 32 : 256) << 20;
 }
 
