@@ -54,6 +54,9 @@ inline bool window_first(bool f32, int64_t group, int64_t window, int64_t k_max,
 // unit at most; then, general path : this one, in us
 //   V rows of a list, bf16: 102 KB (k 400) 21.4 : 20.0, 154 KB (k 1207) 32.9 : 33.9, 512 KB (k 2000) 25.5 : 31.8; fp32, which has one
 //   launch more in the general path: 16 KB 24.7 : 15.9, 358 KB 27.9 : 26.6, 512 KB 27.7 : 30.5, 1 MB 34.4 : 43.0
+//   keys of the pool, bf16, heads of 128 in groups of 2 and 4, lists of 16 to 128 KB: 100 MB 45.2 : 45.0 to 41.2 : 39.3, 180 MB 61.1 : 61.5,
+//   65.5 : 64.2 and, partly filled pages, 45.8 : 46.5, 42.9 : 41.7; 240 MB 70.9 : 72.5, 76.2 : 78.4, pages 61.8 : 63.9, 55.6 : 56.9;
+//   others of up to 4: 240 MB heads of 128 alone 64.3 : 63.4, heads of 64 in twos 71.6 : 67.5, pages 56.6 : 59.3;
 //   keys of the pool, bf16, groups of up to 4: 164 MB 57.1 : 57.2, 205 MB 76.0 : 73.1, 410 MB 110.6 : 112.0 and 103.6 : 105.7;
 //   groups of 8, whose window takes 70 KB of LDS: 20 MB 30.6 : 27.0, 33 MB 37.5 : 37.0, 51 MB 40.3 : 43.4, 82 MB 46.4 : 53.4
 //   fp32, 350 MB to 1 GB: groups of up to 4, and of 8 with heads of 128, 0.98 to 1.12 times as fast, so no limit there; groups of 8
@@ -67,7 +70,7 @@ inline bool short_step(bool f32, int64_t head_dim, int64_t units, int64_t group,
     if (units * (window / 64 + pool / 64 + 2) > int64_t(1) << 23) return false;  // threads of a flat grid are counted in 32 bits
     const int64_t row = head_dim * (f32 ? 4 : 2), list = k_max * row, keys = units * pool * row;
     if (f32) return list <= 384 << 10 && (group < 8 || head_dim > 64 || (keys <= 256 << 20 && keys * list <= int64_t(13000) << 30));
-    return list <= 128 << 10 && keys <= int64_t(group == 8 ? 32 : 256) << 20;
+    return list <= 128 << 10 && keys <= int64_t(group == 8 ? 32 : group > 1 && head_dim > 64 ? 192 : 256) << 20;
 }
 
 }  // namespace hgca

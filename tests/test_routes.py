@@ -37,7 +37,9 @@ SHORT = [
     ((1, 64, 4, 1, 256, 2048, 64), 1), ((0, 128, 8, 4, 256, 2048, 512), 1), ((0, 128, 8, 4, 256, 2048, 513), 0),
     ((1, 128, 8, 4, 256, 2048, 768), 1), ((1, 128, 8, 4, 256, 2048, 769), 0), ((1, 64, 8, 4, 256, 4096, 1536), 1), ((1, 64, 8, 4, 256, 4096, 1537), 0),
     ((0, 64, 64, 4, 256, 2048, 64), 1), ((0, 64, 65, 4, 256, 2048, 64), 0), ((0, 64, 32, 8, 256, 2048, 64), 1), ((0, 64, 33, 8, 256, 2048, 64), 0),
-    ((0, 128, 8, 4, 256, 131072, 64), 1), ((0, 128, 8, 4, 256, 131073, 64), 0), ((0, 128, 8, 8, 256, 16384, 64), 1), ((0, 128, 8, 8, 256, 16385, 64), 0),
+    ((0, 128, 8, 4, 256, 98304, 64), 1), ((0, 128, 8, 4, 256, 98305, 64), 0), ((0, 128, 8, 2, 256, 98305, 64), 0),
+    ((0, 128, 8, 1, 256, 131072, 64), 1), ((0, 128, 8, 1, 256, 131073, 64), 0), ((0, 64, 8, 4, 256, 262144, 64), 1), ((0, 64, 8, 4, 256, 262145, 64), 0),
+    ((0, 128, 8, 8, 256, 16384, 64), 1), ((0, 128, 8, 8, 256, 16385, 64), 0),
     # fp32 heads of 64 in groups of 8: the pool's keys and the list together
     ((1, 64, 8, 8, 1024, 16384, 1536), 1), ((1, 64, 8, 8, 1024, 32768, 1536), 0), ((1, 64, 32, 8, 1024, 12800, 64), 1), ((1, 64, 29, 8, 374, 17015, 141), 1),
     ((1, 64, 32, 8, 300, 32768, 64), 1), ((1, 64, 32, 8, 300, 32769, 64), 0), ((1, 64, 32, 8, 1024, 12800, 640), 0),
