@@ -194,9 +194,7 @@ __device__ __forceinline__ void value_pass(const KernelArgs &a, float (*s_p)[LD]
     for (int g = 0; g < NH; ++g)
 #pragma unroll
         for (int e = 0; e < EPL; ++e) {
-            float v = acc[g][e];
-#pragma unroll
-            for (int off = LPR; off < kWave; off <<= 1) v += __shfl_xor(v, off, kWave);
+            const float v = strided_sum<LPR>(acc[g][e]);
             if (r == 0) s_red[w][g][c * EPL + e] = v;
         }
     __syncthreads();

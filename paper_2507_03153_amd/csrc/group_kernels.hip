@@ -41,12 +41,7 @@ __global__ __launch_bounds__(kUBlock) void union_lists_kernel(const int32_t *idx
     for (int w0 = 0; w0 < words; w0 += kUBlock, buf ^= 1) {
         uint32_t word = w0 + tid < words ? s_bits[w0 + tid] : 0u;
         const int c = __popc(word);
-        int incl = c;                            // inclusive scan over the wave
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            const int v = __shfl_up(incl, off, kWave);
-            if (lane >= off) incl += v;
-        }
+        const int incl = (int)wave_inclusive_scan((uint32_t)c);
         if (lane == kWave - 1) s_wave[buf][w] = incl;
         __syncthreads();                         // s_wave is double-buffered: one barrier per step
         int before = 0, total = 0;

@@ -127,12 +127,7 @@ struct Sel {
     // Exclusive prefix sum over the workgroup; *total receives the sum of all values.
     static __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *scratch, uint32_t *total) {
         const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
-        uint32_t incl = v;
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            const uint32_t up = __shfl_up(incl, off, kWave);
-            if (lane >= off) incl += up;
-        }
+        const uint32_t incl = wave_inclusive_scan(v);
         if (lane == kWave - 1) scratch[w] = incl;
         __syncthreads();
         uint32_t before = 0, all = 0;
@@ -237,11 +232,8 @@ struct Sel {
                 mn = fminf(mn, finite_or(s[e], INFINITY));
             }
         }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            mn = fminf(mn, __shfl_xor(mn, off, kWave));
-            mx = fmaxf(mx, __shfl_xor(mx, off, kWave));
-        }
+        mn = wave_min(mn);
+        mx = wave_max(mx);
         if (lane == 0) { sh.wave_min[w] = mn; sh.wave_max[w] = mx; }
         // the padding will be counted into bin 0: start that bin at minus the number of pads
         for (int i = tid; i < kBins; i += kSelBlock) sh.hist[i] = (i == 0) ? (uint32_t)(n - padded) : 0u;
@@ -439,11 +431,8 @@ struct Sel {
 #pragma unroll
             for (int e = 0; e < 4; ++e) { mx = fmaxf(mx, finite_or(s[e], -INFINITY)); mn = fminf(mn, finite_or(s[e], INFINITY)); }
         }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            mn = fminf(mn, __shfl_xor(mn, off, kWave));
-            mx = fmaxf(mx, __shfl_xor(mx, off, kWave));
-        }
+        mn = wave_min(mn);
+        mx = wave_max(mx);
         if (lane == 0) { sh.wave_min[w] = mn; sh.wave_max[w] = mx; }
         for (int i = tid; i < kBins; i += kSelBlock) sh.hist[i] = 0u;
         if (tid == 0) sh.n_cand = 0;
@@ -675,11 +664,8 @@ struct Sel {
                 }
             }
         }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            mn = fminf(mn, __shfl_xor(mn, off, kWave));
-            mx = fmaxf(mx, __shfl_xor(mx, off, kWave));
-        }
+        mn = wave_min(mn);
+        mx = wave_max(mx);
         if (lane == 0) { sh.wave_min[w] = mn; sh.wave_max[w] = mx; }
         // the padding will be counted into bin 0: start that bin at minus the number of pads
         for (int i = tid; i < kBins; i += kSelBlock) sh.hist[i] = (i == 0) ? (uint32_t)(n - padded) : 0u;

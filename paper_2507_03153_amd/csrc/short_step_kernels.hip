@@ -144,12 +144,10 @@ __global__ __launch_bounds__(kLargeBlock) void select_attend_kernel(SelectArgs a
     else attend(std::integral_constant<int, 8>{});
 #pragma unroll
     for (int e = 0; e < EPL; ++e) {
-#pragma unroll
-        for (int off = LPR; off < kWave; off <<= 1) acc[e] += __shfl_xor(acc[e], off, kWave);
+        acc[e] = strided_sum<LPR>(acc[e]);
         if (r == 0) sh.f.acc[w][c * EPL + e] = acc[e];
     }
-#pragma unroll
-    for (int off = LPR; off < kWave; off <<= 1) l += __shfl_xor(l, off, kWave);      // the lanes of a row hold the same
+    l = strided_sum<LPR>(l);                     // the lanes of a row hold the same
     if (lane == 0) sh.f.l_list[w] = l;
     if (sg < np) {
         const float wgt = pm == -INFINITY ? 0.f : expf(pm - M);

@@ -37,7 +37,7 @@ template <bool STOP_WHEN_FULL, int BLOCK = kRowBlock>
 __device__ __forceinline__ int threshold_compact(CompactShared &sh, const float *wr, int n, double thr, int32_t *out,
                                                  int start, int k_max, int value_offset, float *wn, float &my_sum)
 {
-    const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
     constexpr int NW = BLOCK / kWave, STEP = BLOCK * kPerThread;
     static_assert(kPerThread * NW <= kWave && BLOCK <= kMaxRowBlock, "one lane per (sub-round, wave) count");
     int base = start;
@@ -70,23 +70,17 @@ __device__ __forceinline__ int threshold_compact(CompactShared &sh, const float 
         __syncthreads();
         // exclusive prefix over the (sub-round, wave) counts of the step, one count per lane
         const int c = lane < kPerThread * NW ? sh.cnt[buf][lane] : 0;
-        int incl = c;
-#pragma unroll
-        for (int off = 1; off < kPerThread * NW; off <<= 1) {
-            const int up = __shfl_up(incl, off, kWave);
-            if (lane >= off) incl += up;
-        }
-        const int excl = incl - c;
+        const int incl = (int)wave_inclusive_scan((uint32_t)c), excl = incl - c;
 #pragma unroll
         for (int e = 0; e < kPerThread; ++e) {
-            const int pos = base + __shfl(excl, e * NW + w, kWave) + below[e];
+            const int pos = base + __builtin_amdgcn_readlane(excl, e * NW + w) + below[e];
             if (keep[e] && pos < k_max) {
                 out[pos] = t0 + e * BLOCK + tid + value_offset;
                 if (wn) wn[pos] = x[e];
                 my_sum += x[e];
             }
         }
-        base += __shfl(incl, kPerThread * NW - 1, kWave);
+        base += __builtin_amdgcn_readlane(incl, kPerThread * NW - 1);
     }
     return base;
 }
