@@ -1,6 +1,6 @@
 // Append stage: N queries per sequence attend to one KV tier (Sec. 2.1: S = Q K^T, A = softmax(S),
 // O = A V with Q in R^{h x N x d}; Alg. 2, append branch), or to two.  Both contractions on the matrix
-// cores, bf16 and fp32.
+// cores; bf16 inputs (fp32 ones: append_f32_kernels.hip).
 //
 // Work unit of the attention kernel: one workgroup = one share of the tokens of one (sequence, KV head) and up to 128
 // query rows (a row = one query x one head of the GQA group, query-major).  Every wave owns 32 rows, so nothing is
@@ -14,128 +14,17 @@
 // In both results a lane's column is the query row lane % 32, so the running maximum, the running sum and the
 // rescaling factor of a row live in the lanes that hold its scores AND its output columns: the online softmax needs
 // one lane exchange per row statistic and no LDS.  The probabilities go from the score registers straight into the B
-// operand of the second contraction (the contraction index is matched by reading V^T in the same token order); in bf16
+// operand of the second contraction (the contraction index is matched by reading V^T in the same token order);
 // they are rounded there, as a high and a low part (two MFMAs, fp32-level accuracy) or, on request, as one part.
 //
 // The weights kernel brings its K rows in the same way (it has no second contraction).
-#include "hgca_launch.hpp"
-#include "row_map.hpp"
+#include "append_device.hpp"
 
 #include <type_traits>
 
 namespace hgca {
 
 namespace {
-
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float float2v __attribute__((ext_vector_type(2)));
-
-constexpr int kStepBlocks = 2;                   // 32-token contraction blocks per step
-constexpr int kStepTokens = 32 * kStepBlocks;
-constexpr int kRowsPerBlock = 128;               // query rows of a workgroup
-constexpr int kAttnWaves = kRowsPerBlock / 32, kAttnBlock = kAttnWaves * kWave;   // of the attention: a wave owns 32 of them
-constexpr int kSub = kMaxChunk;                  // entries of the table of rows (paged tiers)
-static_assert(kStepTokens == kLineStep, "shares of a line are whole steps");
-static_assert(kSub * 16 % kStepTokens == 0, "a pass is a whole number of steps");
-
-// Where the rows of a pass over part of a split live.  A contiguous tier is plain arithmetic.  A paged tier gets a
-// table in LDS with one entry per 16 tokens (block sizes are multiples of 16: the row of the granule's first token for
-// this KV head), so a lookup is a shift, whatever the block size, and one filling of kSub entries covers a whole split
-// and the load pipeline is not drained for refills.
-constexpr int kGranule = 16;
-struct BlockRows {
-    const uint32_t *table;                       // LDS; nullptr => row = base + j
-    uint32_t base;
-};
-
-// tokens a pass may cover so that its granules fit the table, a multiple of the step
-__device__ __forceinline__ int pass_length(const KvDev &kv, int nt_total) {
-    return kv.block_table ? kSub * kGranule : max(nt_total, 1);
-}
-
-// `first` is the tier position of the pass's first token, a multiple of kGranule (splits and passes are cut at whole
-// steps), nt the number of tokens; contains a barrier iff the tier is paged (uniform over the workgroup).
-template <int BLOCK>
-__device__ __forceinline__ BlockRows make_block_rows(uint32_t *s_tab, const KvDev &kv, int n_kv_heads, int b, int kvh,
-                                                     int first, int nt)
-{
-    BlockRows m;
-    if (!kv.block_table) {
-        m.table = nullptr;
-        m.base = (uint32_t)(((int64_t)b * n_kv_heads + kvh) * kv.cap + first);
-        return m;
-    }
-    const int32_t *blocks = kv.block_table + (int64_t)b * kv.max_blocks + (kv.first_block ? kv.first_block[b] : 0);
-    const int n_gr = (nt + kGranule - 1) / kGranule;             // <= kSub by pass_length
-    for (int i = threadIdx.x; i < n_gr; i += BLOCK) {
-        const int tok = first + i * kGranule;
-        s_tab[i] = (uint32_t)(((int64_t)blocks[tok / kv.block_size] * n_kv_heads + kvh) * kv.block_size + tok % kv.block_size);
-    }
-    __syncthreads();
-    m.table = s_tab;
-    m.base = 0;
-    return m;
-}
-
-// Reductions over the two halves of a wave (lanes n and n + 32 hold partial results of one query row):
-// v_permlane32_swap of a register with itself returns the lower half twice and the upper half twice, one VALU
-// instruction where a lane shuffle would go through the LDS pipeline.
-__device__ __forceinline__ float halves_max(float x) {
-    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-__device__ __forceinline__ float halves_sum(float x) {
-    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
-
-// Where a query row of a (sequence, KV head) pair lives: query r / G, head r % G of the group.
-struct RowInfo {
-    bool valid;
-    int query;
-    int64_t out_row;                             // (b * N + query) * Hq + head
-};
-
-template <int G>
-__device__ __forceinline__ RowInfo row_info(const AppendArgs &a, int b, int kvh, int r) {
-    RowInfo ri;
-    ri.valid = r < a.n_q * G;
-    ri.query = ri.valid ? r / G : 0;
-    ri.out_row = ((int64_t)b * a.n_q + ri.query) * a.sh.n_q_heads + kvh * G + (ri.valid ? r % G : 0);
-    return ri;
-}
-
-// LDS stage of the attention kernel: the rows of a step are brought in by LDS-direct loads (global_load_lds, 16
-// bytes per lane, no registers in between).  One such instruction fills 1024 consecutive bytes of LDS with whatever
-// 64 pieces its lanes address, so the layout inside each 1 KB group is chosen by the lane -> global address map:
-//   K: row-major rows with the 16-byte pieces of a row XOR-swizzled by the row, so that the 16 rows an A-operand
-//      read touches land on different banks without padding;
-//   V: quads of four rows, interleaved in 32-byte chunks ([quad][column chunk][row of the quad][32 bytes]), so that
-//      the 4 rows x 32 bytes a 16-lane group takes with one transpose read are 128 consecutive bytes and the two
-//      groups of a half wave, which take neighbouring chunks, 256.
-// fp32 rows: K as above; V row-major, the 128-byte chunks of every second quad of rows exchanged in pairs, so that the
-// two halves of a wave, which read the same columns of rows four apart, find them on different banks.
-template <typename T, int D, int NW> struct DmaStage {
-    static constexpr bool kF32 = sizeof(T) == 4;
-    static constexpr int kRowBytes = D * sizeof(T);
-    static constexpr int kPieces = kRowBytes / 16;               // 16-byte pieces per row
-    static constexpr int kSwizzled = kPieces < 16 ? kPieces : 16;
-    static constexpr int kGroupRows = 1024 / kRowBytes;          // rows per load instruction of a wave
-    static constexpr int kGroups = kStepTokens / kGroupRows;     // per step and tensor
-    static constexpr int kLoads = kGroups / NW;                  // per wave, step and tensor
-    static constexpr int kBytes = kStepTokens * kRowBytes;       // per step and tensor
-    static_assert(kGroups % NW == 0 && kLoads >= 1, "the waves share the groups of a step evenly");
-
-    static __device__ __forceinline__ int k_swizzle(int row) { return (row / (16 / kSwizzled)) % kSwizzled; }
-    // byte offset, in a K stage, of logical piece `piece` of step row `row`
-    static __device__ __forceinline__ int k_offset(int row, int piece) {
-        return row * kRowBytes + 16 * (piece ^ k_swizzle(row));
-    }
-    // byte offset, in a bf16 V stage, of the 32-byte column chunk `dt` of step row `row`
-    static __device__ __forceinline__ int v_offset(int row, int dt) {
-        return (row / 4) * (4 * kRowBytes) + dt * 128 + (row % 4) * 32;
-    }
-};
 
 constexpr int kNonTemporal = 2;                  // cache policy of a load: streamed once
 
@@ -149,21 +38,18 @@ __device__ __forceinline__ void wait_for_own_loads() { __builtin_amdgcn_s_waitcn
 // that the pass's end cuts computes rows per lane (tokens behind the end read the last row).  The row numbers of a
 // paged tier are looked up before the first load is issued: an LDS read placed after an LDS-direct load waits for it.
 // POLICY is the loads' cache policy: 0, or kNonTemporal where the rows pass once and are not to stay in the caches.
-template <typename T, int D, int NW, int POLICY>
+template <int D, int NW, int POLICY>
 __device__ __forceinline__ void dma_step(const KvDev &kv, const BlockRows &rows, int step, int nsub, char *k_stage,
                                          char *v_stage)
 {
-    using S = DmaStage<T, D, NW>;
+    using S = DmaStage<D, NW>;
     static_assert(kGranule % S::kGroupRows == 0, "a load stays inside a granule");
     constexpr int kQuadLanes = 4 * S::kRowBytes / 16;
     const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     // what lands at byte 16 * lane of the wave's u-th group: the row inside the group and the byte of the row
-    const int k_row = lane / S::kPieces, v_row = S::kF32 ? k_row : 4 * (lane / kQuadLanes) + (lane % 8) / 2;
+    const int k_row = lane / S::kPieces, v_row = 4 * (lane / kQuadLanes) + (lane % 8) / 2;
     auto k_byte = [&](int u) { return 16 * ((lane % S::kPieces) ^ S::k_swizzle((w + NW * u) * S::kGroupRows + k_row)); };
-    auto v_byte = [&](int u) {
-        if (S::kF32) return 16 * ((lane % S::kPieces) ^ (8 * (((w + NW * u) * S::kGroupRows + v_row) / 4 % 2)));
-        return 16 * (2 * ((lane % kQuadLanes) / 8) + lane % 2);
-    };
+    const int v_byte = 16 * (2 * ((lane % kQuadLanes) / 8) + lane % 2);
     typedef const __attribute__((address_space(1))) void *GlobalPtr;
     typedef __attribute__((address_space(3))) void *LdsPtr;
     if ((step + 1) * kStepTokens <= nsub) {                      // uniform over the workgroup
@@ -181,7 +67,7 @@ __device__ __forceinline__ void dma_step(const KvDev &kv, const BlockRows &rows,
 #pragma unroll
         for (int u = 0; u < S::kLoads; ++u) {
             const size_t at = (size_t)row[u] * S::kRowBytes;
-            const uint32_t k_off = k_row * S::kRowBytes + k_byte(u), v_off = v_row * S::kRowBytes + v_byte(u);
+            const uint32_t k_off = k_row * S::kRowBytes + k_byte(u), v_off = v_row * S::kRowBytes + v_byte;
             __builtin_amdgcn_global_load_lds((GlobalPtr)(kv.k + at + k_off), (LdsPtr)(k_stage + (w + NW * u) * 1024), 16, 0, POLICY);
             __builtin_amdgcn_global_load_lds((GlobalPtr)(kv.v + at + v_off), (LdsPtr)(v_stage + (w + NW * u) * 1024), 16, 0, POLICY);
         }
@@ -199,7 +85,7 @@ __device__ __forceinline__ void dma_step(const KvDev &kv, const BlockRows &rows,
     for (int u = 0; u < S::kLoads; ++u) {
         __builtin_amdgcn_global_load_lds((GlobalPtr)(kv.k + (size_t)kr[u] * S::kRowBytes + k_byte(u)),
                                          (LdsPtr)(k_stage + (w + NW * u) * 1024), 16, 0, 0);
-        __builtin_amdgcn_global_load_lds((GlobalPtr)(kv.v + (size_t)vr[u] * S::kRowBytes + v_byte(u)),
+        __builtin_amdgcn_global_load_lds((GlobalPtr)(kv.v + (size_t)vr[u] * S::kRowBytes + v_byte),
                                          (LdsPtr)(v_stage + (w + NW * u) * 1024), 16, 0, 0);
     }
 }
@@ -211,72 +97,8 @@ __device__ __forceinline__ floatx16 score_mfma(const uint4 &a, const uint4 &b, f
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// The whole contraction of a 32 x 32 tile in fp32 (slices of 8 columns, an instruction per column of a piece).  The
-// instructions go round eight accumulators that are added pairwise: one chain of D / 2 additions would cost the scores
-// three times the rounding error of the tree that a vector dot product forms (weights off by 1e-6 instead of 4e-7).
-template <int KK, typename Piece>
-__device__ __forceinline__ floatx16 score_tile_f32(Piece piece, const uint4 (&b)[KK])
-{
-    constexpr int C = 8;
-    floatx16 c[C];
-#pragma unroll
-    for (int i = 0; i < C; ++i) c[i] = floatx16{};
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-        const floatx4 x = __builtin_bit_cast(floatx4, piece(kk)), y = __builtin_bit_cast(floatx4, b[kk]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) c[(4 * kk + e) % C] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], y[e], c[(4 * kk + e) % C], 0, 0, 0);
-    }
-#pragma unroll
-    for (int n = C / 2; n > 0; n /= 2)
-#pragma unroll
-        for (int i = 0; i < n; ++i) c[i] += c[i + n];
-    return c[0];
-}
-
-constexpr int kXcds = 8;
 constexpr int kWAhead = 2;                       // query pieces of the weights pass that are read ahead
 constexpr int kAhead = 2;                        // slices of the score contraction whose K pieces are read ahead
-
-// The sums of a wave's rows over the tier positions [begin, end) -- of a row only [begin, row_end) -- on the vector
-// units, one token after the other.  As in the kernel below, the two halves of a wave hold the even and the odd 16-byte
-// pieces of their row's query and the output columns 32 dt + 8 (i / 4) + 4 hw + i % 4; all lanes of the wave take part.
-template <int D>
-__device__ __forceinline__ void append_sums_again(const KvDev &kv, int n_kv_heads, int b, int kvh, int begin, int row_end,
-                                                  int end, const uint4 (&q)[D / 8], int hw, float m0, float scale2,
-                                                  floatx16 (&acc)[D / 32])
-{
-#pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt) acc[dt] = floatx16{};
-    const int32_t *blocks = kv.block_table ? kv.block_table + (int64_t)b * kv.max_blocks + (kv.first_block ? kv.first_block[b] : 0)
-                                           : nullptr;
-#pragma unroll 1
-    for (int tok = begin; tok < end; ++tok) {
-        const int64_t row = blocks ? ((int64_t)blocks[tok / kv.block_size] * n_kv_heads + kvh) * kv.block_size + tok % kv.block_size
-                                   : ((int64_t)b * n_kv_heads + kvh) * kv.cap + tok;
-        const char *k = kv.k + row * (D * 4), *v = kv.v + row * (D * 4) + 16 * hw;
-        float s = 0.f;
-#pragma unroll
-        for (int kk = 0; kk < D / 8; ++kk) {
-            const float4 x = *reinterpret_cast<const float4 *>(k + 16 * (2 * kk + hw));
-            const floatx4 y = __builtin_bit_cast(floatx4, q[kk]);
-            s = fmaf(x.w, y[3], fmaf(x.z, y[2], fmaf(x.y, y[1], fmaf(x.x, y[0], s))));
-        }
-        s = halves_sum(s);
-        if (tok >= row_end) continue;
-        const float p = __builtin_amdgcn_exp2f((s - m0) * scale2);
-#pragma unroll
-        for (int dt = 0; dt < D / 32; ++dt)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                const float4 x = *reinterpret_cast<const float4 *>(v + 128 * dt + 32 * q4);
-                acc[dt][4 * q4] = fmaf(p, x.x, acc[dt][4 * q4]);
-                acc[dt][4 * q4 + 1] = fmaf(p, x.y, acc[dt][4 * q4 + 1]);
-                acc[dt][4 * q4 + 2] = fmaf(p, x.z, acc[dt][4 * q4 + 2]);
-                acc[dt][4 * q4 + 3] = fmaf(p, x.w, acc[dt][4 * q4 + 3]);
-            }
-    }
-}
 
 // A workgroup: four waves of 32 query rows over one share of the tokens of one (sequence, KV head).  The scores come
 // from v_mfma_f32_32x32x16_bf16, whose result gives a lane 16 scores of ONE row per 32 tokens (the other 16 are the
@@ -299,19 +121,12 @@ __device__ __forceinline__ void append_sums_again(const KvDev &kv, int n_kv_head
 // A launch may serve TWO tiers (the complete pool and the window of an append turn: Alg. 2 runs the two attentions side
 // by side) as one line of tokens cut into equal shares (LineDev): a workgroup goes through its part of the first tier
 // and its part of the second, usually only one of them, each with the tier's view, mask rule and slot.
-//
-// fp32 inputs run the same kernel on v_mfma_f32_32x32x2_f32: products and sums in fp32 throughout, the weights as they
-// are (SPLIT_P has no meaning).  Its stages take 128 KB, one workgroup per unit; the pass is bound by the matrix
-// instruction (154 TFLOP/s dense).  2 x 24 queries on 5 K tokens, 32 / 8 heads: 340 us as one-query attention per query,
-// K and V read once per query -> 75 us.
-template <typename T, int D, int G, bool SPLIT_P, bool TWO>
-__global__ __launch_bounds__(kAttnBlock, sizeof(T) == 2 ? 2 : 1) void append_attn_kernel(AppendArgs a1, AppendArgs a2,
-                                                                                          LineDev line, int streamed)
+template <int D, int G, bool SPLIT_P, bool TWO>
+__global__ __launch_bounds__(kAttnBlock, 2) void append_attn_kernel(AppendArgs a1, AppendArgs a2, LineDev line, int streamed)
 {
-    constexpr bool F32 = sizeof(T) == 4;
     constexpr int NW = kAttnWaves, BLOCK = kAttnBlock;
-    using S = DmaStage<T, D, NW>;
-    constexpr int KK = D * (int)sizeof(T) / 32;                  // slices of the score contraction
+    using S = DmaStage<D, NW>;
+    constexpr int KK = D / 16;                  // slices of the score contraction
     constexpr int DT = D / 32, NT = kStepTokens / 32;            // 32-column tiles of the output, 32-token tiles of a step
     constexpr float kLog2e = 1.4426950408889634f;
     // two stages per tensor as separate arrays: the compiler then knows that a load into one stage does not
@@ -353,12 +168,10 @@ __global__ __launch_bounds__(kAttnBlock, sizeof(T) == 2 ? 2 : 1) void append_att
     // offset per 16-column slice because of the swizzle) and of the second.  The V^T operand (8 tokens of one column
     // per lane) comes from two transpose reads: lane j of a 16-lane group points at columns 4(j%4).. of row j/4 of a
     // quad of tokens, the two groups of a half wave at neighbouring column chunks.
-    // In fp32 the operand is one float per lane: column n of the 32-column tile, the tile's chunk exchanged with its
-    // neighbour in the upper half's rows.
     int k_lane[KK];
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) k_lane[kk] = S::k_offset(n, 2 * kk + hw);
-    const int v_lane = F32 ? 4 * hw * S::kRowBytes + 4 * n : S::v_offset(4 * hw + lane % 16 / 4, lane / 16 % 2) + 8 * (lane % 4);
+    const int v_lane = S::v_offset(4 * hw + lane % 16 / 4, lane / 16 % 2) + 8 * (lane % 4);
     const LineCut cut(line, b);
     // one tier's part of the share: steps [step_begin, step_end) of the tier, which go to `slot` (see LineDev); all uniform
     auto serve = [&](const AppendArgs &a, int step_begin, int step_end, int slot) {
@@ -384,27 +197,22 @@ __global__ __launch_bounds__(kAttnBlock, sizeof(T) == 2 ? 2 : 1) void append_att
             auto k_piece = [&](int t, int kk) {
                 return *reinterpret_cast<const uint4 *>(k_stage + t * 32 * S::kRowBytes + k_lane[kk]);
             };
-            if constexpr (F32) {
+            // a slice's K pieces are read kAhead slices before the matrix instructions that take them (the scheduler, left
+            // alone, puts the reads right before their use, and every pair of instructions waits for LDS)
+            uint4 kf[KK][NT];
+            auto read_slice = [&](int kk) {
 #pragma unroll
-                for (int t = 0; t < NT; ++t) c[t] = score_tile_f32<KK>([&](int kk) { return k_piece(t, kk); }, qop);
-            } else {
-                // a slice's K pieces are read kAhead slices before the matrix instructions that take them (the scheduler, left
-                // alone, puts the reads right before their use, and every pair of instructions waits for LDS)
-                uint4 kf[KK][NT];
-                auto read_slice = [&](int kk) {
+                for (int t = 0; t < NT; ++t) kf[kk][t] = k_piece(t, kk);
+            };
 #pragma unroll
-                    for (int t = 0; t < NT; ++t) kf[kk][t] = k_piece(t, kk);
-                };
+            for (int kk = 0; kk < kAhead; ++kk) read_slice(kk);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int kk = 0; kk < kAhead; ++kk) read_slice(kk);
+            for (int kk = 0; kk < KK; ++kk) {
+                if (kk + kAhead < KK) read_slice(kk + kAhead);
+#pragma unroll
+                for (int t = 0; t < NT; ++t) c[t] = score_mfma(kf[kk][t], qop[kk], c[t]);        // the accumulators take turns
                 __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int kk = 0; kk < KK; ++kk) {
-                    if (kk + kAhead < KK) read_slice(kk + kAhead);
-#pragma unroll
-                    for (int t = 0; t < NT; ++t) c[t] = score_mfma(kf[kk][t], qop[kk], c[t]);        // the accumulators take turns
-                    __builtin_amdgcn_sched_barrier(0);
-                }
             }
             bf16x8 vop[2][DT];
             auto read_v = [&](int g, bf16x8 (&x)[DT]) {
@@ -420,7 +228,7 @@ __global__ __launch_bounds__(kAttnBlock, sizeof(T) == 2 ? 2 : 1) void append_att
             // they save where several blocks of rows share K and V (5 sequences of 40 heads, 144 queries, whole turn 497 -> 520 us, 480 without;
             // 200 queries x 4 heads 529 -> 546, 492; one block of rows the same within 1 %).  In one part heads of 64 gain 2 to 5 % from them,
             // heads of 128 1 to 3 %.
-            constexpr bool kReadAheadV = !F32 && (D > 64 || !SPLIT_P);
+            constexpr bool kReadAheadV = D > 64 || !SPLIT_P;
             if constexpr (kReadAheadV) {             // the first V rows travel while the maxima are formed
                 read_v(0, vop[0]);
                 __builtin_amdgcn_sched_barrier(0);
@@ -443,9 +251,9 @@ __global__ __launch_bounds__(kAttnBlock, sizeof(T) == 2 ? 2 : 1) void append_att
                 const float m_new = fmaxf(m, halves_max(mx));
                 // a row that has seen nothing yet keeps m = -inf: shift by 0 then, every exponent is -inf and gives 0
                 const float shift_new = (m_new == -INFINITY) ? 0.f : -m_new * scale2;
-                // exactly 1 for a row whose maximum stands, however many other rows of the wave find new ones: in bf16 the
-                // difference of the two shifts as the weights have them (rounded), in fp32 they are not used
-                const float corr = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(F32 ? (m - m_new) * scale2 : shift_new - shift);
+                // exactly 1 for a row whose maximum stands, however many other rows of the wave find new ones: the
+                // difference of the two shifts as the weights have them (rounded)
+                const float corr = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(shift_new - shift);
                 shift = shift_new;
                 m = m_new;
                 l *= corr;
@@ -453,32 +261,6 @@ __global__ __launch_bounds__(kAttnBlock, sizeof(T) == 2 ? 2 : 1) void append_att
                 for (int dt = 0; dt < DT; ++dt) acc[dt] *= corr;
             }
             float sum[4] = {0.f, 0.f, 0.f, 0.f};     // four chains
-            if constexpr (F32) {
-                // the weight of token 32 t + 8 (r / 4) + 4 hw + r % 4 is the B operand of a two-token contraction as it
-                // stands; s - m first: the difference is exact to its own size
-                const float m0 = m == -INFINITY ? 0.f : m;
-                // a step's products go to sums of their own: shorter chains of additions
-                floatx16 part[DT];
-#pragma unroll
-                for (int dt = 0; dt < DT; ++dt) part[dt] = floatx16{};
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const float p = __builtin_amdgcn_exp2f((c[t][r] - m0) * scale2);
-                        sum[r % 4] += p;
-                        const char *v = v_stage + (32 * t + 8 * (r / 4) + r % 4) * S::kRowBytes + v_lane;
-#pragma unroll
-                        for (int dt = 0; dt < DT; ++dt) {
-                            const float x = *reinterpret_cast<const float *>(v + 128 * (dt ^ hw));
-                            part[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(x, p, part[dt], 0, 0, 0);
-                        }
-                    }
-#pragma unroll
-                for (int dt = 0; dt < DT; ++dt) acc[dt] += part[dt];
-                l += (sum[0] + sum[1]) + (sum[2] + sum[3]);
-                return;
-            }
             // 16 tokens at a time: contraction index 8 hw + i of group g stands for the token whose weight the lane holds
             // there, 16 g + 8 (i / 4) + 4 hw + i % 4 of the step
             bf16x8 ph, pl;
@@ -539,8 +321,8 @@ __global__ __launch_bounds__(kAttnBlock, sizeof(T) == 2 ? 2 : 1) void append_att
             // waits for its own loads) orders both.
             const int steps = (nsub + kStepTokens - 1) / kStepTokens;
             auto request = [&](int s, char *k, char *v) {            // (the policy is part of the instructions)
-                if (streamed) dma_step<T, D, NW, kNonTemporal>(kv, rows, s, nsub, k, v);
-                else dma_step<T, D, NW, 0>(kv, rows, s, nsub, k, v);
+                if (streamed) dma_step<D, NW, kNonTemporal>(kv, rows, s, nsub, k, v);
+                else dma_step<D, NW, 0>(kv, rows, s, nsub, k, v);
             };
             request(0, s_k0, s_v0);
             auto step = [&](int s, const char *k_cur, const char *v_cur, char *k_next, char *v_next) {
@@ -564,23 +346,7 @@ __global__ __launch_bounds__(kAttnBlock, sizeof(T) == 2 ? 2 : 1) void append_att
             }
         }
 
-        // A weight of 0 keeps a V row out of the products above only while the row is finite (0 * inf is NaN).  Where that
-        // may have happened -- steps with tokens that some rows do not see, and sums that are not finite -- the wave forms its
-        // sums again on the vector units, every row from what it sees and nothing else (m and l do not depend on V).  In bf16 the
-        // V rows of every token of a tier have to be finite.
-        if constexpr (F32) {
-            bool again = false;
-            if (wave_live && (nt_total % kStepTokens != 0 || vis_min < t0 + nt_total)) {         // uniform over the wave
-                bool finite = true;
-#pragma unroll
-                for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) finite &= fabsf(acc[dt][i]) < INFINITY;
-                again = __any(!finite);
-            }
-            if (again) append_sums_again<D>(kv, a1.sh.n_kv_heads, b, kvh, t0, min(t0 + nt_total, vis), t0 + nt_total, qop, hw,
-                                            m == -INFINITY ? 0.f : m, scale2, acc);
-        }
+        // (the V rows of every token of a tier have to be finite: a weight of 0 keeps a row out of the products only then)
 
         // partial of every valid row: the lane holds output columns 32 dt + 8 q + 4 hw .. + 3 of its row
         l = halves_sum(l);
@@ -630,19 +396,13 @@ __global__ __launch_bounds__(kAttnBlock, sizeof(T) == 2 ? 2 : 1) void append_att
 // A launch over few tokens is a chain of latencies: K is requested before the queries, and a share with fewer tiles than
 // waves deals a tile's rows to several waves, which add up through LDS (100 queries over 512 tokens 8.2 -> 4.8 us, 16
 // queries x 4 heads over 3.5 K tokens 6.8 -> 5.4; workgroups of 64 tokens with a row tile per wave: 4.7 and 4.6).
-//
-// fp32 inputs: the same with v_mfma_f32_32x32x2_f32, four waves (queries and slots take 128 KB).  2 x 24 queries on 5 K
-// tokens: 137 us on the vector units, one tier per launch -> 36 us.
-constexpr int kWTile = 32;
-template <typename T, int D> struct WeightsStage {
-    static constexpr int kWaves = sizeof(T) == 2 ? 8 : 4, kBlock = kWaves * kWave;
-    static constexpr int kRowBytes = D * sizeof(T), kPieces = kRowBytes / 16, kGroupRows = 1024 / kRowBytes;
+template <int D> struct WeightsStage {
+    static constexpr int kWaves = 8, kBlock = kWaves * kWave;
+    static constexpr int kRowBytes = D * 2, kPieces = kRowBytes / 16, kGroupRows = 1024 / kRowBytes;
     static constexpr int kSwizzled = kPieces < 16 ? kPieces : 16;
     static __device__ __forceinline__ int swizzle(int row) { return (row / (16 / kSwizzled)) % kSwizzled; }
     static __device__ __forceinline__ int offset(int row, int piece) { return row * kRowBytes + 16 * (piece ^ swizzle(row)); }
 };
-constexpr int kWManyRowTokens = 2048;            // tokens of a block that more than one pass over the rows goes through
-
 // Heads of 64 in groups of up to 4 leave room for two workgroups on a unit (128 registers, 52 KB): row tiles are worked off pair by
 // pair there.  Four at a time, a pair weighed beside the next one's products, take 166 to 175 registers and the second workgroup:
 // 12 sequences, 16 / 8 heads, 14 K tokens, 48 / 100 queries 43.0 -> 47.8, 84.9 -> 96.6 us, with a window as well 54.2 -> 66.3, 109 ->
@@ -650,15 +410,13 @@ constexpr int kWManyRowTokens = 2048;            // tokens of a block that more 
 // groups of 8 never had the room.  The registers of groups of 2 over two tiers come to 150 left alone, 125 when they are bounded; the
 // others stay below by themselves, and 3 sequences of 40 heads take 38.6 us with the bound.)
 template <int D, int G, bool TWO> constexpr bool kWTwoPerUnit = D == 64 && (G < 4 || (G == 4 && !TWO));
-template <typename T, int D, int G, bool TWO>
-__global__ __launch_bounds__(sizeof(T) == 2 ? 512 : 256, sizeof(T) == 2 ? (D == 64 && G == 2 && TWO ? 4 : 2) : 1) void append_weights_kernel(
+template <int D, int G, bool TWO>
+__global__ __launch_bounds__(WeightsStage<D>::kBlock, D == 64 && G == 2 && TWO ? 4 : 2) void append_weights_kernel(
     AppendArgs a1, AppendArgs a2, LineDev line, int streamed)
 {
-    using S = WeightsStage<T, D>;
-    static_assert(S::kBlock == (sizeof(T) == 2 ? 512 : 256), "the launch bounds above");
+    using S = WeightsStage<D>;
     constexpr int kWWaves = S::kWaves, kWBlock = S::kBlock;
-    constexpr bool F32 = sizeof(T) == 4;
-    constexpr int kSpreadLive = F32 ? 2 : 3;     // row tiles from which dealing them out to idle waves pays
+    constexpr int kSpreadLive = 3;               // row tiles from which dealing them out to idle waves pays
     constexpr int KK = S::kRowBytes / 32, RT = kRowsPerBlock / 32, NS = G < 4 ? G : 4;
     constexpr float kLog2e = 1.4426950408889634f;
     typedef const __attribute__((address_space(1))) void *GlobalPtr;
@@ -672,8 +430,8 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 512 : 256, sizeof(T) == 2 ? (D == 
     const int tid = threadIdx.x, lane = tid % kWave, w = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int n = lane % 32, hw = lane / 32;
     const int n_rows = a1.n_q * G, n_qb = (n_rows + kRowsPerBlock - 1) / kRowsPerBlock;
-    // bf16: exponents in units of ln 2 for the bare v_exp_f32; fp32: expf of the scaled score minus lse, rounded once
-    const float unit = F32 ? 1.f : kLog2e, inv_n = 1.f / (float)a1.n_q, scale = a1.sh.sm_scale * unit;
+    // exponents in units of ln 2 for the bare v_exp_f32
+    const float unit = kLog2e, inv_n = 1.f / (float)a1.n_q, scale = a1.sh.sm_scale * unit;
     const int frag0 = S::offset(n, hw);          // operand of row / token n; slice kk is an exclusive-or of 32 kk away
     char *const slot = s_k[w];
 
@@ -801,7 +559,6 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 512 : 256, sizeof(T) == 2 ? (D == 
                     auto q_piece = [&](int x, int kk) {
                         return *reinterpret_cast<const uint4 *>(s_q + x * 32 * S::kRowBytes + (frag0 ^ (32 * kk)));
                     };
-                    auto scores = [&](int x) { return score_tile_f32<KK>([&](int kk) { return q_piece(x, kk); }, kf); };
                     auto shift_of = [&](int x, int q4) {         // of rows 32 x + 8 q4 + 4 hw .. + 3
                         return *reinterpret_cast<const float4 *>(s_shift + 32 * x + 8 * q4 + 4 * hw);
                     };
@@ -809,8 +566,7 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 512 : 256, sizeof(T) == 2 ? (D == 
                         const float s4[4] = {sh.x, sh.y, sh.z, sh.w};
 #pragma unroll
                         for (int e = 0; e < 4; ++e)
-                            c[4 * q4 + e] = F32 ? expf(fmaf(c[4 * q4 + e], scale, s4[e]))
-                                                : __builtin_amdgcn_exp2f(fmaf(c[4 * q4 + e], scale, s4[e]));
+                            c[4 * q4 + e] = __builtin_amdgcn_exp2f(fmaf(c[4 * q4 + e], scale, s4[e]));
                     };
                     auto weigh = [&](int x, floatx16 &c) {
 #pragma unroll
@@ -822,13 +578,7 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 512 : 256, sizeof(T) == 2 ? (D == 
                     // beside the products of the next pair.
                     auto tiles_of = [&](int x, auto count, floatx16 (&c)[decltype(count)::value]) {
                         constexpr int NP = decltype(count)::value, ALL = NP * KK, W = NP > 1 ? 2 : 1;
-                        if constexpr (F32) {
-#pragma unroll
-                            for (int i = 0; i < NP; ++i) {
-                                c[i] = scores(x + i);
-                                weigh(x + i, c[i]);
-                            }
-                        } else if constexpr (kWTwoPerUnit<D, G, TWO>) {
+                        if constexpr (kWTwoPerUnit<D, G, TWO>) {
                             static_assert(NP <= W, "pair by pair");
                             uint4 qf[ALL];
                             auto read = [&](int i) {             // the i-th piece in the order of use
@@ -893,7 +643,7 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 512 : 256, sizeof(T) == 2 ? (D == 
                         for (int r = 0; r < 16; ++r) sum[r % NS] += c[r];
                     };
                     if (live == RT && spread == 1 && tok0 + kWTile <= seen_by_all) {     // uniform over the wave: straight-line code
-                        constexpr int NP = !F32 && kWTwoPerUnit<D, G, TWO> ? 2 : RT;
+                        constexpr int NP = kWTwoPerUnit<D, G, TWO> ? 2 : RT;
 #pragma unroll
                         for (int x = 0; x < RT; x += NP) {
                             floatx16 c[NP];
@@ -950,50 +700,50 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 512 : 256, sizeof(T) == 2 ? (D == 
     if constexpr (TWO) serve(a2, cut.first_steps);
 }
 
-template <typename T, int D, bool SPLIT_P, bool TWO>
+template <int D, bool SPLIT_P, bool TWO>
 hipError_t launch_attn_tiers(const AppendArgs &a, const AppendArgs &a2, const LineDev &line, dim3 grid, int streamed,
                              hipStream_t s)
 {
     const dim3 block(kAttnBlock);
     switch (a.sh.group) {
-    case 1: hipLaunchKernelGGL((append_attn_kernel<T, D, 1, SPLIT_P, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
-    case 2: hipLaunchKernelGGL((append_attn_kernel<T, D, 2, SPLIT_P, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
-    case 4: hipLaunchKernelGGL((append_attn_kernel<T, D, 4, SPLIT_P, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
-    case 8: hipLaunchKernelGGL((append_attn_kernel<T, D, 8, SPLIT_P, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
+    case 1: hipLaunchKernelGGL((append_attn_kernel<D, 1, SPLIT_P, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
+    case 2: hipLaunchKernelGGL((append_attn_kernel<D, 2, SPLIT_P, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
+    case 4: hipLaunchKernelGGL((append_attn_kernel<D, 4, SPLIT_P, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
+    case 8: hipLaunchKernelGGL((append_attn_kernel<D, 8, SPLIT_P, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-template <typename T, int D, bool SPLIT_P>
+template <int D, bool SPLIT_P>
 hipError_t launch_attn_group(const AppendArgs &a, const AppendArgs &a2, const LineDev &line, int two, dim3 grid,
                              int streamed, hipStream_t s)
 {
-    return two ? launch_attn_tiers<T, D, SPLIT_P, true>(a, a2, line, grid, streamed, s)
-               : launch_attn_tiers<T, D, SPLIT_P, false>(a, a2, line, grid, streamed, s);
+    return two ? launch_attn_tiers<D, SPLIT_P, true>(a, a2, line, grid, streamed, s)
+               : launch_attn_tiers<D, SPLIT_P, false>(a, a2, line, grid, streamed, s);
 }
 
-template <typename T, int D, bool TWO>
+template <int D, bool TWO>
 hipError_t launch_weights_tiers(const AppendArgs &a, const AppendArgs &a2, const LineDev &line, dim3 grid, int streamed,
                                 hipStream_t s)
 {
-    const dim3 block(WeightsStage<T, D>::kBlock);
+    const dim3 block(WeightsStage<D>::kBlock);
     switch (a.sh.group) {
-    case 1: hipLaunchKernelGGL((append_weights_kernel<T, D, 1, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
-    case 2: hipLaunchKernelGGL((append_weights_kernel<T, D, 2, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
-    case 4: hipLaunchKernelGGL((append_weights_kernel<T, D, 4, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
-    case 8: hipLaunchKernelGGL((append_weights_kernel<T, D, 8, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
+    case 1: hipLaunchKernelGGL((append_weights_kernel<D, 1, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
+    case 2: hipLaunchKernelGGL((append_weights_kernel<D, 2, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
+    case 4: hipLaunchKernelGGL((append_weights_kernel<D, 4, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
+    case 8: hipLaunchKernelGGL((append_weights_kernel<D, 8, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-template <typename T, int D>
+template <int D>
 hipError_t launch_weights_group(const AppendArgs &a, const AppendArgs &a2, const LineDev &line, int two, dim3 grid,
                                 int streamed, hipStream_t s)
 {
-    return two ? launch_weights_tiers<T, D, true>(a, a2, line, grid, streamed, s)
-               : launch_weights_tiers<T, D, false>(a, a2, line, grid, streamed, s);
+    return two ? launch_weights_tiers<D, true>(a, a2, line, grid, streamed, s)
+               : launch_weights_tiers<D, false>(a, a2, line, grid, streamed, s);
 }
 
 }  // namespace
@@ -1012,8 +762,10 @@ hipError_t launch_append_attn(int dtype, int head_dim, const AppendArgs &a, cons
     const int64_t blocks = (streams + kXcds - 1) / kXcds * kXcds * n_qb;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
     const dim3 grid = n_qb == 1 ? dim3(line.shares, a.sh.n_kv_heads, a.sh.batch) : dim3((unsigned)blocks);
+    const int two = second ? 1 : 0;
+    if (dtype == 0) return launch_append_attn_f32(head_dim, a, a2, line, two, grid, s);
     const int64_t kv_bytes = 2 * (int64_t)a.sh.batch * a.sh.n_kv_heads * ((int64_t)a.kv.cap + (second ? second->kv.cap : 0)) *
-                             head_dim * (dtype == 0 ? 4 : 2);
+                             head_dim * 2;
     // One block of rows reads every K and V row once: past what the last cache holds (256 MB, by capacity) the loads leave the
     // caches alone.  1.07 GB, 8 x 32 queries, loads without arithmetic 217 -> 185 us, the attention of both tiers 249 -> 243;
     // 537 MB, 4 x 16 queries, whole turn 192 -> 179; 134 MB and less no difference.  Several blocks read the rows again:
@@ -1021,15 +773,12 @@ hipError_t launch_append_attn(int dtype, int head_dim, const AppendArgs &a, cons
     // A managed cache that is filled to a part of its capacity loses nothing: 5 to 50 % of 0.9 to 1.0 GB, whole turns 0.99 to 1.07 times
     // as fast streamed, also where what is in it would fit the last cache for the weights pass.
     const int streamed = n_qb == 1 && kv_bytes >= (int64_t(256) << 20) ? 1 : 0;
-    const int two = second ? 1 : 0;
-    if (dtype == 0 && head_dim == 64) return launch_attn_group<float, 64, false>(a, a2, line, two, grid, streamed, s);
-    if (dtype == 0 && head_dim == 128) return launch_attn_group<float, 128, false>(a, a2, line, two, grid, streamed, s);
     if (dtype == 1 && head_dim == 64)
-        return a.one_part_p ? launch_attn_group<bf16_t, 64, false>(a, a2, line, two, grid, streamed, s)
-                            : launch_attn_group<bf16_t, 64, true>(a, a2, line, two, grid, streamed, s);
+        return a.one_part_p ? launch_attn_group<64, false>(a, a2, line, two, grid, streamed, s)
+                            : launch_attn_group<64, true>(a, a2, line, two, grid, streamed, s);
     if (dtype == 1 && head_dim == 128)
-        return a.one_part_p ? launch_attn_group<bf16_t, 128, false>(a, a2, line, two, grid, streamed, s)
-                            : launch_attn_group<bf16_t, 128, true>(a, a2, line, two, grid, streamed, s);
+        return a.one_part_p ? launch_attn_group<128, false>(a, a2, line, two, grid, streamed, s)
+                            : launch_attn_group<128, true>(a, a2, line, two, grid, streamed, s);
     return hipErrorInvalidValue;
 }
 
@@ -1043,18 +792,17 @@ hipError_t launch_append_weights(int dtype, int head_dim, const AppendArgs &a, c
         return hipErrorInvalidValue;             // the two tiers share the queries and the launch shape
     // (a flat grid would be short of numbers: its threads are counted in 32 bits per dimension)
     const dim3 grid(line.shares, a.sh.n_kv_heads, a.sh.batch);
+    const int two = second ? 1 : 0;
+    if (dtype == 0) return launch_append_weights_f32(head_dim, a, a2, line, two, grid, s);
     // K rows that pass once and are too many to stay in the L2 caches anyway (32 MB, by capacity) are streamed past them:
-    // 470 MB 106 -> 94 us, 33 MB (fp32) 15.1 -> 13.9; 11 MB, which do stay, 5.3 us as they are and 5.7 streamed.  More than
+    // 470 MB 106 -> 94 us; 11 MB, which do stay, 5.3 us as they are and 5.7 streamed.  More than
     // one pass over the rows reads K again: 33 queries x 4 heads 192 us as they are, 211 streamed.
     const bool one_pass = (int64_t)a.n_q * a.sh.group <= kRowsPerBlock;
-    const int64_t row_bytes = (int64_t)head_dim * (dtype == 0 ? 4 : 2);
+    const int64_t row_bytes = (int64_t)head_dim * 2;
     const int64_t k_bytes = (int64_t)a.sh.batch * a.sh.n_kv_heads * ((int64_t)a.kv.cap + (second ? second->kv.cap : 0)) * row_bytes;
-    const int streamed = (one_pass || dtype == 0) && k_bytes >= (int64_t(16) << 20) ? 1 : 0;
-    const int two = second ? 1 : 0;
-    if (dtype == 0 && head_dim == 64) return launch_weights_group<float, 64>(a, a2, line, two, grid, streamed, s);
-    if (dtype == 0 && head_dim == 128) return launch_weights_group<float, 128>(a, a2, line, two, grid, streamed, s);
-    if (dtype == 1 && head_dim == 64) return launch_weights_group<bf16_t, 64>(a, a2, line, two, grid, streamed, s);
-    if (dtype == 1 && head_dim == 128) return launch_weights_group<bf16_t, 128>(a, a2, line, two, grid, streamed, s);
+    const int streamed = one_pass && k_bytes >= (int64_t(16) << 20) ? 1 : 0;
+    if (dtype == 1 && head_dim == 64) return launch_weights_group<64>(a, a2, line, two, grid, streamed, s);
+    if (dtype == 1 && head_dim == 128) return launch_weights_group<128>(a, a2, line, two, grid, streamed, s);
     return hipErrorInvalidValue;
 }
 

@@ -1017,7 +1017,7 @@ int line_shares(int64_t units, int64_t tokens, int most, int places, int overhea
 // with 45; 8 x 32 queries x 4 heads over 32 K tokens 260 with 8 (two workgroups per compute unit), 282 with 4.
 // (With the weights rounded to bf16, fewer shares also mean fewer weights that are exactly 1: 55 queries over 5.6 K tokens 6.7e-4
 // off with 30 shares, 6.3e-4 with 45.)
-// In fp32 a compute unit holds one workgroup, whose steps are several times as long as its start and its partial.
+// In fp32 a compute unit holds one workgroup.
 int append_shares(const hgca_shape *s, int32_t n_q, int64_t tokens, int most)
 {
     const int64_t units = append_units(s, n_q);
@@ -1041,23 +1041,25 @@ int append_shares(const hgca_shape *s, int32_t n_q, int64_t tokens, int most)
 }
 
 // fp32, few queries: one-query attention per (sequence, query) with the split kernels of the decode path, which read K and V
-// once per query and work out no more than its rows, against the matrix instructions, which work out 32 rows whatever
+// once per query and work out no more than its rows, against the matrix instructions, which work out 16 rows whatever
 // there are.  The lower estimate has it, in us: query by query 6 + 1.5 per head of a group, and the K and V bytes of all
-// queries at what the vector units take (28 TB/s over the heads of a group) or the rows come from (20 TB/s out of L2,
+// queries at what the vector units take (45 TB/s over the heads of a group) or the rows come from (20 TB/s out of L2,
 // 13.7 out of the last cache, 7.6 out of memory); on the matrix instructions 7, and the steps of a workgroup, one at a time
-// per compute unit, 9.8 each (head_dim 128).  Measured, query by query against matrix: 4 sequences, 32 heads, 4 K tokens,
-// 1 / 4 / 5 queries 80 : 314, 278 : 315, 351 : 316 us; 2 sequences, 32 / 8 heads, 4 K tokens, 2 / 4 / 8 queries 30 : 47,
-// 49 : 48, 86 : 48; one sequence, 4 heads of 64, 2 K tokens, 8 / 32 queries 8.2 : 11.3, 12.2 : 11.7.
+// per compute unit, 3.4 each and up to 2.7 more with 128 rows (head_dim 128).  Measured, query by query : matrix, 4 sequences, 32
+// heads, 4 K tokens, 1 / 2 / 4 queries 81 : 115, 148 : 116, 284 : 117 us; 1 K tokens, 2 / 4 27 : 36, 41 : 36; 2 sequences, 32 / 8 heads,
+// 4 K tokens, 1 / 2 / 4 queries 18 : 23, 21 : 23, 33 : 24; 4 sequences, 40 heads of 64, 4 K tokens, 2 / 4 queries 90 : 114, 185 : 116; one
+// sequence, 64 / 8 heads, 16 K tokens, 1 / 4 queries 39 : 37, 101 : 40.  (With fp32 matrix instructions a step took 9.8.)
 bool f32_query_by_query(const hgca_shape *s, int32_t n_q, int64_t tokens, int most)
 {
     const int g = group_of(s);
     const double set = (double)s->batch * s->n_kv_heads * tokens * s->head_dim * 8;              // bytes of K and V
     const double source = set <= 16e6 ? 20e6 : set <= 256e6 ? 13.7e6 : 7.6e6;                    // bytes per us
-    const double by_query = 6 + 1.5 * g + set * n_q / std::min(28e6 / g, source);
+    const double by_query = 6 + 1.5 * g + set * n_q / std::min(45e6 / g, source);
     const int64_t shares = append_shares(s, n_q, tokens, most), places = HGCA_APPEND_TARGET_WGS / 2;
     const int64_t steps = (tokens + kLineStep - 1) / kLineStep;
     const int64_t turns = (shares * append_units(s, n_q) + places - 1) / places * ((steps + shares - 1) / shares);
-    return by_query < 7 + turns * 9.8 * s->head_dim / 128;
+    const double step = 3.4 + 2.7 * std::min<int64_t>(128, (int64_t)n_q * g) / 128;
+    return by_query < 7 + turns * step * s->head_dim / 128;
 }
 
 struct AppendWs {

@@ -191,6 +191,11 @@ hipError_t launch_append_attn(int dtype, int head_dim, const AppendArgs &first, 
 // the weights of one tier (second = nullptr) or of two (same queries and shape), as a line
 hipError_t launch_append_weights(int dtype, int head_dim, const AppendArgs &first, const AppendArgs *second, const LineDev &line,
                                  hipStream_t s);
+// the same on fp32 inputs (two = 0: a2 is not used); these check nothing, the two above call them
+hipError_t launch_append_attn_f32(int head_dim, const AppendArgs &a, const AppendArgs &a2, const LineDev &line, int two, dim3 grid,
+                                  hipStream_t s);
+hipError_t launch_append_weights_f32(int head_dim, const AppendArgs &a, const AppendArgs &a2, const LineDev &line, int two,
+                                     dim3 grid, hipStream_t s);
 // ---- KV manager over a block pool (mirrors hgca_cache_state; all pointers device memory) ----
 
 constexpr int32_t kCacheWindowFull = 1, kCacheContextFull = 2, kCacheListFull = 4;   // sticky bits of *status

@@ -1,0 +1,97 @@
+"""fp32 append stage with products of bf16 parts: edges of its tiles (16 rows, 32 tokens), values that have no parts, and
+its error against 64 bits."""
+import numpy as np
+import pytest
+
+from test_gpu_append import gpu, to_paged  # noqa: F401
+from test_gpu_append_fp32 import reference
+
+pytestmark = pytest.mark.gpu
+
+
+def weights_reference(q, K, lens, lse, scale, causal, cap):
+    B, N, Hq, d = q.shape
+    G = Hq // K.shape[1]
+    a = np.zeros((B, Hq, cap))
+    for b in range(B):
+        for i in range(N):
+            n = max(int(lens[b]) - N + i + 1, 0) if causal else int(lens[b])
+            for h in range(Hq):
+                a[b, h, :n] += np.exp((K[b, h // G, :n].astype(np.float64) @ q[b, i, h].astype(np.float64)) * scale - lse[b, i, h])
+    return a / N
+
+
+def run(gpu, q, K, V, lens, causal, paged):
+    torch, hgca, runner = gpu
+    B, N, Hq, d = q.shape
+    Hkv, cap = K.shape[1:3]
+    g = lambda a: runner._to_gpu(a, "cuda:0")
+    shape = hgca.Shape(hgca.F32, B, Hq, Hkv, d, d ** -0.5)
+    tier = to_paged(runner, hgca, torch, K, V, lens, cap, 16, 4, "cuda:0") if paged else hgca.Tier(g(K), g(V), cap, g(lens))
+    o, lse = torch.full((B, N, Hq, d), float("nan"), device="cuda:0"), torch.full((B, N, Hq), float("nan"), device="cuda:0")
+    a = torch.full((B, Hq, cap), float("nan"), device="cuda:0")
+    hgca.append_attn(shape, g(q), tier, causal, o, lse, hgca.append_workspace(shape, N, cap, "cuda:0"))
+    hgca.append_weights(shape, g(q), tier, causal, lse, a)
+    torch.cuda.synchronize()
+    return (x.cpu().numpy().astype(np.float64) for x in (o, lse, a))
+
+
+@pytest.mark.parametrize("causal", [True, False], ids=["causal", "whole"])
+@pytest.mark.parametrize("kw", [
+    dict(N=60, Hq=4, Hkv=4, d=64, lens=(31, 33)), dict(N=64, Hq=4, Hkv=2, d=128, lens=(32, 65)),         # 60 and 128 rows
+    dict(N=31, Hq=8, Hkv=2, d=128, lens=(64, 1), paged=True), dict(N=17, Hq=16, Hkv=2, d=128, lens=(97, 129)),   # 124, 136
+    dict(N=16, Hq=16, Hkv=2, d=64, lens=(700, 481)), dict(N=65, Hq=8, Hkv=4, d=64, lens=(300, 95), paged=True),  # 128, 130
+], ids=["mha_d64", "gqa2", "gqa4_paged", "gqa8", "gqa8_d64", "gqa2_d64_paged"])
+def test_edges_of_tiles(gpu, kw, causal):  # noqa: F811
+    N, Hq, Hkv, d, lens = (kw[x] for x in ("N", "Hq", "Hkv", "d", "lens"))
+    lens, cap, B = np.array(lens, np.int32), max(kw["lens"]) + 5, 2
+    rng = np.random.default_rng(N)
+    q, K, V = (rng.standard_normal(s).astype(np.float32) for s in ((B, N, Hq, d), (B, Hkv, cap, d), (B, Hkv, cap, d)))
+    o, lse, a = run(gpu, q, K, V, lens, causal, kw.get("paged"))
+    o_ref, l_ref = reference(q, K, V, lens, d ** -0.5, causal)
+    empty = np.isneginf(l_ref)
+    assert np.array_equal(np.isneginf(lse), empty) and np.all(o[empty] == 0)
+    assert np.max(np.abs(lse[~empty] - l_ref[~empty])) <= 1e-5 and np.max(np.abs(o - o_ref)) <= 1e-5
+    a_ref = weights_reference(q, K, lens, np.where(empty, 0.0, l_ref), d ** -0.5, causal, cap)
+    assert np.max(np.abs(a - a_ref)) <= 1e-5
+
+
+@pytest.mark.parametrize("kw", [dict(N=40, Hq=8, Hkv=2, d=128), dict(N=40, Hq=16, Hkv=2, d=64), dict(N=130, Hq=4, Hkv=4, d=64)],
+                         ids=["gqa4", "gqa8_d64", "mha_d64"])
+def test_values_without_parts(gpu, kw):  # noqa: F811
+    """Keys with an infinite component that every query meets with the same sign (their scores are -inf: they weigh nothing),
+    keys whose products overflow a part but not the sum's type, and V entries that round to infinity in 16 bits."""
+    N, Hq, Hkv, d = (kw[x] for x in ("N", "Hq", "Hkv", "d"))
+    B, cap, lens = 2, 260, np.array((260, 201), np.int32)
+    rng = np.random.default_rng(d)
+    q, K, V = (rng.standard_normal(s).astype(np.float32) for s in ((B, N, Hq, d), (B, Hkv, cap, d), (B, Hkv, cap, d)))
+    q[..., 0], q[..., 1] = 1.0, 1e-38
+    K[..., 0] = 0.0
+    K[:, :, 3::17, 0] = -np.inf
+    K[:, :, 5::19, 1] = np.float32(3.4e38)                       # times 1e-38: 3.4, an ordinary term of the score
+    # finite, but its upper part is not.  One to a column: a weight is at most 1 before the sum is divided, so one such entry
+    # stays below the largest fp32 number (3.4028e38), and the sum of several may not, whatever forms their products.
+    for i in range(8):
+        V[:, :, 2 + 23 * i, 3 + i] = np.float32(3.4e38)
+    o, lse, a = run(gpu, q, K, V, lens, False, False)
+    o_ref, l_ref = reference(q, K, V, lens, d ** -0.5, False)
+    assert np.max(np.abs(lse - l_ref)) <= 1e-5
+    assert np.max(np.abs(o - o_ref) / np.maximum(np.abs(o_ref).max(axis=(0, 1, 2)), 1.0)) <= 1e-5
+    a_ref = weights_reference(q, K, lens, l_ref, d ** -0.5, False, cap)
+    assert np.max(np.abs(a - a_ref)) <= 1e-5 and np.all(a[:, :, 3:200:17] == 0)
+
+
+def test_error_against_64_bits(gpu):  # noqa: F811
+    """The products of parts are as good as fp32 ones: a score of 128 products is off by a few units of 2^-24 of its terms, and so
+    are the weights and O, whose error is that of their scores: 24 queries over 3000 tokens stay below 8 * 2^-24 relative (2-norm)."""
+    B, N, Hq, Hkv, d, cap = 1, 24, 4, 2, 128, 3000
+    lens = np.array((cap,), np.int32)
+    rng = np.random.default_rng(11)
+    q, K, V = (rng.standard_normal(s).astype(np.float32) for s in ((B, N, Hq, d), (B, Hkv, cap, d), (B, Hkv, cap, d)))
+    q *= 2.0
+    o, lse, a = run(gpu, q, K, V, lens, False, False)
+    o_ref, l_ref = reference(q, K, V, lens, d ** -0.5, False)
+    a_ref = weights_reference(q, K, lens, l_ref, d ** -0.5, False, cap)
+    off = lambda x, y: float(np.linalg.norm(x - y) / np.linalg.norm(y))
+    print(off(o, o_ref), off(lse, l_ref), off(a, a_ref))
+    assert off(o, o_ref) <= 8 * 2.0 ** -24 and off(lse, l_ref) <= 2 * 2.0 ** -24 and off(a, a_ref) <= 8 * 2.0 ** -24
