@@ -67,19 +67,39 @@ __device__ __forceinline__ float number_or_least(float s) { return s == s ? s : 
 // Four consecutive scores starting at position t (a multiple of 4); positions at or beyond n read -inf.  A row starts
 // on any multiple of 4 bytes (the capacity may be odd), which is all a 16-byte load asks for: rows of 61 003 scores,
 // loaded score by score where the row was not 16-byte aligned, 40.4 -> 22.2 us together with the smaller sample.
+__device__ __forceinline__ float4 load4_whole(const float *sc, int t)
+{
+    typedef float unaligned4 __attribute__((ext_vector_type(4), aligned(4)));
+    const unaligned4 v = *reinterpret_cast<const unaligned4 *>(sc + t);
+    return make_float4(v.x, v.y, v.z, v.w);
+}
 __device__ __forceinline__ float4 load4_padded(const float *sc, int t, int n)
 {
-    if (t + 3 < n) {
-        typedef float unaligned4 __attribute__((ext_vector_type(4), aligned(4)));
-        const unaligned4 v = *reinterpret_cast<const unaligned4 *>(sc + t);
-        return make_float4(v.x, v.y, v.z, v.w);
-    }
+    if (t + 3 < n) return load4_whole(sc, t);
     float4 v = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
     if (t < n) v.x = sc[t];
     if (t + 1 < n) v.y = sc[t + 1];
     if (t + 2 < n) v.z = sc[t + 2];
     if (t + 3 < n) v.w = sc[t + 3];
     return v;
+}
+
+// The scores of U steps of a wave: step u takes positions t + 256 u .. + 3 of the lane (t: the wave's first position + 4 lane).
+// Where all of them exist no load stands behind a test of the lane's own, so that they are in flight together (256 rows of
+// 122 880 scores 32.8 -> 31.0 us, 32 of 61 003 16.9 -> 16.5).  Steps from `steps` on, and positions from n on, give -inf.
+template <int U>
+__device__ __forceinline__ void load_steps(const float *sc, int t, int steps, int n, float4 (&v)[U])
+{
+    if (steps >= U && __builtin_amdgcn_readfirstlane(t) + U * kStep <= n) {     // uniform over the wave
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = load4_whole(sc, t + kStep * u);
+        return;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        v[u] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+        if (u < steps) v[u] = load4_padded(sc, min(t + kStep * u, (n + 3) / 4 * 4), n);
+    }
 }
 
 // Positions below the current lane among the set bits of a lane mask.
@@ -431,8 +451,8 @@ struct Sel {
         for (int u = 0; u < kSampleLoads; ++u) {
             const int j = u * kSelBlock + tid;                       // float4 of the sample
             const int c = j / (kSampleChunk / 4);
-            const int start = (int)((int64_t)c * (n - kSampleChunk) / (kSampleChunks - 1)) & ~3;
-            v[u] = load4_padded(sc, start + 4 * (j % (kSampleChunk / 4)), n);
+            const int start = (int)((int64_t)c * (n - kSampleChunk) / (kSampleChunks - 1)) & ~3;         // <= n - kSampleChunk
+            v[u] = load4_whole(sc, start + 4 * (j % (kSampleChunk / 4)));
         }
         float mn = INFINITY, mx = -INFINITY;
 #pragma unroll
@@ -490,11 +510,7 @@ struct Sel {
         constexpr int U = 4;                                         // steps whose loads are in flight together
         for (int i0 = 0; i0 < steps; i0 += U) {
             float4 r[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                r[u] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-                if (i0 + u < steps) r[u] = load4_padded(sc, min(pos0 + kStep * (i0 + u), (n + 3) / 4 * 4), n);
-            }
+            load_steps<U>(sc, pos0 + kStep * i0, steps - i0, n, r);
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const float s[4] = {r[u].x, r[u].y, r[u].z, r[u].w};
