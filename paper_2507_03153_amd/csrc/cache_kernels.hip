@@ -169,6 +169,9 @@ __global__ __launch_bounds__(kRowBlock) void evict_kernel(CacheDev c, int32_t n_
     evict_row(s_compact, c, blockIdx.x, n_q_heads, beta, l_cur, false, 0);
 }
 
+constexpr int kTailBlock = 1024;                 // threads where a row is a compute unit's work alone
+constexpr int64_t kTailLargeRows = 256;          // compute units
+
 // The tail of a decode step over the managed cache as one launch, one workgroup per (sequence, query head) row:
 // merge_state over the row's split partials (set p: the window's, set q: the salient list's), the window's attention
 // weights A_gpu = e^{s - lse_window} from the scaled scores the split kernels left in a_gpu, Alg. 1's moving average
@@ -177,13 +180,17 @@ __global__ __launch_bounds__(kRowBlock) void evict_kernel(CacheDev c, int32_t n_
 // scores and averages are requested together with the partials, so the launch costs one round trip to memory.
 // With token_pending the step's token was written into the window by the split kernels and its length is still the
 // old one: the length this step works with is taken from the same rule (pending_window_len) and stored here.
-template <int D, bool OUT_BF16>
-__global__ __launch_bounds__(kRowBlock) void decode_tail_kernel(Partials p, Partials q, void *o, float *lse, float *a_gpu,
+// A row is a compute unit's work where there are no more rows than units: with 256 threads the weights of a window of 4096, 16 per
+// thread of the one wave on a SIMD, take as long as everything before them, so such launches have 1024 threads: 8 steps of 256
+// rows 533 -> 519 us.  More rows share units and hide each other's chains: 384 and 512 rows the same either way, 768 rows of a
+// window of 1024 551 : 584, 2048 rows of 256 918 : 1014.
+template <int D, bool OUT_BF16, int BLOCK>
+__global__ __launch_bounds__(BLOCK) void decode_tail_kernel(Partials p, Partials q, void *o, float *lse, float *a_gpu,
                                                                 CacheDev c, int32_t n_q_heads, float alpha, double beta,
                                                                 int32_t token_pending)
 {
     static_assert(kFoldBlock == kRowBlock, "one workgroup shape for the fold and the row passes");
-    constexpr int PF = 16;                                     // entries per thread requested before the fold
+    constexpr int PF = 16 * kRowBlock / BLOCK;                 // entries per thread requested before the fold
     __shared__ FoldShared<D> s_fold;
     __shared__ CompactShared s_compact;
     const int64_t row = blockIdx.x;
@@ -193,7 +200,7 @@ __global__ __launch_bounds__(kRowBlock) void decode_tail_kernel(Partials p, Part
     float s[PF], h[PF];
 #pragma unroll
     for (int e = 0; e < PF; ++e) {
-        const int j = tid + e * kRowBlock;
+        const int j = tid + e * BLOCK;
         s[e] = j < cap ? ar[j] : 0.f;                          // beyond the length: not used
         h[e] = j < cap ? m[j] : 0.f;
     }
@@ -202,11 +209,11 @@ __global__ __launch_bounds__(kRowBlock) void decode_tail_kernel(Partials p, Part
                                                      c.max_blocks, &fail_bits)
                                 : c.win_lens[b];
     const int nc = min(max(n, 0), cap);
-    const float lse_w = fold_row<D, OUT_BF16, true>(s_fold, p, q, o, lse, nullptr, row);
+    const float lse_w = fold_row<D, OUT_BF16, true, BLOCK>(s_fold, p, q, o, lse, nullptr, row);
     // A row that evicts nothing only reports its arrival (the sequence's last row stores the length): that round
     // trip runs beside the weights pass, which reads nothing the arrival changes.
     const bool evicts = blocks_to_evict(c, n) > 0;             // uniform over the sequence's workgroups
-    if (!evicts) evict_row(s_compact, c, row, n_q_heads, beta, n, token_pending != 0, fail_bits);
+    if (!evicts) evict_row<BLOCK>(s_compact, c, row, n_q_heads, beta, n, token_pending != 0, fail_bits);
 
     const float keep = 1.f - alpha;
     auto update = [&](int j, float sj, float hj) {
@@ -216,13 +223,13 @@ __global__ __launch_bounds__(kRowBlock) void decode_tail_kernel(Partials p, Part
     };
 #pragma unroll
     for (int e = 0; e < PF; ++e) {
-        const int j = tid + e * kRowBlock;
+        const int j = tid + e * BLOCK;
         if (j < cap) update(j, s[e], h[e]);
     }
-    for (int j = PF * kRowBlock + tid; j < cap; j += kRowBlock) update(j, ar[j], m[j]);
+    for (int j = PF * BLOCK + tid; j < cap; j += BLOCK) update(j, ar[j], m[j]);
     if (evicts) {
         __syncthreads();                                       // the row's averages are written before they are thresholded
-        evict_row(s_compact, c, row, n_q_heads, beta, n, token_pending != 0, fail_bits);
+        evict_row<BLOCK>(s_compact, c, row, n_q_heads, beta, n, token_pending != 0, fail_bits);
     }
 }
 
@@ -233,7 +240,6 @@ __global__ __launch_bounds__(kRowBlock) void decode_tail_kernel(Partials p, Part
 // the row.  The three steps of a row need nothing from other rows.  A row is long (28 672 pool entries on the 8B shape)
 // and there are about as many rows as compute units, so the walk over it is a chain of steps, each a load, a barrier
 // and a prefix: 1024 threads make it a quarter as long (47 -> 23 us for 256 rows).
-constexpr int kTailBlock = 1024;
 __global__ __launch_bounds__(kTailBlock) void append_tail_kernel(CacheDev c, const float *a_gpu, const float *a_cpu,
                                                                 int32_t n_q_heads, int32_t n_new, float alpha, double beta)
 {
@@ -247,9 +253,20 @@ __global__ __launch_bounds__(kTailBlock) void append_tail_kernel(CacheDev c, con
         const float keep = 1.f - alpha;
         float *m = c.a_maw + row * c.win_cap;
         const float *a = a_gpu + row * c.win_cap;
-        for (int j = tid; j < n; j += kTailBlock) {
-            const float x = a[j];
-            m[j] = j >= first_new ? x : fmaf(alpha, x, keep * m[j]);
+        constexpr int U = 4;                                   // entries per thread in flight together
+        for (int j0 = tid; j0 < n; j0 += U * kTailBlock) {
+            float x[U], old[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int j = min(j0 + u * kTailBlock, n - 1);
+                x[u] = a[j];
+                old[u] = m[j];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int j = j0 + u * kTailBlock;
+                if (j < n) m[j] = j >= first_new ? x[u] : fmaf(alpha, x[u], keep * old[u]);
+            }
         }
     }
     // re-evaluation over the pool row
@@ -341,11 +358,15 @@ hipError_t launch_decode_tail(int head_dim, int64_t n_rows, const Partials &p, c
                               int32_t token_pending, hipStream_t s)
 {
     if (n_rows == 0) return hipSuccess;
-    const dim3 grid((unsigned)n_rows), block(kRowBlock);
+    const dim3 grid((unsigned)n_rows);
+    const bool large = n_rows <= kTailLargeRows;
 #define HGCA_TAIL_CASE(D, BF)                                                                                       \
-    if (head_dim == D && o_dtype == (BF ? 1 : 0))                                                                   \
-        hipLaunchKernelGGL((decode_tail_kernel<D, BF>), grid, block, 0, s, p, q, o, lse, a_gpu, c, n_q_heads, alpha, beta, \
-                           token_pending)
+    if (head_dim == D && o_dtype == (BF ? 1 : 0) && large)                                                          \
+        hipLaunchKernelGGL((decode_tail_kernel<D, BF, kTailBlock>), grid, dim3(kTailBlock), 0, s, p, q, o, lse, a_gpu, c, n_q_heads, \
+                           alpha, beta, token_pending);                                                             \
+    else if (head_dim == D && o_dtype == (BF ? 1 : 0))                                                              \
+        hipLaunchKernelGGL((decode_tail_kernel<D, BF, kRowBlock>), grid, dim3(kRowBlock), 0, s, p, q, o, lse, a_gpu, c, n_q_heads, \
+                           alpha, beta, token_pending)
     HGCA_TAIL_CASE(64, false);
     else HGCA_TAIL_CASE(64, true);
     else HGCA_TAIL_CASE(128, false);

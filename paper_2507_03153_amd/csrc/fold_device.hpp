@@ -37,8 +37,8 @@ __device__ __forceinline__ void line_sets(const LineDev &line, const Partials &t
 // the SG groups are then added through LDS.  Called by all kFoldBlock threads of a workgroup.  With WANT_P the
 // log-sum-exp of set p alone (the window part of a step: its attention weights are normalised by it) is formed by
 // the last wave, stored to lse_p[row] if lse_p is given, and returned to every thread; otherwise 0 is returned.
-// lse_q (with WANT_P only) receives the same for set q.
-template <int D, bool OUT_BF16, bool WANT_P>
+// lse_q (with WANT_P only) receives the same for set q.  A workgroup may have more threads (BLOCK): they join the barriers.
+template <int D, bool OUT_BF16, bool WANT_P, int BLOCK = kFoldBlock>
 __device__ __forceinline__ float fold_row(FoldShared<D> &sh, const Partials &p, const Partials &q, void *o, float *lse,
                                           float *lse_p, int64_t row, float *lse_q = nullptr)
 {
@@ -47,7 +47,8 @@ __device__ __forceinline__ float fold_row(FoldShared<D> &sh, const Partials &p, 
     constexpr int PRE = 4;                       // splits per thread whose loads are issued before anything is used
 
     const int tid = threadIdx.x, sg = tid / C4, c4 = tid % C4;
-    const int np = p.n_splits, n = np + q.n_splits;
+    const bool folds = BLOCK == kFoldBlock || tid < kFoldBlock;      // uniform over a wave
+    const int np = p.n_splits, n = folds ? np + q.n_splits : 0;
     auto m_of = [&](int s) { return s < np ? p.m[row * p.stride + s] : q.m[row * q.stride + (s - np)]; };
     auto l_of = [&](int s) { return s < np ? p.l[row * p.stride + s] : q.l[row * q.stride + (s - np)]; };
     auto o_of = [&](int s) {
@@ -71,7 +72,7 @@ __device__ __forceinline__ float fold_row(FoldShared<D> &sh, const Partials &p, 
     float M = -INFINITY;
     for (int s = tid; s < n; s += kFoldBlock) M = fmaxf(M, m_of(s));
     M = wave_max(M);
-    if (tid % kWave == 0) sh.M[tid / kWave] = M;
+    if (tid % kWave == 0 && folds) sh.M[tid / kWave] = M;
     // set p alone, on the last wave: a lane per split, fixed reduction order
     if (WANT_P && tid / kWave == kFoldWaves - 1) {
         const int lane = tid % kWave;
@@ -121,8 +122,10 @@ __device__ __forceinline__ float fold_row(FoldShared<D> &sh, const Partials &p, 
             acc.z = fmaf(v.z, wgt, acc.z); acc.w = fmaf(v.w, wgt, acc.w);
         }
     }
-    sh.acc[sg][c4] = acc;
-    if (c4 == 0) sh.L[sg] = L;
+    if (folds) {
+        sh.acc[sg][c4] = acc;
+        if (c4 == 0) sh.L[sg] = L;
+    }
     __syncthreads();
     if (tid < C4) {
         float Lt = 0.f;
