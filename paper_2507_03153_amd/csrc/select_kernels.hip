@@ -19,8 +19,8 @@
 // row (8 192 scores, 2 048 in the small workgroups: runs of 256 spread evenly over the row), one pass over the row
 // that retains the few per cent at or above it in LDS, and the steps above on the retained entries only.  It gives
 // the same result or gives up (then the steps above run on the whole row, held as one byte per score or re-read
-// from memory).  Measured: 256 rows of 122 880 scores, k = 4096: 63 -> 38 us, 35 with the smaller sample (by itself, over and
-// over; 41 in a step, right behind the score pass); 1280 rows of 14 336, k = 1024:
+// from memory).  Measured: 256 rows of 122 880 scores, k = 4096: 63 -> 38 us, 35 with the smaller sample, 31 with
+// lane exchanges and loads without a test each (by itself, over and over; 34 in a step, right behind the score pass); 1280 rows of 14 336, k = 1024:
 // 48 -> 35 us; 2048 rows of 14 336, k = 1433: 68 -> 51 us; 512 rows of 50 000, k = 2500: 53 -> 32 us.
 //
 // A row is one CU's work; with a handful of VALU operations per score and pass the
