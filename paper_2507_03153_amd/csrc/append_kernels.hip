@@ -20,6 +20,7 @@
 // The weights kernel brings its K rows in the same way (it has no second contraction).
 #include "append_device.hpp"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace hgca {
@@ -27,6 +28,7 @@ namespace hgca {
 namespace {
 
 constexpr int kNonTemporal = 2;                  // cache policy of a load: streamed once
+constexpr int64_t kLastCache = int64_t(256) << 20;
 
 // s_waitcnt vmcnt(0) (expcnt and lgkmcnt fields at their maxima = no wait): an LDS-direct load has landed in LDS
 // when the wave's memory-load counter has counted it down.  Every wave does this before the barrier after which
@@ -37,8 +39,8 @@ __device__ __forceinline__ void wait_for_own_loads() { __builtin_amdgcn_s_waitcn
 // a full step its address is a scalar (the granule's row) plus an offset that is the lane's for good; only a step
 // that the pass's end cuts computes rows per lane (tokens behind the end read the last row).  The row numbers of a
 // paged tier are looked up before the first load is issued: an LDS read placed after an LDS-direct load waits for it.
-// POLICY is the loads' cache policy: 0, or kNonTemporal where the rows pass once and are not to stay in the caches.
-template <int D, int NW, int POLICY>
+// POLICY_K and POLICY_V are the loads' cache policies: 0, or kNonTemporal where the rows are not to stay in the caches.
+template <int D, int NW, int POLICY_K, int POLICY_V>
 __device__ __forceinline__ void dma_step(const KvDev &kv, const BlockRows &rows, int step, int nsub, char *k_stage,
                                          char *v_stage)
 {
@@ -68,8 +70,8 @@ __device__ __forceinline__ void dma_step(const KvDev &kv, const BlockRows &rows,
         for (int u = 0; u < S::kLoads; ++u) {
             const size_t at = (size_t)row[u] * S::kRowBytes;
             const uint32_t k_off = k_row * S::kRowBytes + k_byte(u), v_off = v_row * S::kRowBytes + v_byte;
-            __builtin_amdgcn_global_load_lds((GlobalPtr)(kv.k + at + k_off), (LdsPtr)(k_stage + (w + NW * u) * 1024), 16, 0, POLICY);
-            __builtin_amdgcn_global_load_lds((GlobalPtr)(kv.v + at + v_off), (LdsPtr)(v_stage + (w + NW * u) * 1024), 16, 0, POLICY);
+            __builtin_amdgcn_global_load_lds((GlobalPtr)(kv.k + at + k_off), (LdsPtr)(k_stage + (w + NW * u) * 1024), 16, 0, POLICY_K);
+            __builtin_amdgcn_global_load_lds((GlobalPtr)(kv.v + at + v_off), (LdsPtr)(v_stage + (w + NW * u) * 1024), 16, 0, POLICY_V);
         }
         return;
     }
@@ -122,7 +124,8 @@ constexpr int kAhead = 2;                        // slices of the score contract
 // by side) as one line of tokens cut into equal shares (LineDev): a workgroup goes through its part of the first tier
 // and its part of the second, usually only one of them, each with the tier's view, mask rule and slot.
 template <int D, int G, bool SPLIT_P, bool TWO>
-__global__ __launch_bounds__(kAttnBlock, 2) void append_attn_kernel(AppendArgs a1, AppendArgs a2, LineDev line, int streamed)
+__global__ __launch_bounds__(kAttnBlock, 2) void append_attn_kernel(AppendArgs a1, AppendArgs a2, LineDev line, int streamed,
+                                                                    int kept_k)
 {
     constexpr int NW = kAttnWaves, BLOCK = kAttnBlock;
     using S = DmaStage<D, NW>;
@@ -321,8 +324,9 @@ __global__ __launch_bounds__(kAttnBlock, 2) void append_attn_kernel(AppendArgs a
             // waits for its own loads) orders both.
             const int steps = (nsub + kStepTokens - 1) / kStepTokens;
             auto request = [&](int s, char *k, char *v) {            // (the policy is part of the instructions)
-                if (streamed) dma_step<D, NW, kNonTemporal>(kv, rows, s, nsub, k, v);
-                else dma_step<D, NW, 0>(kv, rows, s, nsub, k, v);
+                if (!streamed) dma_step<D, NW, 0, 0>(kv, rows, s, nsub, k, v);
+                else if (16 * (steps - s) <= kept_k * steps) dma_step<D, NW, 0, kNonTemporal>(kv, rows, s, nsub, k, v);
+                else dma_step<D, NW, kNonTemporal, kNonTemporal>(kv, rows, s, nsub, k, v);
             };
             request(0, s_k0, s_v0);
             auto step = [&](int s, const char *k_cur, const char *v_cur, char *k_next, char *v_next) {
@@ -412,7 +416,7 @@ template <int D> struct WeightsStage {
 template <int D, int G, bool TWO> constexpr bool kWTwoPerUnit = D == 64 && (G < 4 || (G == 4 && !TWO));
 template <int D, int G, bool TWO>
 __global__ __launch_bounds__(WeightsStage<D>::kBlock, D == 64 && G == 2 && TWO ? 4 : 2) void append_weights_kernel(
-    AppendArgs a1, AppendArgs a2, LineDev line, int streamed)
+    AppendArgs a1, AppendArgs a2, LineDev line, int streamed, int from_end)
 {
     using S = WeightsStage<D>;
     constexpr int kWWaves = S::kWaves, kWBlock = S::kBlock;
@@ -503,8 +507,11 @@ __global__ __launch_bounds__(WeightsStage<D>::kBlock, D == 64 && G == 2 && TWO ?
                 const int live = (min(n_rows - qb * kRowsPerBlock, kRowsPerBlock) + 31) / 32;        // 32-row tiles with rows that exist
                 // a block with fewer tiles than there are waves: several waves take a tile's rows in turn and add up at the end
                 const int spread_bits = live < kSpreadLive ? 0 : 4 * tiles <= kWWaves ? 2 : 2 * tiles <= kWWaves ? 1 : 0;
-                const int spread = 1 << spread_bits, part = w % spread, tile_first = w >> spread_bits, tile_step = kWWaves >> spread_bits;
-                if (tile_first < tiles) request(tile_first);     // first: it has the longest way
+                const int spread = 1 << spread_bits, part = w % spread, stride = kWWaves >> spread_bits;
+                const int tile_first = from_end ? tiles - 1 - (w >> spread_bits) : w >> spread_bits;
+                const int tile_step = from_end ? -stride : stride;
+                auto is_tile = [&](int t) { return (unsigned)t < (unsigned)tiles; };
+                if (is_tile(tile_first)) request(tile_first);    // first: it has the longest way
                 // rows that do not exist repeat the last query of their head with a shift of -inf: they weigh nothing, and
                 // what a non-finite key gives them it gives an existing row of that head too
                 auto existing = [&](int r) { return r < n_rows ? r : n_rows - G + r % G; };
@@ -543,13 +550,13 @@ __global__ __launch_bounds__(WeightsStage<D>::kBlock, D == 64 && G == 2 && TWO ?
                         }
                     }
                 };
-                for (int tile = tile_first; tile < tiles; tile += tile_step) {
+                for (int tile = tile_first; is_tile(tile); tile += tile_step) {
                     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // the tile's rows are in the slot
                     uint4 kf[KK];
 #pragma unroll
                     for (int kk = 0; kk < KK; ++kk) kf[kk] = *reinterpret_cast<const uint4 *>(slot + (frag0 ^ (32 * kk)));
                     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // ... and in registers: the slot is free
-                    if (tile + tile_step < tiles) request(tile + tile_step);
+                    if (is_tile(tile + tile_step)) request(tile + tile_step);
                     store();                     // (its write overlaps with this tile's arithmetic)
                     const int tok0 = p0 + tile * kWTile;
                     float sum[NS];
@@ -701,15 +708,15 @@ __global__ __launch_bounds__(WeightsStage<D>::kBlock, D == 64 && G == 2 && TWO ?
 }
 
 template <int D, bool SPLIT_P, bool TWO>
-hipError_t launch_attn_tiers(const AppendArgs &a, const AppendArgs &a2, const LineDev &line, dim3 grid, int streamed,
+hipError_t launch_attn_tiers(const AppendArgs &a, const AppendArgs &a2, const LineDev &line, dim3 grid, int streamed, int kept_k,
                              hipStream_t s)
 {
     const dim3 block(kAttnBlock);
     switch (a.sh.group) {
-    case 1: hipLaunchKernelGGL((append_attn_kernel<D, 1, SPLIT_P, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
-    case 2: hipLaunchKernelGGL((append_attn_kernel<D, 2, SPLIT_P, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
-    case 4: hipLaunchKernelGGL((append_attn_kernel<D, 4, SPLIT_P, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
-    case 8: hipLaunchKernelGGL((append_attn_kernel<D, 8, SPLIT_P, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
+    case 1: hipLaunchKernelGGL((append_attn_kernel<D, 1, SPLIT_P, TWO>), grid, block, 0, s, a, a2, line, streamed, kept_k); break;
+    case 2: hipLaunchKernelGGL((append_attn_kernel<D, 2, SPLIT_P, TWO>), grid, block, 0, s, a, a2, line, streamed, kept_k); break;
+    case 4: hipLaunchKernelGGL((append_attn_kernel<D, 4, SPLIT_P, TWO>), grid, block, 0, s, a, a2, line, streamed, kept_k); break;
+    case 8: hipLaunchKernelGGL((append_attn_kernel<D, 8, SPLIT_P, TWO>), grid, block, 0, s, a, a2, line, streamed, kept_k); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -717,22 +724,22 @@ hipError_t launch_attn_tiers(const AppendArgs &a, const AppendArgs &a2, const Li
 
 template <int D, bool SPLIT_P>
 hipError_t launch_attn_group(const AppendArgs &a, const AppendArgs &a2, const LineDev &line, int two, dim3 grid,
-                             int streamed, hipStream_t s)
+                             int streamed, int kept_k, hipStream_t s)
 {
-    return two ? launch_attn_tiers<D, SPLIT_P, true>(a, a2, line, grid, streamed, s)
-               : launch_attn_tiers<D, SPLIT_P, false>(a, a2, line, grid, streamed, s);
+    return two ? launch_attn_tiers<D, SPLIT_P, true>(a, a2, line, grid, streamed, kept_k, s)
+               : launch_attn_tiers<D, SPLIT_P, false>(a, a2, line, grid, streamed, kept_k, s);
 }
 
 template <int D, bool TWO>
-hipError_t launch_weights_tiers(const AppendArgs &a, const AppendArgs &a2, const LineDev &line, dim3 grid, int streamed,
+hipError_t launch_weights_tiers(const AppendArgs &a, const AppendArgs &a2, const LineDev &line, dim3 grid, int streamed, int from_end,
                                 hipStream_t s)
 {
     const dim3 block(WeightsStage<D>::kBlock);
     switch (a.sh.group) {
-    case 1: hipLaunchKernelGGL((append_weights_kernel<D, 1, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
-    case 2: hipLaunchKernelGGL((append_weights_kernel<D, 2, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
-    case 4: hipLaunchKernelGGL((append_weights_kernel<D, 4, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
-    case 8: hipLaunchKernelGGL((append_weights_kernel<D, 8, TWO>), grid, block, 0, s, a, a2, line, streamed); break;
+    case 1: hipLaunchKernelGGL((append_weights_kernel<D, 1, TWO>), grid, block, 0, s, a, a2, line, streamed, from_end); break;
+    case 2: hipLaunchKernelGGL((append_weights_kernel<D, 2, TWO>), grid, block, 0, s, a, a2, line, streamed, from_end); break;
+    case 4: hipLaunchKernelGGL((append_weights_kernel<D, 4, TWO>), grid, block, 0, s, a, a2, line, streamed, from_end); break;
+    case 8: hipLaunchKernelGGL((append_weights_kernel<D, 8, TWO>), grid, block, 0, s, a, a2, line, streamed, from_end); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -740,16 +747,33 @@ hipError_t launch_weights_tiers(const AppendArgs &a, const AppendArgs &a2, const
 
 template <int D>
 hipError_t launch_weights_group(const AppendArgs &a, const AppendArgs &a2, const LineDev &line, int two, dim3 grid,
-                                int streamed, hipStream_t s)
+                                int streamed, int from_end, hipStream_t s)
 {
-    return two ? launch_weights_tiers<D, true>(a, a2, line, grid, streamed, s)
-               : launch_weights_tiers<D, false>(a, a2, line, grid, streamed, s);
+    return two ? launch_weights_tiers<D, true>(a, a2, line, grid, streamed, from_end, s)
+               : launch_weights_tiers<D, false>(a, a2, line, grid, streamed, from_end, s);
+}
+
+int64_t k_bytes_of(const AppendArgs &a, const AppendArgs *second, int head_dim)
+{
+    return (int64_t)a.sh.batch * a.sh.n_kv_heads * ((int64_t)a.kv.cap + (second ? second->kv.cap : 0)) * head_dim * 2;
+}
+
+// A turn's weights pass reads again the K rows that its attention has just streamed (one block of rows).  From 512 MB of K and V
+// on (by capacity; a managed cache counts its window twice), the K rows of the last sixteenths of every share, 12 at most and as
+// many as the last cache holds of K, are left to the caches, and the weights pass walks its shares from the end.  Whole turns,
+// everything streamed : so, us: 8 x 32 queries 1.1 GB 381 : 377, 12 x 8 queries 1.7 GB 460 : 450; 4 x 32 queries 576 MB 227 : 224;
+// 2 x 16 queries in groups of 8, 512 MB 218 : 212; 6 x 32 queries of 32 / 16 heads of 64, 864 MB 286 : 276.  Below, 0.99 to 1.01 times as
+// fast (288 MB 140.2 : 140.4, 330 MB 149.4 : 150.6, 482 MB 198.9 : 200.6).  All of K kept, or walked from the start, gains less;
+// attention alone loses 1 to 5 % (16 queries, 288 MB 65.5 : 69.3).
+int kept_sixteenths(int64_t kv_bytes)
+{
+    return kv_bytes >= 2 * kLastCache ? (int)std::min<int64_t>(12, 32 * kLastCache / kv_bytes) : 0;
 }
 
 }  // namespace
 
 hipError_t launch_append_attn(int dtype, int head_dim, const AppendArgs &a, const AppendArgs *second, const LineDev &line,
-                              hipStream_t s)
+                              bool weights_follow, hipStream_t s)
 {
     if (a.sh.batch == 0 || a.n_q == 0) return hipSuccess;
     const AppendArgs &a2 = second ? *second : a;
@@ -764,26 +788,26 @@ hipError_t launch_append_attn(int dtype, int head_dim, const AppendArgs &a, cons
     const dim3 grid = n_qb == 1 ? dim3(line.shares, a.sh.n_kv_heads, a.sh.batch) : dim3((unsigned)blocks);
     const int two = second ? 1 : 0;
     if (dtype == 0) return launch_append_attn_f32(head_dim, a, a2, line, two, grid, s);
-    const int64_t kv_bytes = 2 * (int64_t)a.sh.batch * a.sh.n_kv_heads * ((int64_t)a.kv.cap + (second ? second->kv.cap : 0)) *
-                             head_dim * 2;
+    const int64_t kv_bytes = 2 * k_bytes_of(a, second, head_dim);
     // One block of rows reads every K and V row once: past what the last cache holds (256 MB, by capacity) the loads leave the
     // caches alone.  1.07 GB, 8 x 32 queries, loads without arithmetic 217 -> 185 us, the attention of both tiers 249 -> 243;
     // 537 MB, 4 x 16 queries, whole turn 192 -> 179; 134 MB and less no difference.  Several blocks read the rows again:
     // three of them (48 queries, groups of 8) 245 -> 265 when streamed.
     // A managed cache that is filled to a part of its capacity loses nothing: 5 to 50 % of 0.9 to 1.0 GB, whole turns 0.99 to 1.07 times
     // as fast streamed, also where what is in it would fit the last cache for the weights pass.
-    const int streamed = n_qb == 1 && kv_bytes >= (int64_t(256) << 20) ? 1 : 0;
+    const int streamed = n_qb == 1 && kv_bytes >= kLastCache ? 1 : 0;
+    const int kept_k = weights_follow && streamed ? kept_sixteenths(kv_bytes) : 0;
     if (dtype == 1 && head_dim == 64)
-        return a.one_part_p ? launch_attn_group<64, false>(a, a2, line, two, grid, streamed, s)
-                            : launch_attn_group<64, true>(a, a2, line, two, grid, streamed, s);
+        return a.one_part_p ? launch_attn_group<64, false>(a, a2, line, two, grid, streamed, kept_k, s)
+                            : launch_attn_group<64, true>(a, a2, line, two, grid, streamed, kept_k, s);
     if (dtype == 1 && head_dim == 128)
-        return a.one_part_p ? launch_attn_group<128, false>(a, a2, line, two, grid, streamed, s)
-                            : launch_attn_group<128, true>(a, a2, line, two, grid, streamed, s);
+        return a.one_part_p ? launch_attn_group<128, false>(a, a2, line, two, grid, streamed, kept_k, s)
+                            : launch_attn_group<128, true>(a, a2, line, two, grid, streamed, kept_k, s);
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_append_weights(int dtype, int head_dim, const AppendArgs &a, const AppendArgs *second,
-                                 const LineDev &line, hipStream_t s)
+                                 const LineDev &line, bool after_attention, hipStream_t s)
 {
     if (a.sh.batch == 0 || a.n_q == 0) return hipSuccess;
     const AppendArgs &a2 = second ? *second : a;
@@ -798,11 +822,11 @@ hipError_t launch_append_weights(int dtype, int head_dim, const AppendArgs &a, c
     // 470 MB 106 -> 94 us; 11 MB, which do stay, 5.3 us as they are and 5.7 streamed.  More than
     // one pass over the rows reads K again: 33 queries x 4 heads 192 us as they are, 211 streamed.
     const bool one_pass = (int64_t)a.n_q * a.sh.group <= kRowsPerBlock;
-    const int64_t row_bytes = (int64_t)head_dim * 2;
-    const int64_t k_bytes = (int64_t)a.sh.batch * a.sh.n_kv_heads * ((int64_t)a.kv.cap + (second ? second->kv.cap : 0)) * row_bytes;
+    const int64_t k_bytes = k_bytes_of(a, second, head_dim);
     const int streamed = one_pass && k_bytes >= (int64_t(16) << 20) ? 1 : 0;
-    if (dtype == 1 && head_dim == 64) return launch_weights_group<64>(a, a2, line, two, grid, streamed, s);
-    if (dtype == 1 && head_dim == 128) return launch_weights_group<128>(a, a2, line, two, grid, streamed, s);
+    const int from_end = after_attention && one_pass && kept_sixteenths(2 * k_bytes) > 0 ? 1 : 0;
+    if (dtype == 1 && head_dim == 64) return launch_weights_group<64>(a, a2, line, two, grid, streamed, from_end, s);
+    if (dtype == 1 && head_dim == 128) return launch_weights_group<128>(a, a2, line, two, grid, streamed, from_end, s);
     return hipErrorInvalidValue;
 }
 

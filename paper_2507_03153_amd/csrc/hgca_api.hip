@@ -1152,7 +1152,7 @@ int hgca_append_attn(const hgca_shape *shape, const void *q, int32_t n_q, const 
     char *base = static_cast<char *>(ws);
     a.part = Partials{reinterpret_cast<float *>(base + w.o), reinterpret_cast<float *>(base + w.m),
                       reinterpret_cast<float *>(base + w.l), line.shares, line.shares};
-    if ((rc = from_hip(launch_append_attn(shape->dtype, shape->head_dim, a, nullptr, line, s))) != HGCA_OK) return rc;
+    if ((rc = from_hip(launch_append_attn(shape->dtype, shape->head_dim, a, nullptr, line, false, s))) != HGCA_OK) return rc;
     const int64_t rows = (int64_t)shape->batch * n_q * shape->n_q_heads;
     return from_hip(launch_combine(shape->head_dim, rows, a.part, o_out, lse_out, s));
 }
@@ -1198,7 +1198,7 @@ namespace {
 // Both tiers of an append turn, either type (the exported call takes bf16 only; a turn over the managed cache both).
 int append_attn_tiers(const hgca_shape *shape, const void *q, int32_t n_q, const hgca_kv_view *window,
                            const hgca_kv_view *pool, int32_t flags, float *o_out, float *lse_out, float *lse_window_out,
-                           float *lse_pool_out, void *ws, size_t ws_bytes, void *hip_stream)
+                           float *lse_pool_out, bool weights_follow, void *ws, size_t ws_bytes, void *hip_stream)
 {
     int rc = check_append(shape, q, n_q, window, true);
     if (rc != HGCA_OK) return rc;
@@ -1224,7 +1224,7 @@ int append_attn_tiers(const hgca_shape *shape, const void *q, int32_t n_q, const
     aw.part = ap.part = Partials{reinterpret_cast<float *>(base + w.o), reinterpret_cast<float *>(base + w.m),
                                  reinterpret_cast<float *>(base + w.l), w.shares + 1, w.shares + 1};
     const LineDev line{pool->seq_lens, window->seq_lens, pool->cap, window->cap, w.shares, n_q * shape->n_q_heads};
-    if ((rc = from_hip(launch_append_attn(shape->dtype, shape->head_dim, ap, &aw, line, s))) != HGCA_OK) return rc;
+    if ((rc = from_hip(launch_append_attn(shape->dtype, shape->head_dim, ap, &aw, line, weights_follow, s))) != HGCA_OK) return rc;
     // merge_state over the partials of both tiers at once; each tier's own lse comes out of the same fold
     const int64_t rows = (int64_t)shape->batch * n_q * shape->n_q_heads;
     float *lse_w = lse_window_out ? lse_window_out : reinterpret_cast<float *>(base + w.lse_w);
@@ -1245,7 +1245,7 @@ int hgca_append_attn_tiers(const hgca_shape *shape, const void *q, int32_t n_q, 
     if ((rc = check_append(shape, q, n_q, pool, true)) != HGCA_OK) return rc;
     if (flags & ~(HGCA_APPEND_CAUSAL_TAIL | HGCA_APPEND_ONE_PART_P)) return HGCA_ERR_INVALID_ARG;
     if (shape->dtype != HGCA_BF16) return HGCA_ERR_UNSUPPORTED;      // fp32 inputs: one call per tier and hgca_lse_merge
-    return append_attn_tiers(shape, q, n_q, window, pool, flags, o_out, lse_out, lse_window_out, lse_pool_out, ws, ws_bytes,
+    return append_attn_tiers(shape, q, n_q, window, pool, flags, o_out, lse_out, lse_window_out, lse_pool_out, false, ws, ws_bytes,
                              hip_stream);
 }
 
@@ -1279,7 +1279,7 @@ namespace {
 
 int append_weights_tiers(const hgca_shape *shape, const void *q, int32_t n_q, const hgca_kv_view *window,
                               const hgca_kv_view *pool, int32_t causal_tail, const float *lse_window, const float *lse_pool,
-                              float *a_gpu, float *a_cpu, void *hip_stream)
+                              float *a_gpu, float *a_cpu, bool after_attention, void *hip_stream)
 {
     int rc = check_append(shape, q, n_q, window, false);
     if (rc != HGCA_OK) return rc;
@@ -1291,7 +1291,8 @@ int append_weights_tiers(const hgca_shape *shape, const void *q, int32_t n_q, co
     const AppendArgs ap = weights_args(shape, q, n_q, pool, 0, lse_pool, a_cpu);
     const LineDev line{pool->seq_lens, window->seq_lens, pool->cap, window->cap,
                        weights_shares(shape, (int64_t)pool->cap + window->cap), 0};
-    return from_hip(launch_append_weights(shape->dtype, shape->head_dim, ap, &aw, line, static_cast<hipStream_t>(hip_stream)));
+    return from_hip(launch_append_weights(shape->dtype, shape->head_dim, ap, &aw, line, after_attention,
+                                          static_cast<hipStream_t>(hip_stream)));
 }
 
 }  // namespace
@@ -1305,7 +1306,7 @@ int hgca_append_weights_tiers(const hgca_shape *shape, const void *q, int32_t n_
     if ((rc = check_append(shape, q, n_q, pool, false)) != HGCA_OK) return rc;
     if (n_q == 0) return HGCA_ERR_INVALID_ARG;       // an average over no query is undefined
     if (shape->dtype != HGCA_BF16) return HGCA_ERR_UNSUPPORTED;      // fp32 inputs: one call per tier
-    return append_weights_tiers(shape, q, n_q, window, pool, causal_tail, lse_window, lse_pool, a_gpu, a_cpu, hip_stream);
+    return append_weights_tiers(shape, q, n_q, window, pool, causal_tail, lse_window, lse_pool, a_gpu, a_cpu, false, hip_stream);
 }
 
 int hgca_append_weights(const hgca_shape *shape, const void *q, int32_t n_q, const hgca_kv_view *tier,
@@ -1318,7 +1319,7 @@ int hgca_append_weights(const hgca_shape *shape, const void *q, int32_t n_q, con
     if (!lse || !a_out) return HGCA_ERR_INVALID_ARG;
     const AppendArgs a = weights_args(shape, q, n_q, tier, causal_tail, lse, a_out);
     const LineDev line{tier->seq_lens, nullptr, tier->cap, 0, weights_shares(shape, tier->cap), 0};
-    return from_hip(launch_append_weights(shape->dtype, shape->head_dim, a, nullptr, line, static_cast<hipStream_t>(hip_stream)));
+    return from_hip(launch_append_weights(shape->dtype, shape->head_dim, a, nullptr, line, false, static_cast<hipStream_t>(hip_stream)));
 }
 
 namespace {
@@ -1394,11 +1395,11 @@ int hgca_managed_append_step(const hgca_shape *shape, const hgca_cache_state *ca
         return rc;
     // gpu_attention over the window (causal among the incoming tokens), cpu_attention over the complete offloaded
     // cache, merge_state per (sequence, query, head): one launch for both tiers and one fold
-    if ((rc = append_attn_tiers(shape, q, n_q, &window, &pool, flags | HGCA_APPEND_CAUSAL_TAIL, o_out, lse_out, lse_w, lse_p,
+    if ((rc = append_attn_tiers(shape, q, n_q, &window, &pool, flags | HGCA_APPEND_CAUSAL_TAIL, o_out, lse_out, lse_w, lse_p, true,
                                 base + w.attn, w.attn_bytes, hip_stream)) != HGCA_OK)
         return rc;
     // A_gpu, A_cpu: the query-averaged weights of the two parts, one launch for both
-    if ((rc = append_weights_tiers(shape, q, n_q, &window, &pool, 1, lse_w, lse_p, a_gpu, a_cpu, hip_stream)) != HGCA_OK)
+    if ((rc = append_weights_tiers(shape, q, n_q, &window, &pool, 1, lse_w, lse_p, a_gpu, a_cpu, true, hip_stream)) != HGCA_OK)
         return rc;
     // Alg. 1: moving averages (the n_q new entries take their first observed weight), re-evaluation of the salient
     // lists (Sec. 3.2.2: ids = A_cpu > beta / A_cpu.size), eviction of as many whole blocks as it takes: per row, one launch

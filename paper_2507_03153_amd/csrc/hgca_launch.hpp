@@ -185,12 +185,14 @@ struct AppendArgs {
     float *a_out;              // weights: [B, Hq, cap]
 };
 // One tier (second = nullptr, `shares` slots) or two as a line (same queries, shape and partials; each tier with its
-// own view and mask rule; `shares` + 1 slots).
+// own view and mask rule; `shares` + 1 slots).  weights_follow: launch_append_weights comes next,
+// on the same tiers.
 hipError_t launch_append_attn(int dtype, int head_dim, const AppendArgs &first, const AppendArgs *second, const LineDev &line,
-                              hipStream_t s);
-// the weights of one tier (second = nullptr) or of two (same queries and shape), as a line
+                              bool weights_follow, hipStream_t s);
+// the weights of one tier (second = nullptr) or of two (same queries and shape), as a line.  after_attention: these rows
+// have just passed launch_append_attn with weights_follow.
 hipError_t launch_append_weights(int dtype, int head_dim, const AppendArgs &first, const AppendArgs *second, const LineDev &line,
-                                 hipStream_t s);
+                                 bool after_attention, hipStream_t s);
 // the same on fp32 inputs (two = 0: a2 is not used); these check nothing, the two above call them
 hipError_t launch_append_attn_f32(int head_dim, const AppendArgs &a, const AppendArgs &a2, const LineDev &line, int two, dim3 grid,
                                   hipStream_t s);
