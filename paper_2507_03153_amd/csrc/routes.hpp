@@ -51,7 +51,9 @@ inline bool window_first(bool f32, int64_t group, int64_t window, int64_t k_max,
 // Whether a step with a selection runs as the two launches of short_step_kernels.hip.  They save two or three dependent
 // launches of 3 to 5 us each; against that a row's list is read by one compute unit alone (its V rows at about 60 GB/s ... 512 KB
 // take 8 us), and a score pass that shares its launch with the window has the window's registers and LDS.  One row per compute
-// unit at most; then, general path : this one, in us
+// unit at most; then, general path : this one, in us (taken when reductions over a wave went through LDS; since then both sides are
+// faster and the order is the same: bf16, one sequence, 32 / 8 heads of 128, pool 20000, k 500 29.3 : 27.4; 180 MB of keys, k 400
+// 60.1 : 59.0; groups of 8 of 64, 29 MB, k 700 32.9 : 30.7; fp32, groups of 8 of 64, 65 MB, 256 KB 42.5 : 42.5)
 //   V rows of a list, bf16: 102 KB (k 400) 21.4 : 20.0, 154 KB (k 1207) 32.9 : 33.9, 512 KB (k 2000) 25.5 : 31.8; fp32, which has one
 //   launch more in the general path: 16 KB 24.7 : 15.9, 358 KB 27.9 : 26.6, 512 KB 27.7 : 30.5, 1 MB 34.4 : 43.0
 //   keys of the pool, bf16, heads of 128 in groups of 2 and 4, lists of 16 to 128 KB: 100 MB 45.2 : 45.0 to 41.2 : 39.3, 180 MB 61.1 : 61.5,

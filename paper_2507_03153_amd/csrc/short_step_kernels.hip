@@ -5,8 +5,8 @@
 // it does.  Here the window's splits share a launch with the score pass (they need nothing from each other), and the
 // workgroup that selects a row's entries attends to them at once and folds the window's partials in.
 // Measured (general path : this one, us per step; the rule and more of both sides stand where the path is chosen): fp32, 4 heads
-// of 64, window 256, pool 2048, k 64: 24.4 : 15.4; fp32, 32 / 8 heads of 128, window 1024, pool 4096, k 400: 38.9 : 30.2;
-// bf16, 64 / 8 heads, window 256, pool 2048, k 64: 24.9 : 19.4.
+// of 64, window 256, pool 2048, k 64: 18.9 : 13.1; fp32, 32 / 8 heads of 128, window 1024, pool 4096, k 400: 24.8 : 23.3;
+// bf16, 64 / 8 heads, window 256, pool 2048, k 64: 22.7 : 16.7.
 #include "attn_device.hpp"
 #include "select_device.hpp"
 
