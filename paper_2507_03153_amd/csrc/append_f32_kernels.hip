@@ -2,11 +2,16 @@
 // append_kernels.hip (work units, orientation of the products, lines of shares), with products on the bf16 matrix instructions.
 //
 // The fp32 matrix instructions do a sixteenth of the bf16 ones' work per cycle.  An fp32 value is the sum of three bf16 parts, each
-// the rounding error of those before (24 bits, exact), and of the nine products of parts the six down to 2^-18 of the whole are
+// the rounding error of those before (24 bits), and of the nine products of parts the six down to 2^-18 of the whole are
 // formed: what is left out is below 2^-26 of it, less than one rounding of a sum.  The products of the upper parts go to
-// accumulators of their own, so that a sum that has nearly reached its size is rounded a few times only.  A value that
-// is not finite, or so large that its upper part rounds to infinity, gives NaN; results that are not finite are formed
-// again on the vector units, every row from what it sees and nothing else.
+// accumulators of their own, so that a sum that has nearly reached its size is rounded a few times only.
+//
+// bf16 has no bits below 2^-133 (2^-126 where subnormal numbers count as 0), so values below 2^-102 may lose lower parts:
+//   queries and softmax weights are taken apart times 2^24 (kUp), which makes the sum of the parts exact whatever they are;
+//   keys lose less than 2^-126, which |q| sm_scale <= 2^90 keeps out of the scores (2^-29 over 128 columns); larger queries become NaN;
+//   V rows lose less than 2^-126 as well, which counts where a sum of them is below 2^-88 (kLeast; 2^-24 of it over 2^14 tokens).
+// Values whose upper part rounds to infinity and values that are not finite give NaN.  Where sums are not finite, or so small,
+// they are formed again on the vector units, every row from what it sees and nothing else.
 //
 // Errors against 64 bits are those of fp32 products (2 x 24 queries on 5 K tokens: O 3.5e-7, weights 2.6e-7 with either).  fp32
 // matrix instructions : parts, us: that turn 137.7 : 97.1 (attention 76 : 45, weights 42 : 33); 8 x 24 queries of 32 / 8 heads of 64 on 17 K
@@ -23,6 +28,10 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 struct Parts {
     u32x4 h, m, l;                               // 8 bf16 each
 };
+
+constexpr float kUp = 0x1p24f, kDown = 0x1p-24f;
+constexpr float kMostQuery = 0x1p90f;            // times the scale
+constexpr float kLeast = 0x1p-88f;
 
 // the parts of x and y into element e of p: eleven vector instructions
 __device__ __forceinline__ void pair_parts(Parts &p, int e, float x, float y)
@@ -41,6 +50,33 @@ __device__ __forceinline__ Parts parts_of(const uint4 &a, const uint4 &b)
     pair_parts(p, 1, __uint_as_float(a.z), __uint_as_float(a.w));
     pair_parts(p, 2, __uint_as_float(b.x), __uint_as_float(b.y));
     pair_parts(p, 3, __uint_as_float(b.z), __uint_as_float(b.w));
+    return p;
+}
+// The power of two that queries are taken apart times, and the scale of the scores that they give (arguments of the kernels: both
+// are at hand wherever they are used, without a register).
+struct QueryScale {
+    float up, scale;
+};
+QueryScale query_scale(float sm_scale)
+{
+    // with a scale as small as this sums of up to 2^128 may be scores of ordinary size, and nothing is lost (2^-60 2^127 2^-126)
+    return sm_scale < 0x1p-60f ? QueryScale{1.f, sm_scale} : QueryScale{kUp, sm_scale * kDown};
+}
+
+// of eight columns of a query
+__device__ __forceinline__ Parts query_parts(const char *src, float sm_scale, float up)
+{
+    const floatx4 a = __builtin_bit_cast(floatx4, load16(src)), b = __builtin_bit_cast(floatx4, load16(src + 16));
+    float most = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) most = fmaxf(fmaxf(most, fabsf(a[i])), fabsf(b[i]));
+    if (most * sm_scale > kMostQuery) up = __uint_as_float(0x7fc00000u);
+    Parts p;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        pair_parts(p, e, a[2 * e] * up, a[2 * e + 1] * up);
+        pair_parts(p, 2 + e, b[2 * e] * up, b[2 * e + 1] * up);
+    }
     return p;
 }
 __device__ __forceinline__ floatx4 mfma(const u32x4 &a, const u32x4 &b, floatx4 c)
@@ -140,7 +176,7 @@ __device__ __forceinline__ void append_rows_again(const KvDev &kv, int n_kv_head
 // one barrier per tile.  Two waves share a SIMD, and one's products hide the other's waits (four waves of 32 rows have half the
 // LDS reads and the registers of one wave per SIMD: every read and every conversion then stands between two products).
 template <int D, bool TWO>
-__global__ __launch_bounds__(kF32Block, 2) void append_attn_f32_kernel(AppendArgs a1, AppendArgs a2, LineDev line)
+__global__ __launch_bounds__(kF32Block, 2) void append_attn_f32_kernel(AppendArgs a1, AppendArgs a2, LineDev line, QueryScale qs)
 {
     using P = PartStage<D>;
     using S = typename P::S;
@@ -170,8 +206,9 @@ __global__ __launch_bounds__(kF32Block, 2) void append_attn_f32_kernel(AppendArg
     const char *q_row = static_cast<const char *>(a1.q) + out_row * (D * 4);
     Parts q[KK];                                 // B operand: columns 32 kk + 8 g .. + 7 of the lane's row
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) q[kk] = parts_of(load16(q_row + 128 * kk + 32 * g), load16(q_row + 128 * kk + 32 * g + 16));
-    const float scale2 = a1.sh.sm_scale * kLog2e;                // scores stay raw; e^{scale (s - m)} = 2^{(s - m) scale2}
+    for (int kk = 0; kk < KK; ++kk) q[kk] = query_parts(q_row + 128 * kk + 32 * g, a1.sh.sm_scale, qs.up);
+    // scores stay raw, but for the queries' power of two; e^{scale (s - m)} = 2^{(s - m) scale2}
+    const float scale2 = qs.scale * kLog2e;
 
     // what the thread brings in: K rows as they stand, V rows in quads (the order in which their stage holds them)
     constexpr int kQuadLanes = 4 * S::kRowBytes / 16;
@@ -289,6 +326,10 @@ __global__ __launch_bounds__(kF32Block, 2) void append_attn_f32_kernel(AppendArg
 #pragma unroll
                     for (int i = 0; i < 4; ++i) c[4 * t + i] = x[i];
                 }
+                float lowest = c[0];             // a score of -inf may be a sum that overflowed: l becomes NaN
+#pragma unroll
+                for (int i = 1; i < 8; ++i) lowest = fminf(lowest, c[i]);
+                l = fmaf(lowest, 0.f, l);
                 const int step0 = t0 + sub0 + tile * kTile, in_pass = nsub - tile * kTile;
                 if (min(in_pass, vis_min - step0) < kTile) {         // uniform over the wave: a length or causal boundary
                     int limit = min(in_pass, vis - step0);
@@ -316,7 +357,7 @@ __global__ __launch_bounds__(kF32Block, 2) void append_attn_f32_kernel(AppendArg
                 l += ((c[0] + c[1]) + (c[2] + c[3])) + ((c[4] + c[5]) + (c[6] + c[7]));
                 Parts p;                         // contraction index 8 g + i is token 16 (i / 4) + 4 g + i % 4
 #pragma unroll
-                for (int e = 0; e < 4; ++e) pair_parts(p, e, c[2 * e], c[2 * e + 1]);
+                for (int e = 0; e < 4; ++e) pair_parts(p, e, c[2 * e] * kUp, c[2 * e + 1] * kUp);
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) {
                     if (dt + 1 < DT) read_v(dt + 1);
@@ -350,16 +391,29 @@ __global__ __launch_bounds__(kF32Block, 2) void append_attn_f32_kernel(AppendArg
         }
 
         // A weight of 0 keeps a V row out of the products above only while the row is finite (0 * inf is NaN), and values that are
-        // not finite, or too large for a bf16, have no parts: where sums are not finite the wave works its share out again.
+        // not finite, or too large or too small, have no parts: where sums are not finite, or next to nothing, the wave works its share
+        // out again.
+        m *= qs.up == kUp ? kDown : 1.f;
         if (wave_live && nt_total > 0) {         // uniform over the wave
-            bool finite = fabsf(l) < INFINITY;
+            float not_finite = l * 0.f, least = INFINITY;            // (the product with 0 is NaN then)
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) finite &= fabsf(acc[dt][i]) < INFINITY;
-            if (__any(!finite))
-                append_rows_again<D>(kv, a1.sh.n_kv_heads, b, kvh, t0, min(t0 + nt_total, vis), t0 + nt_total, q_row, g, scale2, m, l,
-                                     acc);
+                for (int i = 0; i < 4; ++i) {
+                    acc[dt][i] *= kDown;
+                    not_finite = fmaf(acc[dt][i], 0.f, not_finite);
+                    least = fminf(least, fabsf(acc[dt][i]));
+                }
+            bool again = not_finite != 0.f;
+            if (__any(least < kLeast)) {         // 0 is no small one
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) again |= acc[dt][i] != 0.f && fabsf(acc[dt][i]) < kLeast;
+            }
+            if (__any(again))
+                append_rows_again<D>(kv, a1.sh.n_kv_heads, b, kvh, t0, min(t0 + nt_total, vis), t0 + nt_total, q_row, g,
+                                     a1.sh.sm_scale * kLog2e, m, l, acc);
         }
 
         // partial of every valid row: the lane holds output columns 16 dt + 4 g .. + 3 of its row
@@ -402,7 +456,8 @@ __device__ __forceinline__ float exp_of(float x)
 constexpr float kNoRow = -1e30f;                 // shift of a row that does not exist: weighs nothing, and exp_of stays a number
 
 template <int D, int G, bool TWO>
-__global__ __launch_bounds__(WeightsF32<D>::kBlock, 2) void append_weights_f32_kernel(AppendArgs a1, AppendArgs a2, LineDev line)
+__global__ __launch_bounds__(WeightsF32<D>::kBlock, 2) void append_weights_f32_kernel(AppendArgs a1, AppendArgs a2, LineDev line,
+                                                                                 QueryScale qs)
 {
     using W = WeightsF32<D>;
     constexpr int kWWaves = W::kWaves, kWBlock = W::kBlock, KK = D / 32, NS = G < 4 ? G : 4;
@@ -416,7 +471,7 @@ __global__ __launch_bounds__(WeightsF32<D>::kBlock, 2) void append_weights_f32_k
     const int tid = threadIdx.x, lane = tid % kWave, w = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int n = lane % 16, lg = lane / 16;
     const int n_rows = a1.n_q * G, n_qb = (n_rows + kRowsPerBlock - 1) / kRowsPerBlock;
-    const float inv_n = 1.f / (float)a1.n_q, scale = a1.sh.sm_scale;
+    const float inv_n = 1.f / (float)a1.n_q;
     const int frag0 = W::offset(n, lg);          // operand of row n of 16; slice kk is an exclusive-or of 64 kk away
 
     const LineCut cut(line, b);
@@ -472,7 +527,7 @@ __global__ __launch_bounds__(WeightsF32<D>::kBlock, 2) void append_weights_f32_k
                         const int r = at < n_rows ? at : n_rows - G + at % G;
                         const char *src = static_cast<const char *>(a1.q) +
                                           (((int64_t)b * a1.n_q + r / G) * a1.sh.n_q_heads + kvh * G + r % G) * (D * 4) + 32 * piece;
-                        const Parts p = parts_of(load16(src), load16(src + 16));
+                        const Parts p = query_parts(src, a1.sh.sm_scale, qs.up);
                         char *dst = s_q + W::offset(row, piece);
                         *reinterpret_cast<u32x4 *>(dst) = p.h;
                         *reinterpret_cast<u32x4 *>(dst + W::kPart) = p.m;
@@ -539,7 +594,7 @@ __global__ __launch_bounds__(WeightsF32<D>::kBlock, 2) void append_weights_f32_k
                             const floatx4 c = ts[t].sum();
 #pragma unroll
                             for (int i = 0; i < 4; ++i) {                            // the head of row r is r % G
-                                const float e = exp_of(fmaf(c[i], scale, s4[i]));
+                                const float e = exp_of(fmaf(c[i], qs.scale, s4[i]));
                                 sum[t][i % NS] += !cut_tile || 16 * x + 4 * lg + i >= first_row + G * 16 * t ? e : 0.f;
                             }
                         }
@@ -569,7 +624,7 @@ __global__ __launch_bounds__(WeightsF32<D>::kBlock, 2) void append_weights_f32_k
                                         const float4 v = *reinterpret_cast<const float4 *>(q + 16 * d);
                                         s = fmaf(u.w, v.w, fmaf(u.z, v.z, fmaf(u.y, v.y, fmaf(u.x, v.x, s))));
                                     }
-                                    s = expf(fmaf(s, scale, s_shift[row]));
+                                    s = expf(fmaf(s, a1.sh.sm_scale, s_shift[row]));
                                     again[i % NS] += !cut_tile || row >= first_row + G * 16 * t ? s : 0.f;
                                 }
 #pragma unroll
@@ -602,8 +657,8 @@ __global__ __launch_bounds__(WeightsF32<D>::kBlock, 2) void append_weights_f32_k
 template <int D>
 hipError_t launch_attn(const AppendArgs &a, const AppendArgs &a2, const LineDev &line, int two, dim3 grid, hipStream_t s)
 {
-    if (two) hipLaunchKernelGGL((append_attn_f32_kernel<D, true>), grid, dim3(kF32Block), 0, s, a, a2, line);
-    else hipLaunchKernelGGL((append_attn_f32_kernel<D, false>), grid, dim3(kF32Block), 0, s, a, a2, line);
+    if (two) hipLaunchKernelGGL((append_attn_f32_kernel<D, true>), grid, dim3(kF32Block), 0, s, a, a2, line, query_scale(a.sh.sm_scale));
+    else hipLaunchKernelGGL((append_attn_f32_kernel<D, false>), grid, dim3(kF32Block), 0, s, a, a2, line, query_scale(a.sh.sm_scale));
     return hipGetLastError();
 }
 
@@ -611,11 +666,12 @@ template <int D, bool TWO>
 hipError_t launch_weights(const AppendArgs &a, const AppendArgs &a2, const LineDev &line, dim3 grid, hipStream_t s)
 {
     const dim3 block(WeightsF32<D>::kBlock);
+    const QueryScale qs = query_scale(a.sh.sm_scale);
     switch (a.sh.group) {
-    case 1: hipLaunchKernelGGL((append_weights_f32_kernel<D, 1, TWO>), grid, block, 0, s, a, a2, line); break;
-    case 2: hipLaunchKernelGGL((append_weights_f32_kernel<D, 2, TWO>), grid, block, 0, s, a, a2, line); break;
-    case 4: hipLaunchKernelGGL((append_weights_f32_kernel<D, 4, TWO>), grid, block, 0, s, a, a2, line); break;
-    case 8: hipLaunchKernelGGL((append_weights_f32_kernel<D, 8, TWO>), grid, block, 0, s, a, a2, line); break;
+    case 1: hipLaunchKernelGGL((append_weights_f32_kernel<D, 1, TWO>), grid, block, 0, s, a, a2, line, qs); break;
+    case 2: hipLaunchKernelGGL((append_weights_f32_kernel<D, 2, TWO>), grid, block, 0, s, a, a2, line, qs); break;
+    case 4: hipLaunchKernelGGL((append_weights_f32_kernel<D, 4, TWO>), grid, block, 0, s, a, a2, line, qs); break;
+    case 8: hipLaunchKernelGGL((append_weights_f32_kernel<D, 8, TWO>), grid, block, 0, s, a, a2, line, qs); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

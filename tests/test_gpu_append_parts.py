@@ -21,12 +21,12 @@ def weights_reference(q, K, lens, lse, scale, causal, cap):
     return a / N
 
 
-def run(gpu, q, K, V, lens, causal, paged):
+def run(gpu, q, K, V, lens, causal, paged, scale=None):
     torch, hgca, runner = gpu
     B, N, Hq, d = q.shape
     Hkv, cap = K.shape[1:3]
     g = lambda a: runner._to_gpu(a, "cuda:0")
-    shape = hgca.Shape(hgca.F32, B, Hq, Hkv, d, d ** -0.5)
+    shape = hgca.Shape(hgca.F32, B, Hq, Hkv, d, d ** -0.5 if scale is None else scale)
     tier = to_paged(runner, hgca, torch, K, V, lens, cap, 16, 4, "cuda:0") if paged else hgca.Tier(g(K), g(V), cap, g(lens))
     o, lse = torch.full((B, N, Hq, d), float("nan"), device="cuda:0"), torch.full((B, N, Hq), float("nan"), device="cuda:0")
     a = torch.full((B, Hq, cap), float("nan"), device="cuda:0")
@@ -79,6 +79,44 @@ def test_values_without_parts(gpu, kw):  # noqa: F811
     assert np.max(np.abs(o - o_ref) / np.maximum(np.abs(o_ref).max(axis=(0, 1, 2)), 1.0)) <= 1e-5
     a_ref = weights_reference(q, K, lens, l_ref, d ** -0.5, False, cap)
     assert np.max(np.abs(a - a_ref)) <= 1e-5 and np.all(a[:, :, 3:200:17] == 0)
+
+
+@pytest.mark.parametrize("case", ["large_and_small", "small_queries", "small_keys", "small_scale", "small_values", "small_weights", "low_scores"])
+@pytest.mark.parametrize("kw", [dict(N=40, Hq=8, Hkv=2, d=128), dict(N=100, Hq=4, Hkv=4, d=64)], ids=["gqa4", "mha_d64"])
+def test_ends_of_the_range(gpu, kw, case):  # noqa: F811
+    """Normal fp32 operands whose lower parts bf16 has no bits for: what they give is as exact as anywhere else."""
+    N, Hq, Hkv, d = (kw[x] for x in ("N", "Hq", "Hkv", "d"))
+    B, cap, lens, scale = 2, 260, np.array((260, 201), np.int32), d ** -0.5
+    rng = np.random.default_rng(d)
+    q, K, V = (rng.standard_normal(s) for s in ((B, N, Hq, d), (B, Hkv, cap, d), (B, Hkv, cap, d)))
+    if case == "large_and_small":                                # 3e38 has a bf16 part of its own; the terms are up to 3
+        q[..., 1] *= 1e-38
+        K[..., 1] = 0.0
+        K[:, :, 5::19, 1] = 3e38
+    elif case in ("small_queries", "small_keys", "small_scale"):
+        a, b = {"small_queries": (-119, 14), "small_keys": (14, -119), "small_scale": (60, 41)}[case]
+        q, K, scale = q * 2.0 ** a, K * 2.0 ** b, scale * 2.0 ** -(a + b)
+    elif case == "small_values":
+        V[..., ::3] *= 2.0 ** -120
+    elif case == "small_weights":                                # weights of some 2^-116, all that a column of V has
+        K[:, :, 7::11] = 0.0
+        q[..., 0], K[..., 0] = d ** 0.5, 82.0
+        K[:, :, 7::11, 0] = 0.0
+        V[..., 4] = 0.0
+        V[:, :, 7::11, 4] = 1e30
+    else:                                                        # all scores alike, far below any sum of scaled products
+        q[...], K[...] = 0.0, 0.0
+        q[..., 0], K[..., 0] = 2.0 ** 50, -2.0 ** 40
+    q, K, V = (x.astype(np.float32) for x in (q, K, V))
+    o, lse, a = run(gpu, q, K, V, lens, False, False, scale)
+    scale = float(np.float32(scale))
+    o_ref, l_ref = reference(q, K, V, lens, scale, False)
+    assert np.max(np.abs(lse - l_ref) / np.maximum(np.abs(l_ref), 1.0)) <= 1e-5
+    # a weight that counts lies 80 below the others here: its score is rounded to 80 * 2^-24, and so is the weight
+    column = np.abs(o_ref).max(axis=(0, 1, 2))
+    assert column.min() > 0 and np.max(np.abs(o - o_ref) / column) <= (4e-5 if case == "small_weights" else 1e-5)
+    if case != "low_scores":                                     # (the weights take the rounding of lse, 2^90 here)
+        assert np.max(np.abs(a - weights_reference(q, K, lens, l_ref, scale, False, cap))) <= 1e-5
 
 
 def test_error_against_64_bits(gpu):  # noqa: F811
