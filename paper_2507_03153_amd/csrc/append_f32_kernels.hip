@@ -11,7 +11,9 @@
 //   keys lose less than 2^-126, which |q| sm_scale <= 2^90 keeps out of the scores (2^-29 over 128 columns); larger queries become NaN;
 //   V rows lose less than 2^-126 as well, which counts where a sum of them is below 2^-88 (kLeast; 2^-24 of it over 2^14 tokens).
 // Values whose upper part rounds to infinity and values that are not finite give NaN.  Where sums are not finite, or so small,
-// they are formed again on the vector units, every row from what it sees and nothing else.
+// they are formed again with fp32 products, every row from what it sees and nothing else: one infinite V row or one NaN key in
+// every share costs the attention of 2 x 24 queries on 5 K tokens 44 -> 110 us (66 with fp32 products throughout), a NaN key every
+// 100 tokens their weights 26 -> 85 (38), a key with scores of -inf 26 -> 44.
 //
 // Errors against 64 bits are those of fp32 products (2 x 24 queries on 5 K tokens: O 3.5e-7, weights 2.6e-7 with either).  fp32
 // matrix instructions : parts, us: that turn 137.7 : 97.1 (attention 76 : 45, weights 42 : 33); 8 x 24 queries of 32 / 8 heads of 64 on 17 K
@@ -100,6 +102,19 @@ struct TileSums {
     __device__ __forceinline__ floatx4 sum() const { return (up[0] + up[1]) + lo; }
 };
 
+// The sums of a 16 x 16 tile with fp32 products: the lane points at its four columns (of every 16) of row n of each operand.
+template <int D> __device__ __forceinline__ floatx4 scores_f32(const char *a, const char *b)
+{
+    floatx4 c[4] = {};                           // a quarter of the columns each
+#pragma unroll 2
+    for (int j = 0; j < D / 16; ++j) {
+        const floatx4 x = __builtin_bit_cast(floatx4, load16(a + 64 * j)), y = __builtin_bit_cast(floatx4, load16(b + 64 * j));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) c[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[e], y[e], c[e], 0, 0, 0);
+    }
+    return (c[0] + c[1]) + (c[2] + c[3]);
+}
+
 // ---- attention -------------------------------------------------------------------------------------------------
 
 constexpr int kTile = 32;                        // tokens that go through LDS at a time
@@ -119,13 +134,14 @@ template <int D> struct PartStage {
     }
 };
 
-// The softmax of a wave's rows over the tier positions [begin, end) -- of a row only [begin, row_end) -- on the vector
-// units, one token after the other: maximum of the raw scores, sum of the weights (in the first lane of a row) and weighted sums of
-// V.  As in the kernel below, a row's four lanes (g) take every fourth 16-byte piece of its query and hold the output columns
-// 16 dt + 4 g .. + 3; all lanes of the wave take part.
+// The softmax of a wave's rows over the tier positions [begin, row_end) (of each row; ascending over the wave's rows) with fp32
+// products: maximum of the raw scores, sums of the weights (the lane's) and of V times them.  As in the kernel below, the four lanes
+// g of row n hold the output columns 16 dt + 4 g .. + 3; all lanes of the wave take part.  Tokens that all rows see pass 16 at a
+// time through the fp32 matrix instructions, the others one by one, as a weight of 0 does not keep an infinity out of a product.
 template <int D>
-__device__ __forceinline__ void append_rows_again(const KvDev &kv, int n_kv_heads, int b, int kvh, int begin, int row_end, int end,
-                                                  const char *q_row, int g, float scale2, float &m, float &l, floatx4 (&acc)[D / 16])
+__device__ __forceinline__ void append_rows_again(const KvDev &kv, int n_kv_heads, int b, int kvh, int begin, int row_end,
+                                                  const char *q_row, int n, int g, float scale2, float &m, float &l,
+                                                  floatx4 (&acc)[D / 16])
 {
     m = -INFINITY;
     l = 0.f;
@@ -133,39 +149,61 @@ __device__ __forceinline__ void append_rows_again(const KvDev &kv, int n_kv_head
     for (int dt = 0; dt < D / 16; ++dt) acc[dt] = floatx4{};
     const int32_t *blocks = kv.block_table ? kv.block_table + (int64_t)b * kv.max_blocks + (kv.first_block ? kv.first_block[b] : 0)
                                            : nullptr;
-    float m0 = 0.f;
-#pragma unroll 1
-    for (int pass = 0; pass < 2; ++pass) {       // the maximum, then the sums
-#pragma unroll 1
-        for (int tok = begin; tok < end; ++tok) {
-            const int64_t row = blocks ? ((int64_t)blocks[tok / kv.block_size] * n_kv_heads + kvh) * kv.block_size + tok % kv.block_size
-                                       : ((int64_t)b * n_kv_heads + kvh) * kv.cap + tok;
-            const char *k = kv.k + row * (D * 4);
-            float s = 0.f;
-#pragma unroll 1
-            for (int i = g; i < D / 4; i += 4) {
-                const float4 x = *reinterpret_cast<const float4 *>(k + 16 * i), y = *reinterpret_cast<const float4 *>(q_row + 16 * i);
-                s = fmaf(x.w, y.w, fmaf(x.z, y.z, fmaf(x.y, y.y, fmaf(x.x, y.x, s))));
-            }
-            s = strided_sum<16>(s);
-            if (tok >= row_end) continue;
-            if (pass == 0) {
-                m = fmaxf(m, s);
-                continue;
-            }
-            const char *v = kv.v + row * (D * 4) + 16 * g;
-            const float p = __builtin_amdgcn_exp2f((s - m0) * scale2);
-            l += g ? 0.f : p;
+    auto row_bytes = [&](int tok) {              // where the token's row begins
+        return (blocks ? ((int64_t)blocks[tok / kv.block_size] * n_kv_heads + kvh) * kv.block_size + tok % kv.block_size
+                       : ((int64_t)b * n_kv_heads + kvh) * kv.cap + tok) * (D * 4);
+    };
+    auto rescale = [&](float mx) {               // the sums to the maximum of what was seen and mx; returns the shift
+        const float m_new = fmaxf(m, mx), corr = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - m_new) * scale2);
+        m = m_new;
+        l *= corr;
 #pragma unroll
-            for (int dt = 0; dt < D / 16; ++dt) {
-                const float4 x = *reinterpret_cast<const float4 *>(v + 64 * dt);
-                acc[dt][0] = fmaf(p, x.x, acc[dt][0]);
-                acc[dt][1] = fmaf(p, x.y, acc[dt][1]);
-                acc[dt][2] = fmaf(p, x.z, acc[dt][2]);
-                acc[dt][3] = fmaf(p, x.w, acc[dt][3]);
-            }
+        for (int dt = 0; dt < D / 16; ++dt) acc[dt] *= corr;
+        return m == -INFINITY ? 0.f : m;
+    };
+    const int all_end = __builtin_amdgcn_readlane(row_end, 0), any_end = __builtin_amdgcn_readlane(row_end, kF32Rows - 1);
+    int tok = begin;
+#pragma unroll 1
+    for (; tok + 16 <= all_end; tok += 16) {     // 16 tokens from a multiple of 16 lie in one block
+        const int64_t at = row_bytes(tok);
+        const floatx4 s = scores_f32<D>(kv.k + at + n * (D * 4) + 16 * g, q_row + 16 * g);       // of tokens 4 g + i
+        const LanePair x = rows_of(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]))), y = halves_of(fmaxf(x.a, x.b));
+        const float m0 = rescale(fmaxf(y.a, y.b));
+        float p[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            p[i] = __builtin_amdgcn_exp2f((s[i] - m0) * scale2);
+            l += p[i];
         }
-        m0 = m == -INFINITY ? 0.f : m;
+        const char *v = kv.v + at + 4 * g * (D * 4) + 4 * n;
+#pragma unroll
+        for (int dt = 0; dt < D / 16; ++dt) {
+            floatx4 part = {};
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                part = __builtin_amdgcn_mfma_f32_16x16x4f32(*reinterpret_cast<const float *>(v + i * (D * 4) + 64 * dt), p[i], part, 0, 0, 0);
+            acc[dt] += part;
+        }
+    }
+#pragma unroll 1
+    for (; tok < any_end; ++tok) {
+        const int64_t at = row_bytes(tok);
+        float s = 0.f;
+#pragma unroll 2
+        for (int i = g; i < D / 4; i += 4) {
+            const float4 x = *reinterpret_cast<const float4 *>(kv.k + at + 16 * i), y = *reinterpret_cast<const float4 *>(q_row + 16 * i);
+            s = fmaf(x.w, y.w, fmaf(x.z, y.z, fmaf(x.y, y.y, fmaf(x.x, y.x, s))));
+        }
+        s = strided_sum<16>(s);
+        if (tok >= row_end) continue;
+        const float p = __builtin_amdgcn_exp2f((s - rescale(s)) * scale2);
+        l += g ? 0.f : p;
+#pragma unroll
+        for (int dt = 0; dt < D / 16; ++dt) {
+            const floatx4 x = __builtin_bit_cast(floatx4, load16(kv.v + at + 64 * dt + 16 * g));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[dt][i] = fmaf(p, x[i], acc[dt][i]);
+        }
     }
 }
 
@@ -411,9 +449,13 @@ __global__ __launch_bounds__(kF32Block, 2) void append_attn_f32_kernel(AppendArg
 #pragma unroll
                     for (int i = 0; i < 4; ++i) again |= acc[dt][i] != 0.f && fabsf(acc[dt][i]) < kLeast;
             }
-            if (__any(again))
-                append_rows_again<D>(kv, a1.sh.n_kv_heads, b, kvh, t0, min(t0 + nt_total, vis), t0 + nt_total, q_row, g,
-                                     a1.sh.sm_scale * kLog2e, m, l, acc);
+            if (__any(again)) {
+                int lane_of = lane;              // nothing of this is worked out, and held in registers, before it is wanted
+                int64_t at = out_row;
+                asm volatile("" : "+v"(lane_of), "+v"(at));
+                append_rows_again<D>(kv, a1.sh.n_kv_heads, b, kvh, t0, min(t0 + nt_total, vis), static_cast<const char *>(a1.q) + at * (D * 4),
+                                     lane_of % 16, lane_of / 16, a1.sh.sm_scale * kLog2e, m, l, acc);
+            }
         }
 
         // partial of every valid row: the lane holds output columns 16 dt + 4 g .. + 3 of its row
@@ -604,32 +646,28 @@ __global__ __launch_bounds__(WeightsF32<D>::kBlock, 2) void append_weights_f32_k
                     for (int t = 0; t < 2; ++t)
 #pragma unroll
                         for (int i = 0; i < NS; ++i) finite &= fabsf(sum[t][i]) < INFINITY;
-                    if (__any(!finite)) {        // values without parts: these sums again on the vector units
-#pragma unroll
-                        for (int t = 0; t < 2; ++t) {
-                            const char *k = k_row(tile, t);
-                            float again[NS] = {};
+                    if (__any(!finite)) {        // values without parts: these sums again with fp32 products
+                        float again[2][NS] = {};
 #pragma unroll 1
-                            for (int x = part; x < 2 * live; x += spread)
+                        for (int x = part; x < 2 * live; x += spread) {
+                            const int at = qb * kRowsPerBlock + 16 * x + n, r = at < n_rows ? at : n_rows - G + at % G;
+                            const char *q = static_cast<const char *>(a1.q) +
+                                            (((int64_t)b * a1.n_q + r / G) * a1.sh.n_q_heads + kvh * G + r % G) * (D * 4);
+#pragma unroll
+                            for (int t = 0; t < 2; ++t) {
+                                const floatx4 c = scores_f32<D>(q + 16 * lg, k_row(tile, t) + 16 * lg);
 #pragma unroll
                                 for (int i = 0; i < 4; ++i) {
-                                    const int row = 16 * x + 4 * lg + i, r = qb * kRowsPerBlock + row;
-                                    if (r >= n_rows) continue;
-                                    const char *q = static_cast<const char *>(a1.q) +
-                                                    (((int64_t)b * a1.n_q + r / G) * a1.sh.n_q_heads + kvh * G + r % G) * (D * 4);
-                                    float s = 0.f;
-#pragma unroll 1
-                                    for (int d = 0; d < D / 4; ++d) {
-                                        const float4 u = *reinterpret_cast<const float4 *>(k + 16 * d);
-                                        const float4 v = *reinterpret_cast<const float4 *>(q + 16 * d);
-                                        s = fmaf(u.w, v.w, fmaf(u.z, v.z, fmaf(u.y, v.y, fmaf(u.x, v.x, s))));
-                                    }
-                                    s = expf(fmaf(s, a1.sh.sm_scale, s_shift[row]));
-                                    again[i % NS] += !cut_tile || row >= first_row + G * 16 * t ? s : 0.f;
+                                    const int row = 16 * x + 4 * lg + i;
+                                    const float e = expf(fmaf(c[i], a1.sh.sm_scale, s_shift[row]));
+                                    again[t][i % NS] += qb * kRowsPerBlock + row < n_rows && (!cut_tile || row >= first_row + G * 16 * t) ? e : 0.f;
                                 }
-#pragma unroll
-                            for (int i = 0; i < NS; ++i) sum[t][i] = fabsf(sum[t][i]) < INFINITY ? sum[t][i] : again[i];
+                            }
                         }
+#pragma unroll
+                        for (int t = 0; t < 2; ++t)
+#pragma unroll
+                            for (int i = 0; i < NS; ++i) sum[t][i] = fabsf(sum[t][i]) < INFINITY ? sum[t][i] : again[t][i];
                     }
                     // rows of a head lie in all four groups of lanes (G = 8: in every second one)
 #pragma unroll

@@ -133,3 +133,36 @@ def test_error_against_64_bits(gpu):  # noqa: F811
     off = lambda x, y: float(np.linalg.norm(x - y) / np.linalg.norm(y))
     print(off(o, o_ref), off(lse, l_ref), off(a, a_ref))
     assert off(o, o_ref) <= 8 * 2.0 ** -24 and off(lse, l_ref) <= 2 * 2.0 ** -24 and off(a, a_ref) <= 8 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("what", ["v", "k"])
+def test_cost_of_values_without_parts(gpu, what):  # noqa: F811
+    """What one infinite V entry or one NaN key costs, seen by every query: its shares are worked out again with fp32 products.
+    Measured 1.9 and 2.8 times the time without (token by token on the vector units 20 and 29 times); 8 leaves room for noise."""
+    torch, hgca, runner = gpu
+    B, N, Hq, Hkv, d, cap = 2, 24, 32, 8, 128, 5120
+    g = torch.Generator(device="cuda:0").manual_seed(2)
+    q, k, v = (torch.randn(*s, generator=g, device="cuda:0") for s in ((B, N, Hq, d), (B, Hkv, cap, d), (B, Hkv, cap, d)))
+    shape = hgca.Shape(hgca.F32, B, Hq, Hkv, d, d ** -0.5)
+    o, lse, a = (torch.zeros(*s, device="cuda:0") for s in ((B, N, Hq, d), (B, N, Hq), (B, Hq, cap)))
+
+    def best(k, v):
+        tier, ws = hgca.Tier(k, v, cap), hgca.append_workspace(shape, N, cap, "cuda:0")
+        times = []
+        for _ in range(6):
+            t = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            t[0].record()
+            for _ in range(4):
+                hgca.append_attn(shape, q, tier, True, o, lse, ws)
+                hgca.append_weights(shape, q, tier, True, lse, a)
+            t[1].record()
+            torch.cuda.synchronize()
+            times.append(t[0].elapsed_time(t[1]))
+        return min(times)
+
+    without = best(k, v)
+    (v if what == "v" else k)[:, :, 7, 3] = float("inf" if what == "v" else "nan")
+    again = best(k, v)
+    print(what, again / without)
+    assert torch.isinf(o[..., 3]).all() if what == "v" else torch.isnan(o).all()
+    assert again <= 8 * without
