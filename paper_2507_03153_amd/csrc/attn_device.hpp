@@ -158,7 +158,14 @@ __device__ __forceinline__ void value_pass(const KernelArgs &a, float (*s_p)[LD]
 #pragma unroll
         for (int e = 0; e < EPL; ++e) acc[g][e] = 0.f;
 
-    auto consume = [&](int base, const uint4 (&vr)[UNROLL]) {
+    auto consume = [&](int base, uint4 (&vr)[UNROLL]) {
+        // A weight of 0 keeps the repeated last row out of a sum only while the row is finite (0 * inf is NaN).  fp32 only: in bf16
+        // V rows have to be finite.
+        if (sizeof(T) == 4 && !GATHER && base + RPI * UNROLL > nt) { // uniform over the workgroup: the last rows
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u)
+                if (base + u * RPI + w * RPW + r >= nt) vr[u] = make_uint4(0u, 0u, 0u, 0u);
+        }
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
             const int j = base + u * RPI + w * RPW + r;

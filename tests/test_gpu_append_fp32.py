@@ -34,9 +34,8 @@ def reference(q, K, V, lens, scale, causal):
     dict(B=2, N=100, Hq=8, Hkv=2, d=128, cap=203, lens=(203, 133)),          # four blocks of rows, steps cut by the length
     dict(B=2, N=150, Hq=4, Hkv=4, d=64, cap=256, lens=(256, 193)),
     dict(B=1, N=33, Hq=8, Hkv=1, d=128, cap=192, lens=(192,), paged=True),
-    # few enough rows to run query by query (where an infinite row seen next to the end of a tier gives NaN)
-    dict(B=2, N=40, Hq=8, Hkv=2, d=128, cap=203, lens=(203, 70), by_query=True),
-    dict(B=2, N=20, Hq=4, Hkv=4, d=64, cap=128, lens=(128, 65), by_query=True),
+    dict(B=2, N=40, Hq=8, Hkv=2, d=128, cap=203, lens=(203, 70)),
+    dict(B=2, N=20, Hq=4, Hkv=4, d=64, cap=128, lens=(128, 65)),             # few enough rows to run query by query
 ], ids=["gqa4", "mha_d64", "gqa8_paged", "gqa4_few", "mha_d64_few"])
 def test_rows_a_query_does_not_see_may_hold_anything(gpu, kw, causal):  # noqa: F811
     """Infinities and NaNs in V rows behind a query's causal limit, and in the last row of a tier whose length is no
@@ -65,8 +64,7 @@ def test_rows_a_query_does_not_see_may_hold_anything(gpu, kw, causal):  # noqa: 
     finite = np.isfinite(o_ref)
     assert finite.any() and not finite.all()
     assert np.array_equal(np.isfinite(o), finite), f"{np.sum(np.isfinite(o) != finite)} of {o.size} outputs differ in kind"
-    if not kw.get("by_query"):
-        assert np.array_equal(np.isnan(o), np.isnan(o_ref)) and np.array_equal(o[np.isinf(o_ref)], o_ref[np.isinf(o_ref)])
+    assert np.array_equal(np.isnan(o), np.isnan(o_ref)) and np.array_equal(o[np.isinf(o_ref)], o_ref[np.isinf(o_ref)])
     assert np.max(np.abs(o[finite] - o_ref[finite])) <= 1e-5
 
 
