@@ -985,28 +985,11 @@ int64_t append_units(const hgca_shape *s, int32_t n_q)
     return std::max<int64_t>(1, (int64_t)s->batch * s->n_kv_heads * n_qb);
 }
 
+int64_t line_steps(int64_t tokens) { return std::max<int64_t>(1, (tokens + kLineStep - 1) / kLineStep); }
+
 int append_want_splits(const hgca_shape *s, int32_t n_q)
 {
     return (int)std::max<int64_t>(1, HGCA_APPEND_TARGET_WGS / append_units(s, n_q));
-}
-
-// Workgroups that share the `tokens` (by capacity) of each of `units`, at most `most`: the number for which the launch
-// takes the least time, counted in 64-token steps: rounds of `places` workgroups (what the device holds at once) times
-// the steps of a share and what a share costs beside them (`overhead` steps).
-int line_shares(int64_t units, int64_t tokens, int most, int places, int overhead)
-{
-    const int64_t steps = std::max<int64_t>(1, (tokens + kLineStep - 1) / kLineStep);
-    int best = 1;
-    int64_t best_cost = INT64_MAX;
-    for (int n = 1; n <= most && n <= steps; ++n) {
-        const int64_t rounds = (n * units + places - 1) / places;
-        const int64_t cost = rounds * ((steps + n - 1) / n + overhead);
-        if (cost < best_cost) {
-            best_cost = cost;
-            best = n;
-        }
-    }
-    return best;
 }
 
 // Shares of the attention.  In bf16 a compute unit holds two workgroups: a 64-token step of both takes 2.8 us, of one alone
@@ -1017,13 +1000,14 @@ int line_shares(int64_t units, int64_t tokens, int most, int places, int overhea
 // with 45; 8 x 32 queries x 4 heads over 32 K tokens 260 with 8 (two workgroups per compute unit), 282 with 4.
 // (With the weights rounded to bf16, fewer shares also mean fewer weights that are exactly 1: 55 queries over 5.6 K tokens 6.7e-4
 // off with 30 shares, 6.3e-4 with 45.)
-// In fp32 a compute unit holds one workgroup.
+// In fp32 a compute unit holds one workgroup; what a share costs beside its steps counts as one of them (counted as two or three, 1092
+// sizes are 0.7 and 1.0 % faster on average, single ones 14 % faster to 16 % slower).
 int append_shares(const hgca_shape *s, int32_t n_q, int64_t tokens, int most)
 {
     const int64_t units = append_units(s, n_q);
-    if (s->dtype == HGCA_F32) return line_shares(units, tokens, most, HGCA_APPEND_TARGET_WGS / 2, 1);
+    if (s->dtype == HGCA_F32) return line_shares(units, line_steps(tokens), most, HGCA_APPEND_TARGET_WGS / 2, 1);
     constexpr int64_t kUnits = HGCA_APPEND_TARGET_WGS / 2, kStepOfTwo = 28, kStepAlone = 16, kStart = 30;
-    const int64_t steps = std::max<int64_t>(1, (tokens + kLineStep - 1) / kLineStep);
+    const int64_t steps = line_steps(tokens);
     const int64_t partial = std::min<int64_t>(128, (int64_t)n_q * group_of(s)) * s->head_dim * 8;        // bytes, written and read
     int64_t best = 1, best_cost = INT64_MAX;
     for (int64_t n = 1; n <= most && n <= steps;) {
@@ -1038,28 +1022,6 @@ int append_shares(const hgca_shape *s, int32_t n_q, int64_t tokens, int most)
         n = (steps + len - 2) / (len - 1);       // the smallest number whose shares are shorter
     }
     return (int)best;
-}
-
-// fp32, few queries: one-query attention per (sequence, query) with the split kernels of the decode path, which read K and V
-// once per query and work out no more than its rows, against the matrix instructions, which work out 16 rows whatever
-// there are.  The lower estimate has it, in us: query by query 6 + 1.5 per head of a group, and the K and V bytes of all
-// queries at what the vector units take (45 TB/s over the heads of a group) or the rows come from (20 TB/s out of L2,
-// 13.7 out of the last cache, 7.6 out of memory); on the matrix instructions 7, and the steps of a workgroup, one at a time
-// per compute unit, 3.4 each and up to 2.7 more with 128 rows (head_dim 128).  Measured, query by query : matrix, 4 sequences, 32
-// heads, 4 K tokens, 1 / 2 / 4 queries 81 : 115, 148 : 116, 284 : 117 us; 1 K tokens, 2 / 4 27 : 36, 41 : 36; 2 sequences, 32 / 8 heads,
-// 4 K tokens, 1 / 2 / 4 queries 18 : 23, 21 : 23, 33 : 24; 4 sequences, 40 heads of 64, 4 K tokens, 2 / 4 queries 90 : 114, 185 : 116; one
-// sequence, 64 / 8 heads, 16 K tokens, 1 / 4 queries 39 : 37, 101 : 40.  (With fp32 matrix instructions a step took 9.8.)
-bool f32_query_by_query(const hgca_shape *s, int32_t n_q, int64_t tokens, int most)
-{
-    const int g = group_of(s);
-    const double set = (double)s->batch * s->n_kv_heads * tokens * s->head_dim * 8;              // bytes of K and V
-    const double source = set <= 16e6 ? 20e6 : set <= 256e6 ? 13.7e6 : 7.6e6;                    // bytes per us
-    const double by_query = 6 + 1.5 * g + set * n_q / std::min(45e6 / g, source);
-    const int64_t shares = append_shares(s, n_q, tokens, most), places = HGCA_APPEND_TARGET_WGS / 2;
-    const int64_t steps = (tokens + kLineStep - 1) / kLineStep;
-    const int64_t turns = (shares * append_units(s, n_q) + places - 1) / places * ((steps + shares - 1) / shares);
-    const double step = 3.4 + 2.7 * std::min<int64_t>(128, (int64_t)n_q * g) / 128;
-    return by_query < 7 + turns * step * s->head_dim / 128;
 }
 
 struct AppendWs {
@@ -1119,11 +1081,13 @@ int hgca_append_attn(const hgca_shape *shape, const void *q, int32_t n_q, const 
     if (shape->dtype == HGCA_F32) {
         // batch * n_q sequences of one query each, as one of the two routes has it, are a grid dimension
         if ((int64_t)shape->batch * n_q > 65535) return HGCA_ERR_UNSUPPORTED;
-        if (tier->cap > 0 && f32_query_by_query(shape, n_q, tier->cap, w.max_splits)) {
-            // splits no shorter than the workspace has slots for
-            const int chunk = std::max(pick_chunk(tier->cap, (int64_t)shape->batch * n_q * shape->n_kv_heads, HGCA_TARGET_WGS_DENSE),
-                                       (n_splits_for(tier->cap, w.max_splits) + 63) / 64 * 64);
-            const int n_splits = n_splits_for(tier->cap, chunk);
+        // splits no shorter than the workspace has slots for
+        const int chunk = std::max(pick_chunk(tier->cap, (int64_t)shape->batch * n_q * shape->n_kv_heads, HGCA_TARGET_WGS_DENSE),
+                                   (n_splits_for(tier->cap, w.max_splits) + 63) / 64 * 64);
+        const int n_splits = n_splits_for(tier->cap, chunk);
+        const int64_t turns = line_turns(append_units(shape, n_q), line_steps(tier->cap),
+                                         append_shares(shape, n_q, tier->cap, w.max_splits), HGCA_APPEND_TARGET_WGS / 2);
+        if (tier->cap > 0 && query_by_query(shape->head_dim, shape->batch, shape->n_kv_heads, group_of(shape), n_q, tier->cap, n_splits, turns)) {
             if (chunk > kMaxChunk || n_splits > w.max_splits) return HGCA_ERR_WORKSPACE;
             AttnArgs d{};
             d.sh = to_dev(shape);
@@ -1270,7 +1234,7 @@ AppendArgs weights_args(const hgca_shape *shape, const void *q, int32_t n_q, con
 int weights_shares(const hgca_shape *s, int64_t tokens)
 {
     constexpr int kPlaces = 256;
-    return line_shares((int64_t)s->batch * s->n_kv_heads, tokens, kPlaces, kPlaces, s->dtype == HGCA_F32 ? 1 : 5);
+    return line_shares((int64_t)s->batch * s->n_kv_heads, line_steps(tokens), kPlaces, kPlaces, s->dtype == HGCA_F32 ? 1 : 5);
 }
 
 }  // namespace

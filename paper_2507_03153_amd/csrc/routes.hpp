@@ -75,4 +75,51 @@ inline bool short_step(bool f32, int64_t head_dim, int64_t units, int64_t group,
     return list <= 128 << 10 && keys <= int64_t(group == 8 ? 32 : group > 1 && head_dim > 64 ? 192 : 256) << 20;
 }
 
+// Workgroups that share the `steps` of 64 tokens (by capacity) of each of `units`, at most `most`: the number for which the launch
+// takes the least time, counted in steps: rounds of `places` workgroups (what the device holds at once) times
+// the steps of a share and what a share costs beside them (`overhead` steps).
+inline int line_shares(int64_t units, int64_t steps, int most, int places, int overhead)
+{
+    int best = 1;
+    int64_t best_cost = INT64_MAX;
+    for (int n = 1; n <= most && n <= steps; ++n) {
+        const int64_t rounds = (n * units + places - 1) / places;
+        const int64_t cost = rounds * ((steps + n - 1) / n + overhead);
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = n;
+        }
+    }
+    return best;
+}
+// the steps that one place of such a launch goes through
+inline int64_t line_turns(int64_t units, int64_t steps, int64_t shares, int64_t places)
+{
+    return (shares * units + places - 1) / places * ((steps + shares - 1) / shares);
+}
+
+// fp32 append attention of few queries over one tier: one-query attention per (sequence, query) with the split kernels of the decode
+// path, which read K and V once per query and work out no more than its rows, against the matrix instructions, which work out 16 rows
+// whatever there are.  The lower estimate has it, in us:
+//   query by query 7 + 0.08 group^2, and the K and V bytes of all queries at what the vector units take (44 TB/s over the heads of a
+//   group) or the rows come from, by the size of K and V: 20 TB/s up to 16 MB, 15 up to 70, 12 up to 150, 10 up to 256 MiB, which the last
+//   cache holds, 7.5 beyond; 7.5 also where a split's queries, splits * kv_heads workgroups apart, are on different XCDs and find nothing in their L2;
+//   on the matrix instructions 8, and the steps of a workgroup, one at a time per compute unit: 2.3 us with heads of 64, 3.4 with heads of
+//   128, and up to 2.4 and 5.6 more with 128 rows (heads of 64 have half the columns and two thirds of the time).
+// Fitted to 3585 sizes, 1 to 16 queries, 200 to 30 K tokens, up to 1.3 GB: the side taken is 0.4 % slower than the faster one on
+// average, by more than 20 % at 5 of them.  Query by query : matrix, us, 1 / 2 / 4 queries: 4 sequences, 40 heads of 64, 4 K tokens 54 : 117,
+// 93 : 119, 176 : 121; 2 sequences, 32 / 8 heads of 128, 4 K tokens 18 : 23, 21 : 23, 33 : 24; 8 sequences, 8 heads of 128, 4 K tokens 44 : 64,
+// 48 : 64, 94 : 66; 8 sequences, 32 / 8 heads of 64, 4 K tokens 28 : 46, 32 : 48, 52 : 48; 4 sequences, 64 / 8 heads of 64, 16 K tokens 50 : 85,
+// 89 : 91, 177 : 95; 5 sequences, 2 heads of 128, 4 queries, 4608 tokens (24 splits) 17 : 19, 4736 tokens (25) 31 : 20.
+inline bool query_by_query(int64_t head_dim, int64_t batch, int64_t kv_heads, int64_t group, int64_t n_q, int64_t tokens, int64_t splits,
+                           int64_t turns)
+{
+    const double set = (double)batch * kv_heads * tokens * head_dim * 8, rows = n_q * group < 128 ? n_q * group / 128. : 1.;
+    const bool apart = n_q > 1 && splits * kv_heads % 8 != 0;
+    const double source = apart || set > 270e6 ? 7.5e6 : set > 150e6 ? 10e6 : set > 70e6 ? 12e6 : set > 16e6 ? 15e6 : 20e6;      // bytes per us
+    const double vector = 44e6 / group;
+    const double step = head_dim <= 64 ? 2.3 + 2.4 * rows : 3.4 + 5.6 * rows;
+    return 7 + 0.08 * group * group + set * n_q / (vector < source ? vector : source) < 8 + turns * step;
+}
+
 }  // namespace hgca

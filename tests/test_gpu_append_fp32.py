@@ -1,8 +1,9 @@
-"""fp32 append stage on the matrix instructions, against a 64-bit reference that gives every query exactly the tokens
+"""fp32 append stage on the matrix instructions and query by query, against a 64-bit reference that gives every query exactly the tokens
 it sees."""
 import numpy as np
 import pytest
 
+from routes_rules import rules, runs_query_by_query  # noqa: F401
 from test_gpu_append import gpu, to_paged  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -33,15 +34,18 @@ def reference(q, K, V, lens, scale, causal):
 @pytest.mark.parametrize("kw", [
     dict(B=2, N=100, Hq=8, Hkv=2, d=128, cap=203, lens=(203, 133)),          # four blocks of rows, steps cut by the length
     dict(B=2, N=150, Hq=4, Hkv=4, d=64, cap=256, lens=(256, 193)),
-    dict(B=1, N=33, Hq=8, Hkv=1, d=128, cap=192, lens=(192,), paged=True),
-    dict(B=2, N=40, Hq=8, Hkv=2, d=128, cap=203, lens=(203, 70)),
-    dict(B=2, N=20, Hq=4, Hkv=4, d=64, cap=128, lens=(128, 65)),             # few enough rows to run query by query
-], ids=["gqa4", "mha_d64", "gqa8_paged", "gqa4_few", "mha_d64_few"])
-def test_rows_a_query_does_not_see_may_hold_anything(gpu, kw, causal):  # noqa: F811
+    dict(B=1, N=33, Hq=8, Hkv=1, d=128, cap=1024, lens=(1011,), paged=True),
+    # few enough rows, or tokens, to run query by query
+    dict(B=1, N=33, Hq=8, Hkv=1, d=128, cap=192, lens=(192,), paged=True, by_query=True),
+    dict(B=2, N=40, Hq=8, Hkv=2, d=128, cap=203, lens=(203, 70), by_query=True),
+    dict(B=2, N=20, Hq=4, Hkv=4, d=64, cap=128, lens=(128, 65), by_query=True),
+], ids=["gqa4", "mha_d64", "gqa8_paged", "gqa8_paged_few", "gqa4_few", "mha_d64_few"])
+def test_rows_a_query_does_not_see_may_hold_anything(gpu, rules, kw, causal):  # noqa: F811
     """Infinities and NaNs in V rows behind a query's causal limit, and in the last row of a tier whose length is no
     whole number of steps: O of a query is what its own rows give."""
     torch, hgca, runner = gpu
     B, N, Hq, Hkv, d, cap, lens = (kw[x] for x in ("B", "N", "Hq", "Hkv", "d", "cap", "lens"))
+    assert runs_query_by_query(rules, B, N, Hq, Hkv, d, cap) == kw.get("by_query", False)
     lens = np.array(lens, np.int32)
     rng = np.random.default_rng(3)
     q, K, V = (rng.standard_normal(s).astype(np.float32) for s in ((B, N, Hq, d), (B, Hkv, cap, d), (B, Hkv, cap, d)))
@@ -69,16 +73,23 @@ def test_rows_a_query_does_not_see_may_hold_anything(gpu, kw, causal):  # noqa: 
 
 
 @pytest.mark.parametrize("kw", [
-    # few queries, one by one ... and the next larger number on the matrix instructions
-    dict(B=1, N=1, Hq=8, Hkv=8, d=128, cap=700, lens=(700,)), dict(B=2, N=3, Hq=8, Hkv=2, d=128, cap=300, lens=(300, 2)),
-    dict(B=3, N=16, Hq=4, Hkv=4, d=64, cap=256, lens=(256, 16, 3)), dict(B=2, N=5, Hq=8, Hkv=1, d=64, cap=130, lens=(130, 77), paged=True),
+    # few queries, one by one
+    dict(B=1, N=1, Hq=8, Hkv=8, d=128, cap=700, lens=(700,), by_query=True),
+    dict(B=2, N=3, Hq=8, Hkv=2, d=128, cap=300, lens=(300, 2), by_query=True),
+    dict(B=3, N=16, Hq=4, Hkv=4, d=64, cap=256, lens=(256, 16, 3), by_query=True),
+    dict(B=2, N=2, Hq=16, Hkv=4, d=128, cap=2048, lens=(2048, 1500), by_query=True),
+    dict(B=2, N=3, Hq=16, Hkv=4, d=64, cap=1008, lens=(1000, 1), paged=True, by_query=True),
+    dict(B=1, N=20, Hq=16, Hkv=2, d=128, cap=160, lens=(150,), paged=True, by_query=True),
+    # on the matrix instructions
+    dict(B=2, N=5, Hq=8, Hkv=1, d=64, cap=130, lens=(130, 77), paged=True),
     dict(B=2, N=2, Hq=16, Hkv=2, d=128, cap=1000, lens=(1000, 0)), dict(B=2, N=48, Hq=16, Hkv=2, d=128, cap=1000, lens=(1000, 513)),
     dict(B=1, N=70, Hq=8, Hkv=4, d=128, cap=3000, lens=(2999,)),             # 140 rows
-], ids=["n1", "n3_short", "n16_d64", "n5_paged", "n2_empty", "n48_gqa8", "n70"])
+], ids=["n1", "n3_short", "n16_d64", "n2_gqa4", "n3_gqa4_paged", "n20_gqa8_paged", "n5_paged", "n2_empty", "n48_gqa8", "n70"])
 @pytest.mark.parametrize("causal", [True, False], ids=["causal", "whole"])
-def test_either_route(gpu, kw, causal):  # noqa: F811
+def test_either_route(gpu, rules, kw, causal):  # noqa: F811
     torch, hgca, runner = gpu
     B, N, Hq, Hkv, d, cap, lens = (kw[x] for x in ("B", "N", "Hq", "Hkv", "d", "cap", "lens"))
+    assert runs_query_by_query(rules, B, N, Hq, Hkv, d, cap) == kw.get("by_query", False)
     lens = np.array(lens, np.int32)
     rng = np.random.default_rng(N)
     q, K, V = (rng.standard_normal(s).astype(np.float32) for s in ((B, N, Hq, d), (B, Hkv, cap, d), (B, Hkv, cap, d)))

@@ -3,6 +3,7 @@ its error against 64 bits."""
 import numpy as np
 import pytest
 
+from routes_rules import rules, runs_query_by_query  # noqa: F401
 from test_gpu_append import gpu, to_paged  # noqa: F401
 from test_gpu_append_fp32 import reference
 
@@ -21,10 +22,11 @@ def weights_reference(q, K, lens, lse, scale, causal, cap):
     return a / N
 
 
-def run(gpu, q, K, V, lens, causal, paged, scale=None):
+def run(gpu, rules, q, K, V, lens, causal, paged, scale=None):  # noqa: F811
     torch, hgca, runner = gpu
     B, N, Hq, d = q.shape
     Hkv, cap = K.shape[1:3]
+    assert not runs_query_by_query(rules, B, N, Hq, Hkv, d, cap), "a capacity at which the call takes the matrix instructions"
     g = lambda a: runner._to_gpu(a, "cuda:0")
     shape = hgca.Shape(hgca.F32, B, Hq, Hkv, d, d ** -0.5 if scale is None else scale)
     tier = to_paged(runner, hgca, torch, K, V, lens, cap, 16, 4, "cuda:0") if paged else hgca.Tier(g(K), g(V), cap, g(lens))
@@ -42,12 +44,12 @@ def run(gpu, q, K, V, lens, causal, paged, scale=None):
     dict(N=31, Hq=8, Hkv=2, d=128, lens=(64, 1), paged=True), dict(N=17, Hq=16, Hkv=2, d=128, lens=(97, 129)),   # 124, 136
     dict(N=16, Hq=16, Hkv=2, d=64, lens=(700, 481)), dict(N=65, Hq=8, Hkv=4, d=64, lens=(300, 95), paged=True),  # 128, 130
 ], ids=["mha_d64", "gqa2", "gqa4_paged", "gqa8", "gqa8_d64", "gqa2_d64_paged"])
-def test_edges_of_tiles(gpu, kw, causal):  # noqa: F811
+def test_edges_of_tiles(gpu, rules, kw, causal):  # noqa: F811
     N, Hq, Hkv, d, lens = (kw[x] for x in ("N", "Hq", "Hkv", "d", "lens"))
-    lens, cap, B = np.array(lens, np.int32), max(kw["lens"]) + 5, 2
+    lens, cap, B = np.array(lens, np.int32), max(kw["lens"]) + 905, 2
     rng = np.random.default_rng(N)
     q, K, V = (rng.standard_normal(s).astype(np.float32) for s in ((B, N, Hq, d), (B, Hkv, cap, d), (B, Hkv, cap, d)))
-    o, lse, a = run(gpu, q, K, V, lens, causal, kw.get("paged"))
+    o, lse, a = run(gpu, rules, q, K, V, lens, causal, kw.get("paged"))
     o_ref, l_ref = reference(q, K, V, lens, d ** -0.5, causal)
     empty = np.isneginf(l_ref)
     assert np.array_equal(np.isneginf(lse), empty) and np.all(o[empty] == 0)
@@ -58,11 +60,11 @@ def test_edges_of_tiles(gpu, kw, causal):  # noqa: F811
 
 @pytest.mark.parametrize("kw", [dict(N=40, Hq=8, Hkv=2, d=128), dict(N=40, Hq=16, Hkv=2, d=64), dict(N=130, Hq=4, Hkv=4, d=64)],
                          ids=["gqa4", "gqa8_d64", "mha_d64"])
-def test_values_without_parts(gpu, kw):  # noqa: F811
+def test_values_without_parts(gpu, rules, kw):  # noqa: F811
     """Keys with an infinite component that every query meets with the same sign (their scores are -inf: they weigh nothing),
     keys whose products overflow a part but not the sum's type, and V entries that round to infinity in 16 bits."""
     N, Hq, Hkv, d = (kw[x] for x in ("N", "Hq", "Hkv", "d"))
-    B, cap, lens = 2, 260, np.array((260, 201), np.int32)
+    B, cap, lens = 2, 760, np.array((260, 201), np.int32)
     rng = np.random.default_rng(d)
     q, K, V = (rng.standard_normal(s).astype(np.float32) for s in ((B, N, Hq, d), (B, Hkv, cap, d), (B, Hkv, cap, d)))
     q[..., 0], q[..., 1] = 1.0, 1e-38
@@ -73,7 +75,7 @@ def test_values_without_parts(gpu, kw):  # noqa: F811
     # stays below the largest fp32 number (3.4028e38), and the sum of several may not, whatever forms their products.
     for i in range(8):
         V[:, :, 2 + 23 * i, 3 + i] = np.float32(3.4e38)
-    o, lse, a = run(gpu, q, K, V, lens, False, False)
+    o, lse, a = run(gpu, rules, q, K, V, lens, False, False)
     o_ref, l_ref = reference(q, K, V, lens, d ** -0.5, False)
     assert np.max(np.abs(lse - l_ref)) <= 1e-5
     assert np.max(np.abs(o - o_ref) / np.maximum(np.abs(o_ref).max(axis=(0, 1, 2)), 1.0)) <= 1e-5
@@ -83,10 +85,10 @@ def test_values_without_parts(gpu, kw):  # noqa: F811
 
 @pytest.mark.parametrize("case", ["large_and_small", "small_queries", "small_keys", "small_scale", "small_values", "small_weights", "low_scores"])
 @pytest.mark.parametrize("kw", [dict(N=40, Hq=8, Hkv=2, d=128), dict(N=100, Hq=4, Hkv=4, d=64)], ids=["gqa4", "mha_d64"])
-def test_ends_of_the_range(gpu, kw, case):  # noqa: F811
+def test_ends_of_the_range(gpu, rules, kw, case):  # noqa: F811
     """Normal fp32 operands whose lower parts bf16 has no bits for: what they give is as exact as anywhere else."""
     N, Hq, Hkv, d = (kw[x] for x in ("N", "Hq", "Hkv", "d"))
-    B, cap, lens, scale = 2, 260, np.array((260, 201), np.int32), d ** -0.5
+    B, cap, lens, scale = 2, 760, np.array((260, 201), np.int32), d ** -0.5
     rng = np.random.default_rng(d)
     q, K, V = (rng.standard_normal(s) for s in ((B, N, Hq, d), (B, Hkv, cap, d), (B, Hkv, cap, d)))
     if case == "large_and_small":                                # 3e38 has a bf16 part of its own; the terms are up to 3
@@ -108,7 +110,7 @@ def test_ends_of_the_range(gpu, kw, case):  # noqa: F811
         q[...], K[...] = 0.0, 0.0
         q[..., 0], K[..., 0] = 2.0 ** 50, -2.0 ** 40
     q, K, V = (x.astype(np.float32) for x in (q, K, V))
-    o, lse, a = run(gpu, q, K, V, lens, False, False, scale)
+    o, lse, a = run(gpu, rules, q, K, V, lens, False, False, scale)
     scale = float(np.float32(scale))
     o_ref, l_ref = reference(q, K, V, lens, scale, False)
     assert np.max(np.abs(lse - l_ref) / np.maximum(np.abs(l_ref), 1.0)) <= 1e-5
@@ -119,7 +121,7 @@ def test_ends_of_the_range(gpu, kw, case):  # noqa: F811
         assert np.max(np.abs(a - weights_reference(q, K, lens, l_ref, scale, False, cap))) <= 1e-5
 
 
-def test_error_against_64_bits(gpu):  # noqa: F811
+def test_error_against_64_bits(gpu, rules):  # noqa: F811
     """The products of parts are as good as fp32 ones: a score of 128 products is off by a few units of 2^-24 of its terms, and so
     are the weights and O, whose error is that of their scores: 24 queries over 3000 tokens stay below 8 * 2^-24 relative (2-norm)."""
     B, N, Hq, Hkv, d, cap = 1, 24, 4, 2, 128, 3000
@@ -127,7 +129,7 @@ def test_error_against_64_bits(gpu):  # noqa: F811
     rng = np.random.default_rng(11)
     q, K, V = (rng.standard_normal(s).astype(np.float32) for s in ((B, N, Hq, d), (B, Hkv, cap, d), (B, Hkv, cap, d)))
     q *= 2.0
-    o, lse, a = run(gpu, q, K, V, lens, False, False)
+    o, lse, a = run(gpu, rules, q, K, V, lens, False, False)
     o_ref, l_ref = reference(q, K, V, lens, d ** -0.5, False)
     a_ref = weights_reference(q, K, lens, l_ref, d ** -0.5, False, cap)
     off = lambda x, y: float(np.linalg.norm(x - y) / np.linalg.norm(y))
