@@ -37,6 +37,7 @@ def test_rows_of_large_and_small_launches_agree(dtype, d, win_blocks):
     large, CL = run(some)                                        # 24 rows
     small, CS = run(B)                                           # 264 rows
     assert int(CL.pool_lens.max()) > 0, "no eviction happened"
+    listed = 0
     for t, (x, y) in enumerate(zip(large, small)):
         for name, a, b in zip(("o", "lse", "a_gpu", "a_maw"), x, y):
             # both launches may cut the window into other splits: fp32 sums in another order
@@ -44,3 +45,11 @@ def test_rows_of_large_and_small_launches_agree(dtype, d, win_blocks):
         for name, a, b in zip(("win_lens", "pool_lens"), x[6:], y[6:]):
             assert torch.equal(a, b), (t, name)
         assert float((x[5] - y[5]).abs().max()) <= 1             # an average that stands at the threshold
+        for b in range(some):
+            for h in range(Hq):
+                p, r = (z[4][b, h, : int(z[5][b, h])] for z in (x, y))
+                for z in (p, r):                                 # in order, and of the pool
+                    assert bool((z[1:] > z[:-1]).all()) and (z.numel() == 0 or (int(z[0]) >= 0 and int(z[-1]) < int(x[7][b]))), (t, b, h)
+                assert len(set(p.tolist()) ^ set(r.tolist())) <= 1, (t, b, h)
+                listed += len(p)
+    assert listed > 100, "next to nothing was listed"
