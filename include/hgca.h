@@ -517,10 +517,17 @@ int hgca_ctx_compact(const hgca_shape *shape, const hgca_kv_view *pool,
                      int32_t ctx_cap, int32_t *cnt_out, void *hip_stream);
 
 /* ---- Append stage (Sec. 2.1: N incoming tokens, Q in R^{h x N x d}; Alg. 2,
- * append branch).  Both contractions run on the matrix cores: bf16 inputs on
- * the bf16 instructions, fp32 inputs (the exact shapes; B * n_q <= 65 535) on
- * the fp32 ones, products and sums in fp32 throughout; a few fp32 queries over
- * one tier run one by one on the vector units where that is faster. ----
+ * append branch).  Both contractions run on the matrix cores, on the bf16
+ * instructions.  fp32 inputs (the exact shapes; B * n_q <= 65 535) are taken
+ * apart there, each value into three bf16 numbers that add up to it; of the
+ * nine products of two values six are formed, what is left out is below 2^-26
+ * of the product, and sums are kept in fp32.  Measured against 64 bits, errors
+ * are those of fp32 products, over the whole range of the type: sums that need
+ * it (values that are not finite or beyond the largest bf16 number, scores
+ * whose products reach 2^104, |q| * sm_scale above 2^90, sums of V below
+ * 2^-88) are formed again with fp32 products, at 1.7 to 2.8 times the time.  A
+ * few fp32 queries over one tier run one by one on the vector units where that
+ * is faster. ----
  *
  * q is [B, N, Hq, d].  Attention of all N queries over one tier; the two parts
  * of the hybrid step are two calls (the window with HGCA_APPEND_CAUSAL_TAIL,
@@ -535,7 +542,7 @@ int hgca_ctx_compact(const hgca_shape *shape, const hgca_kv_view *pool,
  * typically ~1e-3 for unit-variance V; lse unaffected), a third fewer matrix
  * instructions.  Without it they enter as a high and a low bf16 part and O
  * keeps fp32-level accuracy (~1e-6).  (Ignored for fp32 inputs, whose weights
- * stay fp32 throughout.)
+ * enter in three parts that add up to them.)
  * Other bits are rejected.  shape.sm_scale must be positive and finite for the
  * append entry points.  o_out is fp32 [B, N, Hq, d], lse_out fp32
  * [B, N, Hq]; a query that sees nothing gives O = 0, lse = -inf.  In fp32 a

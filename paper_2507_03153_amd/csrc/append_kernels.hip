@@ -760,7 +760,8 @@ int64_t k_bytes_of(const AppendArgs &a, const AppendArgs *second, int head_dim)
 
 // A turn's weights pass reads again the K rows that its attention has just streamed (one block of rows).  From 512 MB of K and V
 // on (by capacity; a managed cache counts its window twice), the K rows of the last sixteenths of every share, 12 at most and as
-// many as the last cache holds of K, are left to the caches, and the weights pass walks its shares from the end.  Whole turns,
+// many as the last cache holds of K, are left to the caches, and the weights pass walks its shares from the end (a paged share in
+// passes of 8192 tokens: the passes in order, each from its end, in both kernels).  Whole turns,
 // everything streamed : so, us: 8 x 32 queries 1.1 GB 381 : 377, 12 x 8 queries 1.7 GB 460 : 450; 4 x 32 queries 576 MB 227 : 224;
 // 2 x 16 queries in groups of 8, 512 MB 218 : 212; 6 x 32 queries of 32 / 16 heads of 64, 864 MB 286 : 276.  Below, 0.99 to 1.01 times as
 // fast (288 MB 140.2 : 140.4, 330 MB 149.4 : 150.6, 482 MB 198.9 : 200.6).  All of K kept, or walked from the start, gains less;

@@ -1,5 +1,5 @@
 """A turn over a managed cache of 512 MB and more leaves part of K to the caches between attention and weights, and the weights pass
-walks its shares from the end: same values as the two calls by themselves, bit for bit, whatever the lengths."""
+walks the passes of its shares from the end: same values as the two calls by themselves, bit for bit, whatever the lengths."""
 import pytest
 
 pytestmark = pytest.mark.gpu
