@@ -364,10 +364,6 @@ __global__ __launch_bounds__(kF32Block, 2) void append_attn_f32_kernel(AppendArg
 #pragma unroll
                     for (int i = 0; i < 4; ++i) c[4 * t + i] = x[i];
                 }
-                float lowest = c[0];             // a score of -inf may be a sum that overflowed: l becomes NaN
-#pragma unroll
-                for (int i = 1; i < 8; ++i) lowest = fminf(lowest, c[i]);
-                l = fmaf(lowest, 0.f, l);
                 const int step0 = t0 + sub0 + tile * kTile, in_pass = nsub - tile * kTile;
                 if (min(in_pass, vis_min - step0) < kTile) {         // uniform over the wave: a length or causal boundary
                     int limit = min(in_pass, vis - step0);
@@ -442,7 +438,8 @@ __global__ __launch_bounds__(kF32Block, 2) void append_attn_f32_kernel(AppendArg
                     not_finite = fmaf(acc[dt][i], 0.f, not_finite);
                     least = fminf(least, fabsf(acc[dt][i]));
                 }
-            bool again = not_finite != 0.f;
+            const int row_end = min(t0 + nt_total, vis);
+            bool again = not_finite != 0.f || (m == -INFINITY && row_end > t0);      // (scores of -inf alone: sums that overflowed)
             if (__any(least < kLeast)) {         // 0 is no small one
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt)
@@ -453,7 +450,7 @@ __global__ __launch_bounds__(kF32Block, 2) void append_attn_f32_kernel(AppendArg
                 int lane_of = lane;              // nothing of this is worked out, and held in registers, before it is wanted
                 int64_t at = out_row;
                 asm volatile("" : "+v"(lane_of), "+v"(at));
-                append_rows_again<D>(kv, a1.sh.n_kv_heads, b, kvh, t0, min(t0 + nt_total, vis), static_cast<const char *>(a1.q) + at * (D * 4),
+                append_rows_again<D>(kv, a1.sh.n_kv_heads, b, kvh, t0, row_end, static_cast<const char *>(a1.q) + at * (D * 4),
                                      lane_of % 16, lane_of / 16, a1.sh.sm_scale * kLog2e, m, l, acc);
             }
         }

@@ -106,9 +106,9 @@ def test_ends_of_the_range(gpu, rules, kw, case):  # noqa: F811
         K[:, :, 7::11, 0] = 0.0
         V[..., 4] = 0.0
         V[:, :, 7::11, 4] = 1e30
-    else:                                                        # all scores alike, far below any sum of scaled products
+    else:                                                        # all scores alike; their products times 2^24 overflow to -inf
         q[...], K[...] = 0.0, 0.0
-        q[..., 0], K[..., 0] = 2.0 ** 50, -2.0 ** 40
+        q[..., 0], K[..., 0] = 2.0 ** 60, -2.0 ** 50
     q, K, V = (x.astype(np.float32) for x in (q, K, V))
     o, lse, a = run(gpu, rules, q, K, V, lens, False, False, scale)
     scale = float(np.float32(scale))
@@ -117,7 +117,7 @@ def test_ends_of_the_range(gpu, rules, kw, case):  # noqa: F811
     # a weight that counts lies 80 below the others here: its score is rounded to 80 * 2^-24, and so is the weight
     column = np.abs(o_ref).max(axis=(0, 1, 2))
     assert column.min() > 0 and np.max(np.abs(o - o_ref) / column) <= (4e-5 if case == "small_weights" else 1e-5)
-    if case != "low_scores":                                     # (the weights take the rounding of lse, 2^90 here)
+    if case != "low_scores":                                     # (the weights take the rounding of lse, 2^107 here)
         assert np.max(np.abs(a - weights_reference(q, K, lens, l_ref, scale, False, cap))) <= 1e-5
 
 
