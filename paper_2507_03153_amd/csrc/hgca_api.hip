@@ -1231,6 +1231,7 @@ AppendArgs weights_args(const hgca_shape *shape, const void *q, int32_t n_q, con
 }
 
 // Workgroups per (sequence, KV head) of the weights pass: one per compute unit, each meets all query rows.
+// (What a share costs beside its steps, fp32, counted as two or four of them instead of one: 179 sizes 0.3 and 0.5 % faster on average.)
 int weights_shares(const hgca_shape *s, int64_t tokens)
 {
     constexpr int kPlaces = 256;
