@@ -16,7 +16,7 @@
 // 100 tokens their weights 26 -> 85 (38), a key with scores of -inf 26 -> 44.
 //
 // Errors against 64 bits are those of fp32 products (2 x 24 queries on 5 K tokens: O 3.5e-7, weights 2.6e-7 with either).  fp32
-// matrix instructions : parts, us: that turn 137.7 : 97.1 (attention 76 : 45, weights 42 : 33); 8 x 24 queries of 32 / 8 heads of 64 on 17 K
+// matrix instructions : parts, us: that turn 137.7 : 93.6 (attention 76 : 45, weights 42 : 30); 8 x 24 queries of 32 / 8 heads of 64 on 17 K
 // tokens 664 : 332; attention alone, 4 x 32 queries of 32 ungrouped heads on 4 K tokens 318 : 133, 8 x 32 queries of 32 / 8 heads on
 // 16 K 643 : 396, 8 queries 626 : 237.  What bounds it now: a share's start (lengths, table of rows, first tiles: some 8 us of 45)
 // and, per 32-token tile, products 3100 cycles of 5500 with 96 rows.

@@ -107,7 +107,7 @@ inline int64_t line_turns(int64_t units, int64_t steps, int64_t shares, int64_t 
 //   on the matrix instructions 8, and the steps of a workgroup, one at a time per compute unit: 2.3 us with heads of 64, 3.4 with heads of
 //   128, and up to 2.4 and 5.6 more with 128 rows (heads of 64 have half the columns and two thirds of the time).
 // Fitted to 3585 sizes, 1 to 16 queries, 200 to 30 K tokens, up to 1.3 GB: the side taken is 0.4 % slower than the faster one on
-// average, by more than 20 % at 5 of them.  Query by query : matrix, us, 1 / 2 / 4 queries: 4 sequences, 40 heads of 64, 4 K tokens 54 : 117,
+// average, by more than 20 % at 5 of them (2.3 % and 139 with the constants before).  Query by query : matrix, us, 1 / 2 / 4 queries: 4 sequences, 40 heads of 64, 4 K tokens 54 : 117,
 // 93 : 119, 176 : 121; 2 sequences, 32 / 8 heads of 128, 4 K tokens 18 : 23, 21 : 23, 33 : 24; 8 sequences, 8 heads of 128, 4 K tokens 44 : 64,
 // 48 : 64, 94 : 66; 8 sequences, 32 / 8 heads of 64, 4 K tokens 28 : 46, 32 : 48, 52 : 48; 4 sequences, 64 / 8 heads of 64, 16 K tokens 50 : 85,
 // 89 : 91, 177 : 95; 5 sequences, 2 heads of 128, 4 queries, 4608 tokens (24 splits) 17 : 19, 4736 tokens (25) 31 : 20.
