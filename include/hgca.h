@@ -525,7 +525,7 @@ int hgca_ctx_compact(const hgca_shape *shape, const hgca_kv_view *pool,
  * are those of fp32 products, over the whole range of the type: sums that need
  * it (values that are not finite or beyond the largest bf16 number, scores
  * whose products reach 2^104, |q| * sm_scale above 2^90, sums of V below
- * 2^-88) are formed again with fp32 products, at 1.7 to 2.8 times the time.  A
+ * 2^-88) are formed again with fp32 products, at 2 to 3.5 times the time.  A
  * few fp32 queries over one tier run one by one on the vector units where that
  * is faster. ----
  *
