@@ -168,3 +168,52 @@ def test_cost_of_values_without_parts(gpu, what):  # noqa: F811
     print(what, again / without)
     assert torch.isinf(o[..., 3]).all() if what == "v" else torch.isnan(o).all()
     assert again <= 8 * without
+
+
+@pytest.mark.parametrize("G,d", [(4, 128), (1, 64)], ids=["gqa4", "mha_d64"])
+def test_turn_over_values_without_parts(gpu, G, d):  # noqa: F811
+    """A managed turn, both tiers in one launch: an infinite V entry of the pool reaches every query, one of the incoming tokens
+    those from its own on, and a key with scores of -inf nobody; weights and the other outputs stay what they are."""
+    torch, hgca, runner = gpu
+    from paper_2507_03153_amd.cache import LayerCache
+    dev, B, Hkv, bs, win_blocks, N = "cuda:0", 2, 2, 16, 12, 20
+    Hq, pool, win = Hkv * G, (336, 0), (100, 64)
+    g = torch.Generator(device=dev).manual_seed(11)
+    C = LayerCache(torch.float32, B, Hq, Hkv, d, bs, win_blocks, win_blocks + 22, 64, d ** -0.5, dev)
+    C.block_table.copy_(torch.randperm(C.block_table.numel(), generator=g, device=dev).int().view(B, -1))
+    C.k_blocks.normal_(generator=g)
+    C.v_blocks.normal_(generator=g)
+    C.pool_lens.copy_(torch.tensor(pool))
+    C.win_lens.copy_(torch.tensor(win))
+    C.first_win_block.copy_(C.pool_lens // bs)
+    q = torch.randn(B, N, Hq, d, generator=g, device=dev)
+    k_in, v_in = (torch.randn(B, N, Hkv, d, generator=g, device=dev) for _ in range(2))
+    q[..., 0] = 1.0
+    C.k_blocks[int(C.block_table[0, 5]), :, 7, 0] = -float("inf")
+    C.v_blocks[int(C.block_table[0, 9]), :, 3, 5] = float("inf")
+    v_in[:, 12, :, 6] = -float("inf")
+    rows = lambda x, b, n: x[C.block_table[b].long()].transpose(0, 1).reshape(Hkv, -1, d)[:, :n].double().cpu().numpy()
+    old = [[rows(x, b, pool[b] + win[b]) for x in (C.k_blocks, C.v_blocks)] for b in range(B)]
+    C.append_buffers(N)
+    C.append_step(q, k_in, v_in, 0.3, 4.0)
+    torch.cuda.synchronize()
+    o, lse, a_cpu, a_gpu = (x.double().cpu().numpy() for x in (C.o_app, C.lse_app, C.a_cpu, C.a_gpu))
+    for b in range(B):
+        K, V = (np.concatenate((x, y[b].transpose(0, 1).double().cpu().numpy()), 1) for x, y in zip(old[b], (k_in, v_in)))
+        n = K.shape[1]
+        a_ref = np.zeros((Hq, n))
+        o_ref, l_ref = reference(q[b:b + 1].cpu().numpy(), K[None], V[None], [n], d ** -0.5, True)
+        for h in range(Hq):
+            for i in range(N):                                   # weights of a tier are normalised over the tier
+                s = K[h // G] @ q[b, i, h].double().cpu().numpy() * d ** -0.5
+                s[n - N + i + 1:] = -np.inf
+                for t in (slice(0, pool[b]), slice(pool[b], n)):
+                    if t.stop > t.start:
+                        p = np.exp(s[t] - s[t].max())
+                        a_ref[h, t] += p / p.sum() / N
+        finite = np.isfinite(o_ref[0])
+        assert np.array_equal(np.isnan(o[b]), np.isnan(o_ref[0])) and np.array_equal(o[b][~finite], o_ref[0][~finite])
+        assert (pool[b] == 0 or np.isposinf(o[b, :, :, 5]).all()) and np.isneginf(o[b, 12:, :, 6]).all() and finite[:12, :, 6].all()
+        assert np.max(np.abs(o[b][finite] - o_ref[0][finite])) <= 1e-5 and np.max(np.abs(lse[b] - l_ref[0])) <= 1e-5
+        assert np.max(np.abs(a_cpu[b, :, :pool[b]] - a_ref[:, :pool[b]]), initial=0) <= 1e-5
+        assert np.max(np.abs(a_gpu[b, :, :win[b] + N] - a_ref[:, pool[b]:])) <= 1e-5

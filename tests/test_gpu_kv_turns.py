@@ -214,7 +214,7 @@ def test_turns_beta_zero_keep_everything(gpu):
 
 
 def test_turns_fp32_inputs(gpu):
-    """fp32 inputs through the same turns (the N-query attention then runs on the fp32 matrix instructions): O and lse of every
+    """fp32 inputs through the same turns (the N-query attention then runs on products of bf16 parts): O and lse of every
     query within 1e-5."""
     _, _, status, _ = run_turns(gpu, B=2, Hq=4, Hkv=2, d=64, block_size=16, win_blocks=3, max_blocks=16, k_max=200,
                                 turns=[("a", 32), ("d", 20), ("a", 25), ("d", 15), ("a", 40), ("d", 9)], alpha=0.3,
